@@ -10,13 +10,16 @@
 // Tiling: one workgroup of WAVES_M x WAVES_N waves computes a BM x BN tile.  Operands
 // go from global memory straight into LDS (16-byte global->LDS loads, no register
 // staging), XOR-swizzled so that the 16-byte fragment reads are conflict-free on the
-// 64-bank LDS.  Three K loops:
-//   ring16 (K % 128 == 0; gemm_ring16_kernel, what every projection of the model
-//          widths runs) slices of 32 columns in a ring of four LDS slots; a slice is
-//          requested three slices (96 columns of MFMA work) before it is read, which
-//          hides the L2/fabric latency that a two-stage pipeline exposes; one barrier
-//          per slice, waits by explicit vmcnt; v_mfma_f32_16x16x32_bf16 (one k-step per
-//          slice) with hand-written fragment reads and hand-counted lgkmcnt waits.
+// 64-bank LDS.  Four K loops:
+//   ping-pong (K % 128 == 0; gemm_ring16_kernel_pp, the 256x256 tile) two LDS buffers of
+//          64 columns filled half tile by half tile, four phases per 64 columns, the two
+//          waves of a SIMD alternating between fragment reads and MFMAs.
+//   ring16 (K % 128 == 0; gemm_ring16_kernel, the smaller tiles) slices of 32 columns
+//          in a ring of four LDS slots; a slice is requested three slices (96 columns of
+//          MFMA work) before it is read, which hides the L2/fabric latency that a
+//          two-stage pipeline exposes; one barrier per slice, waits by explicit vmcnt;
+//          v_mfma_f32_16x16x32_bf16 (one k-step per slice) with hand-written fragment
+//          reads and hand-counted lgkmcnt waits.
 //   ring   (gemm_ring_kernel) the same ring with v_mfma_f32_32x32x16_bf16 and
 //          compiler-scheduled fragment reads; kept as a cross-check behind
 //          cc_debug_set_launch.
@@ -765,7 +768,7 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gemm_ring_kernel(
                                               m0, bn, M, epi_for_tile(epi, vb - vb0, m0));
 }
 
-// The same ring with 16x16x32 MFMAs and hand-written fragment reads (the 256-wide tiles).
+// The same ring with 16x16x32 MFMAs and hand-written fragment reads.
 template <int BM, int BN, int WAVES_M, int WAVES_N, class BSrc, class Epi>
 __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gemm_ring16_kernel(
     const bf16_t* __restrict__ A, int lda, int M, int K, int tiles_m, int tiles_n, int GM, int nb, int vb0,
@@ -1057,14 +1060,251 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gemm_ring16_kernel(
     }
 }
 
-// Tile shapes: 256x256 (8 waves of 128x64, least LDS and L2 traffic per flop, one
-// workgroup per CU), 192x256 (8 waves of 96x64, ring loop only, measured at 0.8 of the
-// large tile's rate: it pays where it saves a half-empty round), 256x128 (8 waves of 64x64, one
-// per CU, ring loop only) and 128x128 (4 waves of 64x64, two per CU, measured at 0.55 to 0.85 of
-// the large tile's rate depending on K).  Every shape runs the 16x16x32 ring loop when K allows
-// it, the 256x256 and 128x128 shapes the staged loop otherwise.  A grid runs as a whole number
-// of "rounds" of workgroups, so the shape is chosen per launch to minimise rounds x tile
-// cost.
+// ------------------------------------------------------------- ping-pong loop
+template <int IMM>
+__device__ __forceinline__ bf16x8 lds_read16(uint32_t addr) {
+    static_assert(IMM >= 0 && IMM < 65536, "ds offset field");
+    bf16x8 v;
+    asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(v) : "v"(addr), "n"(IMM));
+    return v;
+}
+
+// The 256x256 tile with the two waves of every SIMD half a phase apart.
+//
+// What bounds it: the matrix pipe at the clock that the power limit leaves (full rounds run at
+// 1.40 PFLOP/s).  The ring loop above keeps its eight waves in step: every wave reads fragments,
+// issues loads and multiplies at the same time, a slice row is half a cache line, and a slice
+// took 1300 clocks for 1024 of matrix pipe.  Here
+//   - a K tile is 64 columns, so a row is one whole 128-byte line and a load moves 8 of them;
+//   - the tile is cut in halves, A0, A1 (128 rows each) and B0, B1 (128 columns each), and a K
+//     tile is four phases, one per quadrant of C: (A0,B0) (A0,B1) (A1,B1) (A1,B0).  A phase has
+//     a memory part (fragment reads, two loads) and a compute part (16 MFMAs, 256 clocks of the
+//     pipe), a barrier behind each.  Waves 4..7 run one barrier behind waves 0..3, and wave w
+//     and w + 4 share a SIMD: one multiplies while the other reads;
+//   - a wave owns 64 x 32 of every quadrant, so it reads 8 + 4 + 8 + 4 fragments per K tile, B0
+//     of the next tile in the last phase (a second register set) to even the phases out.
+// LDS: two buffers of one K tile (2 x 64 KB), filled half tile by half tile.  The half read in
+// phase p is refilled two phases later (both groups have read it by then) and the refill is
+// waited for five phases after its issue:
+//   phase   reads      loads          waited for before the first barrier (5 younger halves out)
+//   1       A0(t)      A1(t+1)        B1(t)
+//   2       B1(t)      B0(t+2)        A1(t)
+//   3       A1(t)      A0(t+2)        B0(t+1)
+//   4       B0(t+1)    B1(t+2)        A0(t+1)
+// A wave waits for its own loads before the first barrier of phase p; both groups have passed
+// such a barrier before either reads in phase p + 1.
+// Slot swizzle: 16-byte chunk c of row r sits at c ^ ((r>>1)&7), free of bank conflicts for the
+// fragment read (lane = row L%16, chunk L/16 of 16 rows).
+// Against the ring loop with this tile (same sums, same bits), microseconds: M = 3404, d = 4096,
+// f = 14336: gate/up 727 -> 642, down 331 -> 290, O 114 -> 107; M = 13363, d = 8192, f = 28672:
+// gate/up 10370 -> 9050, down 5480 -> 4450, QKV 1990 -> 1720, O 1520 -> 1260.  Raising the
+// wave's priority around the MFMAs, waiting for the reads after the barrier instead of before it,
+// and issuing the loads before the reads: each within 1 %.
+template <class BSrc, class Epi>
+__global__ __launch_bounds__(512, 2) void gemm_ring16_kernel_pp(
+    const bf16_t* __restrict__ A, int lda, int M, int K, int tiles_m, int tiles_n, int GM, int nb, int vb0,
+    BSrc bsrc, Epi epi) {
+    constexpr int H = 128, BM = 2 * H, BN = 2 * H;
+    constexpr int UM = 4, UN = 2;                      // 16x16 accumulator tiles of a wave in one quadrant
+    constexpr int LPH = 2;                             // loads of a wave per half tile
+    constexpr int ROWB = 128;                          // bytes of a K tile's row
+    constexpr int HALF = H * ROWB, BUF = 4 * HALF;     // a buffer is A0 | A1 | B0 | B1
+    static_assert(2 * BUF >= H * BN * 4, "half of the fp32 tile fits for the epilogue");
+    __shared__ __align__(16) char smem[2 * BUF];
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wr = wave >> 2, wc = wave & 3;           // wave row = group
+    int bm, bn;
+    const int vb = tile_of_block(blockIdx.x, nb, vb0, tiles_m, tiles_n, GM, &bm, &bn);
+    const int m0 = bm * BM;
+    const int64_t kz = (int64_t)blockIdx.y * K * 2;    // K is this launch's share per workgroup row
+
+    // ---- global -> LDS: a wave moves rows 16 wave .. 16 wave + 15 of every half, 8 per load; lane L
+    //      fills slot L%8 of row L/8.  Wave-uniform bases advance along K in scalar registers. ----
+    uint32_t ao[2][LPH], bo[2][LPH];
+    const int a_rows = M - m0;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const int left = bsrc.template rows_left<BN>(bn, h);
+#pragma unroll
+        for (int i = 0; i < LPH; ++i) {
+            const int rl = (wave * LPH + i) * 8 + (lane >> 3);
+            const int c = (lane & 7) ^ ((rl >> 1) & 7);
+            const int ra = min(h * H + rl, a_rows - 1), rb = min(rl, left - 1);   // rows past the end repeat the last
+            ao[h][i] = (uint32_t)((ra * lda + c * 8) * 2);
+            bo[h][i] = (uint32_t)((rb * bsrc.ldb + c * 8) * 2);
+        }
+    }
+    const char* const abase = reinterpret_cast<const char*>(A + (int64_t)m0 * lda) + kz;
+    const char* const bbase[2] = {reinterpret_cast<const char*>(bsrc.template base<BN>(bn, 0)) + kz,
+                                  reinterpret_cast<const char*>(bsrc.template base<BN>(bn, 1)) + kz};
+    auto scalar_ptr = [](const char* p) -> const char* {   // keeps the base in scalar registers
+        const uint64_t u = reinterpret_cast<uint64_t>(p);
+        const uint64_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)u);
+        const uint64_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(u >> 32));
+        return reinterpret_cast<const char*>((hi << 32) | lo);
+    };
+    auto load_half = [&](const char* base, uint32_t (&off)[LPH], int lds_at, int kt) __attribute__((always_inline)) {
+        unrolled<LPH>([&](auto ic) __attribute__((always_inline)) {
+            constexpr int i = decltype(ic)::value;
+            const char* g = scalar_ptr(base + (int64_t)kt * ROWB - i * 1024);   // the immediate adds it back
+            asm volatile("" : "+v"(off[i]));   // keeps the offset a 32-bit register operand of the load
+            dma16_at<i * 1024>(g + off[i], reinterpret_cast<bf16_t*>(smem + lds_at + wave * LPH * 1024));
+        });
+    };
+    auto load_a = [&](int h, int buf, int kt) __attribute__((always_inline)) { load_half(abase, ao[h], buf * BUF + h * HALF, kt); };
+    auto load_b = [&](int h, int buf, int kt) __attribute__((always_inline)) { load_half(bbase[h], bo[h], buf * BUF + (2 + h) * HALF, kt); };
+
+    f32x4 acc[2][2][UM][UN];                           // [row half][column half]
+#pragma unroll
+    for (int x = 0; x < 4; ++x)
+#pragma unroll
+        for (int i = 0; i < UM; ++i)
+#pragma unroll
+            for (int j = 0; j < UN; ++j) acc[x >> 1][x & 1][i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const int frow = lane & 15, fk = lane >> 4;
+    const int fsw = (frow >> 1) & 7;
+    const uint32_t smem_base = (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void*)smem;
+    uint32_t a_addr[2][2], b_addr[2][2];               // [buffer][k-step of 32 columns]
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks) {
+            const uint32_t at = smem_base + b * BUF + frow * ROWB + ((fk + 4 * ks) ^ fsw) * 16;
+            a_addr[b][ks] = at + wr * (H / 2) * ROWB;
+            b_addr[b][ks] = at + 2 * HALF + wc * (H / 4) * ROWB;
+        }
+    bf16x8 af[2][UM], b0[2][2][UN], b1[2][UN];         // [k-step][16-row tile]; B0 of two K tiles
+    auto read_a = [&](auto bufc, auto hc) __attribute__((always_inline)) {
+        constexpr int buf = decltype(bufc)::value, h = decltype(hc)::value;
+        unrolled<2 * UM>([&](auto xc) __attribute__((always_inline)) {
+            constexpr int x = decltype(xc)::value, ks = x / UM, i = x % UM;
+            af[ks][i] = lds_read16<h * HALF + i * 16 * ROWB>(a_addr[buf][ks]);
+        });
+    };
+    auto read_b = [&](auto bufc, auto hc, bf16x8 (&dst)[2][UN]) __attribute__((always_inline)) {
+        constexpr int buf = decltype(bufc)::value, h = decltype(hc)::value;
+        unrolled<2 * UN>([&](auto xc) __attribute__((always_inline)) {
+            constexpr int x = decltype(xc)::value, ks = x / UN, i = x % UN;
+            dst[ks][i] = lds_read16<h * HALF + i * 16 * ROWB>(b_addr[buf][ks]);
+        });
+    };
+    // orders the uses of hand-read fragments behind the wait in front of this
+    auto arrived_a = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int x = 0; x < 2 * UM; ++x) asm volatile("" : "+v"(af[x / UM][x % UM]));
+    };
+    auto arrived_b = [&](bf16x8 (&dst)[2][UN]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int x = 0; x < 2 * UN; ++x) asm volatile("" : "+v"(dst[x / UN][x % UN]));
+    };
+    // end of a memory part: at most VM of this wave's loads are out, its reads have returned
+    auto wait_bar = [&](auto vmc) __attribute__((always_inline)) {
+        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" : : "n"(decltype(vmc)::value));
+        wg_barrier();
+    };
+    auto compute = [&](f32x4 (&c)[UM][UN], bf16x8 (&b)[2][UN]) __attribute__((always_inline)) {
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+            for (int i = 0; i < UM; ++i)
+#pragma unroll
+                for (int j = 0; j < UN; ++j) c[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[ks][i], b[ks][j], c[i][j], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        wg_barrier();
+    };
+#define CC_IC(x) std::integral_constant<int, (x)>{}
+    // One K tile; `left` = K tiles after this one whose loads are still to be issued or waited for
+    // (2: steady state, 1: the last but one, 0: the last).
+    auto k_tile = [&](auto bufc, auto leftc, int kt) __attribute__((always_inline)) {
+        constexpr int buf = decltype(bufc)::value, left = decltype(leftc)::value;
+        read_a(bufc, CC_IC(0));
+        if constexpr (left > 0) load_a(1, buf ^ 1, kt + 1);
+        wait_bar(CC_IC(left > 0 ? 5 * LPH : LPH));
+        arrived_a();
+        arrived_b(b0[buf]);
+        compute(acc[0][0], b0[buf]);
+
+        read_b(bufc, CC_IC(1), b1);
+        if constexpr (left > 1) load_b(0, buf, kt + 2);
+        wait_bar(CC_IC(left > 1 ? 5 * LPH : left > 0 ? 4 * LPH : 0));
+        arrived_b(b1);
+        compute(acc[0][1], b1);
+
+        read_a(bufc, CC_IC(1));
+        if constexpr (left > 1) load_a(0, buf, kt + 2);
+        wait_bar(CC_IC(left > 1 ? 5 * LPH : left > 0 ? 3 * LPH : 0));
+        arrived_a();
+        compute(acc[1][1], b1);
+
+        if constexpr (left > 0) read_b(CC_IC(buf ^ 1), CC_IC(0), b0[buf ^ 1]);
+        if constexpr (left > 1) load_b(1, buf, kt + 2);
+        wait_bar(CC_IC(left > 1 ? 5 * LPH : left > 0 ? 2 * LPH : 0));
+        if constexpr (left > 0) arrived_b(b0[buf ^ 1]);
+        compute(acc[1][0], b0[buf]);
+    };
+    const int KT = K / 64;                             // even and >= 2 (K % 128 == 0)
+    load_b(0, 0, 0);
+    load_a(0, 0, 0);
+    load_b(1, 0, 0);
+    load_a(1, 0, 0);
+    load_b(0, 1, 1);
+    load_a(0, 1, 1);
+    load_b(1, 1, 1);
+    wait_bar(CC_IC(5 * LPH));                          // B0(0) and A0(0) are in place
+    read_b(CC_IC(0), CC_IC(0), b0[0]);
+    asm volatile("s_waitcnt lgkmcnt(0)");
+    arrived_b(b0[0]);
+    if (wr) wg_barrier();                              // the second group runs one barrier behind
+    int kt = 0;
+    for (; kt + 2 < KT; kt += 2) {
+        k_tile(CC_IC(0), CC_IC(2), kt);
+        k_tile(CC_IC(1), CC_IC(2), kt + 1);
+    }
+    k_tile(CC_IC(0), CC_IC(1), kt);
+    k_tile(CC_IC(1), CC_IC(0), kt + 1);
+    if (!wr) wg_barrier();
+#undef CC_IC
+
+    // ---- epilogue: one row half at a time through LDS as fp32 [H][BN], column c of row r at
+    //      c ^ 16*((r>>2)&3) (the four 16-lane groups of an accumulator store hit disjoint banks) ----
+    constexpr int TPR = BN / 8, RPP = 512 / TPR;       // threads per row, rows per pass
+    float* stage = reinterpret_cast<float*>(smem);
+    const auto e2 = epi_for_tile(epi, vb - vb0, m0);
+    const int cc = (tid % TPR) * 8;
+#pragma unroll
+    for (int ha = 0; ha < 2; ++ha) {
+        __syncthreads();
+#pragma unroll
+        for (int hb = 0; hb < 2; ++hb)
+#pragma unroll
+            for (int i = 0; i < UM; ++i)
+#pragma unroll
+                for (int j = 0; j < UN; ++j)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) {
+                        const int r = wr * (H / 2) + i * 16 + 4 * fk + v;
+                        const int c = hb * H + wc * (H / 4) + j * 16 + frow;
+                        stage[r * BN + (c ^ (fk << 4))] = acc[ha][hb][i][j][v];
+                    }
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < H / RPP; ++k) {
+            const int r = tid / TPR + k * RPP;
+            const int m = m0 + ha * H + r;
+            if (m < M) e2.template operator()<BN>(m, bn, cc, stage + r * BN, ((r >> 2) & 3) << 4);
+        }
+    }
+}
+
+// Tile shapes: 256x256 (ping-pong loop, 8 waves, least LDS and L2 traffic per flop, one
+// workgroup per CU), 192x256 (8 waves of 96x64, ring loop only, 0.70 of the large tile's rate:
+// it pays where it saves a half-empty round), 256x128 (8 waves of 64x64, one per CU, ring loop
+// only, 0.61) and 128x128 (4 waves of 64x64, two per CU, 0.58).  Where K is not a multiple of
+// 128 the 256x256 and 128x128 shapes run the staged loop.  A grid runs as a whole number of
+// "rounds" of workgroups, so the shape is chosen per launch to minimise rounds x tile cost.
 template <class BSrc, class Epi>
 void launch_gemm(const bf16_t* A, int lda, int M, int N_tiles_cols, int K, int ldb, int gm_big,
                  BSrc bsrc, Epi epi, float* ws, int64_t ws_floats, const cc_launch_override& ovr,
@@ -1091,8 +1331,8 @@ void launch_gemm(const bf16_t* A, int lda, int M, int N_tiles_cols, int K, int l
     bool ring = K % (BKS * NS) == 0 && (int64_t)lda * 256 * 2 < (1ll << 31) &&
                 (int64_t)ldb * 256 * 2 < (1ll << 31);
     if (ovr.gemm_staged) ring = false;
-    const double cb = cost(256, 256, 1, 1.00), cm = cost(192, 256, 1, 0.80), ch = cost(256, 128, 1, 0.70),
-                 cs = cost(128, 128, 2, 0.67);
+    const double cb = cost(256, 256, 1, 1.00), cm = cost(192, 256, 1, 0.70), ch = cost(256, 128, 1, 0.61),
+                 cs = cost(128, 128, 2, 0.58);
     char pick = cb <= cs ? 'b' : 's';
     double best = cb <= cs ? cb : cs;
     if (ring && ch < best) pick = 'h', best = ch;               // these two have no staged variant
@@ -1102,13 +1342,13 @@ void launch_gemm(const bf16_t* A, int lda, int M, int N_tiles_cols, int K, int l
     // fills at most half the chip (all tiles, if there is no full round) are computed by S
     // workgroup rows, each over K/S columns, with S x tiles <= CUs, and a finishing pass; the full
     // rounds before them run as a launch of their own.  256-wide tiles only.  Times in
-    // microseconds: 0.75 per 32-column slice of a 256x256 tile, 6 per round for the ends of a tile,
+    // microseconds: 0.65 per 32-column slice of a 256x256 tile, 6 per round for the ends of a tile,
     // the finishing pass at 4 TB/s plus 10 for the two extra launches (measured: QKV at M = 3928,
     // 384 tiles, takes 208 split against 199 with the 192-row tile, so the estimate has to be
     // 10 % below the unsplit one to be taken).
     int S = 1;
     if (ring && ws) {
-        const double slice_us = 0.75 * K / BKS / 65536.0;       // per unit of tile area
+        const double slice_us = 0.65 * K / BKS / 65536.0;       // per unit of tile area
         auto rem_of = [&](int bm) {
             const long tiles = (long)((M + bm - 1) / bm) * ((N_tiles_cols + 255) / 256);
             return (int)(tiles % n_cu == 0 && tiles > 0 ? n_cu : tiles % n_cu);
@@ -1128,7 +1368,7 @@ void launch_gemm(const bf16_t* A, int lda, int M, int N_tiles_cols, int K, int l
                                                                pick == 's' ? 2 : 1, 1);
             const double t_unsplit = t_best;
             for (int bm = 256; bm >= 192; bm -= 64) {
-                const double tile_us = bm * 256.0 / (bm == 256 ? 1.0 : 0.80) * slice_us;
+                const double tile_us = bm * 256.0 / (bm == 256 ? 1.0 : 0.70) * slice_us;
                 const long full_rounds = rounds_of(bm, 256, 1, 1) - 1;
                 const int rem = rem_of(bm);
                 for (int sp = 2; sp <= 16; ++sp) {
@@ -1149,6 +1389,9 @@ void launch_gemm(const bf16_t* A, int lda, int M, int N_tiles_cols, int K, int l
 #define CC_LAUNCH(KERN, BM_, BN_, WM_, WN_, EPI_T, EPI_V, K_, NB_, VB0_, GY_)                              \
     hipLaunchKernelGGL((KERN<BM_, BN_, WM_, WN_, BSrc, EPI_T>), dim3(NB_, GY_), dim3(WM_ * WN_ * 64), 0, s, A, \
                        lda, M, K_, tiles_m, tiles_n, GM, NB_, VB0_, bsrc, EPI_V)
+#define CC_LAUNCH_PP(EPI_T, EPI_V, K_, NB_, VB0_, GY_)                                                      \
+    hipLaunchKernelGGL((gemm_ring16_kernel_pp<BSrc, EPI_T>), dim3(NB_, GY_), dim3(512), 0, s, A, lda, M, K_,    \
+                       tiles_m, tiles_n, GM, NB_, VB0_, bsrc, EPI_V)
 #define CC_LAUNCH_NT(BM_, BN_, WM_, WN_)                                                                    \
     hipLaunchKernelGGL((gemm_nt_kernel<BM_, BN_, WM_, WN_, BSrc, Epi>), dim3(n_tiles), dim3(WM_ * WN_ * 64), 0, \
                        s, A, lda, M, K, tiles_m, tiles_n, GM, bsrc, epi)
@@ -1156,8 +1399,8 @@ void launch_gemm(const bf16_t* A, int lda, int M, int N_tiles_cols, int K, int l
         const int rem = n_tiles % n_cu == 0 ? n_cu : n_tiles % n_cu, full = n_tiles - rem;
         EpiPartial pe{ws, (int64_t)rem * 65536, 0, 0};
         if (pick == 'b' && mfma16) {
-            if (full) CC_LAUNCH(gemm_ring16_kernel, 256, 256, 2, 4, Epi, epi, K, full, 0, 1);
-            CC_LAUNCH(gemm_ring16_kernel, 256, 256, 2, 4, EpiPartial, pe, K / S, rem, full, S);
+            if (full) CC_LAUNCH_PP(Epi, epi, K, full, 0, 1);
+            CC_LAUNCH_PP(EpiPartial, pe, K / S, rem, full, S);
         } else if (pick == 'b') {
             if (full) CC_LAUNCH(gemm_ring_kernel, 256, 256, 2, 4, Epi, epi, K, full, 0, 1);
             CC_LAUNCH(gemm_ring_kernel, 256, 256, 2, 4, EpiPartial, pe, K / S, rem, full, S);
@@ -1171,7 +1414,7 @@ void launch_gemm(const bf16_t* A, int lda, int M, int N_tiles_cols, int K, int l
         hipLaunchKernelGGL((splitk_finish_kernel<Epi>), dim3(rem, (bm + 7) / 8), dim3(256), 0, s, ws,
                            (int64_t)rem * 65536, S, M, bm, full, tiles_m, tiles_n, GM, epi);
     } else if (pick == 'b') {
-        if (ring && mfma16) CC_LAUNCH(gemm_ring16_kernel, 256, 256, 2, 4, Epi, epi, K, n_tiles, 0, 1);
+        if (ring && mfma16) CC_LAUNCH_PP(Epi, epi, K, n_tiles, 0, 1);
         else if (ring) CC_LAUNCH(gemm_ring_kernel, 256, 256, 2, 4, Epi, epi, K, n_tiles, 0, 1);
         else CC_LAUNCH_NT(256, 256, 2, 4);
     } else if (pick == 'm') {
@@ -1187,6 +1430,7 @@ void launch_gemm(const bf16_t* A, int lda, int M, int N_tiles_cols, int K, int l
     }
 #undef CC_LAUNCH
 #undef CC_LAUNCH_NT
+#undef CC_LAUNCH_PP
 }
 
 }  // namespace
