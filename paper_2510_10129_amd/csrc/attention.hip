@@ -24,13 +24,16 @@
 // SIMD belong to the same workgroup, one to group A and one to group B, and
 // the workgroup barrier separates phases: while A runs the softmax of tile t, B
 // runs P V of tile t-1 and Q K^T of tile t, and the other way round in the next
-// phase.  A wave issues its global -> LDS loads at the end of its matrix phase
-// (group A the V tiles, group B the K tiles), while its SIMD partner is in the
-// vector part of its softmax: next to a partner that keeps the matrix pipe busy
-// such a load holds the issuing wave several times as long.
+// phase.  A wave issues its global -> LDS loads in its softmax phase, one after every
+// second group of four exponentials (group A the V tiles, group B the K tiles): the four of
+// them back to back at the end of the matrix phase queue up behind each other and lengthen
+// the phase that the matrix pipe is busy in.  The form of the load decides: scalar base plus
+// 32-bit lane offset and one LDS base for the four.  With 64-bit vector addresses and the LDS
+// base rewritten between them the same placement ran 18 % slower.  At 64k context, 64 query
+// heads and M = 13363: 12.05 -> 11.72 ms; M = 16576 at 16k: 2.05 -> 1.99 ms.
 //
 // K and V tiles (64 keys) go from the cache straight into LDS with 16-byte
-// global->LDS loads, row-major as they are stored, three stages each.  K
+// global->LDS loads, row-major as they are stored, three stages of K, four of V.  K
 // fragments are plain 16-byte LDS reads; the V^T fragments (contraction index =
 // key) come from the row-major V tile through the transposing LDS read
 // ds_read_b64_tr_b16, so V is never transposed in registers.  Both tiles are
@@ -108,10 +111,10 @@ __global__ __launch_bounds__(512, 1) void sparse_attn_kernel(
     constexpr int NI = BN_KEYS / RPI / 4; // such instructions per wave, tile and tensor
 
     constexpr int TILE = BN_KEYS * D_H;   // elements of one K or V tile
-    // three stages per tensor: K tile t lives in stage t % 3, V tile t in stage 3 + t % 3
-    __shared__ __align__(16) bf16_t smem[6 * TILE];
+    // K tile t lives in stage t % 3, V tile t in stage 3 + t % 4
+    __shared__ __align__(16) bf16_t smem[7 * TILE];
     auto k_stage = [&](int t) __attribute__((always_inline)) { return smem + (t % 3) * TILE; };
-    auto v_stage = [&](int t) __attribute__((always_inline)) { return smem + (3 + t % 3) * TILE; };
+    auto v_stage = [&](int t) __attribute__((always_inline)) { return smem + (3 + t % 4) * TILE; };
 
     __shared__ int simd_waves[4], group_waves[2];
 
@@ -211,33 +214,37 @@ __global__ __launch_bounds__(512, 1) void sparse_attn_kernel(
     const int r0 = wave * RPI + l_row;                 // logical row of instruction 0
     const int k_col = (l_p ^ kswz(r0)) * 8;
     const int v_col = ((((l_p >> 2) ^ vswz(r0)) << 2) | (l_p & 3)) * 8;
-    const int koff = r0 * (int)st + k_col;             // 32-bit lane offsets from a wave-uniform tile base
-    const int voff = r0 * (int)st + v_col;
-    const int64_t istep = (int64_t)(4 * RPI) * st - 512;   // next instruction: 4 RPI rows on, minus its 1 KB immediate
     const int wave_slot = wave * NI * RPI * D_H;
-    auto dma_k = [&](bf16_t* ks, int j0) __attribute__((always_inline)) {
-        const bf16_t* kb = kbase + (int64_t)j0 * st;
-        if (j0 + BN_KEYS <= N) {
-            static_for<NI>([&](auto i) { dma16<i.value * 1024>(kb + i.value * istep + koff, ks + wave_slot); });
-        } else {   // last tile of the cache: rows past N-1 are clamped (they are masked anyway)
-            const int rmax = N - 1 - j0;
-            static_for<NI>([&](auto i) {
-                const int64_t r = min(r0 + i.value * 4 * RPI, rmax);
-                dma16<i.value * 1024>(kb + r * st + k_col - i.value * 512, ks + wave_slot);
-            });
-        }
+    // Group A loads V tiles, group B K tiles: a wave-uniform base per tile (scalar registers) plus
+    // 32-bit lane offsets that are the same for every tile; from the tile on that reaches past the
+    // cache (only a workgroup's last one can) rows past N-1 are clamped (they are masked anyway).
+    const char* const lbase = reinterpret_cast<const char*>(grp == 0 ? vbase : kbase);
+    const int l_col = grp == 0 ? v_col : k_col;
+    uint32_t loff[NI];
+    auto set_loff = [&](int rmax) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < NI; ++i) loff[i] = (uint32_t)(min(r0 + i * 4 * RPI, rmax) * (int)st + l_col) * 2;
     };
-    auto dma_v = [&](bf16_t* vs, int j0) __attribute__((always_inline)) {
-        const bf16_t* vb = vbase + (int64_t)j0 * st;
-        if (j0 + BN_KEYS <= N) {
-            static_for<NI>([&](auto i) { dma16<i.value * 1024>(vb + i.value * istep + voff, vs + wave_slot); });
-        } else {
-            const int rmax = N - 1 - j0;
-            static_for<NI>([&](auto i) {
-                const int64_t r = min(r0 + i.value * 4 * RPI, rmax);
-                dma16<i.value * 1024>(vb + r * st + v_col - i.value * 512, vs + wave_slot);
-            });
-        }
+    set_loff(BN_KEYS);
+    auto tile_at = [&](int t) __attribute__((always_inline)) -> const char* {
+        const int j0 = j_a + t * BN_KEYS;
+        if (j0 + BN_KEYS > N) set_loff(N - 1 - j0);
+        return lbase + (int64_t)j0 * st * 2;
+    };
+    auto scalar_ptr = [](const char* p) -> const char* {   // keeps the base in scalar registers
+        const uint64_t u = reinterpret_cast<uint64_t>(p);
+        const uint64_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)u);
+        const uint64_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(u >> 32));
+        return reinterpret_cast<const char*>((hi << 32) | lo);
+    };
+    auto load_part = [&](const char* tile, bf16_t* stage, auto ic) __attribute__((always_inline)) {
+        constexpr int i = decltype(ic)::value;
+        const char* b = scalar_ptr(tile - i * 1024);           // the immediate adds it back
+        asm volatile("" : "+v"(loff[i]));   // keeps the offset a 32-bit register operand of the load
+        dma16<i * 1024>(reinterpret_cast<const bf16_t*>(b + loff[i]), stage + wave_slot);
+    };
+    auto load_tile = [&](const char* tile, bf16_t* stage) __attribute__((always_inline)) {
+        static_for<NI>([&](auto i) __attribute__((always_inline)) { load_part(tile, stage, i); });
     };
 
     // ---- fragment addresses: LDS byte addresses in the stage this wave reads next (they
@@ -271,7 +278,8 @@ __global__ __launch_bounds__(512, 1) void sparse_attn_kernel(
     f32x16 s[2];       // S^T tile: 64 keys x 32 query rows
     bf16x8 pf[4];      // its probabilities as B operand of the second contraction
 
-    auto softmax = [&](int j0) __attribute__((always_inline)) {
+    // `load`: the four loads of this wave's next tile go between the exponentials, evenly apart
+    auto softmax = [&](int j0, auto load) __attribute__((always_inline)) {
         // ---- causal mask (only in tiles that reach past the wave's first row),
         //      online softmax in base 2 with the 1/sqrt(d_h) scale folded into the exponent ----
         if (j0 + BN_KEYS - 1 > wave_min) {
@@ -312,9 +320,14 @@ __global__ __launch_bounds__(512, 1) void sparse_attn_kernel(
         float psum = 0.0f;
         // four scores at a time: exponentials, their sum and their bf16 pair conversions are
         // finished before the next four start (keeps only four probabilities live)
-#pragma unroll
-        for (int c = 0; c < 8; ++c) {
-            const int kt = c >> 2, v0 = (c & 3) * 4;
+        static_for<8>([&](auto chunk) __attribute__((always_inline)) {
+            constexpr int c = decltype(chunk)::value;
+            constexpr int kt = c >> 2, v0 = (c & 3) * 4;
+            if constexpr (c * NI % 8 == 0) {
+                __builtin_amdgcn_sched_barrier(0);
+                load(std::integral_constant<int, c * NI / 8>{});
+                __builtin_amdgcn_sched_barrier(0);
+            }
             float pv[4];
 #pragma unroll
             for (int u = 0; u < 4; ++u) pv[u] = __builtin_amdgcn_exp2f(fmaf(s[kt][v0 + u], scale_log2, -m_use));
@@ -329,7 +342,7 @@ __global__ __launch_bounds__(512, 1) void sparse_attn_kernel(
             dst[(v0 & 7) + 1] = lo[1];
             dst[(v0 & 7) + 2] = hi[0];
             dst[(v0 & 7) + 3] = hi[1];
-        }
+            });
         l_run += psum;
     };
     // End of a phase: all of this wave's global -> LDS loads but the newest tile's
@@ -400,17 +413,15 @@ __global__ __launch_bounds__(512, 1) void sparse_attn_kernel(
     };
 
     // ---- phases.  P0: A scores(0).  P(2t+1): A softmax(t) | B values(t-1), scores(t).
-    //      P(2t+2): A values(t), scores(t+1) | B softmax(t).  A wave issues its loads at the
-    //      end of its matrix phase, while its SIMD partner is in the softmax: next to a partner
-    //      that keeps the matrix pipe busy a vector-memory instruction takes several times as
-    //      long to issue.  Group A loads V(t+2) at the end of P(2t+2) into the stage V(t-1)
-    //      left at the end of P(2t+1); it is first read in P(2t+6); group A lets only its newest
-    //      tile stay in flight across a barrier, so V(t+2) has landed by the end of P(2t+4).
-    //      Group B loads K(t+3) at the end of P(2t+3) into the stage K(t) left at the end of
-    //      P(2t+1); first read in P(2t+6), landed by the end of P(2t+5) (group B waits for all
-    //      but its newest tile after issuing K(t+4)).  Every wave passes 2 n_tiles + 3
-    //      barriers; tiles past a wave's own last key only cost it the barriers and its loads.
-    //      The scores of tile my_tiles (computed from whatever its stage holds) are never used.
+    //      P(2t+2): A values(t), scores(t+1) | B softmax(t).  A wave issues its loads in its
+    //      softmax phase, between the exponentials.  Group A loads V(t+2) in P(2t+1) into the
+    //      stage of V(t-2), which group B left in P(2t-1); first read in P(2t+6).  Group A lets
+    //      only its newest tile stay in flight at the end of P(2t+1): V(t+1) has landed, and is
+    //      first read in P(2t+4).  Group B loads K(t+3) in P(2t+2) into the stage of K(t), which it
+    //      left in P(2t+1); at the end of P(2t+2) K(t+2) has landed, first read in P(2t+4).
+    //      Every wave passes 2 n_tiles + 3 barriers; tiles past a wave's own last key only cost it
+    //      the barriers and its loads.  The scores of tile my_tiles (computed from whatever its
+    //      stage holds) are never used.
     const int my_tiles = wave_limit < 0 ? 0 : max(0, min(wave_limit / BN_KEYS + 1 - ta, n_tiles));
     using yes = std::integral_constant<int, 1>;
     using no = std::integral_constant<int, 0>;
@@ -421,15 +432,15 @@ __global__ __launch_bounds__(512, 1) void sparse_attn_kernel(
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) kaddr[ks] += kd;
         if (also_v) {
-            const int vd = v_at == 2 ? -4 * TILE : 2 * TILE;
-            v_at = v_at == 2 ? 0 : v_at + 1;
+            const int vd = v_at == 3 ? -6 * TILE : 2 * TILE;
+            v_at = v_at == 3 ? 0 : v_at + 1;
 #pragma unroll
             for (int dt = 0; dt < DT; ++dt) vaddr[dt] += vd;
         }
     };
     if (grp == 0) {
-        dma_v(v_stage(0), j_a);
-        if (n_tiles > 1) dma_v(v_stage(1), j_a + BN_KEYS);
+        load_tile(tile_at(0), v_stage(0));
+        if (n_tiles > 1) load_tile(tile_at(1), v_stage(1));
         phase_end(n_tiles > 1);                            // K(0), V(0) are in place
         if (my_tiles > 0) {                                // P0
             matrix_phase(no{});
@@ -437,20 +448,23 @@ __global__ __launch_bounds__(512, 1) void sparse_attn_kernel(
         }
         phase_end(n_tiles > 1);
         for (int t = 0; t < n_tiles; ++t) {
-            if (t < my_tiles) softmax(j_a + t * BN_KEYS);
-            phase_end(t + 1 < n_tiles);                    // V(t) has landed
+            const char* next = tile_at(min(t + 2, n_tiles - 1));   // past the end: the last tile again, unused
+            if (t < my_tiles)
+                softmax(j_a + t * BN_KEYS, [&](auto i) __attribute__((always_inline)) { load_part(next, v_stage(t + 2), i); });
+            else
+                load_tile(next, v_stage(t + 2));
+            phase_end(true);                               // V(t), V(t+1) have landed
             if (t < my_tiles) {
                 matrix_phase(yes{});
                 advance(true);
             }
-            if (t + 2 < n_tiles) dma_v(v_stage(t + 2), j_a + (t + 2) * BN_KEYS);
             phase_end(true);
         }
         phase_end(false);
     } else {
-        dma_k(k_stage(0), j_a);
-        if (n_tiles > 1) dma_k(k_stage(1), j_a + BN_KEYS);
-        if (n_tiles > 2) dma_k(k_stage(2), j_a + 2 * BN_KEYS);
+        load_tile(tile_at(0), k_stage(0));
+        if (n_tiles > 1) load_tile(tile_at(1), k_stage(1));
+        if (n_tiles > 2) load_tile(tile_at(2), k_stage(2));
         if (n_tiles > 2) __builtin_amdgcn_s_waitcnt(((2 * NI) & 0xF) | (((2 * NI) >> 4) << 14) | (0x7 << 4) | (0xF << 8));
         phase_end(n_tiles > 1);                            // K(0), V(0) are in place
         phase_end(true);                                   // P0
@@ -460,16 +474,21 @@ __global__ __launch_bounds__(512, 1) void sparse_attn_kernel(
         }
         phase_end(n_tiles > 2);                            // K(1) has landed
         for (int t = 0; t < n_tiles; ++t) {
-            if (t < my_tiles) softmax(j_a + t * BN_KEYS);
-            phase_end(true);
+            const char* next = tile_at(min(t + 3, n_tiles - 1));   // past the end: the last tile again, unused
+            if (t < my_tiles)
+                softmax(j_a + t * BN_KEYS, [&](auto i) __attribute__((always_inline)) { load_part(next, k_stage(t), i); });
+            else
+                load_tile(next, k_stage(t));
+            phase_end(true);                               // K(t+2) has landed
             if (t < my_tiles) {
                 matrix_phase(yes{});
                 advance(true);
             }
-            if (t + 3 < n_tiles) dma_k(k_stage(t), j_a + (t + 3) * BN_KEYS);
-            phase_end(t + 3 < n_tiles);                    // K(t+2) has landed
+            phase_end(true);
         }
     }
+
+    __builtin_amdgcn_s_waitcnt((0x7 << 4) | (0xF << 8));   // the unused loads of the last tiles have landed
 
     // ---- normalise and write: lane holds 4 consecutive d per (dt, v/4) ----
     float l_tot = l_run + __shfl_xor(l_run, 32);
