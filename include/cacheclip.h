@@ -293,7 +293,7 @@ typedef struct cc_launch_override {
     int32_t gemm_mfma32;  /* 1: the ring loop with 32x32x16 MFMAs instead of 16x16x32 */
     int32_t gemm_gm;      /* > 0: row tiles per band of the XCD-aware tile order */
     int32_t gemm_splitk;  /* > 0: shares of K (1 = never split) */
-    int32_t attn_splits;  /* > 0: key splits of the attention launch (1 = never split) */
+    int32_t attn_splits;  /* > 0: pieces that the longest attention block is cut into, about (1 = never cut) */
 } cc_launch_override;
 cc_status cc_debug_set_launch(cc_ctx* ctx, const cc_launch_override* o);
 

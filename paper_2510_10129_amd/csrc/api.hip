@@ -144,7 +144,7 @@ cc_status cc_create(cc_ctx** out, const cc_model_desc* desc, void* hip_stream) {
     memset(c->prof_ms, 0, sizeof(c->prof_ms));
     memset(c->prof_n, 0, sizeof(c->prof_n));
     c->rope = nullptr; c->xn = nullptr; c->q = nullptr; c->o = nullptr; c->y = nullptr;
-    c->mn = nullptr; c->act = nullptr; c->attn_part = nullptr; c->gemm_part = nullptr; c->score = nullptr; c->n_sel = nullptr; c->flag = nullptr;
+    c->mn = nullptr; c->act = nullptr; c->attn_part = nullptr; c->attn_table = nullptr; c->gemm_part = nullptr; c->score = nullptr; c->n_sel = nullptr; c->flag = nullptr;
     c->pinned = nullptr;
     const cc_model_desc& m = c->m;
     const size_t Mc = (size_t)m.M_cap, nq = (size_t)m.H_q * m.d_h;
@@ -165,9 +165,10 @@ cc_status cc_create(cc_ctx** out, const cc_model_desc* desc, void* hip_stream) {
     alloc((void**)&c->y, Mc * m.d * 4);
     alloc((void**)&c->mn, Mc * m.d * 2);
     alloc((void**)&c->act, Mc * m.f * 2);
-    // room for up to 8 key splits of the attention while the launch is small enough to want them
-    c->attn_part_rows = (int64_t)std::min<size_t>(Mc * m.H_q * 8, 196608);
-    alloc((void**)&c->attn_part, (size_t)c->attn_part_rows * (m.d_h + 4) * 4);
+    // two pieces of blocks for every workgroup of an even attention grid: at most 512 slots, 69 MB
+    c->attn_slots = 2 * cc_attn_even_workgroups(m, m.M_cap, m.N_cap);
+    alloc((void**)&c->attn_part, (size_t)c->attn_slots * 256 * (m.d_h + 4) * 4);
+    alloc((void**)&c->attn_table, (1024 + 2) * sizeof(int));
     // shares of a split-K projection: up to 8 x [M_cap][widest padded output], at most 128 MB
     {
         const size_t widest = std::max<size_t>(std::max<size_t>((size_t)m.d, nq + 2 * (size_t)m.H_kv * m.d_h), 2 * (size_t)m.f);
@@ -200,7 +201,7 @@ cc_status cc_destroy(cc_ctx* c) {
     for (auto& p : c->used) { (void)hipEventDestroy(p.a); (void)hipEventDestroy(p.b); }
     for (auto& p : c->pool) { (void)hipEventDestroy(p.a); (void)hipEventDestroy(p.b); }
     (void)hipFree(c->rope); (void)hipFree(c->xn); (void)hipFree(c->q); (void)hipFree(c->o);
-    (void)hipFree(c->y); (void)hipFree(c->mn); (void)hipFree(c->act); (void)hipFree(c->attn_part); (void)hipFree(c->gemm_part);
+    (void)hipFree(c->y); (void)hipFree(c->mn); (void)hipFree(c->act); (void)hipFree(c->attn_part); (void)hipFree(c->attn_table); (void)hipFree(c->gemm_part);
     (void)hipFree(c->score);
     (void)hipFree(c->n_sel); (void)hipFree(c->flag);
     if (c->pinned) (void)hipHostFree(c->pinned);
@@ -410,7 +411,7 @@ cc_status cc_step_sparse_attention(cc_ctx* c, const void* q, int32_t M, const in
     }
     {
         cc_prof_scope ps(c, CC_K_ATTN);
-        cc_launch_attention((const bf16_t*)q, M, idx, c->m, *kv, (bf16_t*)o, c->attn_part, c->attn_part_rows, c->ovr, c->stream);
+        cc_launch_attention((const bf16_t*)q, M, idx, c->m, *kv, (bf16_t*)o, c->attn_part, c->attn_slots, c->attn_table, c->ovr, c->stream);
     }
     CC_HIP(c, hipGetLastError());
     return CC_OK;

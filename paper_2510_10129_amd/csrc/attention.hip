@@ -46,6 +46,7 @@
 // workgroup id modulo H_kv picks the kv head, so the workgroups resident on
 // one XCD walk the same K/V stream through that XCD's L2.
 #include "cc_internal.h"
+#include <algorithm>
 #include <type_traits>
 
 namespace {
@@ -99,11 +100,50 @@ __device__ __forceinline__ bf16x4 lds_read_tr(const bf16_t* p) {
     return __builtin_amdgcn_ds_read_tr16_b64_v4bf16((bf16x4 __attribute__((address_space(3)))*)p);
 }
 
-template <int D_H>
-__global__ __launch_bounds__(512, 1) void sparse_attn_kernel(
-    const bf16_t* __restrict__ q, int M, const int32_t* __restrict__ idx, int H_q, int H_kv,
+constexpr int LDS_TILES = 7;              // K tile t lives in stage t % 3, V tile t in stage 3 + t % 4
+
+// Group (0: A, 1: B) and slot of this wave.  The two waves that share a SIMD must land in different
+// groups: the SIMD id comes from the hardware id register (HW_ID bits 5:4), the first
+// wave to register on a SIMD joins group A (0), the second group B (1).  Should the
+// eight waves not sit two per SIMD, the split falls back to wave index order (correct,
+// but the phases of a SIMD's waves then no longer alternate).
+__device__ __forceinline__ void wave_role(int* simd_waves, int* group_waves, int& grp, int& widx) {
+    const int tid = threadIdx.x, lane = tid & 63;
+    if (tid < 4) simd_waves[tid] = 0;
+    if (tid < 2) group_waves[tid] = 0;
+    __syncthreads();
+    int a = 0, b = 0;
+    if (lane == 0) {
+        const int simd = __builtin_amdgcn_s_getreg(((2 - 1) << 11) | (4 << 6) | 4);
+        a = atomicAdd(&simd_waves[simd & 3], 1) & 1;
+        b = atomicAdd(&group_waves[a], 1);
+    }
+    grp = __builtin_amdgcn_readfirstlane(a);
+    widx = __builtin_amdgcn_readfirstlane(b);
+    __syncthreads();
+    if (group_waves[0] != 4) {
+        const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+        grp = w >> 2;
+        widx = w & 3;
+    }
+}
+
+// last position that the 256 columns of row tile rt see (rows are sorted)
+__device__ __forceinline__ int last_key(const int32_t* idx, int M, int g, int rt) {
+    return idx[min(M - 1, (rt * 256 + 255) / g)];
+}
+
+// Key tiles ta .. ta + n_tiles - 1 (n_tiles >= 1) of the 256 columns of row tile rt and kv head kvh.
+// PIECE and slot >= 0: the sums stay unnormalised and go to part's slot.  Off: type
+// of the lane offsets of the global -> LDS loads.  Can be called again by the same
+// workgroup: every wave's reads of LDS lie before its last barrier, and a wave only loads
+// into rows that it has loaded (and waited for) itself.
+template <int D_H, bool PIECE, class Off>
+__device__ __forceinline__ void attend(
+    const bf16_t* __restrict__ q, int M, const int32_t* __restrict__ idx, int H_q, int g,
     const bf16_t* __restrict__ Kc, const bf16_t* __restrict__ Vc, int64_t st, int64_t sh, int N,
-    bf16_t* __restrict__ o, int n_row_tiles, float scale_log2, int n_splits, float* __restrict__ part) {
+    bf16_t* __restrict__ o, float scale_log2, float* __restrict__ part, bf16_t* smem, int grp, int widx,
+    int kvh, int rt, int ta, int n_tiles, int slot) {
     constexpr int KS = D_H / 16;          // k-steps of the QK^T contraction
     constexpr int DT = D_H / 32;          // 32-row tiles of O^T
     constexpr int CPRW = D_H / 8;         // 16-byte chunks per cache row
@@ -111,67 +151,18 @@ __global__ __launch_bounds__(512, 1) void sparse_attn_kernel(
     constexpr int NI = BN_KEYS / RPI / 4; // such instructions per wave, tile and tensor
 
     constexpr int TILE = BN_KEYS * D_H;   // elements of one K or V tile
-    // K tile t lives in stage t % 3, V tile t in stage 3 + t % 4
-    __shared__ __align__(16) bf16_t smem[7 * TILE];
     auto k_stage = [&](int t) __attribute__((always_inline)) { return smem + (t % 3) * TILE; };
     auto v_stage = [&](int t) __attribute__((always_inline)) { return smem + (3 + t % 4) * TILE; };
 
-    __shared__ int simd_waves[4], group_waves[2];
-
-    const int tid = threadIdx.x, lane = tid & 63;
-    // Group and slot of this wave.  The two waves that share a SIMD must land in different
-    // groups: the SIMD id comes from the hardware id register (HW_ID bits 5:4), the first
-    // wave to register on a SIMD joins group A (0), the second group B (1).  Should the
-    // eight waves not sit two per SIMD, the split falls back to wave index order (correct,
-    // but the phases of a SIMD's waves then no longer alternate).
-    int grp, widx;
-    {
-        if (tid < 4) simd_waves[tid] = 0;
-        if (tid < 2) group_waves[tid] = 0;
-        __syncthreads();
-        int a = 0, b = 0;
-        if (lane == 0) {
-            const int simd = __builtin_amdgcn_s_getreg(((2 - 1) << 11) | (4 << 6) | 4);
-            a = atomicAdd(&simd_waves[simd & 3], 1) & 1;
-            b = atomicAdd(&group_waves[a], 1);
-        }
-        grp = __builtin_amdgcn_readfirstlane(a);
-        widx = __builtin_amdgcn_readfirstlane(b);
-        __syncthreads();
-        if (group_waves[0] != 4) {
-            const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-            grp = w >> 2;
-            widx = w & 3;
-        }
-    }
+    const int lane = threadIdx.x & 63;
     const int wave = widx;                              // role in the cooperative tile loads
-    const int g = H_q / H_kv;
-    const int kvh = blockIdx.x % H_kv;
-    const int rt = n_row_tiles - 1 - blockIdx.x / H_kv;
-
     const int qr = lane & 31, hf = lane >> 5;
-    const int col = rt * 256 + (grp * 4 + widx) * 32 + qr;       // flat (token, head) column
+    const int col_in = (grp * 4 + widx) * 32 + qr;      // column within the row tile
+    const int col = rt * 256 + col_in;                  // flat (token, head) column
     const int mi = col / g, hg = col - mi * g;
     const bool valid = mi < M;
     const int limit = valid ? idx[mi] : -1;
-    const int last_row = min(M - 1, (rt * 256 + 255) / g);
-    const int kmax = idx[last_row];                    // rows are sorted: the block's longest span
-    // Key split: workgroup blockIdx.y of n_splits takes key tiles ta .. ta + n_tiles - 1 of the
-    // block's span and leaves unnormalised fp32 partial results for the merge kernel.
-    const int all_tiles = kmax / BN_KEYS + 1;
-    const int tiles_per = (all_tiles + n_splits - 1) / n_splits;
-    const int ta = blockIdx.y * tiles_per;
-    const int n_tiles = min(all_tiles - ta, tiles_per);
-    const int j_a = ta * BN_KEYS;                      // first key of this workgroup
-    const int64_t part_row = valid ? ((int64_t)blockIdx.y * M + mi) * H_q + kvh * g + hg : 0;
-    if (n_tiles <= 0) {                                // more splits than tiles: an empty part
-        if (valid && hf == 0) {
-            float* pm = part + part_row * (D_H + 4) + D_H;
-            pm[0] = -INFINITY;
-            pm[1] = 0.0f;
-        }
-        return;
-    }
+    const int j_a = ta * BN_KEYS;                       // first key of this piece
 
     // wave-wide largest limit (tiles beyond it are skipped by this wave) and smallest
     // limit of a valid row (tiles that end at or below it need no mask)
@@ -220,10 +211,10 @@ __global__ __launch_bounds__(512, 1) void sparse_attn_kernel(
     // cache (only a workgroup's last one can) rows past N-1 are clamped (they are masked anyway).
     const char* const lbase = reinterpret_cast<const char*>(grp == 0 ? vbase : kbase);
     const int l_col = grp == 0 ? v_col : k_col;
-    uint32_t loff[NI];
+    Off loff[NI];
     auto set_loff = [&](int rmax) __attribute__((always_inline)) {
 #pragma unroll
-        for (int i = 0; i < NI; ++i) loff[i] = (uint32_t)(min(r0 + i * 4 * RPI, rmax) * (int)st + l_col) * 2;
+        for (int i = 0; i < NI; ++i) loff[i] = ((Off)min(r0 + i * 4 * RPI, rmax) * (Off)st + (Off)l_col) * 2;
     };
     set_loff(BN_KEYS);
     auto tile_at = [&](int t) __attribute__((always_inline)) -> const char* {
@@ -240,7 +231,7 @@ __global__ __launch_bounds__(512, 1) void sparse_attn_kernel(
     auto load_part = [&](const char* tile, bf16_t* stage, auto ic) __attribute__((always_inline)) {
         constexpr int i = decltype(ic)::value;
         const char* b = scalar_ptr(tile - i * 1024);           // the immediate adds it back
-        asm volatile("" : "+v"(loff[i]));   // keeps the offset a 32-bit register operand of the load
+        asm volatile("" : "+v"(loff[i]));   // keeps the (32-bit) offset a register operand of the load
         dma16<i * 1024>(reinterpret_cast<const bf16_t*>(b + loff[i]), stage + wave_slot);
     };
     auto load_tile = [&](const char* tile, bf16_t* stage) __attribute__((always_inline)) {
@@ -493,7 +484,7 @@ __global__ __launch_bounds__(512, 1) void sparse_attn_kernel(
     // ---- normalise and write: lane holds 4 consecutive d per (dt, v/4) ----
     float l_tot = l_run + __shfl_xor(l_run, 32);
     if (!valid) return;
-    if (n_splits == 1) {
+    if (!PIECE || slot < 0) {
         const float inv = 1.0f / l_tot;
         bf16_t* op = o + ((int64_t)mi * H_q + kvh * g + hg) * D_H;
 #pragma unroll
@@ -506,8 +497,9 @@ __global__ __launch_bounds__(512, 1) void sparse_attn_kernel(
                 *reinterpret_cast<bf16x4*>(op + dt * 32 + 8 * vq + 4 * hf) = w;
             }
     } else {
-        // part row: d_h unnormalised sums, then the exponent's reference point and the row sum
-        float* pp = part + part_row * (D_H + 4);
+        // as the registers lie, so that every store is one contiguous KB: [wave][D_H / 8][lane] four
+        // unnormalised sums, then [lane] the exponent's reference point and the row sum
+        float* pp = part + (int64_t)slot * 256 * (D_H + 4) + (grp * 4 + widx) * 32 * (D_H + 4);
 #pragma unroll
         for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
@@ -515,98 +507,236 @@ __global__ __launch_bounds__(512, 1) void sparse_attn_kernel(
                 f32x4 w;
 #pragma unroll
                 for (int u = 0; u < 4; ++u) w[u] = acc_o[dt][vq * 4 + u];
-                *reinterpret_cast<f32x4*>(pp + dt * 32 + 8 * vq + 4 * hf) = w;
+                *reinterpret_cast<f32x4*>(pp + (dt * 4 + vq) * 256 + lane * 4) = w;
             }
-        if (hf == 0) {
-            pp[D_H] = m_run;
-            pp[D_H + 1] = l_tot;
+        *reinterpret_cast<float2*>(pp + 32 * D_H + lane * 2) = make_float2(m_run, l_tot);
+    }
+}
+
+// One block of 256 columns per workgroup, longest first.  Off: 64 bits only for token strides that
+// a 32-bit lane offset cannot hold.
+#define CC_ATTN_ARGS                                                                                        \
+    const bf16_t *__restrict__ q, int M, const int32_t *__restrict__ idx, int H_q, int H_kv,                \
+        const bf16_t *__restrict__ Kc, const bf16_t *__restrict__ Vc, int64_t st, int64_t sh, int N,        \
+        bf16_t *__restrict__ o, int n_row_tiles, float scale_log2
+template <int D_H, class Off>
+__device__ __forceinline__ void attend_block(CC_ATTN_ARGS) {
+    __shared__ __align__(16) bf16_t smem[LDS_TILES * BN_KEYS * D_H];
+    __shared__ int simd_waves[4], group_waves[2];
+    int grp, widx;
+    wave_role(simd_waves, group_waves, grp, widx);
+    const int g = H_q / H_kv, kvh = blockIdx.x % H_kv, rt = n_row_tiles - 1 - blockIdx.x / H_kv;
+    attend<D_H, false, Off>(q, M, idx, H_q, g, Kc, Vc, st, sh, N, o, scale_log2, nullptr, smem, grp, widx, kvh, rt, 0,
+                            last_key(idx, M, g, rt) / BN_KEYS + 1, -1);
+}
+template <int D_H>
+__global__ __launch_bounds__(512, 1) void sparse_attn_kernel(CC_ATTN_ARGS) {
+    attend_block<D_H, uint32_t>(q, M, idx, H_q, H_kv, Kc, Vc, st, sh, N, o, n_row_tiles, scale_log2);
+}
+template <int D_H>
+__global__ __launch_bounds__(512, 1) void wide_stride_attn_kernel(CC_ATTN_ARGS) {
+    attend_block<D_H, uint64_t>(q, M, idx, H_q, H_kv, Kc, Vc, st, sh, N, o, n_row_tiles, scale_log2);
+}
+
+// Even grid.  A block costs as many key tiles as its last row can see, so a grid of a few hundred
+// blocks ends unevenly: its makespan is the longest block or one more round.  Here every workgroup (one
+// per CU) takes the same number of units of one long sequence: the blocks of kv head 0 by row
+// tile, those of head 1, ...; a block of L key tiles is L + EVEN_START units long, the first of
+// them for what a block costs besides its tiles (query loads, first tiles, output).  A range
+// covers some whole blocks and, at its ends, pieces of two; the pieces go to slots 2 w and 2 w + 1
+// of range w (a piece of the block that the range starts in, of a later one) and
+// attn_merge_kernel combines the pieces of a block.  Consecutive ranges run on one XCD, so that its
+// L2 serves one kv head when H_kv = 8.
+constexpr int EVEN_START = 5;             // 3 and 5 units measured: 5 is 1 % of the layer faster
+constexpr int EVEN_RANGES = 256;          // one a CU
+constexpr int EVEN_MAX_TILES = 1024;      // row tiles whose first units fit the LDS table
+// table: [n_row_tiles + 2] the first unit of every row tile within a head, their sum, units per range
+template <int D_H>
+__global__ __launch_bounds__(512, 1) void even_attn_kernel(CC_ATTN_ARGS, int per_min, float* __restrict__ part,
+                                                           int* __restrict__ table) {
+    __shared__ __align__(16) bf16_t smem[LDS_TILES * BN_KEYS * D_H];
+    __shared__ int simd_waves[4], group_waves[2], wave_units[8];
+    __shared__ int pre[EVEN_MAX_TILES + 1];
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int g = H_q / H_kv;
+    int grp, widx;
+    wave_role(simd_waves, group_waves, grp, widx);
+
+    // first unit of every row tile: exclusive scan, two row tiles a thread
+    int len[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+        len[i] = 2 * tid + i < n_row_tiles ? last_key(idx, M, g, 2 * tid + i) / BN_KEYS + 1 + EVEN_START : 0;
+    int inc = len[0] + len[1];
+    for (int off = 1; off < 64; off <<= 1) {
+        const int v = __shfl_up(inc, off);
+        if (lane >= off) inc += v;
+    }
+    if (lane == 63) wave_units[w] = inc;
+    __syncthreads();
+    int base = inc - len[0] - len[1];
+    for (int i = 0; i < w; ++i) base += wave_units[i];
+    pre[2 * tid] = base;
+    pre[2 * tid + 1] = base + len[0];
+    if (tid == 511) pre[EVEN_MAX_TILES] = base + len[0] + len[1];
+    __syncthreads();
+    const int head_units = __builtin_amdgcn_readfirstlane(pre[n_row_tiles]);   // tiles past the last have no units
+    const int total = head_units * H_kv, n_wg = gridDim.x;
+    const int per = max(per_min, (total + n_wg - 1) / n_wg);
+    if (blockIdx.x == 0) {
+        for (int t = tid; t <= n_row_tiles; t += 512) table[t] = pre[t];
+        if (tid == 0) table[n_row_tiles + 1] = per;
+    }
+    // workgroup ids go round-robin to the 8 XCDs: each gets consecutive ranges
+    const int x = blockIdx.x & 7, xq = n_wg >> 3, xr = n_wg & 7;
+    const int range = x * xq + min(x, xr) + (int)(blockIdx.x >> 3);
+    int u = range * per, stop = min(u + per, total);     // units of the whole sequence, then of head kvh
+    if (u < total) {
+        int kvh = u / head_units;
+        u -= kvh * head_units;
+        stop -= kvh * head_units;
+        int rt = 0;                                      // last row tile whose first unit is <= u
+        for (int hi = n_row_tiles - 1; rt < hi;) {
+            const int mid = (rt + hi + 1) >> 1;
+            if (pre[mid] <= u) rt = mid; else hi = mid - 1;
+        }
+        rt = __builtin_amdgcn_readfirstlane(rt);
+        for (int later = 0; u < stop; later = 1) {
+            const int b0 = __builtin_amdgcn_readfirstlane(pre[rt]), b1 = __builtin_amdgcn_readfirstlane(pre[rt + 1]);
+            const int ta = max(0, u - b0 - EVEN_START), te = min(b1, stop) - b0 - EVEN_START;
+            if (te > ta) {
+                const bool whole = ta == 0 && te == b1 - b0 - EVEN_START;
+                attend<D_H, true, uint32_t>(q, M, idx, H_q, g, Kc, Vc, st, sh, N, o, scale_log2, part, smem, grp, widx,
+                                            kvh, rt, ta, te - ta, whole ? -1 : 2 * range + later);
+            }
+            u = b1;
+            if (++rt == n_row_tiles) {
+                rt = 0;
+                ++kvh;
+                u = 0;
+                stop -= head_units;
+            }
         }
     }
 }
 
-// Merge of a key-split launch: o = sum_s 2^(m_s - m) O_s / sum_s 2^(m_s - m) l_s with m = max m_s.
-// One thread per (token, head) row and four output elements.
+// Combines the pieces of the blocks that an even grid has cut:
+// o = sum_s 2^(m_s - m) O_s / sum_s 2^(m_s - m) l_s with m = max m_s, pieces in the order of their keys.
+// Workgroup (block, 32 of its columns = one wave of the attention kernel); a thread holds the same
+// elements as the lane that wrote them, a wave of this kernel D_H / 4 of a column's.  Four
+// pieces at a time, so that their loads are out together.
 template <int D_H>
-__global__ __launch_bounds__(256) void attn_merge_kernel(const float* __restrict__ part, int64_t rows,
-                                                         int n_splits, bf16_t* __restrict__ o) {
-    constexpr int TPR = D_H / 4;
-    const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    const int64_t row = t / TPR;
-    const int d0 = (int)(t % TPR) * 4;
-    if (row >= rows) return;
-    float m = -INFINITY;
-    for (int sp = 0; sp < n_splits; ++sp) m = fmaxf(m, part[(sp * rows + row) * (D_H + 4) + D_H]);
-    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-    float l = 0.0f;
-    for (int sp = 0; sp < n_splits; ++sp) {
-        const float* pp = part + (sp * rows + row) * (D_H + 4);
-        const float ms = pp[D_H];
-        if (ms == -INFINITY) continue;                 // an empty part: its sums were never written
-        const float w = __builtin_amdgcn_exp2f(ms - m);
-        const f32x4 v = *reinterpret_cast<const f32x4*>(pp + d0);
-        acc += v * w;
-        l += pp[D_H + 1] * w;
+__global__ __launch_bounds__(256) void attn_merge_kernel(const float* __restrict__ part, const int* __restrict__ table,
+                                                         int M, int H_q, int H_kv, int n_row_tiles,
+                                                         bf16_t* __restrict__ o) {
+    constexpr int NV = D_H / 32;                         // 16-byte groups of a thread
+    const int g = H_q / H_kv, kvh = blockIdx.x / n_row_tiles, rt = blockIdx.x - kvh * n_row_tiles;
+    const int per = table[n_row_tiles + 1], head = kvh * table[n_row_tiles];
+    const int first = head + table[rt], end = head + table[rt + 1];
+    const int w0 = (first + EVEN_START) / per, w1 = (end - 1) / per;   // the ranges that hold its key tiles
+    if (w0 == w1) return;
+    const int lane = threadIdx.x & 63, v0 = (threadIdx.x >> 6) * NV;
+    const int col = rt * 256 + blockIdx.y * 32 + (lane & 31), mi = col / g, hg = col - mi * g;
+    if (mi >= M) return;
+    float m = -INFINITY, l = 0.0f;
+    f32x4 acc[NV];
+#pragma unroll
+    for (int i = 0; i < NV; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int wb = w0; wb <= w1; wb += 4) {
+        f32x4 v[4][NV];
+        float2 ml[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int w = min(wb + k, w1);               // past the end: the last piece again, with weight 0
+            const float* pp = part + (int64_t)(2 * w + (w * per < first ? 1 : 0)) * 256 * (D_H + 4) + blockIdx.y * 32 * (D_H + 4);
+            ml[k] = *reinterpret_cast<const float2*>(pp + 32 * D_H + lane * 2);
+#pragma unroll
+            for (int i = 0; i < NV; ++i) v[k][i] = *reinterpret_cast<const f32x4*>(pp + (v0 + i) * 256 + lane * 4);
+        }
+        float mn = m;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) mn = fmaxf(mn, ml[k].x);
+        const float ref = mn == -INFINITY ? 0.0f : mn;   // no key of this column so far
+        const float keep = __builtin_amdgcn_exp2f(m - ref);
+        l *= keep;
+#pragma unroll
+        for (int i = 0; i < NV; ++i) acc[i] *= keep;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const float f = wb + k <= w1 ? __builtin_amdgcn_exp2f(ml[k].x - ref) : 0.0f;
+            l += ml[k].y * f;
+#pragma unroll
+            for (int i = 0; i < NV; ++i) acc[i] += v[k][i] * f;
+        }
+        m = mn;
     }
     const float inv = l > 0.0f ? 1.0f / l : 0.0f;
-    bf16x4 w;
+    bf16_t* op = o + ((int64_t)mi * H_q + kvh * g + hg) * D_H + 4 * (lane >> 5);
 #pragma unroll
-    for (int u = 0; u < 4; ++u) w[u] = (bf16_t)(acc[u] * inv);
-    *reinterpret_cast<bf16x4*>(o + row * D_H + d0) = w;
+    for (int i = 0; i < NV; ++i) {
+        bf16x4 r;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) r[e] = (bf16_t)(acc[i][e] * inv);
+        *reinterpret_cast<bf16x4*>(op + 8 * (v0 + i)) = r;
+    }
 }
 
 }  // namespace
 
+int cc_attn_even_workgroups(const cc_model_desc& m, int64_t M, int64_t N) {
+    // a range of fewer than five units would be mostly start and merge
+    const int64_t tiles = (M * (m.H_q / m.H_kv) + 255) / 256 * m.H_kv;
+    const int64_t units = tiles * ((N + BN_KEYS - 1) / BN_KEYS + EVEN_START);
+    return (int)std::min<int64_t>(EVEN_RANGES, std::max(units / 5 + 1, 8 * tiles));
+}
+
 void cc_launch_attention(const bf16_t* q, int M, const int32_t* idx, const cc_model_desc& m,
-                         const cc_kv_layer& kv, bf16_t* o, float* part, int64_t part_rows,
+                         const cc_kv_layer& kv, bf16_t* o, float* part, int slots, int* table,
                          const cc_launch_override& ovr, hipStream_t s) {
     if (M <= 0) return;
     const int g = m.H_q / m.H_kv;
     const int n_row_tiles = (int)(((int64_t)M * g + 255) / 256);   // 256 (token, head) columns each
     const float scale_log2 = 1.4426950408889634f / sqrtf((float)m.d_h);
-    // A grid that does not fill the chip is split along the keys: S workgroups per block, each over
-    // 1/S of the block's key tiles, and a merge pass.  Model, in key-tile times: the longest
-    // workgroup (t_max / S tiles) or the whole work spread over the CUs, whichever is longer; the
-    // work is taken as half of blocks x t_max (spans grow with the position of the block's last
-    // token) with 30 % on top for the uneven end, as measured; plus the merge's traffic.
-    const int64_t rows = (int64_t)M * m.H_q;
-    static const int n_cu = [] {
-        int dev = 0, n = 256;
-        if (hipGetDevice(&dev) == hipSuccess)
-            (void)hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev);
-        return n > 0 ? n : 256;
-    }();
     const int n_wg = n_row_tiles * m.H_kv;
     const int t_max = (kv.N + BN_KEYS - 1) / BN_KEYS;
-    int S = 1;
-    if (ovr.attn_splits > 0) {                        // test override (cc_debug_set_launch)
-        S = ovr.attn_splits;
-    } else if (part && n_wg < 2 * n_cu) {
-        const double tile_us = m.d_h == 128 ? 1.9 : 1.0;
-        const double spread = 1.3 * 0.5 * (double)n_wg * t_max / n_cu;
-        double best = t_max > spread ? t_max : spread;
-        for (int sp = 2; sp <= 8 && sp <= t_max; ++sp) {
-            if (sp * rows > part_rows) break;
-            const double longest = (double)((t_max + sp - 1) / sp);
-            const double merge_us = 3.0 + (double)(sp * rows) * (m.d_h + 4) * 4 / 4.0e6;
-            const double c = (longest > spread ? longest : spread) + merge_us / tile_us;
-            if (c < 0.95 * best) best = c, S = sp;
-        }
+#define CC_ATTN_LAUNCH(KERN, GRID, ...)                                                                       \
+    do {                                                                                                      \
+        if (m.d_h == 128)                                                                                     \
+            hipLaunchKernelGGL(KERN<128>, dim3(GRID), dim3(512), 0, s, q, M, idx, m.H_q, m.H_kv,              \
+                               (const bf16_t*)kv.K, (const bf16_t*)kv.V, kv.stride_token, kv.stride_head,     \
+                               kv.N, o, n_row_tiles, scale_log2, ##__VA_ARGS__);                              \
+        else                                                                                                  \
+            hipLaunchKernelGGL(KERN<64>, dim3(GRID), dim3(512), 0, s, q, M, idx, m.H_q, m.H_kv,               \
+                               (const bf16_t*)kv.K, (const bf16_t*)kv.V, kv.stride_token, kv.stride_head,     \
+                               kv.N, o, n_row_tiles, scale_log2, ##__VA_ARGS__);                              \
+    } while (0)
+    // 64 rows of a tile, 2 bytes an element, in an unsigned 32-bit lane offset
+    const bool wide = kv.stride_token >= (1ll << 32) / (2 * (BN_KEYS + 1));
+    // Even grid where one block per workgroup would leave much of the chip idle: up to 1.25 blocks
+    // per CU.  Its ranges walk their keys out of step, so that an XCD's L2 serves less of the
+    // cache traffic and a tile takes 2.1 us against 1.8, and the pieces are written and read once more.
+    // Microseconds with one block per workgroup and with even ranges, H_q = 32, H_kv = 8, d_h = 128:
+    // 16k context, 144 blocks 358 / 192, 264: 403 / 335, 320: 417 / 382, 432: 489 / 496; 4k context,
+    // 168: 102 / 76, 424: 125 / 150; four kv heads at 29k, 328: 700 / 597.
+    const int per_min = ovr.attn_splits > 1 ? (t_max + ovr.attn_splits - 1) / ovr.attn_splits : 5;   // the override: about that many pieces of the longest block
+    const bool even = ovr.attn_splits > 1 || (ovr.attn_splits == 0 && 4 * n_wg <= 5 * EVEN_RANGES);
+    const int64_t most_units = (int64_t)n_wg * (t_max + EVEN_START);
+    int ranges = 0;
+    if (even && !wide && n_row_tiles <= EVEN_MAX_TILES && most_units < (1 << 30)) {
+        ranges = (int)std::min<int64_t>(most_units / per_min + 1, slots / 2);
+        if (ovr.attn_splits == 0) ranges = std::min(ranges, EVEN_RANGES);
     }
-    if (S < 1 || !part || S * rows > part_rows) S = 1;
-    if (S > t_max) S = t_max;
-    dim3 grid(n_row_tiles * m.H_kv, S), block(512);
-    if (m.d_h == 128)
-        hipLaunchKernelGGL(sparse_attn_kernel<128>, grid, block, 0, s, q, M, idx, m.H_q, m.H_kv,
-                           (const bf16_t*)kv.K, (const bf16_t*)kv.V, kv.stride_token, kv.stride_head,
-                           kv.N, o, n_row_tiles, scale_log2, S, part);
-    else
-        hipLaunchKernelGGL(sparse_attn_kernel<64>, grid, block, 0, s, q, M, idx, m.H_q, m.H_kv,
-                           (const bf16_t*)kv.K, (const bf16_t*)kv.V, kv.stride_token, kv.stride_head,
-                           kv.N, o, n_row_tiles, scale_log2, S, part);
-    if (S > 1) {
-        const int64_t threads = rows * (m.d_h / 4);
-        dim3 mg((unsigned)((threads + 255) / 256));
-        if (m.d_h == 128) hipLaunchKernelGGL(attn_merge_kernel<128>, mg, dim3(256), 0, s, part, rows, S, o);
-        else hipLaunchKernelGGL(attn_merge_kernel<64>, mg, dim3(256), 0, s, part, rows, S, o);
+    if (ranges > 0) {
+        CC_ATTN_LAUNCH(even_attn_kernel, ranges, per_min, part, table);
+        const dim3 mg(n_wg, 8);
+        if (m.d_h == 128)
+            hipLaunchKernelGGL(attn_merge_kernel<128>, mg, dim3(256), 0, s, part, table, M, m.H_q, m.H_kv, n_row_tiles, o);
+        else
+            hipLaunchKernelGGL(attn_merge_kernel<64>, mg, dim3(256), 0, s, part, table, M, m.H_q, m.H_kv, n_row_tiles, o);
+    } else if (wide) {
+        CC_ATTN_LAUNCH(wide_stride_attn_kernel, n_wg);
+    } else {
+        CC_ATTN_LAUNCH(sparse_attn_kernel, n_wg);
     }
+#undef CC_ATTN_LAUNCH
 }

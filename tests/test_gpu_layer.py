@@ -389,6 +389,61 @@ def test_stage_attention_score_jumps_on_both_sides_of_the_rescale_threshold(spli
     ctx.close()
 
 
+@pytest.mark.parametrize("splits", [0, 3, 64])
+@pytest.mark.parametrize("H_q,H_kv,d_h,N,M", [(8, 8, 128, 1300, 600),     # ranges over several row tiles and heads
+                                              (14, 2, 64, 700, 257),      # 257 rows: the last row tile holds 7 columns
+                                              (32, 1, 128, 129, 1),       # one row tile of 32 columns
+                                              (12, 3, 128, 4100, 64)])    # three heads, ranges of a block's middle
+def test_stage_attention_even_grid(H_q, H_kv, d_h, N, M, splits):
+    """Equal ranges of the blocks' key tiles: cut in a block's first units, between tiles, at block
+    and head ends, with more ranges than the workspace has slots for; against the oracle."""
+    rng = np.random.default_rng(N + M)
+    model = ModelShape(H_q * d_h, H_q, H_kv, d_h, 64, 1e4, 1e-5, False, 1)
+    idx = np.sort(rng.choice(N - 1, size=M - 1, replace=False)) if M > 1 else np.zeros(0, np.int64)
+    idx = np.r_[idx, N - 1]
+    qb = gen.f32_to_bf16_bits((rng.standard_normal((M, H_q, d_h)) * 2.0).astype(np.float32))
+    Kb = gen.f32_to_bf16_bits(rng.standard_normal((N, H_kv, d_h)).astype(np.float32))
+    Vb = gen.f32_to_bf16_bits(rng.standard_normal((N, H_kv, d_h)).astype(np.float32))
+    ctx = _ctx(model, N, M)
+    ctx.debug_set_launch(attn_splits=splits)
+    kv, q, o = cc.KVLayer(dev_bf16(Kb), dev_bf16(Vb)), dev_bf16(qb).view(M, -1), []
+    for _ in range(2):                              # the second call meets the workspace of the first
+        o.append(torch.full((M, H_q * d_h), float("nan"), dtype=torch.bfloat16, device=DEV))
+        ctx.step_sparse_attention(q, M, dev_i32(idx), kv, o[-1], _lib.FLAG_CHECK_IDX)
+    torch.cuda.synchronize()
+    qf, Kf, Vf = obf.bits_to_f64(qb), obf.bits_to_f64(Kb), obf.bits_to_f64(Vb)
+    ref = np.stack([layer.attend_row(qf[i], Kf, Vf, int(idx[i]), H_q // H_kv)[0].reshape(-1) for i in range(M)])
+    mx, mn = err_stats(bits_f64(host_bits(o[0])), ref)
+    assert mx <= MAX_ABS and mn <= MEAN_ABS, (mx, mn)
+    assert torch.equal(o[0], o[1])
+    ctx.close()
+
+
+def test_stage_attention_token_stride_past_32_bit_offsets():
+    """Token strides whose 64-row tiles do not fit an unsigned 32-bit byte offset."""
+    H_q, H_kv, d_h, N, st = 4, 1, 128, 3, (1 << 25) + 8
+    rng = np.random.default_rng(5)
+    model = ModelShape(H_q * d_h, H_q, H_kv, d_h, 64, 1e4, 1e-5, False, 1)
+    qb = gen.f32_to_bf16_bits(rng.standard_normal((N, H_q, d_h)).astype(np.float32))
+    Kb = gen.f32_to_bf16_bits(rng.standard_normal((N, H_kv, d_h)).astype(np.float32))
+    Vb = gen.f32_to_bf16_bits(rng.standard_normal((N, H_kv, d_h)).astype(np.float32))
+    far = []
+    for bits in (Kb, Vb):
+        t = torch.zeros(st * (N - 1) + d_h, dtype=torch.bfloat16, device=DEV)
+        v = t.as_strided((N, H_kv, d_h), (st, d_h, 1))
+        v.copy_(dev_bf16(bits))
+        far.append(v)
+    ctx = _ctx(model, N, N)
+    o = torch.full((N, H_q * d_h), float("nan"), dtype=torch.bfloat16, device=DEV)
+    ctx.step_sparse_attention(dev_bf16(qb).view(N, -1), N, dev_i32(np.arange(N)), cc.KVLayer(*far), o)
+    torch.cuda.synchronize()
+    qf, Kf, Vf = obf.bits_to_f64(qb), obf.bits_to_f64(Kb), obf.bits_to_f64(Vb)
+    ref = np.stack([layer.attend_row(qf[i], Kf, Vf, i, H_q // H_kv)[0].reshape(-1) for i in range(N)])
+    mx, mn = err_stats(bits_f64(host_bits(o)), ref)
+    assert mx <= MAX_ABS and mn <= MEAN_ABS, (mx, mn)
+    ctx.close()
+
+
 def test_stage_attention_never_reads_past_the_valid_slots():
     """The cache allocation is longer than kv->N and holds NaN beyond it: the last key tile is
     cut at N (loads are clamped to slot N-1), so nothing of it reaches the output."""
