@@ -10,7 +10,7 @@
 // Tiling: one workgroup of WAVES_M x WAVES_N waves computes a BM x BN tile.  Operands
 // go from global memory straight into LDS (16-byte global->LDS loads, no register
 // staging), XOR-swizzled so that the 16-byte fragment reads are conflict-free on the
-// 64-bank LDS.  Four K loops:
+// 64-bank LDS.  Five K loops:
 //   ping-pong (K % 128 == 0; gemm_ring16_kernel_pp, the 256x256 tile) two LDS buffers of
 //          64 columns filled half tile by half tile, four phases per 64 columns, the two
 //          waves of a SIMD alternating between fragment reads and MFMAs.
@@ -20,6 +20,8 @@
 //          two-stage pipeline exposes; one barrier per slice, waits by explicit vmcnt;
 //          v_mfma_f32_16x16x32_bf16 (one k-step per slice) with hand-written fragment
 //          reads and hand-counted lgkmcnt waits.
+//   thin   (any K % 64 == 0; gemm_thin_kernel, 64x128 tiles) for few rows: six slots of 64
+//          columns, so that the weight stream keeps five of them on the way.
 //   ring   (gemm_ring_kernel) the same ring with v_mfma_f32_32x32x16_bf16 and
 //          compiler-scheduled fragment reads; kept as a cross-check behind
 //          cc_debug_set_launch.
@@ -28,6 +30,7 @@
 // The accumulators are written back through LDS so that every global store is
 // 16 or 32 contiguous bytes per lane along the row.
 #include "cc_internal.h"
+#include <algorithm>
 #include <type_traits>
 
 namespace {
@@ -207,17 +210,17 @@ struct EpiDown {
 };
 
 // Split-K: workgroup row blockIdx.y of a launch computes the products over its share of K and
-// leaves its fp32 tile in a workspace [share][tile slot][256][256] (slot = the tile's index
+// leaves its fp32 tile in a workspace [share][tile slot][ROWS][BN] (slot = the tile's index
 // within the launch); splitk_finish_kernel adds the shares and applies the launch's own
 // epilogue functor.
+template <int ROWS>
 struct EpiPartial {
     float* ws;
-    int64_t share_stride;     // floats per share: slots * 65536
+    int64_t share_stride;     // floats per share: slots * ROWS * BN
     int slot, m0;             // set by the kernel: this workgroup's slot and first row
     template <int BN>
     __device__ __forceinline__ void operator()(int m, int bn, int cc, const float* crow, int swz) const {
-        static_assert(BN == 256, "slots are 256 columns wide");
-        float* dst = ws + blockIdx.y * share_stride + (int64_t)slot * 65536 + (m - m0) * 256 + cc;
+        float* dst = ws + blockIdx.y * share_stride + (int64_t)slot * (ROWS * BN) + (m - m0) * BN + cc;
         const f32x4* cr = reinterpret_cast<const f32x4*>(crow + (cc ^ swz));
         reinterpret_cast<f32x4*>(dst)[0] = cr[0];
         reinterpret_cast<f32x4*>(dst)[1] = cr[1];
@@ -225,8 +228,9 @@ struct EpiPartial {
 };
 template <class Epi>
 __device__ __forceinline__ Epi epi_for_tile(const Epi& e, int, int) { return e; }
-__device__ __forceinline__ EpiPartial epi_for_tile(const EpiPartial& e, int slot, int m0) {
-    EpiPartial r = e;
+template <int ROWS>
+__device__ __forceinline__ EpiPartial<ROWS> epi_for_tile(const EpiPartial<ROWS>& e, int slot, int m0) {
+    EpiPartial<ROWS> r = e;
     r.slot = slot;
     r.m0 = m0;
     return r;
@@ -234,14 +238,15 @@ __device__ __forceinline__ EpiPartial epi_for_tile(const EpiPartial& e, int slot
 
 __device__ __forceinline__ void tile_of_seq(int vb, int tiles_m, int tiles_n, int GM, int* bm, int* bn);
 
-// One workgroup per 8 rows of one tile slot: sums the shares of each 8-column chunk into an LDS
-// row, then every thread calls the functor on its chunk (functors may read other chunks of the
-// row: the RoPE partner, the up half of a gate/up tile).
-template <class Epi>
+// One workgroup per 2048 / BN rows of one tile slot: sums the shares of each 8-column chunk into an
+// LDS row, then every thread calls the functor on its chunk (functors may read other chunks of the
+// row: the RoPE partner, the up half of a gate/up tile).  The loads of four shares are issued
+// together; the shares are added in ascending order.
+template <int SLOT_ROWS, int BN, class Epi>
 __global__ __launch_bounds__(256) void splitk_finish_kernel(const float* __restrict__ ws, int64_t share_stride,
                                                             int n_shares, int M, int BM, int vb0, int tiles_m,
                                                             int tiles_n, int GM, Epi epi) {
-    constexpr int BN = 256, TPR = BN / 8, ROWS = 256 / TPR;
+    constexpr int TPR = BN / 8, ROWS = 256 / TPR;
     __shared__ __align__(16) float stage[ROWS][BN];
     const int r = threadIdx.x / TPR, cc = (threadIdx.x % TPR) * 8;
     int bm, bn;
@@ -249,9 +254,24 @@ __global__ __launch_bounds__(256) void splitk_finish_kernel(const float* __restr
     const int row = blockIdx.y * ROWS + r, m = bm * BM + row;
     const bool on = row < BM && m < M;
     if (on) {
-        const float* src = ws + (int64_t)blockIdx.x * 65536 + row * 256 + cc;
+        const float* src = ws + (int64_t)blockIdx.x * (SLOT_ROWS * BN) + row * BN + cc;
         f32x4 a = {0.f, 0.f, 0.f, 0.f}, b = {0.f, 0.f, 0.f, 0.f};
-        for (int sp = 0; sp < n_shares; ++sp) {
+        int sp = 0;
+        for (; sp + 4 <= n_shares; sp += 4) {
+            f32x4 x[4][2];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const f32x4* p = reinterpret_cast<const f32x4*>(src + (sp + u) * share_stride);
+                x[u][0] = p[0];
+                x[u][1] = p[1];
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                a += x[u][0];
+                b += x[u][1];
+            }
+        }
+        for (; sp < n_shares; ++sp) {
             const f32x4* p = reinterpret_cast<const f32x4*>(src + sp * share_stride);
             a += p[0];
             b += p[1];
@@ -1299,6 +1319,161 @@ __global__ __launch_bounds__(512, 2) void gemm_ring16_kernel_pp(
     }
 }
 
+// ------------------------------------------------------------------ thin tiles
+// 64x128 tiles for few rows, where a call reads a whole weight matrix for one or two row tiles.
+//
+// What bounds it: the weight stream from HBM, so bytes in flight count and matrix work does not.
+// The 256-row tiles above pad 64 rows to 256: three quarters of the MFMAs, of the A loads and of
+// the LDS reads are for rows that do not exist, and with 96 KB a K tile the ring holds little of B.
+// Here a slice is 64 columns (whole 128-byte lines, 8 KB of A + 16 KB of B) and six slots (144 KB
+// of LDS, one workgroup per CU) keep five slices = 80 KB of weights per CU on the way.  Four waves
+// of 64x32; one barrier per slice; any K % 64 == 0.  Column tile bn starts bn slices into K and
+// wraps round: rows of a weight matrix are a power of two bytes apart as often as not, and
+// workgroups that walk K in step then ask the same few memory channels at any one time (a layer of
+// 64 rows, d = 4096: 176 us in step, 164 rotated).
+// Swizzle and fragment layout as in the ping-pong loop.
+// M = 64, d = 4096, f = 14336, microseconds with the finishing pass, before and now: gate/up 65 ->
+// 43 (5.4 TB/s of weights), down 38 -> 31, QKV 25 -> 19, O 22 -> 15; M = 237, d = 256, f = 1024: down 15 -> 9,
+// QKV 12 -> 7.  Slices of 128 columns in three slots: the same within 2 % over these shapes, gate/up
+// slower by a fifth at 64 rows.
+constexpr int THIN_M = 64, THIN_N = 128, THIN_SLOTS = 6;
+template <class BSrc, class Epi>
+__global__ __launch_bounds__(256, 1) void gemm_thin_kernel(const bf16_t* __restrict__ A, int lda, int M, int K,
+                                                           int tiles_m, int tiles_n, int GM, int nb,
+                                                           BSrc bsrc, Epi epi) {
+    constexpr int BM = THIN_M, BN = THIN_N, D = THIN_SLOTS, ROWB = 128;
+    constexpr int A_L = 2, B_L = 4, LPS = A_L + B_L;   // loads of a wave and slice (8 rows each)
+    constexpr int SLOT = (BM + BN) * ROWB;
+    static_assert(BM * BN * 4 <= D * SLOT && LPS * (D - 2) < 64, "epilogue space, vmcnt range");
+    __shared__ __align__(16) char smem[D * SLOT];
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    int bm, bn;
+    const int vb = tile_of_block(blockIdx.x, nb, 0, tiles_m, tiles_n, GM, &bm, &bn);
+    const int m0 = bm * BM;
+    const int64_t kz = (int64_t)blockIdx.y * K * 2;    // K is this launch's share per workgroup row
+
+    // ---- global -> LDS: wave w moves rows 16w .. of A and 32w .. of B; lane L fills slot L%8 of row L/8 ----
+    uint32_t ao[A_L], bo[B_L];
+    const int hb = wave >> 1;                          // half of the tile that the wave's B rows lie in
+    const int left = bsrc.template rows_left<BN>(bn, hb);
+#pragma unroll
+    for (int i = 0; i < A_L; ++i) {
+        const int r = wave * 16 + i * 8 + (lane >> 3);
+        ao[i] = (uint32_t)((min(r, M - m0 - 1) * lda + ((lane & 7) ^ ((r >> 1) & 7)) * 8) * 2);
+    }
+#pragma unroll
+    for (int i = 0; i < B_L; ++i) {
+        const int r = wave * 32 + i * 8 + (lane >> 3);
+        bo[i] = (uint32_t)((min(r - hb * (BN / 2), left - 1) * bsrc.ldb + ((lane & 7) ^ ((r >> 1) & 7)) * 8) * 2);
+    }
+    const char* const abase = reinterpret_cast<const char*>(A + (int64_t)m0 * lda) + kz;
+    const char* const bbase = reinterpret_cast<const char*>(bsrc.template base<BN>(bn, hb)) + kz;
+    auto scalar_ptr = [](const char* p) -> const char* {   // keeps the base in scalar registers
+        const uint64_t u = reinterpret_cast<uint64_t>(p);
+        const uint64_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)u);
+        const uint64_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(u >> 32));
+        return reinterpret_cast<const char*>((hi << 32) | lo);
+    };
+    const int KT = K / 64, rot = bn % KT;
+    auto load_slice = [&](int n, int slot) __attribute__((always_inline)) {
+        const int t = n + rot < KT ? n + rot : n + rot - KT;
+        unrolled<B_L>([&](auto ic) __attribute__((always_inline)) {
+            constexpr int i = decltype(ic)::value;
+            const char* g = scalar_ptr(bbase + (int64_t)t * ROWB - i * 1024);   // the immediate adds it back
+            asm volatile("" : "+v"(bo[i]));
+            dma16_at<i * 1024>(g + bo[i], reinterpret_cast<bf16_t*>(smem + slot * SLOT + BM * ROWB + wave * B_L * 1024));
+        });
+        unrolled<A_L>([&](auto ic) __attribute__((always_inline)) {
+            constexpr int i = decltype(ic)::value;
+            const char* g = scalar_ptr(abase + (int64_t)t * ROWB - i * 1024);
+            asm volatile("" : "+v"(ao[i]));
+            dma16_at<i * 1024>(g + ao[i], reinterpret_cast<bf16_t*>(smem + slot * SLOT + wave * A_L * 1024));
+        });
+    };
+
+    f32x4 acc[4][2];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const int frow = lane & 15, fk = lane >> 4;
+    const int fsw = (frow >> 1) & 7;
+    const uint32_t smem_base = (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void*)smem;
+    uint32_t a_addr[2], b_addr[2];                     // [k-step of 32 columns]
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) {
+        a_addr[ks] = smem_base + frow * ROWB + ((fk + 4 * ks) ^ fsw) * 16;
+        b_addr[ks] = a_addr[ks] + (BM + wave * 32) * ROWB;
+    }
+#pragma unroll
+    for (int t = 0; t < D - 1; ++t)
+        if (t < KT) load_slice(t, t);
+    int rd = 0, wrs = D - 1;                           // slot of slice t, slot of slice t + D - 1
+    for (int t = 0; t < KT; ++t) {
+        // slice t has landed when at most the loads of the younger ones are out
+        switch (min(KT - 1 - t, D - 2)) {
+            case 4: asm volatile("s_waitcnt vmcnt(%0)" : : "n"(4 * LPS)); break;
+            case 3: asm volatile("s_waitcnt vmcnt(%0)" : : "n"(3 * LPS)); break;
+            case 2: asm volatile("s_waitcnt vmcnt(%0)" : : "n"(2 * LPS)); break;
+            case 1: asm volatile("s_waitcnt vmcnt(%0)" : : "n"(1 * LPS)); break;
+            default: asm volatile("s_waitcnt vmcnt(0)"); break;
+        }
+        static_assert(D - 2 == 4, "cases of the wait");
+        wg_barrier();                                  // for every wave; and slot wrs (slice t - 1) has been read
+        if (t + D - 1 < KT) load_slice(t + D - 1, wrs);
+        __builtin_amdgcn_sched_barrier(0);
+        bf16x8 af[2][4], bf[2][2];
+        const uint32_t at = rd * SLOT;
+        const uint32_t a0 = a_addr[0] + at, a1 = a_addr[1] + at, b0 = b_addr[0] + at, b1 = b_addr[1] + at;
+        unrolled<2>([&](auto ic) __attribute__((always_inline)) { bf[0][ic.value] = lds_read16<ic.value * 16 * ROWB>(b0); });
+        unrolled<4>([&](auto ic) __attribute__((always_inline)) { af[0][ic.value] = lds_read16<ic.value * 16 * ROWB>(a0); });
+        unrolled<2>([&](auto ic) __attribute__((always_inline)) { bf[1][ic.value] = lds_read16<ic.value * 16 * ROWB>(b1); });
+        unrolled<4>([&](auto ic) __attribute__((always_inline)) { af[1][ic.value] = lds_read16<ic.value * 16 * ROWB>(a1); });
+        unrolled<2>([&](auto kc) __attribute__((always_inline)) {
+            constexpr int ks = decltype(kc)::value;
+            if constexpr (ks == 0) asm volatile("s_waitcnt lgkmcnt(6)");
+            else asm volatile("s_waitcnt lgkmcnt(0)");
+#pragma unroll
+            for (int i = 0; i < 4; ++i) asm volatile("" : "+v"(af[ks][i]));
+#pragma unroll
+            for (int j = 0; j < 2; ++j) asm volatile("" : "+v"(bf[ks][j]));
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int j = 0; j < 2; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[ks][i], bf[ks][j], acc[i][j], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+        });
+        wrs = rd;
+        rd = rd + 1 == D ? 0 : rd + 1;
+    }
+
+    // ---- epilogue through LDS as fp32 [BM][BN], column c of row r at c ^ 16*((r>>2)&3) ----
+    __syncthreads();
+    float* stage = reinterpret_cast<float*>(smem);
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int r = i * 16 + 4 * fk + v, c = wave * 32 + j * 16 + frow;
+                stage[r * BN + (c ^ (fk << 4))] = acc[i][j][v];
+            }
+    __syncthreads();
+    const auto e2 = epi_for_tile(epi, vb, m0);
+    constexpr int TPR = BN / 8, RPP = 256 / TPR;
+    const int cc = (tid % TPR) * 8;
+#pragma unroll
+    for (int k = 0; k < BM / RPP; ++k) {
+        const int r = tid / TPR + k * RPP;
+        const int m = m0 + r;
+        if (m < M) e2.template operator()<BN>(m, bn, cc, stage + r * BN, ((r >> 2) & 3) << 4);
+    }
+}
+
 // Tile shapes: 256x256 (ping-pong loop, 8 waves, least LDS and L2 traffic per flop, one
 // workgroup per CU), 192x256 (8 waves of 96x64, ring loop only, 0.70 of the large tile's rate:
 // it pays where it saves a half-empty round), 256x128 (8 waves of 64x64, one per CU, ring loop
@@ -1347,8 +1522,10 @@ void launch_gemm(const bf16_t* A, int lda, int M, int N_tiles_cols, int K, int l
     // 384 tiles, takes 208 split against 199 with the 192-row tile, so the estimate has to be
     // 10 % below the unsplit one to be taken).
     int S = 1;
+    const double slice_us = 0.65 * K / BKS / 65536.0;           // per unit of tile area
+    double t_best = best * slice_us + 6.0 * rounds_of(pick == 's' ? 128 : pick == 'm' ? 192 : 256,
+                                                      (pick == 'b' || pick == 'm') ? 256 : 128, pick == 's' ? 2 : 1, 1);
     if (ring && ws) {
-        const double slice_us = 0.65 * K / BKS / 65536.0;       // per unit of tile area
         auto rem_of = [&](int bm) {
             const long tiles = (long)((M + bm - 1) / bm) * ((N_tiles_cols + 255) / 256);
             return (int)(tiles % n_cu == 0 && tiles > 0 ? n_cu : tiles % n_cu);
@@ -1363,9 +1540,6 @@ void launch_gemm(const bf16_t* A, int lda, int M, int N_tiles_cols, int K, int l
             const int bm = pick == 'm' ? 192 : 256;
             if (sp > 1 && sp <= 16 && split_ok(bm, sp, BKS * NS)) S = sp, pick = bm == 192 ? 'm' : 'b';
         } else if (!force && !ovr.gemm_staged) {
-            double t_best = best * slice_us + 6.0 * rounds_of(pick == 's' ? 128 : pick == 'm' ? 192 : 256,
-                                                               (pick == 'b' || pick == 'm') ? 256 : 128,
-                                                               pick == 's' ? 2 : 1, 1);
             const double t_unsplit = t_best;
             for (int bm = 256; bm >= 192; bm -= 64) {
                 const double tile_us = bm * 256.0 / (bm == 256 ? 1.0 : 0.70) * slice_us;
@@ -1379,6 +1553,50 @@ void launch_gemm(const bf16_t* A, int lda, int M, int N_tiles_cols, int K, int l
                 }
             }
         }
+    }
+    // Few rows: 64x128 tiles (gemm_thin_kernel), K cut into S_thin shares where the grid leaves CUs idle.
+    // Microseconds: THIN_SLICE_US per 64-column slice and round, 5 for the ends of a tile, the
+    // weights no faster than 4 TB/s, a finishing pass 5 plus its traffic.  Measured (event time, cold weights,
+    // 64x128 tiles against the larger ones): down, d = 4096, M = 1 / 64 / 128: 28 / 34 / 43 against 35 / 42 / 49,
+    // M = 192: 62 against 50; QKV, M = 128 / 400: 29 / 64 against 33 / 48; gate/up, M = 64 / 128 / 192: 77 / 89 /
+    // 113 against 80 / 83 / 86.  The estimate has to be a tenth below the other's to be taken.
+    constexpr double THIN_SLICE_US = 0.47;
+    const long thin_tiles = (long)((M + THIN_M - 1) / THIN_M) * ((N_tiles_cols + THIN_N - 1) / THIN_N);
+    const bool thin_ok = (int64_t)lda * THIN_M * 2 < (1ll << 31) && (int64_t)ldb * THIN_N * 2 < (1ll << 31);
+    int S_thin = 1;
+    auto thin_split_ok = [&](int sp) {
+        return (K / 64) % sp == 0 && ws && (double)sp * thin_tiles * (THIN_M * THIN_N) <= (double)ws_floats;
+    };
+    if (thin_ok && force == 't') {
+        pick = 't', S = 1;
+        if (ovr.gemm_splitk > 1 && thin_split_ok(ovr.gemm_splitk)) S_thin = ovr.gemm_splitk;
+    } else if (thin_ok && !force && !ovr.gemm_staged && !ovr.gemm_mfma32 && ovr.gemm_splitk == 0) {
+        double t_thin = 0.9 * t_best;
+        for (int sp = 1; sp <= 16; ++sp) {
+            if (sp > 1 && (!thin_split_ok(sp) || K / sp < 256 || thin_tiles * sp > n_cu)) continue;
+            const long rounds = (thin_tiles * sp + n_cu - 1) / n_cu;
+            double t = rounds * ((double)(K / sp / 64) * THIN_SLICE_US + 5.0);
+            t = std::max(t, 2.0 * N_tiles_cols * K / 4.0e6);
+            if (sp > 1) t += 5.0 + (double)sp * thin_tiles * (THIN_M * THIN_N) * 8 / 5.0e6;
+            if (t < t_thin) t_thin = t, pick = 't', S = 1, S_thin = sp;
+        }
+    }
+    if (pick == 't') {
+        const int tiles_m = (M + THIN_M - 1) / THIN_M, tiles_n = (N_tiles_cols + THIN_N - 1) / THIN_N;
+        const int GM = std::min(ovr.gemm_gm > 0 ? ovr.gemm_gm : 4, tiles_m);
+        const int nt = (int)thin_tiles;
+        if (S_thin == 1) {
+            hipLaunchKernelGGL((gemm_thin_kernel<BSrc, Epi>), dim3(nt), dim3(256), 0, s, A, lda, M, K, tiles_m, tiles_n,
+                               GM, nt, bsrc, epi);
+        } else {
+            constexpr int SLOT = THIN_M * THIN_N;
+            EpiPartial<THIN_M> pe{ws, (int64_t)nt * SLOT, 0, 0};
+            hipLaunchKernelGGL((gemm_thin_kernel<BSrc, EpiPartial<THIN_M>>), dim3(nt, S_thin), dim3(256), 0, s, A, lda, M,
+                               K / S_thin, tiles_m, tiles_n, GM, nt, bsrc, pe);
+            hipLaunchKernelGGL((splitk_finish_kernel<THIN_M, THIN_N, Epi>), dim3(nt, THIN_M * THIN_N / 2048), dim3(256), 0, s,
+                               ws, (int64_t)nt * SLOT, S_thin, M, THIN_M, 0, tiles_m, tiles_n, GM, epi);
+        }
+        return;
     }
     const int bm = pick == 's' ? 128 : pick == 'm' ? 192 : 256, bn = (pick == 'b' || pick == 'm') ? 256 : 128;
     const int tiles_m = (M + bm - 1) / bm, tiles_n = (N_tiles_cols + bn - 1) / bn;
@@ -1397,21 +1615,21 @@ void launch_gemm(const bf16_t* A, int lda, int M, int N_tiles_cols, int K, int l
                        s, A, lda, M, K, tiles_m, tiles_n, GM, bsrc, epi)
     if (S > 1) {
         const int rem = n_tiles % n_cu == 0 ? n_cu : n_tiles % n_cu, full = n_tiles - rem;
-        EpiPartial pe{ws, (int64_t)rem * 65536, 0, 0};
+        EpiPartial<256> pe{ws, (int64_t)rem * 65536, 0, 0};
         if (pick == 'b' && mfma16) {
             if (full) CC_LAUNCH_PP(Epi, epi, K, full, 0, 1);
-            CC_LAUNCH_PP(EpiPartial, pe, K / S, rem, full, S);
+            CC_LAUNCH_PP(EpiPartial<256>, pe, K / S, rem, full, S);
         } else if (pick == 'b') {
             if (full) CC_LAUNCH(gemm_ring_kernel, 256, 256, 2, 4, Epi, epi, K, full, 0, 1);
-            CC_LAUNCH(gemm_ring_kernel, 256, 256, 2, 4, EpiPartial, pe, K / S, rem, full, S);
+            CC_LAUNCH(gemm_ring_kernel, 256, 256, 2, 4, EpiPartial<256>, pe, K / S, rem, full, S);
         } else if (mfma16) {
             if (full) CC_LAUNCH(gemm_ring16_kernel, 192, 256, 2, 4, Epi, epi, K, full, 0, 1);
-            CC_LAUNCH(gemm_ring16_kernel, 192, 256, 2, 4, EpiPartial, pe, K / S, rem, full, S);
+            CC_LAUNCH(gemm_ring16_kernel, 192, 256, 2, 4, EpiPartial<256>, pe, K / S, rem, full, S);
         } else {
             if (full) CC_LAUNCH(gemm_ring_kernel, 192, 256, 2, 4, Epi, epi, K, full, 0, 1);
-            CC_LAUNCH(gemm_ring_kernel, 192, 256, 2, 4, EpiPartial, pe, K / S, rem, full, S);
+            CC_LAUNCH(gemm_ring_kernel, 192, 256, 2, 4, EpiPartial<256>, pe, K / S, rem, full, S);
         }
-        hipLaunchKernelGGL((splitk_finish_kernel<Epi>), dim3(rem, (bm + 7) / 8), dim3(256), 0, s, ws,
+        hipLaunchKernelGGL((splitk_finish_kernel<256, 256, Epi>), dim3(rem, (bm + 7) / 8), dim3(256), 0, s, ws,
                            (int64_t)rem * 65536, S, M, bm, full, tiles_m, tiles_n, GM, epi);
     } else if (pick == 'b') {
         if (ring && mfma16) CC_LAUNCH_PP(Epi, epi, K, n_tiles, 0, 1);

@@ -786,3 +786,46 @@ def test_llama8b_layer_16k_every_slot_recomputed():
     16576 cache slots of the 16k workload is recomputed in one call (idx = 0..N-1).  Every K/V row
     against the oracle, the layer output on the stratified sample."""
     _device_drawn_layer_case("C3", 0, 16, 13, dense=True)
+
+
+@pytest.mark.parametrize("M,splitk", [(1, 0), (64, 0), (65, 3), (203, 0), (203, 5), (130, 7)])
+def test_stage_projections_on_thin_tiles(M, splitk):
+    """64x128 tiles forced: partial and whole row tiles, columns past the last tile, K of fewer
+    slices (5) than the kernel has slots and of 7 and 15, shares of K down to one slice; a share
+    count that does not divide a projection's slices is ignored for it.  Same bounds as above."""
+    model = ModelShape(320, 15, 5, 64, 448, 1e4, 1e-5, True, 1)
+    N = 500
+    rng = np.random.default_rng(M + splitk)
+    w = gen.layer_weights(model, 0, seed=22)
+    xb = _x_bits(N, model.d, 8)
+    idx = np.sort(rng.choice(N, size=M, replace=False))
+    ctx = _ctx(model, N, N)
+    ctx.debug_set_launch(gemm_tile="t", gemm_splitk=splitk)
+    dw, hid, xf = dev_weights(w), dev_bf16(xb), obf.bits_to_f64(xb[idx])
+    xn = torch.empty((M, model.d), dtype=torch.bfloat16, device=DEV)
+    ctx.step_gather_rmsnorm(hid, dev_i32(idx), M, dw.w_in_norm, xn)
+    Ks = np.zeros((N, model.H_kv, model.d_h), np.uint16)
+    Kd, Vd = dev_bf16(Ks), dev_bf16(Ks)
+    q = torch.empty((M, model.H_q * model.d_h), dtype=torch.bfloat16, device=DEV)
+    ctx.step_qkv_rope_scatter(xn, M, dev_i32(idx), dw.w_qkv, dw.b_qkv, cc.KVLayer(Kd, Vd), q, _lib.FLAG_CHECK_IDX)
+    q_ref, k_ref, v_ref = layer.qkv_rows(xf, w, model, idx)
+    for got, ref in ((host_bits(q).reshape(M, model.H_q, -1), q_ref), (host_bits(Kd)[idx], k_ref), (host_bits(Vd)[idx], v_ref)):
+        mx, mn = err_stats(bits_f64(got), ref)
+        assert mx <= MAX_ABS and mn <= MEAN_ABS, (mx, mn)
+    rest = np.setdiff1d(np.arange(N), idx)
+    assert not host_bits(Kd)[rest].any() and not host_bits(Vd)[rest].any()
+    ob = _x_bits(M, model.H_q * model.d_h, 9, 0.5)
+    y = torch.full((M + 1, model.d), 7.0, dtype=torch.float32, device=DEV)
+    ctx.step_oproj_residual(dev_bf16(ob), M, dw.w_o, hid, dev_i32(idx), y)
+    y_ref = xf + obf.bits_to_f64(ob) @ obf.bits_to_f64(w["w_o"]).T
+    yf = y[:M].cpu().numpy().astype(np.float64)
+    assert err_stats(yf, y_ref)[0] <= 1e-4 and bool((y[M] == 7.0).all())      # fp32 sums of exact bf16 products
+    out = torch.full((M + 1, model.d), 7.0, dtype=torch.bfloat16, device=DEV)
+    ctx.step_mlp(y, M, dw.w_post_norm, dw.w_gate, dw.w_up, dw.w_down, out)
+    torch.cuda.synchronize()
+    m = layer.rmsnorm(yf, obf.bits_to_f64(w["w_post_norm"]), model.rms_eps)
+    z = yf + (layer.silu(m @ obf.bits_to_f64(w["w_gate"]).T) * (m @ obf.bits_to_f64(w["w_up"]).T)) \
+        @ obf.bits_to_f64(w["w_down"]).T
+    mx, mn = err_stats(bits_f64(host_bits(out))[:M], z)
+    assert mx <= MAX_ABS and mn <= MEAN_ABS and bool((out[M] == 7.0).all()), (mx, mn)
+    ctx.close()
