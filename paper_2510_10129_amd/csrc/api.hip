@@ -12,7 +12,10 @@
 // code this name is only a handle for hipGetSymbolAddress; the device address it yields (one
 // per device) is what kernels, copies and fills are given.
 #define CC_NOALLOC_T_MAX 131072
-#define CC_NOALLOC_SCRATCH_BYTES (1u << 20)       // scores [T_MAX] fp32 in the first half; the rest is spare
+#define CC_NOALLOC_SCRATCH_BYTES (1u << 20)       // scores [T_MAX] fp32 in the first half, then the two below
+#define CC_NOALLOC_RANGE_AT (CC_NOALLOC_T_MAX * 4)                          // key ranges [T_MAX / 64]
+#define CC_NOALLOC_SEL_AT (CC_NOALLOC_RANGE_AT + CC_NOALLOC_T_MAX / 64 * 8)   // cc_sel_buf
+static_assert(CC_NOALLOC_SEL_AT + sizeof(cc_sel_buf) <= CC_NOALLOC_SCRATCH_BYTES, "static scratch");
 static __device__ __align__(256) unsigned char scratch[CC_NOALLOC_SCRATCH_BYTES];
 
 namespace {
@@ -144,7 +147,7 @@ cc_status cc_create(cc_ctx** out, const cc_model_desc* desc, void* hip_stream) {
     memset(c->prof_ms, 0, sizeof(c->prof_ms));
     memset(c->prof_n, 0, sizeof(c->prof_n));
     c->rope = nullptr; c->xn = nullptr; c->q = nullptr; c->o = nullptr; c->y = nullptr;
-    c->mn = nullptr; c->act = nullptr; c->attn_part = nullptr; c->attn_table = nullptr; c->gemm_part = nullptr; c->score = nullptr; c->n_sel = nullptr; c->flag = nullptr;
+    c->mn = nullptr; c->act = nullptr; c->attn_part = nullptr; c->attn_table = nullptr; c->gemm_part = nullptr; c->score = nullptr; c->key_range = nullptr; c->sel = nullptr; c->n_sel = nullptr; c->flag = nullptr;
     c->pinned = nullptr;
     const cc_model_desc& m = c->m;
     const size_t Mc = (size_t)m.M_cap, nq = (size_t)m.H_q * m.d_h;
@@ -176,6 +179,10 @@ cc_status cc_create(cc_ctx** out, const cc_model_desc* desc, void* hip_stream) {
     }
     alloc((void**)&c->gemm_part, (size_t)c->gemm_part_floats * 4);
     alloc((void**)&c->score, (size_t)m.T_cap * 4);
+    if (cc_select_uses_ranges(m.T_cap)) {
+        alloc((void**)&c->key_range, (size_t)m.T_cap * sizeof(uint2));   // a score kernel has at most T workgroups
+        alloc((void**)&c->sel, sizeof(cc_sel_buf));
+    }
     alloc((void**)&c->n_sel, 4);
     alloc((void**)&c->flag, 4);
     if (e == hipSuccess) e = hipHostMalloc((void**)&c->pinned, 2 * sizeof(int32_t), hipHostMallocDefault);
@@ -202,7 +209,7 @@ cc_status cc_destroy(cc_ctx* c) {
     for (auto& p : c->pool) { (void)hipEventDestroy(p.a); (void)hipEventDestroy(p.b); }
     (void)hipFree(c->rope); (void)hipFree(c->xn); (void)hipFree(c->q); (void)hipFree(c->o);
     (void)hipFree(c->y); (void)hipFree(c->mn); (void)hipFree(c->act); (void)hipFree(c->attn_part); (void)hipFree(c->attn_table); (void)hipFree(c->gemm_part);
-    (void)hipFree(c->score);
+    (void)hipFree(c->score); (void)hipFree(c->key_range); (void)hipFree(c->sel);
     (void)hipFree(c->n_sel); (void)hipFree(c->flag);
     if (c->pinned) (void)hipHostFree(c->pinned);
     delete c;
@@ -222,7 +229,7 @@ cc_status cc_step_column_scores(cc_ctx* c, const float* attn, int32_t Q_a, int32
     if (Q_a < 1 || T < 1 || ld < T) return fail(c, CC_ERR_SHAPE, "need Q_a >= 1, T >= 1, ld >= T");
     {
         cc_prof_scope ps(c, CC_K_COLSUM);
-        cc_launch_colsum(attn, Q_a, T, ld, score, c->stream);
+        cc_launch_colsum(attn, Q_a, T, ld, score, nullptr, c->stream);
     }
     CC_HIP(c, hipGetLastError());
     return CC_OK;
@@ -231,7 +238,8 @@ cc_status cc_step_column_scores(cc_ctx* c, const float* attn, int32_t Q_a, int32
 // Validates the descriptors, enqueues the block-score launches (CC_BLK_SEGS batch elements
 // each) and returns the number of scores in *T_out.
 static cc_status block_scores(cc_ctx* c, const cc_aux_block* blocks, int32_t n_blocks, int32_t H,
-                              int32_t Q_a, int64_t T_max, float* score, int32_t* T_out) {
+                              int32_t Q_a, int64_t T_max, float* score, uint2* key_range, int32_t* T_out,
+                              int32_t* n_range) {
     if (!blocks || !score) return fail(c, CC_ERR_NULL, "blocks and score must not be NULL");
     if (n_blocks < 1 || H < 1 || Q_a < 1) return fail(c, CC_ERR_SHAPE, "need n_blocks >= 1, H >= 1, Q_a >= 1");
     int64_t T = 0;
@@ -244,6 +252,7 @@ static cc_status block_scores(cc_ctx* c, const cc_aux_block* blocks, int32_t n_b
         T += b.len;
         if (T > T_max) return fail(c, T_max == (int64_t)c->m.T_cap ? CC_ERR_WORKSPACE : CC_ERR_SHAPE, "sum of len exceeds the score capacity");
     }
+    *n_range = 0;
     int32_t t0 = 0;
     for (int i0 = 0; i0 < n_blocks; i0 += CC_BLK_SEGS) {
         cc_blk_args a;
@@ -256,7 +265,8 @@ static cc_status block_scores(cc_ctx* c, const cc_aux_block* blocks, int32_t n_b
             t0 += b.len;
         }
         cc_prof_scope ps(c, CC_K_BLOCK_SCORES);
-        cc_launch_block_scores(a, H, Q_a, score, c->stream);
+        cc_launch_block_scores(a, H, Q_a, score, key_range ? key_range + *n_range : nullptr, c->stream);
+        *n_range += a.n_blocks;
     }
     CC_HIP(c, hipGetLastError());
     *T_out = (int32_t)T;
@@ -266,8 +276,8 @@ static cc_status block_scores(cc_ctx* c, const cc_aux_block* blocks, int32_t n_b
 cc_status cc_step_block_scores(cc_ctx* c, const cc_aux_block* blocks, int32_t n_blocks, int32_t H,
                                int32_t Q_a, float* score) {
     if (!c) return fail(nullptr, CC_ERR_NULL, "ctx must not be NULL");
-    int32_t T = 0;
-    return block_scores(c, blocks, n_blocks, H, Q_a, INT32_MAX, score, &T);
+    int32_t T = 0, n_range = 0;
+    return block_scores(c, blocks, n_blocks, H, Q_a, INT32_MAX, score, nullptr, &T, &n_range);
 }
 
 cc_status cc_select_blocks(cc_ctx* c, const cc_aux_block* blocks, int32_t n_blocks, int32_t H,
@@ -280,15 +290,15 @@ cc_status cc_select_blocks(cc_ctx* c, const cc_aux_block* blocks, int32_t n_bloc
     if (window < 1 || window > 1024) return fail(c, CC_ERR_SHAPE, "window must be in [1, 1024]");
     if (tau < 0 || tau > window) return fail(c, CC_ERR_SHAPE, "tau must be in [0, window]");
     if (n_tail < 0 || idx_offset < 0) return fail(c, CC_ERR_SHAPE, "idx_offset and n_tail must be >= 0");
-    int32_t T = 0;
-    cc_status st = block_scores(c, blocks, n_blocks, H, Q_a, c->m.T_cap, c->score, &T);
+    int32_t T = 0, n_range = 0;      // key ranges are written wherever a selection on this context may need them
+    cc_status st = block_scores(c, blocks, n_blocks, H, Q_a, c->m.T_cap, c->score, c->key_range, &T, &n_range);
     if (st != CC_OK) return st;
     const int k = (int)(((int64_t)T * (int64_t)recomp_bp) / 10000);
     const int tau_eff = tau > 0 ? tau : (5 * window + 7) / 8;
     {
         cc_prof_scope ps(c, CC_K_SELECT);
         cc_launch_select(c->score, T, k, window, tau_eff, (flags & CC_FLAG_NO_GROUPING) ? 0 : 1,
-                         idx_offset, n_tail, idx_out, n_out, c->stream);
+                         idx_offset, n_tail, idx_out, n_out, c->key_range, n_range, c->sel, c->stream);
     }
     CC_HIP(c, hipGetLastError());
     if (n_out_host) {
@@ -315,12 +325,12 @@ cc_status cc_select(cc_ctx* c, const float* attn, int32_t Q_a, int32_t T, int64_
     const int tau_eff = tau > 0 ? tau : (5 * window + 7) / 8;
     {
         cc_prof_scope ps(c, CC_K_COLSUM);
-        cc_launch_colsum(attn, Q_a, T, ld, c->score, c->stream);
+        cc_launch_colsum(attn, Q_a, T, ld, c->score, cc_select_uses_ranges(T) ? c->key_range : nullptr, c->stream);
     }
     {
         cc_prof_scope ps(c, CC_K_SELECT);
         cc_launch_select(c->score, T, k, window, tau_eff, (flags & CC_FLAG_NO_GROUPING) ? 0 : 1,
-                         idx_offset, n_tail, idx_out, n_out, c->stream);
+                         idx_offset, n_tail, idx_out, n_out, c->key_range, (T + 63) / 64, c->sel, c->stream);
     }
     CC_HIP(c, hipGetLastError());
     if (n_out_host) {
@@ -350,9 +360,11 @@ cc_status cc_select_noalloc(void* hip_stream, const float* attn, int32_t Q_a, in
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     const int k = (int)(((int64_t)T * (int64_t)recomp_bp) / 10000);
     const int tau_eff = tau > 0 ? tau : (5 * window + 7) / 8;
-    cc_launch_colsum(attn, Q_a, T, ld, score, stream);
+    uint2* key_range = reinterpret_cast<uint2*>(static_cast<char*>(sp) + CC_NOALLOC_RANGE_AT);
+    cc_sel_buf* sel = reinterpret_cast<cc_sel_buf*>(static_cast<char*>(sp) + CC_NOALLOC_SEL_AT);
+    cc_launch_colsum(attn, Q_a, T, ld, score, cc_select_uses_ranges(T) ? key_range : nullptr, stream);
     cc_launch_select(score, T, k, window, tau_eff, (flags & CC_FLAG_NO_GROUPING) ? 0 : 1, idx_offset, n_tail,
-                     idx_out, n_out, stream);
+                     idx_out, n_out, key_range, (T + 63) / 64, sel, stream);
     e = hipGetLastError();
     if (e != hipSuccess) return fail(nullptr, CC_ERR_HIP, std::string("launch: ") + hipGetErrorString(e));
     return CC_OK;

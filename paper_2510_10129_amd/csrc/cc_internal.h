@@ -41,6 +41,8 @@ struct cc_ctx {
     float* gemm_part;  // [gemm_part_floats]  fp32 shares of a split-K projection
     int64_t gemm_part_floats;
     float* score;      // [T_cap]
+    uint2* key_range;  // [T_cap]  smallest and largest score key of every workgroup of a score kernel
+    struct cc_sel_buf* sel;   // workspace of a selection by several workgroups (NULL: T_cap needs none)
     int32_t* n_sel;    // [1]
     int32_t* flag;     // [1] idx check result
     int32_t* pinned;   // host pinned [2]
@@ -95,12 +97,29 @@ struct cc_blk_args {
     cc_blk_seg seg[CC_BLK_SEGS];
     int32_t n_seg, n_blocks;
 };
-void cc_launch_block_scores(const cc_blk_args& a, int H, int Q_a, float* score, hipStream_t s);
+// key_range (may be NULL): one entry per workgroup of 64 columns.
+void cc_launch_block_scores(const cc_blk_args& a, int H, int Q_a, float* score, uint2* key_range, hipStream_t s);
 void cc_launch_copy(void* dst, const void* src, int64_t bytes, hipStream_t s);
 void cc_launch_rope_table(float2* table, int n_pos, int d_h, double base, hipStream_t s);
-void cc_launch_colsum(const float* attn, int Q_a, int T, int64_t ld, float* score, hipStream_t s);
+void cc_launch_colsum(const float* attn, int Q_a, int T, int64_t ld, float* score, uint2* key_range, hipStream_t s);
+// Workspace of a selection by several workgroups, a tile of CC_SEL_TILE tokens each.
+#define CC_SEL_TILE 4096
+#define CC_SEL_TILES 32                          // 131072 tokens
+struct cc_sel_buf {
+    uint32_t hist[CC_SEL_TILES][1024];           // a tile's counts of 2048 bins, two to a word
+    uint16_t list[CC_SEL_TILES][CC_SEL_TILE];    // a tile's tokens of the threshold bin, ascending
+    uint64_t cand[CC_SEL_TILES * CC_SEL_TILE / 64];
+    uint64_t marked[CC_SEL_TILES * CC_SEL_TILE / 64];
+    uint32_t list_n[CC_SEL_TILES], marked_n[CC_SEL_TILES];
+    uint32_t base, krem, bin_count;              // threshold bin: first key, keys taken of it, keys in it
+    int32_t shift;                               // its width: 2^shift keys
+};
+typedef cc_sel_buf* cc_sel_ws;
+// Whether a selection over T tokens takes key_range (n_range entries) and ws; otherwise they may be NULL.
+bool cc_select_uses_ranges(int T);
 void cc_launch_select(const float* score, int T, int k, int window, int tau, int grouping,
-                      int idx_offset, int n_tail, int32_t* idx_out, int32_t* n_out, hipStream_t s);
+                      int idx_offset, int n_tail, int32_t* idx_out, int32_t* n_out, const uint2* key_range,
+                      int n_range, cc_sel_ws ws, hipStream_t s);
 void cc_launch_check_idx(const int32_t* idx, int M, int lo, int hi, int strict, int32_t* flag,
                          hipStream_t s);
 void cc_launch_gather_rmsnorm(const bf16_t* hidden, const int32_t* gather_idx, int M, int d,

@@ -223,3 +223,33 @@ def test_blocks_window_sweep_and_no_prefix(ctx, name, prefix):
             idx, n = ctx.select_blocks(dev_blocks, 2000, w, 0, 0 if grouping else _lib.FLAG_NO_GROUPING, P, wl.Q)
             assert n == len(ref) and np.array_equal(idx[:n].cpu().numpy(), ref), (name, prefix, w, grouping)
         print(f"{name} prefix={P} w={w}: M_sel/T = {(len(osel.select_from_scores(s, 2000, w, 0, True, P, wl.Q)) - wl.Q) / wl.T:.3f}")
+
+
+@pytest.mark.parametrize("T", [16384, 16385, 20479, 20480, 20545, 45001, 131072])
+def test_selection_by_several_workgroups_edges(ctx, T):
+    """Both sides of the size where several workgroups share a selection and of its 4096-token
+    tiles: windows that reach over tile edges (up to 1024 tokens), equal scores at the threshold in
+    many tiles, one score alone, a threshold bin over and under its list, every token and none."""
+    rng = np.random.default_rng(T)
+    smooth = rng.random((2, T)).astype(np.float32)
+    runs = smooth.copy()
+    for e in range(4096, T, 4096):                        # runs of high scores across tile edges
+        runs[:, e - 300:e + 300] += 2.0
+    runs[:, -40:] += 2.0                                  # and at the end
+    for w, tau in ((1, 0), (7, 0), (64, 20), (65, 0), (1000, 400), (1024, 1)):
+        _check(ctx, runs, 2000, w, tau, True, 5, 3)
+    _check(ctx, smooth, 2000, 16, 0, False, 0, 0)
+    tied = rng.integers(1, 6, size=(1, T)).astype(np.float32) * 0.25        # crowded: the one-workgroup selection
+    _check(ctx, tied, 3000, 16, 0, True, 1, 2)
+    some = smooth.copy()
+    some[:, rng.choice(T, size=min(T // 2, 7000), replace=False)] = 0.5    # equal sums at the median, within the list
+    for bp in (4500, 5000, 6000):
+        _check(ctx, some, bp, 8, 0, True, 0, 1)
+    spread = np.exp(rng.standard_normal((1, T)) * 12.0).astype(np.float32)  # many binades, zeros and one huge score
+    spread[0, ::3] = 0.0
+    spread[0, T // 2] = 3e38
+    for bp in (1, 1500, 6600, 6700, 9999):
+        _check(ctx, spread, bp, 16, 1, True, 64, 0)
+    _check(ctx, np.full((1, T), 0.125, np.float32), 5000, 8, 5, True, 0, 0)
+    for bp in (0, 10000):
+        _check(ctx, smooth, bp, 8, 0, True, 2, 7)
