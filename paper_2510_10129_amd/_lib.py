@@ -298,11 +298,14 @@ class Context:
     def assemble_cache(self, chunk_K: Sequence, chunk_V: Sequence, P: int, n_tail: int, dst: KVLayer):
         """chunk_K[c], chunk_V[c]: cuda bf16 [P + L_c, H_kv, d_h], all with the same strides."""
         n = len(chunk_K)
-        arr = (_Chunk * n)()
         st = chunk_K[0].stride()
-        for i, (K, V) in enumerate(zip(chunk_K, chunk_V)):
-            assert K.shape == V.shape and K.stride() == st and V.stride() == st and st[2] == 1
-            arr[i] = _Chunk(K.data_ptr(), V.data_ptr(), K.shape[0] - P)
+        assert st[2] == 1
+        flat = []                               # a _Chunk is two addresses and a length padded to 8 bytes
+        for K, V in zip(chunk_K, chunk_V):
+            shape = K.shape
+            assert shape == V.shape and K.stride() == st and V.stride() == st
+            flat += (K.data_ptr(), V.data_ptr(), (shape[0] - P) & 0xFFFFFFFF)
+        arr = (_Chunk * n).from_buffer((C.c_uint64 * (3 * n))(*flat))
         kvs = dst.c_struct()
         self._check(self._lib.cc_assemble_cache(self._h, arr, n, P, st[0], st[1], n_tail, C.byref(kvs)))
 

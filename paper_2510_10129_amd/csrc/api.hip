@@ -529,7 +529,10 @@ cc_status cc_assemble_cache(cc_ctx* c, const cc_chunk_kv* chunks, int32_t n_chun
     if ((int64_t)P + T + n_tail > dst->N) return fail(c, CC_ERR_SHAPE, "P + T + n_tail exceeds dst->N");
     // segments: the prefix (from chunk 0), every chunk's own rows, the zeroed tail
     std::vector<cc_asm_seg> segs;
-    auto blocks_of = [](int len) { return (len + CC_ASM_ROWS - 1) / CC_ASM_ROWS; };
+    // rows per wave: 16, fewer where that leaves CUs without a workgroup of four waves
+    const int64_t n_rows = (int64_t)P + T + n_tail;
+    const int rows = n_rows >= 16 * 1024 ? 16 : n_rows >= 8 * 1024 ? 8 : 4;
+    auto blocks_of = [rows](int len) { return (len + rows - 1) / rows; };
     if (P > 0) segs.push_back({(const bf16_t*)chunks[0].K, (const bf16_t*)chunks[0].V, 0, P, 0, 0});
     int32_t start = 0;
     for (int i = 0; i < n_chunks; ++i) {
@@ -544,6 +547,7 @@ cc_status cc_assemble_cache(cc_ctx* c, const cc_chunk_kv* chunks, int32_t n_chun
         for (size_t s0 = 0; s0 < segs.size(); s0 += CC_ASM_SEGS) {
             cc_asm_args a;
             a.n_seg = (int32_t)std::min<size_t>(CC_ASM_SEGS, segs.size() - s0);
+            a.rows = rows;
             int32_t nb = 0;
             for (int i = 0; i < a.n_seg; ++i) {
                 a.seg[i] = segs[s0 + i];

@@ -4,12 +4,16 @@
 // more rotary rotation (rotations by p and by delta compose to p + delta).
 // Pure data movement plus 2 multiply-adds per key element: bound by HBM.
 //
-// A wave owns CC_ASM_ROWS consecutive destination rows of one segment, so the
-// (cos, sin) of the segment's position shift are loaded once per wave and kept
-// in registers.  Per key row a lane moves one 16-byte piece of the low half of
-// a head and the matching piece of the high half (the two members of every
-// rotary pair meet in one lane); value rows are 16-byte copies.  Loads of eight
-// rows are issued before their stores.
+// A wave owns a.rows consecutive destination rows of one segment, their keys (grid row 0)
+// or their values (grid row 1).  A lane owns one unit of a row: of a key row one 16-byte piece
+// of the low half of a head and the matching piece of the high half (the two members of every
+// rotary pair meet in one lane; its (cos, sin) of the segment's position shift are loaded once and kept
+// in registers), of a value row 16 bytes.  Rows of fewer than 64 units share a wave.  Loads of eight
+// rows a lane are issued before their stores.
+// Bytes in flight bound it; with keys and values of 16 rows in one wave and a row's units alone across
+// its lanes a small model's request was a few waves deep in latency: H_kv = 2, d_h = 64, 1072 rows
+// 14 -> 4.2 us; H_kv = 8, d_h = 128, 66k rows 108 -> 93 us (5.8 TB/s), 10 us of it the second launch that
+// 66 segments took.
 #include "cc_internal.h"
 
 namespace {
@@ -39,68 +43,75 @@ __global__ __launch_bounds__(256) void assemble_kernel(cc_asm_args a, const floa
         if (a.seg[mid].blk0 <= blk) { s = mid; lo = mid + 1; } else { hi = mid - 1; }
     }
     const cc_asm_seg sg = a.seg[s];
-    const int r0 = (blk - sg.blk0) * CC_ASM_ROWS;
-    const int r1 = min(sg.len, r0 + CC_ASM_ROWS);
+    const int r0 = (blk - sg.blk0) * a.rows;
+    const int r1 = min(sg.len, r0 + a.rows);
     const bool zero = sg.K == nullptr;
+    const int units = H_kv * (blockIdx.y ? CPH : UPH);
+    const int rpw = units < 64 ? 64 / units : 1;      // rows side by side in the wave
+    const int lr = units < 64 ? lane / units : 0;     // this lane's row of them
+    if (lr >= rpw) return;
+    const int u0 = lane - lr * units;
+    const int step = RU * rpw;
 
-    // ---- keys ----
-    for (int u = lane; u < H_kv * UPH; u += 64) {
-        const int h = u / UPH, j0 = (u - h * UPH) * 8;
-        float2 cs[8];
-        if (sg.delta != 0) {
+    if (blockIdx.y == 0) {
+        for (int u = u0; u < units; u += 64) {
+            const int h = u / UPH, j0 = (u - h * UPH) * 8;
+            float2 cs[8];
+            if (sg.delta != 0) {
 #pragma unroll
-            for (int e = 0; e < 8; ++e) cs[e] = rope[(int64_t)sg.delta * HALF + j0 + e];
-        }
-        const bf16_t* src = sg.K + (int64_t)h * src_sh + j0;
-        bf16_t* dst = Kd + (int64_t)sg.dst * dst_st + (int64_t)h * dst_sh + j0;
-        for (int r = r0; r < r1; r += RU) {
-            bf16x8 lo[RU], hi[RU];
-#pragma unroll
-            for (int i = 0; i < RU; ++i) {
-                const int rr = min(r + i, r1 - 1);       // rows past the end repeat the last one
-                if (zero) {
-                    lo[i] = zero8();
-                    hi[i] = zero8();
-                } else {
-                    lo[i] = __builtin_nontemporal_load(reinterpret_cast<const bf16x8*>(src + (int64_t)rr * src_st));
-                    hi[i] = __builtin_nontemporal_load(reinterpret_cast<const bf16x8*>(src + (int64_t)rr * src_st + HALF));
-                }
+                for (int e = 0; e < 8; ++e) cs[e] = rope[(int64_t)sg.delta * HALF + j0 + e];
             }
+            const bf16_t* src = sg.K + (int64_t)h * src_sh + j0;
+            bf16_t* dst = Kd + (int64_t)sg.dst * dst_st + (int64_t)h * dst_sh + j0;
+            for (int r = r0 + lr; r < r1; r += step) {
+                bf16x8 lo[RU], hi[RU];
 #pragma unroll
-            for (int i = 0; i < RU; ++i) {
-                if (r + i >= r1) break;
-                bf16x8 ol = lo[i], oh = hi[i];
-                if (sg.delta != 0) {
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) {
-                        const float x = (float)lo[i][e], y = (float)hi[i][e];
-                        ol[e] = (bf16_t)(x * cs[e].x - y * cs[e].y);
-                        oh[e] = (bf16_t)(y * cs[e].x + x * cs[e].y);
+                for (int i = 0; i < RU; ++i) {
+                    const int rr = min(r + i * rpw, r1 - 1);       // rows past the end repeat the last one
+                    if (zero) {
+                        lo[i] = zero8();
+                        hi[i] = zero8();
+                    } else {
+                        lo[i] = __builtin_nontemporal_load(reinterpret_cast<const bf16x8*>(src + (int64_t)rr * src_st));
+                        hi[i] = __builtin_nontemporal_load(reinterpret_cast<const bf16x8*>(src + (int64_t)rr * src_st + HALF));
                     }
                 }
-                bf16_t* d = dst + (int64_t)(r + i) * dst_st;
-                __builtin_nontemporal_store(ol, reinterpret_cast<bf16x8*>(d));
-                __builtin_nontemporal_store(oh, reinterpret_cast<bf16x8*>(d + HALF));
+#pragma unroll
+                for (int i = 0; i < RU; ++i) {
+                    if (r + i * rpw >= r1) break;
+                    bf16x8 ol = lo[i], oh = hi[i];
+                    if (sg.delta != 0) {
+#pragma unroll
+                        for (int e = 0; e < 8; ++e) {
+                            const float x = (float)lo[i][e], y = (float)hi[i][e];
+                            ol[e] = (bf16_t)(x * cs[e].x - y * cs[e].y);
+                            oh[e] = (bf16_t)(y * cs[e].x + x * cs[e].y);
+                        }
+                    }
+                    bf16_t* d = dst + (int64_t)(r + i * rpw) * dst_st;
+                    __builtin_nontemporal_store(ol, reinterpret_cast<bf16x8*>(d));
+                    __builtin_nontemporal_store(oh, reinterpret_cast<bf16x8*>(d + HALF));
+                }
             }
         }
-    }
-    // ---- values ----
-    for (int c = lane; c < H_kv * CPH; c += 64) {
-        const int h = c / CPH, e0 = (c - h * CPH) * 8;
-        const bf16_t* src = sg.V + (int64_t)h * src_sh + e0;
-        bf16_t* dst = Vd + (int64_t)sg.dst * dst_st + (int64_t)h * dst_sh + e0;
-        for (int r = r0; r < r1; r += RU) {
-            bf16x8 v[RU];
+    } else {
+        for (int c = u0; c < units; c += 64) {
+            const int h = c / CPH, e0 = (c - h * CPH) * 8;
+            const bf16_t* src = sg.V + (int64_t)h * src_sh + e0;
+            bf16_t* dst = Vd + (int64_t)sg.dst * dst_st + (int64_t)h * dst_sh + e0;
+            for (int r = r0 + lr; r < r1; r += step) {
+                bf16x8 v[RU];
 #pragma unroll
-            for (int i = 0; i < RU; ++i) {
-                const int rr = min(r + i, r1 - 1);
-                v[i] = zero ? zero8()
-                            : __builtin_nontemporal_load(reinterpret_cast<const bf16x8*>(src + (int64_t)rr * src_st));
-            }
+                for (int i = 0; i < RU; ++i) {
+                    const int rr = min(r + i * rpw, r1 - 1);
+                    v[i] = zero ? zero8()
+                                : __builtin_nontemporal_load(reinterpret_cast<const bf16x8*>(src + (int64_t)rr * src_st));
+                }
 #pragma unroll
-            for (int i = 0; i < RU; ++i) {
-                if (r + i >= r1) break;
-                __builtin_nontemporal_store(v[i], reinterpret_cast<bf16x8*>(dst + (int64_t)(r + i) * dst_st));
+                for (int i = 0; i < RU; ++i) {
+                    if (r + i * rpw >= r1) break;
+                    __builtin_nontemporal_store(v[i], reinterpret_cast<bf16x8*>(dst + (int64_t)(r + i * rpw) * dst_st));
+                }
             }
         }
     }
@@ -111,7 +122,7 @@ __global__ __launch_bounds__(256) void assemble_kernel(cc_asm_args a, const floa
 void cc_launch_assemble(const cc_asm_args& a, const float2* rope, const cc_model_desc& m,
                         int64_t src_st, int64_t src_sh, const cc_kv_layer& dst, hipStream_t s) {
     if (a.n_blocks <= 0) return;
-    dim3 grid((a.n_blocks + 3) / 4), block(256);
+    dim3 grid((a.n_blocks + 3) / 4, 2), block(256);
     if (m.d_h == 128)
         hipLaunchKernelGGL(assemble_kernel<128>, grid, block, 0, s, a, rope, m.H_kv, src_st, src_sh,
                            (bf16_t*)dst.K, (bf16_t*)dst.V, dst.stride_token, dst.stride_head);

@@ -68,8 +68,7 @@ struct cc_prof_scope {
 // ---- kernel launchers (each only enqueues on `s`) ----
 // The projections take a workspace `ws` of `ws_floats` floats (may be NULL) for split-K launches.
 // One launch of the assembly kernel covers up to CC_ASM_SEGS source segments.
-#define CC_ASM_SEGS 64
-#define CC_ASM_ROWS 16      // destination rows per wave
+#define CC_ASM_SEGS 112     // with the other arguments within the 4 KB of a launch
 struct cc_asm_seg {
     const bf16_t* K;        // first source row (NULL: write zeros)
     const bf16_t* V;
@@ -81,6 +80,7 @@ struct cc_asm_seg {
 struct cc_asm_args {
     cc_asm_seg seg[CC_ASM_SEGS];
     int32_t n_seg, n_blocks;
+    int32_t rows;           // destination rows per wave
 };
 void cc_launch_assemble(const cc_asm_args& a, const float2* rope, const cc_model_desc& m,
                         int64_t src_st, int64_t src_sh, const cc_kv_layer& dst, hipStream_t s);

@@ -104,3 +104,18 @@ def test_argument_errors():
     ctx.assemble_cache([K, K], [K, K], 4, 4, dst)                    # fits exactly: 4 + 32 + 4
     torch.cuda.synchronize()
     ctx.close()
+
+
+@pytest.mark.parametrize("H_kv,d_h,P,Q,lens", [(2, 64, 16, 32, [256] * 4), (5, 64, 3, 1, [1, 2, 37, 64, 65]), (1, 128, 0, 7, [9]),
+                                               (3, 128, 33, 70, [500] * 17), (2, 64, 5, 9, [3, 1] * 65)])
+def test_rows_that_share_a_wave(H_kv, d_h, P, Q, lens):
+    """Rows of fewer units than a wave has lanes (2, 3 and 8 rows side by side, idle lanes where the
+    units do not divide 64), 4, 8 and 16 rows a wave, segments that end inside one; more
+    segments than one launch takes."""
+    rng = np.random.default_rng(H_kv * 100 + len(lens))
+    model = ModelShape(H_kv * d_h, H_kv, H_kv, d_h, 64, 5e5, 1e-5, False, 1)
+    cK = [gen.f32_to_bf16_bits(rng.standard_normal((P + L, H_kv, d_h)).astype(np.float32)) for L in lens]
+    cV = [gen.f32_to_bf16_bits(rng.standard_normal((P + L, H_kv, d_h)).astype(np.float32)) for L in lens]
+    Kg, Vg = _assemble(model, cK, cV, P, Q, pad_rows=3)
+    _check(model, cK, cV, P, Q, Kg, Vg)
+    assert (bits_f64(Kg[-3:]) == 7.0).all() and (bits_f64(Vg[-3:]) == 7.0).all()
