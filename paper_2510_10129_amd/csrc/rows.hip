@@ -7,105 +7,136 @@ __device__ __forceinline__ float wave_sum(float v) {
     return v;
 }
 
-// One wave per recomputed token, the whole row held in registers between the
-// sum of squares and the scaled write (one pass over HBM): lane L owns the
-// 16-byte chunks L, L+64, ... of row gather_idx[i], so every load and store of a
-// wave covers 1 KiB of contiguous row.  NCH = chunks per lane (d <= 512*NCH).
-template <int NCH>
+// Sum over the WPR waves of a row (WPR 1 or 4; a workgroup is four waves).
+template <int WPR>
+__device__ __forceinline__ float row_sum(float v) {
+    v = wave_sum(v);
+    if constexpr (WPR == 4) {
+        __shared__ float part[4];
+        if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = v;
+        __syncthreads();
+        v = (part[0] + part[1]) + (part[2] + part[3]);
+    }
+    return v;
+}
+
+// WPR waves per recomputed token, the whole row held in registers between the
+// sum of squares and the scaled write (one pass over HBM): lane L of them owns the
+// 16-byte chunks L, L + 64 WPR, ... of row gather_idx[i], so every load and store of a
+// wave covers 1 KiB of contiguous row.  NCH = chunks per lane (d <= 512*NCH*WPR).
+// Four waves a row wherever a wave would have more than two loads of it: they hold the row and the
+// weights' chunks in flight together, and a lane's share fits the registers of full occupancy.
+// Event microseconds, one wave and four, d = 4096: M = 64: 9.2 -> 6.1, 884: 10.1 -> 7.6, 2047: 12.4 -> 11.1;
+// d = 8192: 64: 13.2 -> 6.5, 2047: 21.3 -> 16.3.
+template <int NCH, int WPR>
 __global__ __launch_bounds__(256) void gather_rmsnorm_kernel(
     const bf16_t* __restrict__ hidden, const int32_t* __restrict__ gather_idx, int M, int d,
     const bf16_t* __restrict__ w, float eps, bf16_t* __restrict__ xn) {
-    const int lane = threadIdx.x & 63;
-    const int i = blockIdx.x * 4 + (threadIdx.x >> 6);
+    const int lane = threadIdx.x % (64 * WPR);
+    const int i = blockIdx.x * (4 / WPR) + threadIdx.x / (64 * WPR);
     if (i >= M) return;
     const int64_t src = gather_idx ? (int64_t)gather_idx[i] : (int64_t)i;
     const bf16x8* row = reinterpret_cast<const bf16x8*>(hidden + src * d);
     const bf16x8* wv = reinterpret_cast<const bf16x8*>(w);
     bf16x8* dst = reinterpret_cast<bf16x8*>(xn + (int64_t)i * d);
     const int nchunk = d >> 3;
-    bf16x8 v[NCH];
+    constexpr int ST = 64 * WPR;
+    bf16x8 v[NCH], g[NCH];
     float ss = 0.0f;
 #pragma unroll
     for (int c = 0; c < NCH; ++c)
-        if (lane + 64 * c < nchunk) v[c] = __builtin_nontemporal_load(row + lane + 64 * c);
+        if (lane + ST * c < nchunk) v[c] = __builtin_nontemporal_load(row + lane + ST * c);
+    if constexpr (WPR == 4) {
+#pragma unroll
+        for (int c = 0; c < NCH; ++c)
+            if (lane + ST * c < nchunk) g[c] = wv[lane + ST * c];
+    }
 #pragma unroll
     for (int c = 0; c < NCH; ++c)
-        if (lane + 64 * c < nchunk) {
+        if (lane + ST * c < nchunk) {
 #pragma unroll
             for (int u = 0; u < 8; ++u) {
                 float f = (float)v[c][u];
                 ss += f * f;
             }
         }
-    const float r = 1.0f / sqrtf(wave_sum(ss) / (float)d + eps);
+    const float r = 1.0f / sqrtf(row_sum<WPR>(ss) / (float)d + eps);
 #pragma unroll
     for (int c = 0; c < NCH; ++c)
-        if (lane + 64 * c < nchunk) {
-            bf16x8 g = wv[lane + 64 * c], o;
+        if (lane + ST * c < nchunk) {
+            bf16x8 o;
+            if constexpr (WPR != 4) g[c] = wv[lane + ST * c];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) o[u] = (bf16_t)((float)v[c][u] * r * (float)g[u]);
-            dst[lane + 64 * c] = o;
+            for (int u = 0; u < 8; ++u) o[u] = (bf16_t)((float)v[c][u] * r * (float)g[c][u]);
+            dst[lane + ST * c] = o;
         }
 }
 
 void cc_launch_gather_rmsnorm(const bf16_t* hidden, const int32_t* gather_idx, int M, int d,
                               const bf16_t* w, float eps, bf16_t* xn, hipStream_t s) {
     if (M <= 0) return;
-    dim3 grid((M + 3) / 4), block(256);
-    if (d <= 1024)
-        hipLaunchKernelGGL(gather_rmsnorm_kernel<2>, grid, block, 0, s, hidden, gather_idx, M, d, w, eps, xn);
-    else if (d <= 4096)
-        hipLaunchKernelGGL(gather_rmsnorm_kernel<8>, grid, block, 0, s, hidden, gather_idx, M, d, w, eps, xn);
-    else if (d <= 8192)
-        hipLaunchKernelGGL(gather_rmsnorm_kernel<16>, grid, block, 0, s, hidden, gather_idx, M, d, w, eps, xn);
-    else
-        hipLaunchKernelGGL(gather_rmsnorm_kernel<32>, grid, block, 0, s, hidden, gather_idx, M, d, w, eps, xn);
+    const bool wide = d > 1024;
+    dim3 grid(wide ? M : (M + 3) / 4), block(256);
+#define CC_NORM(NCH, WPR) hipLaunchKernelGGL((gather_rmsnorm_kernel<NCH, WPR>), grid, block, 0, s, hidden, gather_idx, M, d, w, eps, xn)
+    if (d <= 1024) CC_NORM(2, 1);
+    else if (d <= 4096) CC_NORM(2, 4);
+    else if (d <= 8192) CC_NORM(4, 4);
+    else CC_NORM(8, 4);
+#undef CC_NORM
 }
 
 // RMSNorm of the fp32 residual rows y [M, d] -> bf16, same scheme (lane owns
-// 16-byte chunks of 4 floats; NCH chunks per lane, d <= 256*NCH).
-template <int NCH>
+// 16-byte chunks of 4 floats; NCH chunks per lane, d <= 256*NCH*WPR;
+// d = 4096: M = 64: 11.0 -> 6.1 us, 884: 13.0 -> 8.7, 2047: 17.2 -> 12.7; d = 8192: 64: 18.0 -> 6.3, 2047: 29.6 -> 19.8).
+template <int NCH, int WPR>
 __global__ __launch_bounds__(256) void rmsnorm_f32_kernel(const float* __restrict__ y, int M, int d,
                                                           const bf16_t* __restrict__ w, float eps,
                                                           bf16_t* __restrict__ out) {
-    const int lane = threadIdx.x & 63;
-    const int i = blockIdx.x * 4 + (threadIdx.x >> 6);
+    const int lane = threadIdx.x % (64 * WPR);
+    const int i = blockIdx.x * (4 / WPR) + threadIdx.x / (64 * WPR);
     if (i >= M) return;
     const f32x4* row = reinterpret_cast<const f32x4*>(y + (int64_t)i * d);
     const bf16x4* wv = reinterpret_cast<const bf16x4*>(w);
     bf16x4* dst = reinterpret_cast<bf16x4*>(out + (int64_t)i * d);
     const int nchunk = d >> 2;
+    constexpr int ST = 64 * WPR;
     f32x4 v[NCH];
+    bf16x4 g[NCH];
     float ss = 0.0f;
 #pragma unroll
     for (int c = 0; c < NCH; ++c)
-        if (lane + 64 * c < nchunk) v[c] = row[lane + 64 * c];
+        if (lane + ST * c < nchunk) v[c] = row[lane + ST * c];
+    if constexpr (WPR == 4) {
+#pragma unroll
+        for (int c = 0; c < NCH; ++c)
+            if (lane + ST * c < nchunk) g[c] = wv[lane + ST * c];
+    }
 #pragma unroll
     for (int c = 0; c < NCH; ++c)
-        if (lane + 64 * c < nchunk) ss += v[c][0] * v[c][0] + v[c][1] * v[c][1] + v[c][2] * v[c][2] + v[c][3] * v[c][3];
-    const float r = 1.0f / sqrtf(wave_sum(ss) / (float)d + eps);
+        if (lane + ST * c < nchunk) ss += v[c][0] * v[c][0] + v[c][1] * v[c][1] + v[c][2] * v[c][2] + v[c][3] * v[c][3];
+    const float r = 1.0f / sqrtf(row_sum<WPR>(ss) / (float)d + eps);
 #pragma unroll
     for (int c = 0; c < NCH; ++c)
-        if (lane + 64 * c < nchunk) {
-            bf16x4 g = wv[lane + 64 * c], o;
+        if (lane + ST * c < nchunk) {
+            bf16x4 o;
+            if constexpr (WPR != 4) g[c] = wv[lane + ST * c];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) o[u] = (bf16_t)(v[c][u] * r * (float)g[u]);
-            dst[lane + 64 * c] = o;
+            for (int u = 0; u < 4; ++u) o[u] = (bf16_t)(v[c][u] * r * (float)g[c][u]);
+            dst[lane + ST * c] = o;
         }
 }
 
 void cc_launch_rmsnorm_f32(const float* y, int M, int d, const bf16_t* w, float eps, bf16_t* out,
                            hipStream_t s) {
     if (M <= 0) return;
-    dim3 grid((M + 3) / 4), block(256);
-    if (d <= 1024)
-        hipLaunchKernelGGL(rmsnorm_f32_kernel<4>, grid, block, 0, s, y, M, d, w, eps, out);
-    else if (d <= 4096)
-        hipLaunchKernelGGL(rmsnorm_f32_kernel<16>, grid, block, 0, s, y, M, d, w, eps, out);
-    else if (d <= 8192)
-        hipLaunchKernelGGL(rmsnorm_f32_kernel<32>, grid, block, 0, s, y, M, d, w, eps, out);
-    else
-        hipLaunchKernelGGL(rmsnorm_f32_kernel<64>, grid, block, 0, s, y, M, d, w, eps, out);
+    const bool wide = d > 512;
+    dim3 grid(wide ? M : (M + 3) / 4), block(256);
+#define CC_NORM(NCH, WPR) hipLaunchKernelGGL((rmsnorm_f32_kernel<NCH, WPR>), grid, block, 0, s, y, M, d, w, eps, out)
+    if (!wide) CC_NORM(2, 1);
+    else if (d <= 4096) CC_NORM(4, 4);
+    else if (d <= 8192) CC_NORM(8, 4);
+    else CC_NORM(16, 4);
+#undef CC_NORM
 }
 
 // Rotary table: entry (p, j) = (cos, sin) of p * base^(-2j/d_h), evaluated in
