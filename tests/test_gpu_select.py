@@ -253,3 +253,14 @@ def test_selection_by_several_workgroups_edges(ctx, T):
     _check(ctx, np.full((1, T), 0.125, np.float32), 5000, 8, 5, True, 0, 0)
     for bp in (0, 10000):
         _check(ctx, smooth, bp, 8, 0, True, 2, 7)
+
+
+def test_block_scores_leave_ranges_for_the_selection(ctx):
+    """Several score launches (more batch elements than one takes, ragged, shorter than a workgroup's
+    columns) in front of a selection by one workgroup and by several."""
+    rng = np.random.default_rng(3)
+    for lens in ([40] * 70, [1] * 130, [int(v) for v in rng.integers(1, 600, size=80)]):
+        blocks = [(rng.random((2, 3, 2 + L + 3), dtype=np.float32), 2, L) for L in lens]
+        ref = osel.select_from_scores(osel.block_scores(blocks), 3000, 8, 0, True, 2, 3)
+        idx, n = ctx.select_blocks(_dev_blocks(blocks), 3000, 8, 0, 0, 2, 3)
+        assert n == len(ref) and np.array_equal(idx[:n].cpu().numpy(), ref), len(lens)
