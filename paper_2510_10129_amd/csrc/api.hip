@@ -168,8 +168,8 @@ cc_status cc_create(cc_ctx** out, const cc_model_desc* desc, void* hip_stream) {
     alloc((void**)&c->y, Mc * m.d * 4);
     alloc((void**)&c->mn, Mc * m.d * 2);
     alloc((void**)&c->act, Mc * m.f * 2);
-    // two pieces of blocks for every workgroup of an even attention grid: at most 512 slots, 69 MB
-    c->attn_slots = 2 * cc_attn_even_workgroups(m, m.M_cap, m.N_cap);
+    // two pieces of blocks for every workgroup of an attention grid that cuts them: at most 512 slots, 69 MB
+    c->attn_slots = 2 * cc_attn_piece_workgroups(m, m.M_cap, m.N_cap);
     alloc((void**)&c->attn_part, (size_t)c->attn_slots * 256 * (m.d_h + 4) * 4);
     alloc((void**)&c->attn_table, (1024 + 2) * sizeof(int));
     // shares of a split-K projection: up to 8 x [M_cap][widest padded output], at most 128 MB

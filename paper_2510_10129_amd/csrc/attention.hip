@@ -46,6 +46,7 @@
 // workgroup id modulo H_kv picks the kv head, so the workgroups resident on
 // one XCD walk the same K/V stream through that XCD's L2.
 #include "cc_internal.h"
+#include "launch_plan.h"
 #include <algorithm>
 #include <type_traits>
 
@@ -547,9 +548,9 @@ __global__ __launch_bounds__(512, 1) void wide_stride_attn_kernel(CC_ATTN_ARGS) 
 // of range w (a piece of the block that the range starts in, of a later one) and
 // attn_merge_kernel combines the pieces of a block.  Consecutive ranges run on one XCD, so that its
 // L2 serves one kv head when H_kv = 8.
-constexpr int EVEN_START = 5;             // 3 and 5 units measured: 5 is 1 % of the layer faster
-constexpr int EVEN_RANGES = 256;          // one a CU
-constexpr int EVEN_MAX_TILES = 1024;      // row tiles whose first units fit the LDS table
+constexpr int EVEN_START = CC_ATTN_EVEN_START;          // 3 and 5 units measured: 5 is 1 % of the layer faster
+constexpr int EVEN_MAX_TILES = CC_ATTN_EVEN_MAX_TILES;
+constexpr int CUS = 256;
 // table: [n_row_tiles + 2] the first unit of every row tile within a head, their sum, units per range
 template <int D_H>
 __global__ __launch_bounds__(512, 1) void even_attn_kernel(CC_ATTN_ARGS, int per_min, float* __restrict__ part,
@@ -620,74 +621,105 @@ __global__ __launch_bounds__(512, 1) void even_attn_kernel(CC_ATTN_ARGS, int per
     }
 }
 
-// Combines the pieces of the blocks that an even grid has cut:
+// Whole blocks cut S ways: workgroup (block, s) takes the s-th of S equal runs of the block's key tiles
+// and leaves its piece in slot block * S + s; attn_merge_kernel combines them.
+template <int D_H, class Off>
+__device__ __forceinline__ void attend_cut(CC_ATTN_ARGS, float* __restrict__ part) {
+    __shared__ __align__(16) bf16_t smem[LDS_TILES * BN_KEYS * D_H];
+    __shared__ int simd_waves[4], group_waves[2];
+    int grp, widx;
+    wave_role(simd_waves, group_waves, grp, widx);
+    const int g = H_q / H_kv, kvh = blockIdx.x % H_kv, rt = n_row_tiles - 1 - blockIdx.x / H_kv, S = gridDim.y;
+    const int L = last_key(idx, M, g, rt) / BN_KEYS + 1, per = (L + S - 1) / S;
+    const int ta = blockIdx.y * per, n = min(per, L - ta);
+    const int slot = (kvh * n_row_tiles + rt) * S + blockIdx.y;
+    if (n <= 0) {                                        // a short block: no keys for this piece
+        float* pp = part + (int64_t)slot * 256 * (D_H + 4) + (threadIdx.x >> 6) * 32 * (D_H + 4);
+        *reinterpret_cast<float2*>(pp + 32 * D_H + (threadIdx.x & 63) * 2) = make_float2(-INFINITY, 0.0f);
+        return;
+    }
+    attend<D_H, true, Off>(q, M, idx, H_q, g, Kc, Vc, st, sh, N, o, scale_log2, part, smem, grp, widx, kvh, rt, ta, n, slot);
+}
+template <int D_H>
+__global__ __launch_bounds__(512, 1) void cut_attn_kernel(CC_ATTN_ARGS, float* __restrict__ part) {
+    attend_cut<D_H, uint32_t>(q, M, idx, H_q, H_kv, Kc, Vc, st, sh, N, o, n_row_tiles, scale_log2, part);
+}
+
+// Combines the pieces of the blocks that an even grid (S = 0) or a cut one (S pieces) has left:
 // o = sum_s 2^(m_s - m) O_s / sum_s 2^(m_s - m) l_s with m = max m_s, pieces in the order of their keys.
-// Workgroup (block, 32 of its columns = one wave of the attention kernel); a thread holds the same
-// elements as the lane that wrote them, a wave of this kernel D_H / 4 of a column's.  Four
-// pieces at a time, so that their loads are out together.
+// Workgroup (block, 32 of its columns = one wave of the attention kernel, 32 of their d's); a
+// thread holds the same elements as the lane that wrote them, four of a column.  Up to eight pieces at
+// a time, so that their loads are out together.  Workgroup id modulo H_kv is the kv head, as in the attention
+// kernels, so that a piece is read through the L2 that it was written to: with the heads one after
+// the other 64 blocks of 3 pieces took 34 us in both launches, so 25 (64 query heads of 8, N = 850,
+// M = 256).  32 d's a workgroup instead of all: 1 to 2 us of a few blocks' merge.
 template <int D_H>
 __global__ __launch_bounds__(256) void attn_merge_kernel(const float* __restrict__ part, const int* __restrict__ table,
-                                                         int M, int H_q, int H_kv, int n_row_tiles,
+                                                         int S, int M, int H_q, int H_kv, int n_row_tiles,
                                                          bf16_t* __restrict__ o) {
-    constexpr int NV = D_H / 32;                         // 16-byte groups of a thread
-    const int g = H_q / H_kv, kvh = blockIdx.x / n_row_tiles, rt = blockIdx.x - kvh * n_row_tiles;
-    const int per = table[n_row_tiles + 1], head = kvh * table[n_row_tiles];
-    const int first = head + table[rt], end = head + table[rt + 1];
-    const int w0 = (first + EVEN_START) / per, w1 = (end - 1) / per;   // the ranges that hold its key tiles
-    if (w0 == w1) return;
-    const int lane = threadIdx.x & 63, v0 = (threadIdx.x >> 6) * NV;
+    const int g = H_q / H_kv, kvh = blockIdx.x % H_kv, rt = blockIdx.x / H_kv;
+    int w0 = 0, w1 = S - 1, per = 1, first = 0;
+    if (S == 0) {                                        // even grid: the ranges that hold the block's key tiles
+        per = table[n_row_tiles + 1];
+        const int head = kvh * table[n_row_tiles], end = head + table[rt + 1];
+        first = head + table[rt];
+        w0 = (first + EVEN_START) / per;
+        w1 = (end - 1) / per;
+        if (w0 == w1) return;
+    }
+    const int lane = threadIdx.x & 63, v0 = blockIdx.z * 4 + (threadIdx.x >> 6);     // 16-byte group of a column
     const int col = rt * 256 + blockIdx.y * 32 + (lane & 31), mi = col / g, hg = col - mi * g;
     if (mi >= M) return;
     float m = -INFINITY, l = 0.0f;
-    f32x4 acc[NV];
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    auto take = [&](auto nc, int wb) __attribute__((always_inline)) {
+        constexpr int NP = decltype(nc)::value;
+        f32x4 v[NP];
+        float2 ml[NP];
 #pragma unroll
-    for (int i = 0; i < NV; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
-    for (int wb = w0; wb <= w1; wb += 4) {
-        f32x4 v[4][NV];
-        float2 ml[4];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
+        for (int k = 0; k < NP; ++k) {
             const int w = min(wb + k, w1);               // past the end: the last piece again, with weight 0
-            const float* pp = part + (int64_t)(2 * w + (w * per < first ? 1 : 0)) * 256 * (D_H + 4) + blockIdx.y * 32 * (D_H + 4);
+            const int slot = S ? (kvh * n_row_tiles + rt) * S + w : 2 * w + (w * per < first ? 1 : 0);
+            const float* pp = part + (int64_t)slot * 256 * (D_H + 4) + blockIdx.y * 32 * (D_H + 4);
             ml[k] = *reinterpret_cast<const float2*>(pp + 32 * D_H + lane * 2);
-#pragma unroll
-            for (int i = 0; i < NV; ++i) v[k][i] = *reinterpret_cast<const f32x4*>(pp + (v0 + i) * 256 + lane * 4);
+            v[k] = *reinterpret_cast<const f32x4*>(pp + v0 * 256 + lane * 4);
         }
         float mn = m;
 #pragma unroll
-        for (int k = 0; k < 4; ++k) mn = fmaxf(mn, ml[k].x);
+        for (int k = 0; k < NP; ++k) mn = fmaxf(mn, ml[k].x);
         const float ref = mn == -INFINITY ? 0.0f : mn;   // no key of this column so far
         const float keep = __builtin_amdgcn_exp2f(m - ref);
         l *= keep;
+        acc *= keep;
 #pragma unroll
-        for (int i = 0; i < NV; ++i) acc[i] *= keep;
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const float f = wb + k <= w1 ? __builtin_amdgcn_exp2f(ml[k].x - ref) : 0.0f;
+        for (int k = 0; k < NP; ++k) {
+            // a piece without keys of this column: a cut grid's empty piece leaves no sums at all
+            const bool on = wb + k <= w1 && ml[k].x != -INFINITY;
+            const float f = on ? __builtin_amdgcn_exp2f(ml[k].x - ref) : 0.0f;
             l += ml[k].y * f;
 #pragma unroll
-            for (int i = 0; i < NV; ++i) acc[i] += v[k][i] * f;
+            for (int e = 0; e < 4; ++e) acc[e] += on ? v[k][e] * f : 0.0f;
         }
         m = mn;
+    };
+    for (int wb = w0; wb <= w1;) {
+        const int left = w1 - wb + 1;
+        if (left > 4) take(std::integral_constant<int, 8>{}, wb), wb += 8;
+        else if (left > 2) take(std::integral_constant<int, 4>{}, wb), wb += 4;
+        else take(std::integral_constant<int, 2>{}, wb), wb += 2;
     }
     const float inv = l > 0.0f ? 1.0f / l : 0.0f;
     bf16_t* op = o + ((int64_t)mi * H_q + kvh * g + hg) * D_H + 4 * (lane >> 5);
+    bf16x4 r;
 #pragma unroll
-    for (int i = 0; i < NV; ++i) {
-        bf16x4 r;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) r[e] = (bf16_t)(acc[i][e] * inv);
-        *reinterpret_cast<bf16x4*>(op + 8 * (v0 + i)) = r;
-    }
+    for (int e = 0; e < 4; ++e) r[e] = (bf16_t)(acc[e] * inv);
+    *reinterpret_cast<bf16x4*>(op + 8 * v0) = r;
 }
 
 }  // namespace
 
-int cc_attn_even_workgroups(const cc_model_desc& m, int64_t M, int64_t N) {
-    // a range of fewer than five units would be mostly start and merge
-    const int64_t tiles = (M * (m.H_q / m.H_kv) + 255) / 256 * m.H_kv;
-    const int64_t units = tiles * ((N + BN_KEYS - 1) / BN_KEYS + EVEN_START);
-    return (int)std::min<int64_t>(EVEN_RANGES, std::max(units / 5 + 1, 8 * tiles));
+int cc_attn_piece_workgroups(const cc_model_desc& m, int64_t M, int64_t N) {
+    return cc_plan_attn_workgroups(CUS, (M * (m.H_q / m.H_kv) + 255) / 256 * m.H_kv, (N + BN_KEYS - 1) / BN_KEYS);
 }
 
 void cc_launch_attention(const bf16_t* q, int M, const int32_t* idx, const cc_model_desc& m,
@@ -712,31 +744,25 @@ void cc_launch_attention(const bf16_t* q, int M, const int32_t* idx, const cc_mo
     } while (0)
     // 64 rows of a tile, 2 bytes an element, in an unsigned 32-bit lane offset
     const bool wide = kv.stride_token >= (1ll << 32) / (2 * (BN_KEYS + 1));
-    // Even grid where one block per workgroup would leave much of the chip idle: up to 1.25 blocks
-    // per CU.  Its ranges walk their keys out of step, so that an XCD's L2 serves less of the
-    // cache traffic and a tile takes 2.1 us against 1.8, and the pieces are written and read once more.
-    // Microseconds with one block per workgroup and with even ranges, H_q = 32, H_kv = 8, d_h = 128:
-    // 16k context, 144 blocks 358 / 192, 264: 403 / 335, 320: 417 / 382, 432: 489 / 496; 4k context,
-    // 168: 102 / 76, 424: 125 / 150; four kv heads at 29k, 328: 700 / 597.
-    const int per_min = ovr.attn_splits > 1 ? (t_max + ovr.attn_splits - 1) / ovr.attn_splits : 5;   // the override: about that many pieces of the longest block
-    const bool even = ovr.attn_splits > 1 || (ovr.attn_splits == 0 && 4 * n_wg <= 5 * EVEN_RANGES);
-    const int64_t most_units = (int64_t)n_wg * (t_max + EVEN_START);
-    int ranges = 0;
-    if (even && !wide && n_row_tiles <= EVEN_MAX_TILES && most_units < (1 << 30)) {
-        ranges = (int)std::min<int64_t>(most_units / per_min + 1, slots / 2);
-        if (ovr.attn_splits == 0) ranges = std::min(ranges, EVEN_RANGES);
-    }
-    if (ranges > 0) {
-        CC_ATTN_LAUNCH(even_attn_kernel, ranges, per_min, part, table);
-        const dim3 mg(n_wg, 8);
-        if (m.d_h == 128)
-            hipLaunchKernelGGL(attn_merge_kernel<128>, mg, dim3(256), 0, s, part, table, M, m.H_q, m.H_kv, n_row_tiles, o);
-        else
-            hipLaunchKernelGGL(attn_merge_kernel<64>, mg, dim3(256), 0, s, part, table, M, m.H_q, m.H_kv, n_row_tiles, o);
+    cc_attn_plan p = cc_plan_attention(CUS, n_row_tiles, m.H_kv, m.d_h, t_max, slots, ovr.attn_splits);
+    if (wide) p.kind = CC_ATTN_WHOLE;
+    if (p.kind == CC_ATTN_EVEN) {
+        CC_ATTN_LAUNCH(even_attn_kernel, p.ranges, p.per_min, part, table);
+    } else if (p.kind == CC_ATTN_CUT) {
+        const dim3 cg(n_wg, p.pieces);
+        CC_ATTN_LAUNCH(cut_attn_kernel, cg, part);
     } else if (wide) {
         CC_ATTN_LAUNCH(wide_stride_attn_kernel, n_wg);
     } else {
         CC_ATTN_LAUNCH(sparse_attn_kernel, n_wg);
+    }
+    if (p.kind != CC_ATTN_WHOLE) {
+        const int S = p.kind == CC_ATTN_CUT ? p.pieces : 0;
+        const dim3 mg(n_wg, 8, m.d_h / 32);
+        if (m.d_h == 128)
+            hipLaunchKernelGGL(attn_merge_kernel<128>, mg, dim3(256), 0, s, part, table, S, M, m.H_q, m.H_kv, n_row_tiles, o);
+        else
+            hipLaunchKernelGGL(attn_merge_kernel<64>, mg, dim3(256), 0, s, part, table, S, M, m.H_q, m.H_kv, n_row_tiles, o);
     }
 #undef CC_ATTN_LAUNCH
 }

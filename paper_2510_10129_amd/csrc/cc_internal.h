@@ -35,9 +35,9 @@ struct cc_ctx {
     float* y;          // [M_cap][d]          residual stream after attention
     bf16_t* mn;        // [M_cap][d]          normalised MLP input
     bf16_t* act;       // [M_cap][f]          silu(gate)*up
-    float* attn_part;  // [attn_slots][256][d_h + 4]  pieces of the blocks that an even attention grid cuts
+    float* attn_part;  // [attn_slots][256][d_h + 4]  pieces of the blocks that an attention grid cuts
     int attn_slots;
-    int* attn_table;   // [1026]  that launch's table of units
+    int* attn_table;   // [1026]  an even attention grid's table of units
     float* gemm_part;  // [gemm_part_floats]  fp32 shares of a split-K projection
     int64_t gemm_part_floats;
     float* score;      // [T_cap]
@@ -130,9 +130,9 @@ void cc_launch_qkv(const bf16_t* xn, int M, const int32_t* idx, const bf16_t* w_
                    const bf16_t* b_qkv, const cc_model_desc& m, const float2* rope,
                    const cc_kv_layer& kv, bf16_t* q_out, float* ws, int64_t ws_floats,
                    const cc_launch_override& ovr, hipStream_t s);
-// Most workgroups that an attention launch of M rows over N slots gives equal shares of its work.
-int cc_attn_even_workgroups(const cc_model_desc& m, int64_t M, int64_t N);
-// `part` ([slots][256][d_h + 4] fp32, two slots a workgroup) and `table` are that launch's workspace.
+// Most workgroups of an attention launch of M rows over N slots that leave pieces of blocks.
+int cc_attn_piece_workgroups(const cc_model_desc& m, int64_t M, int64_t N);
+// `part` ([slots][256][d_h + 4] fp32, two slots a workgroup) and `table` are the workspace of pieces.
 void cc_launch_attention(const bf16_t* q, int M, const int32_t* idx, const cc_model_desc& m,
                          const cc_kv_layer& kv, bf16_t* o, float* part, int slots, int* table,
                          const cc_launch_override& ovr, hipStream_t s);

@@ -419,6 +419,59 @@ def test_stage_attention_even_grid(H_q, H_kv, d_h, N, M, splits):
     ctx.close()
 
 
+# (H_q, H_kv, d_h, N, M): grids whose blocks are cut into runs of key tiles
+CUT_SHAPES = [(8, 8, 128, 1300, 40), (14, 2, 64, 700, 257), (32, 1, 128, 229, 1), (12, 3, 128, 600, 64), (64, 2, 64, 300, 9),
+              (16, 16, 128, 2050, 20)]
+
+
+@pytest.mark.parametrize("rows", ["spread", "first and last"])
+@pytest.mark.parametrize("H_q,H_kv,d_h,N,M", CUT_SHAPES)
+def test_stage_attention_cut_blocks(H_q, H_kv, d_h, N, M, rows):
+    """Blocks cut into up to eight runs of key tiles, by default: runs that do not divide a block's tiles,
+    blocks of one tile whose other pieces are empty (rows at the very first slots), columns without a
+    key in a piece, ragged last row tiles; against the oracle, and twice on one workspace."""
+    rng = np.random.default_rng(N * 3 + M)
+    model = ModelShape(H_q * d_h, H_q, H_kv, d_h, 64, 1e4, 1e-5, False, 1)
+    if rows == "spread":
+        idx = np.r_[np.sort(rng.choice(N - 1, size=M - 1, replace=False)), N - 1]
+    else:
+        idx = np.r_[np.arange(M // 2), np.arange(N - (M - M // 2), N)]
+    qb = gen.f32_to_bf16_bits((rng.standard_normal((M, H_q, d_h)) * 2.0).astype(np.float32))
+    Kb = gen.f32_to_bf16_bits(rng.standard_normal((N, H_kv, d_h)).astype(np.float32))
+    Vb = gen.f32_to_bf16_bits(rng.standard_normal((N, H_kv, d_h)).astype(np.float32))
+    ctx = _ctx(model, N, M)
+    kv, q, o = cc.KVLayer(dev_bf16(Kb), dev_bf16(Vb)), dev_bf16(qb).view(M, -1), []
+    for _ in range(2):                              # the second call meets the workspace of the first
+        o.append(torch.full((M, H_q * d_h), float("nan"), dtype=torch.bfloat16, device=DEV))
+        ctx.step_sparse_attention(q, M, dev_i32(idx), kv, o[-1], _lib.FLAG_CHECK_IDX)
+    torch.cuda.synchronize()
+    qf, Kf, Vf = obf.bits_to_f64(qb), obf.bits_to_f64(Kb), obf.bits_to_f64(Vb)
+    ref = np.stack([layer.attend_row(qf[i], Kf, Vf, int(idx[i]), H_q // H_kv)[0].reshape(-1) for i in range(M)])
+    mx, mn = err_stats(bits_f64(host_bits(o[0])), ref)
+    assert mx <= MAX_ABS and mn <= MEAN_ABS, (mx, mn)
+    assert torch.equal(o[0], o[1])
+    ctx.close()
+
+
+@pytest.mark.parametrize("H_q,H_kv,d_h,N,M", [(64, 8, 128, 330, 256), (64, 8, 128, 592, 512), (4, 2, 64, 70, 16)])
+def test_stage_attention_short_contexts_are_not_cut(H_q, H_kv, d_h, N, M):
+    """Blocks of a few key tiles where pieces and their merge cost more than they save: the default has
+    the bits of the launch that never cuts a block."""
+    rng = np.random.default_rng(N)
+    model = ModelShape(H_q * d_h, H_q, H_kv, d_h, 64, 1e4, 1e-5, False, 1)
+    idx = np.r_[np.sort(rng.choice(N - 1, size=M - 1, replace=False)), N - 1]
+    q = dev_bf16(gen.f32_to_bf16_bits((rng.standard_normal((M, H_q * d_h)) * 2.0).astype(np.float32)))
+    K, V = (dev_bf16(gen.f32_to_bf16_bits(rng.standard_normal((N, H_kv, d_h)).astype(np.float32))) for _ in range(2))
+    o = [torch.full((M, H_q * d_h), float("nan"), dtype=torch.bfloat16, device=DEV) for _ in range(2)]
+    ctx = _ctx(model, N, M)
+    for splits in (0, 1):
+        ctx.debug_set_launch(attn_splits=splits)
+        ctx.step_sparse_attention(q, M, dev_i32(idx), cc.KVLayer(K, V), o[splits])
+    torch.cuda.synchronize()
+    assert torch.equal(o[0], o[1])
+    ctx.close()
+
+
 def test_stage_attention_token_stride_past_32_bit_offsets():
     """Token strides whose 64-row tiles do not fit an unsigned 32-bit byte offset."""
     H_q, H_kv, d_h, N, st = 4, 1, 128, 3, (1 << 25) + 8

@@ -122,6 +122,22 @@ def test_even_and_wide_attention_kernel_reads_are_waited_for(tmp_path):
 
 
 @pytest.mark.skipif(shutil.which(HIPCC) is None, reason="hipcc not found")
+def test_cut_attention_kernel_reads_are_waited_for(tmp_path):
+    out = tmp_path / "attention.s"
+    cmd = [HIPCC, *build.FLAGS, "-S", "--cuda-device-only", "-o", str(out),
+           os.path.join(build.CSRC, "attention.hip")]
+    r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    assert r.returncode == 0, r.stdout
+    kernels = re.findall(r"^(_ZN\S*cut_attn_kernel\S*):[^\n]*\n(.*?)\.end_amdhsa_kernel", out.read_text(),
+                         flags=re.S | re.M)
+    assert len(kernels) >= 2, [k[0] for k in kernels]
+    for name, body in kernels:
+        seen, bad = audit(body)
+        assert seen >= 40, (name, seen)
+        assert not bad, (name, bad[:5])
+
+
+@pytest.mark.skipif(shutil.which(HIPCC) is None, reason="hipcc not found")
 def test_gemm_ring16_kernel_reads_are_waited_for(tmp_path):
     out = tmp_path / "gemm.s"
     cmd = [HIPCC, *build.FLAGS, "-S", "--cuda-device-only", "-o", str(out), os.path.join(build.CSRC, "gemm.hip")]

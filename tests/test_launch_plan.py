@@ -1,0 +1,89 @@
+"""The host's rules for launch shapes (csrc/launch_plan.h), compiled by the host compiler and asked
+without a GPU: on either side of each line the choice that was measured faster there."""
+import ctypes as C
+import shutil
+import subprocess
+
+import pytest
+
+from paper_2510_10129_amd import build
+from test_gpu_layer import CUT_SHAPES
+
+CXX = shutil.which("g++") or shutil.which("c++")
+pytestmark = pytest.mark.skipif(CXX is None, reason="no host C++ compiler")
+
+SHIM = r"""
+#include "launch_plan.h"
+extern "C" {
+void plan_attention(int n_cu, int n_row_tiles, int H_kv, int d_h, int t_max, int slots, int ovr, int* out) {
+    const cc_attn_plan p = cc_plan_attention(n_cu, n_row_tiles, H_kv, d_h, t_max, slots, ovr);
+    out[0] = p.kind, out[1] = p.pieces, out[2] = p.ranges, out[3] = p.per_min;
+}
+int plan_attn_workgroups(int n_cu, int64_t tiles, int64_t t_max) { return cc_plan_attn_workgroups(n_cu, tiles, t_max); }
+}
+"""
+WHOLE, CUT, EVEN = 0, 1, 2
+
+
+@pytest.fixture(scope="module")
+def plan(tmp_path_factory):
+    d = tmp_path_factory.mktemp("plan")
+    (d / "shim.cpp").write_text(SHIM)
+    cmd = [CXX, "-std=c++17", "-O1", "-Wall", "-Werror", "-shared", "-fPIC", "-I", build.CSRC, "-I", build.ROOT + "/include",
+           str(d / "shim.cpp"), "-o", str(d / "shim.so")]
+    r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    assert r.returncode == 0, r.stdout
+    return C.CDLL(str(d / "shim.so"))
+
+
+def attn(plan, H_q, H_kv, d_h, N, M, n_cu=256, ovr=0, slots=None):
+    n_row_tiles, t_max = -(-M * (H_q // H_kv) // 256), -(-N // 64)
+    plan.plan_attn_workgroups.argtypes = [C.c_int, C.c_int64, C.c_int64]
+    slots = 2 * plan.plan_attn_workgroups(n_cu, n_row_tiles * H_kv, t_max) if slots is None else slots
+    out = (C.c_int * 4)()
+    plan.plan_attention(n_cu, n_row_tiles, H_kv, d_h, t_max, slots, ovr, out)
+    return tuple(out) + (slots,)
+
+
+@pytest.mark.parametrize("H_q,H_kv,d_h,N,M,kind", [
+    (64, 8, 128, 330, 256, WHOLE),      # 20.5 us against 21.1 cut and 26.8 in even ranges
+    (64, 8, 128, 592, 512, WHOLE),      # 26.4, 29.1, 33.6
+    (64, 8, 128, 2112, 1024, WHOLE),    # 56.5, 63.6, 64.9
+    (64, 8, 128, 6000, 1536, WHOLE),    # 158, 158, 168 (384 blocks)
+    (4, 2, 64, 70, 16, WHOLE),          # 7.6, 9.2, 10.3
+    (12, 12, 64, 170, 32, WHOLE),       # 8.8, 9.9 cut
+    (64, 8, 128, 1104, 16, CUT),        # 29.6, 14.5, 15.6
+    (64, 8, 128, 1104, 256, CUT),       # 35.5, 27.5, 28.8
+    (32, 8, 128, 592, 64, CUT),         # 25.5, 15.9, 18.2
+    (32, 8, 64, 850, 512, CUT),         # 24.1, 18.3, 24.3
+    (32, 32, 128, 20000, 16, CUT),      # 363, 62, 67
+    (4, 2, 64, 12000, 64, EVEN),        # 185, 33.8, 22.0
+    (64, 8, 128, 4224, 512, EVEN),      # 92, 64, 57
+    (28, 4, 128, 20000, 1536, EVEN),    # 390, 254, 213
+])
+def test_attention_grid_is_the_one_measured_faster(plan, H_q, H_kv, d_h, N, M, kind):
+    assert attn(plan, H_q, H_kv, d_h, N, M)[0] == kind
+
+
+@pytest.mark.parametrize("shape", CUT_SHAPES)
+def test_shapes_of_the_cut_grid_tests_are_cut(plan, shape):
+    assert attn(plan, *shape)[0] == CUT
+
+
+def test_attention_plans_fit_their_workspace(plan):
+    """Every plan over a wide range of sizes: pieces and ranges within the slots and, for a cut grid, one
+    round of workgroups, no empty runs by construction, and no piece shorter than the tiles allow."""
+    for n_cu in (32, 256):
+        for H_q, H_kv in ((1, 1), (4, 2), (28, 4), (64, 8), (32, 32), (96, 96)):
+            for N in (1, 64, 65, 200, 1000, 4096, 33000, 131072, 1000000):
+                for M in (1, 7, 64, 257, 1024, 5000, 20000):
+                    for ovr in (0, 1, 2, 64):
+                        for slots in (None, 2, 6):              # more rows than the context was made for: fewer slots
+                            kind, pieces, ranges, per_min, have = attn(plan, H_q, H_kv, 128, N, M, n_cu, ovr, slots)
+                            n_wg = -(-M * (H_q // H_kv) // 256) * H_kv
+                            if kind == CUT:
+                                assert 2 <= pieces <= min(8, -(-N // 64)) and n_wg * pieces <= min(n_cu, have)
+                            elif kind == EVEN:
+                                assert 1 <= ranges <= have // 2 and per_min >= 1
+                                assert ovr or ranges <= n_cu
+                            assert kind == WHOLE or ovr != 1
