@@ -645,6 +645,11 @@ __global__ __launch_bounds__(512, 1) void cut_attn_kernel(CC_ATTN_ARGS, float* _
     attend_cut<D_H, uint32_t>(q, M, idx, H_q, H_kv, Kc, Vc, st, sh, N, o, n_row_tiles, scale_log2, part);
 }
 
+template <int D_H>
+__global__ __launch_bounds__(512, 1) void wide_stride_cut_attn_kernel(CC_ATTN_ARGS, float* __restrict__ part) {
+    attend_cut<D_H, uint64_t>(q, M, idx, H_q, H_kv, Kc, Vc, st, sh, N, o, n_row_tiles, scale_log2, part);
+}
+
 // Combines the pieces of the blocks that an even grid (S = 0) or a cut one (S pieces) has left:
 // o = sum_s 2^(m_s - m) O_s / sum_s 2^(m_s - m) l_s with m = max m_s, pieces in the order of their keys.
 // Workgroup (block, 32 of its columns = one wave of the attention kernel, 32 of their d's); a
@@ -744,13 +749,13 @@ void cc_launch_attention(const bf16_t* q, int M, const int32_t* idx, const cc_mo
     } while (0)
     // 64 rows of a tile, 2 bytes an element, in an unsigned 32-bit lane offset
     const bool wide = kv.stride_token >= (1ll << 32) / (2 * (BN_KEYS + 1));
-    cc_attn_plan p = cc_plan_attention(CUS, n_row_tiles, m.H_kv, m.d_h, t_max, slots, ovr.attn_splits);
-    if (wide) p.kind = CC_ATTN_WHOLE;
+    const cc_attn_plan p = cc_plan_attention(CUS, n_row_tiles, m.H_kv, m.d_h, t_max, slots, wide, ovr.attn_splits);
     if (p.kind == CC_ATTN_EVEN) {
         CC_ATTN_LAUNCH(even_attn_kernel, p.ranges, p.per_min, part, table);
     } else if (p.kind == CC_ATTN_CUT) {
         const dim3 cg(n_wg, p.pieces);
-        CC_ATTN_LAUNCH(cut_attn_kernel, cg, part);
+        if (wide) CC_ATTN_LAUNCH(wide_stride_cut_attn_kernel, cg, part);
+        else CC_ATTN_LAUNCH(cut_attn_kernel, cg, part);
     } else if (wide) {
         CC_ATTN_LAUNCH(wide_stride_attn_kernel, n_wg);
     } else {

@@ -41,11 +41,12 @@ inline int cc_plan_attn_workgroups(int n_cu, int64_t tiles, int64_t t_max) {
 //   512 rows 92.3 / 63.6 / 56.7;
 //   28 of 4, d_h = 128, N = 20000, 1536 rows 390 / 254 / 213;  32 of 32, N = 20000, 16 rows 363 / 62 / 67.
 // The choice is within 1.1 % of the best of all tried, on average.
-inline cc_attn_plan cc_plan_attention(int n_cu, int n_row_tiles, int H_kv, int d_h, int t_max, int slots,
+// `wide`: token strides that need 64-bit lane offsets, for which there is no even grid.
+inline cc_attn_plan cc_plan_attention(int n_cu, int n_row_tiles, int H_kv, int d_h, int t_max, int slots, bool wide,
                                       int override_pieces) {
     const int64_t n_wg = (int64_t)n_row_tiles * H_kv;
     const int64_t most_units = n_wg * (t_max + CC_ATTN_EVEN_START);
-    const bool even_ok = n_row_tiles <= CC_ATTN_EVEN_MAX_TILES && most_units < (1 << 30) && slots >= 2;
+    const bool even_ok = !wide && n_row_tiles <= CC_ATTN_EVEN_MAX_TILES && most_units < (1 << 30) && slots >= 2;
     cc_attn_plan p = {CC_ATTN_WHOLE, 1, 0, 0};
     auto even = [&](int per_min, int64_t most_ranges) {
         p.kind = CC_ATTN_EVEN;
@@ -54,7 +55,9 @@ inline cc_attn_plan cc_plan_attention(int n_cu, int n_row_tiles, int H_kv, int d
     };
     if (override_pieces == 1) return p;
     if (override_pieces > 1) {
+        const int cut = (int)std::min<int64_t>({override_pieces, t_max, slots / n_wg});
         if (even_ok) even((t_max + override_pieces - 1) / override_pieces, slots);
+        else if (wide && cut > 1) p.kind = CC_ATTN_CUT, p.pieces = cut;
         return p;
     }
     const double tile_us = d_h == 128 ? 1.75 : 1.5, slot_us = 0.2 * 256 * (d_h + 4) * 4 / 1e6;

@@ -472,26 +472,34 @@ def test_stage_attention_short_contexts_are_not_cut(H_q, H_kv, d_h, N, M):
     ctx.close()
 
 
-def test_stage_attention_token_stride_past_32_bit_offsets():
-    """Token strides whose 64-row tiles do not fit an unsigned 32-bit byte offset."""
-    H_q, H_kv, d_h, N, st = 4, 1, 128, 3, (1 << 25) + 8
+@pytest.mark.parametrize("splits", [0, 1, 3])
+@pytest.mark.parametrize("st", [33038208,               # the largest that runs with 32-bit lane offsets
+                                33038216,               # the smallest that runs with 64-bit ones
+                                (1 << 25) + (1 << 20)])
+def test_stage_attention_token_stride_past_32_bit_offsets(st, splits):
+    """Token strides on both sides of what an unsigned 32-bit byte offset holds for a 64-row tile, over two
+    whole tiles and a cut one, every block whole and cut into pieces."""
+    H_q, H_kv, d_h, N = 4, 1, 128, 150
+    assert (63 * st * 2 + 2 * d_h >= 1 << 32) == (st > 1 << 25)     # row 63 of a tile: only the last stride needs 64 bits
     rng = np.random.default_rng(5)
     model = ModelShape(H_q * d_h, H_q, H_kv, d_h, 64, 1e4, 1e-5, False, 1)
-    qb = gen.f32_to_bf16_bits(rng.standard_normal((N, H_q, d_h)).astype(np.float32))
+    idx = np.r_[0, 1, 62, 63, 64, 127, 128, 149]
+    M = len(idx)
+    qb = gen.f32_to_bf16_bits((rng.standard_normal((M, H_q, d_h)) * 2.0).astype(np.float32))
     Kb = gen.f32_to_bf16_bits(rng.standard_normal((N, H_kv, d_h)).astype(np.float32))
     Vb = gen.f32_to_bf16_bits(rng.standard_normal((N, H_kv, d_h)).astype(np.float32))
     far = []
-    for bits in (Kb, Vb):
-        t = torch.zeros(st * (N - 1) + d_h, dtype=torch.bfloat16, device=DEV)
-        v = t.as_strided((N, H_kv, d_h), (st, d_h, 1))
+    for bits in (Kb, Vb):                           # 10 GB each; what lies between the rows is never read
+        v = torch.empty(st * (N - 1) + d_h, dtype=torch.bfloat16, device=DEV).as_strided((N, H_kv, d_h), (st, d_h, 1))
         v.copy_(dev_bf16(bits))
         far.append(v)
-    ctx = _ctx(model, N, N)
-    o = torch.full((N, H_q * d_h), float("nan"), dtype=torch.bfloat16, device=DEV)
-    ctx.step_sparse_attention(dev_bf16(qb).view(N, -1), N, dev_i32(np.arange(N)), cc.KVLayer(*far), o)
+    ctx = _ctx(model, N, M)
+    ctx.debug_set_launch(attn_splits=splits)
+    o = torch.full((M, H_q * d_h), float("nan"), dtype=torch.bfloat16, device=DEV)
+    ctx.step_sparse_attention(dev_bf16(qb).view(M, -1), M, dev_i32(idx), cc.KVLayer(*far), o)
     torch.cuda.synchronize()
     qf, Kf, Vf = obf.bits_to_f64(qb), obf.bits_to_f64(Kb), obf.bits_to_f64(Vb)
-    ref = np.stack([layer.attend_row(qf[i], Kf, Vf, i, H_q // H_kv)[0].reshape(-1) for i in range(N)])
+    ref = np.stack([layer.attend_row(qf[i], Kf, Vf, int(idx[i]), H_q // H_kv)[0].reshape(-1) for i in range(M)])
     mx, mn = err_stats(bits_f64(host_bits(o)), ref)
     assert mx <= MAX_ABS and mn <= MEAN_ABS, (mx, mn)
     ctx.close()

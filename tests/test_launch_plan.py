@@ -15,8 +15,8 @@ pytestmark = pytest.mark.skipif(CXX is None, reason="no host C++ compiler")
 SHIM = r"""
 #include "launch_plan.h"
 extern "C" {
-void plan_attention(int n_cu, int n_row_tiles, int H_kv, int d_h, int t_max, int slots, int ovr, int* out) {
-    const cc_attn_plan p = cc_plan_attention(n_cu, n_row_tiles, H_kv, d_h, t_max, slots, ovr);
+void plan_attention(int n_cu, int n_row_tiles, int H_kv, int d_h, int t_max, int slots, int wide, int ovr, int* out) {
+    const cc_attn_plan p = cc_plan_attention(n_cu, n_row_tiles, H_kv, d_h, t_max, slots, wide, ovr);
     out[0] = p.kind, out[1] = p.pieces, out[2] = p.ranges, out[3] = p.per_min;
 }
 int plan_attn_workgroups(int n_cu, int64_t tiles, int64_t t_max) { return cc_plan_attn_workgroups(n_cu, tiles, t_max); }
@@ -36,12 +36,12 @@ def plan(tmp_path_factory):
     return C.CDLL(str(d / "shim.so"))
 
 
-def attn(plan, H_q, H_kv, d_h, N, M, n_cu=256, ovr=0, slots=None):
+def attn(plan, H_q, H_kv, d_h, N, M, n_cu=256, ovr=0, slots=None, wide=0):
     n_row_tiles, t_max = -(-M * (H_q // H_kv) // 256), -(-N // 64)
     plan.plan_attn_workgroups.argtypes = [C.c_int, C.c_int64, C.c_int64]
     slots = 2 * plan.plan_attn_workgroups(n_cu, n_row_tiles * H_kv, t_max) if slots is None else slots
     out = (C.c_int * 4)()
-    plan.plan_attention(n_cu, n_row_tiles, H_kv, d_h, t_max, slots, ovr, out)
+    plan.plan_attention(n_cu, n_row_tiles, H_kv, d_h, t_max, slots, wide, ovr, out)
     return tuple(out) + (slots,)
 
 
@@ -70,6 +70,14 @@ def test_shapes_of_the_cut_grid_tests_are_cut(plan, shape):
     assert attn(plan, *shape)[0] == CUT
 
 
+def test_wide_token_strides_are_cut_but_not_into_even_ranges(plan):
+    assert attn(plan, 8, 1, 128, 4096, 64)[0] == EVEN
+    assert attn(plan, 8, 1, 128, 4096, 64, wide=1)[:2] == (CUT, 8)
+    assert attn(plan, 8, 1, 128, 4096, 64, wide=1, ovr=3)[:2] == (CUT, 3)
+    assert attn(plan, 8, 1, 128, 4096, 64, wide=1, ovr=1)[0] == WHOLE
+    assert attn(plan, 8, 1, 128, 4096, 64, wide=1, ovr=64, slots=6)[:2] == (CUT, 3)
+
+
 def test_attention_plans_fit_their_workspace(plan):
     """Every plan over a wide range of sizes: pieces and ranges within the slots and, for a cut grid, one
     round of workgroups, no empty runs by construction, and no piece shorter than the tiles allow."""
@@ -77,13 +85,15 @@ def test_attention_plans_fit_their_workspace(plan):
         for H_q, H_kv in ((1, 1), (4, 2), (28, 4), (64, 8), (32, 32), (96, 96)):
             for N in (1, 64, 65, 200, 1000, 4096, 33000, 131072, 1000000):
                 for M in (1, 7, 64, 257, 1024, 5000, 20000):
-                    for ovr in (0, 1, 2, 64):
+                    for ovr, wide in ((0, 0), (1, 0), (2, 0), (64, 0), (0, 1), (1, 1), (3, 1), (64, 1)):
                         for slots in (None, 2, 6):              # more rows than the context was made for: fewer slots
-                            kind, pieces, ranges, per_min, have = attn(plan, H_q, H_kv, 128, N, M, n_cu, ovr, slots)
+                            kind, pieces, ranges, per_min, have = attn(plan, H_q, H_kv, 128, N, M, n_cu, ovr, slots, wide)
                             n_wg = -(-M * (H_q // H_kv) // 256) * H_kv
                             if kind == CUT:
-                                assert 2 <= pieces <= min(8, -(-N // 64)) and n_wg * pieces <= min(n_cu, have)
+                                assert 2 <= pieces <= -(-N // 64) and n_wg * pieces <= have
+                                assert ovr or (pieces <= 8 and n_wg * pieces <= n_cu)
                             elif kind == EVEN:
                                 assert 1 <= ranges <= have // 2 and per_min >= 1
                                 assert ovr or ranges <= n_cu
                             assert kind == WHOLE or ovr != 1
+                            assert not (wide and kind == EVEN)
