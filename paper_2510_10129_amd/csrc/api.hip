@@ -107,6 +107,16 @@ cc_status check_idx_sync(cc_ctx* c, const int32_t* idx, int M, int hi, int stric
 
 }  // namespace
 
+int cc_device_cus() {
+    static const int n_cu = [] {
+        int dev = 0, n = 256;
+        if (hipGetDevice(&dev) == hipSuccess)
+            (void)hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev);
+        return n > 0 ? n : 256;
+    }();
+    return n_cu;
+}
+
 cc_prof_scope::cc_prof_scope(cc_ctx* ctx, int kind) : c(ctx), on(ctx->prof) {
     if (!on) return;
     if (c->pool.empty()) {

@@ -550,7 +550,6 @@ __global__ __launch_bounds__(512, 1) void wide_stride_attn_kernel(CC_ATTN_ARGS) 
 // L2 serves one kv head when H_kv = 8.
 constexpr int EVEN_START = CC_ATTN_EVEN_START;          // 3 and 5 units measured: 5 is 1 % of the layer faster
 constexpr int EVEN_MAX_TILES = CC_ATTN_EVEN_MAX_TILES;
-constexpr int CUS = 256;
 // table: [n_row_tiles + 2] the first unit of every row tile within a head, their sum, units per range
 template <int D_H>
 __global__ __launch_bounds__(512, 1) void even_attn_kernel(CC_ATTN_ARGS, int per_min, float* __restrict__ part,
@@ -724,7 +723,7 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(const float* __restrict
 }  // namespace
 
 int cc_attn_piece_workgroups(const cc_model_desc& m, int64_t M, int64_t N) {
-    return cc_plan_attn_workgroups(CUS, (M * (m.H_q / m.H_kv) + 255) / 256 * m.H_kv, (N + BN_KEYS - 1) / BN_KEYS);
+    return cc_plan_attn_workgroups(cc_device_cus(), (M * (m.H_q / m.H_kv) + 255) / 256 * m.H_kv, (N + BN_KEYS - 1) / BN_KEYS);
 }
 
 void cc_launch_attention(const bf16_t* q, int M, const int32_t* idx, const cc_model_desc& m,
@@ -749,7 +748,7 @@ void cc_launch_attention(const bf16_t* q, int M, const int32_t* idx, const cc_mo
     } while (0)
     // 64 rows of a tile, 2 bytes an element, in an unsigned 32-bit lane offset
     const bool wide = kv.stride_token >= (1ll << 32) / (2 * (BN_KEYS + 1));
-    const cc_attn_plan p = cc_plan_attention(CUS, n_row_tiles, m.H_kv, m.d_h, t_max, slots, wide, ovr.attn_splits);
+    const cc_attn_plan p = cc_plan_attention(cc_device_cus(), n_row_tiles, m.H_kv, m.d_h, t_max, slots, wide, ovr.attn_splits);
     if (p.kind == CC_ATTN_EVEN) {
         CC_ATTN_LAUNCH(even_attn_kernel, p.ranges, p.per_min, part, table);
     } else if (p.kind == CC_ATTN_CUT) {

@@ -65,6 +65,9 @@ struct cc_prof_scope {
     ~cc_prof_scope();
 };
 
+// Compute units of the device that is current at the first call (256 where it does not say).
+int cc_device_cus();
+
 // ---- kernel launchers (each only enqueues on `s`) ----
 // The projections take a workspace `ws` of `ws_floats` floats (may be NULL) for split-K launches.
 // One launch of the assembly kernel covers up to CC_ASM_SEGS source segments.

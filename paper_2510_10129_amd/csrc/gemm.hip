@@ -1484,12 +1484,7 @@ template <class BSrc, class Epi>
 void launch_gemm(const bf16_t* A, int lda, int M, int N_tiles_cols, int K, int ldb, int gm_big,
                  BSrc bsrc, Epi epi, float* ws, int64_t ws_floats, const cc_launch_override& ovr,
                  hipStream_t s) {
-    static const int n_cu = [] {
-        int dev = 0, n = 256;
-        if (hipGetDevice(&dev) == hipSuccess)
-            (void)hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev);
-        return n > 0 ? n : 256;
-    }();
+    const int n_cu = cc_device_cus();
     // Test overrides (cc_debug_set_launch): tile shape, staged K loop, the 32x32x16 ring loop,
     // band height of the tile order, number of K shares (1 = none).
     const char force = (char)ovr.gemm_tile;                   // 0: the launcher's choice

@@ -70,6 +70,13 @@ def test_shapes_of_the_cut_grid_tests_are_cut(plan, shape):
     assert attn(plan, *shape)[0] == CUT
 
 
+@pytest.mark.parametrize("n_cu,kind", [(256, EVEN), (64, EVEN), (32, WHOLE)])
+def test_attention_grid_follows_the_number_of_compute_units(plan, n_cu, kind):
+    """64 blocks over 4096 slots: a quarter of 256 compute units, two rounds of 32."""
+    got, _, ranges, _, slots = attn(plan, 32, 8, 128, 4096, 512, n_cu)
+    assert got == kind and ranges in (0, n_cu) and slots == 2 * n_cu
+
+
 def test_wide_token_strides_are_cut_but_not_into_even_ranges(plan):
     assert attn(plan, 8, 1, 128, 4096, 64)[0] == EVEN
     assert attn(plan, 8, 1, 128, 4096, 64, wide=1)[:2] == (CUT, 8)
