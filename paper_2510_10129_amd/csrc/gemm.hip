@@ -30,6 +30,7 @@
 // The accumulators are written back through LDS so that every global store is
 // 16 or 32 contiguous bytes per lane along the row.
 #include "cc_internal.h"
+#include "launch_plan.h"
 #include <algorithm>
 #include <type_traits>
 
@@ -586,8 +587,9 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gemm_nt_kernel(
 }
 
 // ------------------------------------------------------------------ ring loop
-constexpr int BKS = 32;   // K columns per slice
-constexpr int NS = 4;     // ring slots
+constexpr int BKS = CC_GEMM_SLICE;   // K columns per slice
+constexpr int NS = 4;                // ring slots
+static_assert(BKS * NS == CC_GEMM_GROUP, "a group is one ring of slices");
 
 template <int BM, int BN, int WAVES_M, int WAVES_N, class BSrc, class Epi>
 __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gemm_ring_kernel(
@@ -1336,7 +1338,7 @@ __global__ __launch_bounds__(512, 2) void gemm_ring16_kernel_pp(
 // 43 (5.4 TB/s of weights), down 38 -> 31, QKV 25 -> 19, O 22 -> 15; M = 237, d = 256, f = 1024: down 15 -> 9,
 // QKV 12 -> 7.  Slices of 128 columns in three slots: the same within 2 % over these shapes, gate/up
 // slower by a fifth at 64 rows.
-constexpr int THIN_M = 64, THIN_N = 128, THIN_SLOTS = 6;
+constexpr int THIN_M = CC_THIN_M, THIN_N = CC_THIN_N, THIN_SLOTS = 6;
 template <class BSrc, class Epi>
 __global__ __launch_bounds__(256, 1) void gemm_thin_kernel(const bf16_t* __restrict__ A, int lda, int M, int K,
                                                            int tiles_m, int tiles_n, int GM, int nb,
@@ -1474,122 +1476,31 @@ __global__ __launch_bounds__(256, 1) void gemm_thin_kernel(const bf16_t* __restr
     }
 }
 
-// Tile shapes: 256x256 (ping-pong loop, 8 waves, least LDS and L2 traffic per flop, one
-// workgroup per CU), 192x256 (8 waves of 96x64, ring loop only, 0.70 of the large tile's rate:
-// it pays where it saves a half-empty round), 256x128 (8 waves of 64x64, one per CU, ring loop
-// only, 0.61) and 128x128 (4 waves of 64x64, two per CU, 0.58).  Where K is not a multiple of
-// 128 the 256x256 and 128x128 shapes run the staged loop.  A grid runs as a whole number of
-// "rounds" of workgroups, so the shape is chosen per launch to minimise rounds x tile cost.
+// cc_plan_gemm picks the tile shape and the shares of K: a grid runs as a whole number of "rounds" of
+// workgroups, so the shape is chosen per launch to minimise rounds x tile cost.
 template <class BSrc, class Epi>
 void launch_gemm(const bf16_t* A, int lda, int M, int N_tiles_cols, int K, int ldb, int gm_big,
                  BSrc bsrc, Epi epi, float* ws, int64_t ws_floats, const cc_launch_override& ovr,
                  hipStream_t s) {
     const int n_cu = cc_device_cus();
-    // Test overrides (cc_debug_set_launch): tile shape, staged K loop, the 32x32x16 ring loop,
-    // band height of the tile order, number of K shares (1 = none).
-    const char force = (char)ovr.gemm_tile;                   // 0: the launcher's choice
-    const bool mfma16 = !ovr.gemm_mfma32;
-    auto rounds_of = [&](int bm, int bn, int per_cu, int shares) {
-        const long tiles = (long)((M + bm - 1) / bm) * ((N_tiles_cols + bn - 1) / bn) * shares;
-        const long slots = (long)n_cu * per_cu;
-        return (tiles + slots - 1) / slots;
-    };
-    auto cost = [&](int bm, int bn, int per_cu, double eff) {
-        return (double)rounds_of(bm, bn, per_cu, 1) * per_cu * bm * bn / eff;
-    };
-    // ring loop: whole groups of NS slices, 32-bit lane offsets within a tile's rows
-    bool ring = K % (BKS * NS) == 0 && (int64_t)lda * 256 * 2 < (1ll << 31) &&
-                (int64_t)ldb * 256 * 2 < (1ll << 31);
-    if (ovr.gemm_staged) ring = false;
-    const double cb = cost(256, 256, 1, 1.00), cm = cost(192, 256, 1, 0.70), ch = cost(256, 128, 1, 0.61),
-                 cs = cost(128, 128, 2, 0.58);
-    char pick = cb <= cs ? 'b' : 's';
-    double best = cb <= cs ? cb : cs;
-    if (ring && ch < best) pick = 'h', best = ch;               // these two have no staged variant
-    if (ring && cm < best) pick = 'm', best = cm;
-    if (force == 'b' || force == 's' || ((force == 'h' || force == 'm') && ring)) pick = force;
-    // Split-K for the part of a grid that leaves most CUs idle: the tiles of a last round that
-    // fills at most half the chip (all tiles, if there is no full round) are computed by S
-    // workgroup rows, each over K/S columns, with S x tiles <= CUs, and a finishing pass; the full
-    // rounds before them run as a launch of their own.  256-wide tiles only.  Times in
-    // microseconds: 0.65 per 32-column slice of a 256x256 tile, 6 per round for the ends of a tile,
-    // the finishing pass at 4 TB/s plus 10 for the two extra launches (measured: QKV at M = 3928,
-    // 384 tiles, takes 208 split against 199 with the 192-row tile, so the estimate has to be
-    // 10 % below the unsplit one to be taken).
-    int S = 1;
-    const double slice_us = 0.65 * K / BKS / 65536.0;           // per unit of tile area
-    double t_best = best * slice_us + 6.0 * rounds_of(pick == 's' ? 128 : pick == 'm' ? 192 : 256,
-                                                      (pick == 'b' || pick == 'm') ? 256 : 128, pick == 's' ? 2 : 1, 1);
-    if (ring && ws) {
-        auto rem_of = [&](int bm) {
-            const long tiles = (long)((M + bm - 1) / bm) * ((N_tiles_cols + 255) / 256);
-            return (int)(tiles % n_cu == 0 && tiles > 0 ? n_cu : tiles % n_cu);
-        };
-        auto split_ok = [&](int bm, int sp, int k_min) {
-            const int rem = rem_of(bm);
-            return (K / (BKS * NS)) % sp == 0 && K / sp >= k_min && (long)rem * sp <= n_cu &&
-                   (double)sp * rem * 65536.0 <= (double)ws_floats;
-        };
-        if (ovr.gemm_splitk > 0) {
-            const int sp = ovr.gemm_splitk;
-            const int bm = pick == 'm' ? 192 : 256;
-            if (sp > 1 && sp <= 16 && split_ok(bm, sp, BKS * NS)) S = sp, pick = bm == 192 ? 'm' : 'b';
-        } else if (!force && !ovr.gemm_staged) {
-            const double t_unsplit = t_best;
-            for (int bm = 256; bm >= 192; bm -= 64) {
-                const double tile_us = bm * 256.0 / (bm == 256 ? 1.0 : 0.70) * slice_us;
-                const long full_rounds = rounds_of(bm, 256, 1, 1) - 1;
-                const int rem = rem_of(bm);
-                for (int sp = 2; sp <= 16; ++sp) {
-                    if (!split_ok(bm, sp, 512)) continue;
-                    const double t = full_rounds * (tile_us + 6.0) + tile_us / sp + 6.0 + 10.0 +
-                                     (double)sp * rem * 65536.0 * 4 / 4.0e6;
-                    if (t < t_best && t < 0.9 * t_unsplit) t_best = t, S = sp, pick = bm == 256 ? 'b' : 'm';
-                }
-            }
-        }
-    }
-    // Few rows: 64x128 tiles (gemm_thin_kernel), K cut into S_thin shares where the grid leaves CUs idle.
-    // Microseconds: THIN_SLICE_US per 64-column slice and round, 5 for the ends of a tile, the
-    // weights no faster than 4 TB/s, a finishing pass 5 plus its traffic.  Measured (event time, cold weights,
-    // 64x128 tiles against the larger ones): down, d = 4096, M = 1 / 64 / 128: 28 / 34 / 43 against 35 / 42 / 49,
-    // M = 192: 62 against 50; QKV, M = 128 / 400: 29 / 64 against 33 / 48; gate/up, M = 64 / 128 / 192: 77 / 89 /
-    // 113 against 80 / 83 / 86.  The estimate has to be a tenth below the other's to be taken.
-    constexpr double THIN_SLICE_US = 0.47;
-    const long thin_tiles = (long)((M + THIN_M - 1) / THIN_M) * ((N_tiles_cols + THIN_N - 1) / THIN_N);
-    const bool thin_ok = (int64_t)lda * THIN_M * 2 < (1ll << 31) && (int64_t)ldb * THIN_N * 2 < (1ll << 31);
-    int S_thin = 1;
-    auto thin_split_ok = [&](int sp) {
-        return (K / 64) % sp == 0 && ws && (double)sp * thin_tiles * (THIN_M * THIN_N) <= (double)ws_floats;
-    };
-    if (thin_ok && force == 't') {
-        pick = 't', S = 1;
-        if (ovr.gemm_splitk > 1 && thin_split_ok(ovr.gemm_splitk)) S_thin = ovr.gemm_splitk;
-    } else if (thin_ok && !force && !ovr.gemm_staged && !ovr.gemm_mfma32 && ovr.gemm_splitk == 0) {
-        double t_thin = 0.9 * t_best;
-        for (int sp = 1; sp <= 16; ++sp) {
-            if (sp > 1 && (!thin_split_ok(sp) || K / sp < 256 || thin_tiles * sp > n_cu)) continue;
-            const long rounds = (thin_tiles * sp + n_cu - 1) / n_cu;
-            double t = rounds * ((double)(K / sp / 64) * THIN_SLICE_US + 5.0);
-            t = std::max(t, 2.0 * N_tiles_cols * K / 4.0e6);
-            if (sp > 1) t += 5.0 + (double)sp * thin_tiles * (THIN_M * THIN_N) * 8 / 5.0e6;
-            if (t < t_thin) t_thin = t, pick = 't', S = 1, S_thin = sp;
-        }
-    }
+    const cc_gemm_plan plan = cc_plan_gemm(n_cu, M, N_tiles_cols, K, lda, ldb, ws != nullptr, ws_floats, ovr);
+    const char pick = plan.tile;
+    const bool ring = plan.ring, mfma16 = !ovr.gemm_mfma32;
+    const int S = plan.shares;
     if (pick == 't') {
         const int tiles_m = (M + THIN_M - 1) / THIN_M, tiles_n = (N_tiles_cols + THIN_N - 1) / THIN_N;
         const int GM = std::min(ovr.gemm_gm > 0 ? ovr.gemm_gm : 4, tiles_m);
-        const int nt = (int)thin_tiles;
-        if (S_thin == 1) {
+        const int nt = tiles_m * tiles_n;
+        if (S == 1) {
             hipLaunchKernelGGL((gemm_thin_kernel<BSrc, Epi>), dim3(nt), dim3(256), 0, s, A, lda, M, K, tiles_m, tiles_n,
                                GM, nt, bsrc, epi);
         } else {
             constexpr int SLOT = THIN_M * THIN_N;
             EpiPartial<THIN_M> pe{ws, (int64_t)nt * SLOT, 0, 0};
-            hipLaunchKernelGGL((gemm_thin_kernel<BSrc, EpiPartial<THIN_M>>), dim3(nt, S_thin), dim3(256), 0, s, A, lda, M,
-                               K / S_thin, tiles_m, tiles_n, GM, nt, bsrc, pe);
+            hipLaunchKernelGGL((gemm_thin_kernel<BSrc, EpiPartial<THIN_M>>), dim3(nt, S), dim3(256), 0, s, A, lda, M,
+                               K / S, tiles_m, tiles_n, GM, nt, bsrc, pe);
             hipLaunchKernelGGL((splitk_finish_kernel<THIN_M, THIN_N, Epi>), dim3(nt, THIN_M * THIN_N / 2048), dim3(256), 0, s,
-                               ws, (int64_t)nt * SLOT, S_thin, M, THIN_M, 0, tiles_m, tiles_n, GM, epi);
+                               ws, (int64_t)nt * SLOT, S, M, THIN_M, 0, tiles_m, tiles_n, GM, epi);
         }
         return;
     }

@@ -7,6 +7,8 @@
 #include <algorithm>
 #include <cmath>
 
+#include "cacheclip.h"
+
 // ---- attention: blocks of 256 (token, query head) columns, n_row_tiles per kv head, up to t_max key
 // tiles each.  WHOLE: a workgroup per block.  CUT: `pieces` workgroups per block, equal runs of its key tiles.
 // EVEN: `ranges` workgroups over the key tiles of all blocks, no range shorter than per_min units. ----
@@ -73,4 +75,109 @@ inline cc_attn_plan cc_plan_attention(int n_cu, int n_row_tiles, int H_kv, int d
     const double pieces = std::min<double>(n_cu, mean * most_units / units);
     if (even_ok && 14.6 + tile_us * units + slot_us * pieces < best) even(cc_attn_even_min(t_max), n_cu);
     return p;
+}
+
+// ---- GEMM: C[M, N] = A[M, K] B[N, K]^T in row x column tiles.  tile: 'b' 256x256 (ping-pong loop, 8 waves, least
+// LDS and L2 traffic per flop, one workgroup per CU), 'm' 192x256 (8 waves of 96x64, ring loop only, 0.70 of the
+// large tile's rate: it pays where it saves a half-empty round), 'h' 256x128 (8 waves of 64x64, one per CU, ring
+// loop only, 0.61), 's' 128x128 (4 waves of 64x64, two per CU, 0.58), 't' 64x128 (thin loop).  Where K is not a multiple
+// of 128 the 256x256 and 128x128 shapes run the staged loop.  shares: of K ('b', 'm': of the last round's tiles
+// only; 't': of all). ----
+#define CC_GEMM_SLICE 32            // K columns of a ring slice
+#define CC_GEMM_GROUP 128           // the ring and ping-pong loops take K in groups of this many columns
+#define CC_THIN_M 64
+#define CC_THIN_N 128
+struct cc_gemm_plan {
+    char tile;
+    bool ring;
+    int shares;
+};
+inline cc_gemm_plan cc_plan_gemm(int n_cu, int M, int N, int K, int64_t lda, int64_t ldb, bool ws, int64_t ws_floats,
+                                 const cc_launch_override& ovr) {
+    const char force = (char)ovr.gemm_tile;                   // 0: the launcher's choice
+    auto tiles_of = [&](int bm, int bn) { return (long)((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
+    auto rounds_of = [&](int bm, int bn, int per_cu) {
+        const long slots = (long)n_cu * per_cu;
+        return (tiles_of(bm, bn) + slots - 1) / slots;
+    };
+    auto cost = [&](int bm, int bn, int per_cu, double eff) {
+        return (double)rounds_of(bm, bn, per_cu) * per_cu * bm * bn / eff;
+    };
+    // ring loop: whole groups of slices, 32-bit lane offsets within a tile's rows
+    const bool ring = K % CC_GEMM_GROUP == 0 && lda * 256 * 2 < (1ll << 31) && ldb * 256 * 2 < (1ll << 31) && !ovr.gemm_staged;
+    const double cb = cost(256, 256, 1, 1.00), cm = cost(192, 256, 1, 0.70), ch = cost(256, 128, 1, 0.61),
+                 cs = cost(128, 128, 2, 0.58);
+    char pick = cb <= cs ? 'b' : 's';
+    double best = cb <= cs ? cb : cs;
+    if (ring && ch < best) pick = 'h', best = ch;               // these two have no staged variant
+    if (ring && cm < best) pick = 'm', best = cm;
+    if (force == 'b' || force == 's' || ((force == 'h' || force == 'm') && ring)) pick = force;
+    // Split-K for the part of a grid that leaves most CUs idle: the tiles of a last round that
+    // fills at most half the chip (all tiles, if there is no full round) are computed by S
+    // workgroup rows, each over K/S columns, with S x tiles <= CUs, and a finishing pass; the full
+    // rounds before them run as a launch of their own.  256-wide tiles only.  Times in
+    // microseconds: 0.65 per 32-column slice of a 256x256 tile, 6 per round for the ends of a tile,
+    // the finishing pass at 4 TB/s plus 10 for the two extra launches (measured: QKV at M = 3928,
+    // 384 tiles, takes 208 split against 199 with the 192-row tile, so the estimate has to be
+    // 10 % below the unsplit one to be taken).
+    int S = 1;
+    const double slice_us = 0.65 * K / CC_GEMM_SLICE / 65536.0;  // per unit of tile area
+    double t_best = best * slice_us + 6.0 * rounds_of(pick == 's' ? 128 : pick == 'm' ? 192 : 256,
+                                                      (pick == 'b' || pick == 'm') ? 256 : 128, pick == 's' ? 2 : 1);
+    if (ring && ws) {
+        auto rem_of = [&](int bm) {
+            const long tiles = tiles_of(bm, 256);
+            return (int)(tiles % n_cu == 0 && tiles > 0 ? n_cu : tiles % n_cu);
+        };
+        auto split_ok = [&](int bm, int sp, int k_min) {
+            const int rem = rem_of(bm);
+            return (K / CC_GEMM_GROUP) % sp == 0 && K / sp >= k_min && (long)rem * sp <= n_cu &&
+                   (double)sp * rem * 65536.0 <= (double)ws_floats;
+        };
+        if (ovr.gemm_splitk > 0) {
+            const int sp = ovr.gemm_splitk;
+            const int bm = pick == 'm' ? 192 : 256;
+            if (sp > 1 && sp <= 16 && split_ok(bm, sp, CC_GEMM_GROUP)) S = sp, pick = bm == 192 ? 'm' : 'b';
+        } else if (!force && !ovr.gemm_staged) {
+            const double t_unsplit = t_best;
+            for (int bm = 256; bm >= 192; bm -= 64) {
+                const double tile_us = bm * 256.0 / (bm == 256 ? 1.0 : 0.70) * slice_us;
+                const long full_rounds = rounds_of(bm, 256, 1) - 1;
+                const int rem = rem_of(bm);
+                for (int sp = 2; sp <= 16; ++sp) {
+                    if (!split_ok(bm, sp, 512)) continue;
+                    const double t = full_rounds * (tile_us + 6.0) + tile_us / sp + 6.0 + 10.0 +
+                                     (double)sp * rem * 65536.0 * 4 / 4.0e6;
+                    if (t < t_best && t < 0.9 * t_unsplit) t_best = t, S = sp, pick = bm == 256 ? 'b' : 'm';
+                }
+            }
+        }
+    }
+    // Few rows: 64x128 tiles (gemm_thin_kernel), K cut into shares where the grid leaves CUs idle.
+    // Microseconds: 0.47 per 64-column slice and round, 5 for the ends of a tile, the
+    // weights no faster than 4 TB/s, a finishing pass 5 plus its traffic.  Measured (event time, cold weights,
+    // 64x128 tiles against the larger ones): down, d = 4096, M = 1 / 64 / 128: 28 / 34 / 43 against 35 / 42 / 49,
+    // M = 192: 62 against 50; QKV, M = 128 / 400: 29 / 64 against 33 / 48; gate/up, M = 64 / 128 / 192: 77 / 89 /
+    // 113 against 80 / 83 / 86.  The estimate has to be a tenth below the other's to be taken.
+    const long thin_tiles = tiles_of(CC_THIN_M, CC_THIN_N);
+    const bool thin_ok = lda * CC_THIN_M * 2 < (1ll << 31) && ldb * CC_THIN_N * 2 < (1ll << 31);
+    auto thin_split_ok = [&](int sp) {
+        return (K / 64) % sp == 0 && ws && (double)sp * thin_tiles * (CC_THIN_M * CC_THIN_N) <= (double)ws_floats;
+    };
+    if (thin_ok && force == 't') {
+        const int sp = ovr.gemm_splitk;
+        return {'t', ring, sp > 1 && thin_split_ok(sp) ? sp : 1};
+    }
+    if (thin_ok && !force && !ovr.gemm_staged && !ovr.gemm_mfma32 && ovr.gemm_splitk == 0) {
+        double t_thin = 0.9 * t_best;
+        for (int sp = 1; sp <= 16; ++sp) {
+            if (sp > 1 && (!thin_split_ok(sp) || K / sp < 256 || thin_tiles * sp > n_cu)) continue;
+            const long rounds = (thin_tiles * sp + n_cu - 1) / n_cu;
+            double t = rounds * ((double)(K / sp / 64) * 0.47 + 5.0);
+            t = std::max(t, 2.0 * N * K / 4.0e6);
+            if (sp > 1) t += 5.0 + (double)sp * thin_tiles * (CC_THIN_M * CC_THIN_N) * 8 / 5.0e6;
+            if (t < t_thin) t_thin = t, pick = 't', S = sp;
+        }
+    }
+    return {pick, ring, S};
 }

@@ -7,6 +7,7 @@ import subprocess
 import pytest
 
 from paper_2510_10129_amd import build
+from paper_2510_10129_amd._lib import LaunchOverride
 from test_gpu_layer import CUT_SHAPES
 
 CXX = shutil.which("g++") or shutil.which("c++")
@@ -18,6 +19,10 @@ extern "C" {
 void plan_attention(int n_cu, int n_row_tiles, int H_kv, int d_h, int t_max, int slots, int wide, int ovr, int* out) {
     const cc_attn_plan p = cc_plan_attention(n_cu, n_row_tiles, H_kv, d_h, t_max, slots, wide, ovr);
     out[0] = p.kind, out[1] = p.pieces, out[2] = p.ranges, out[3] = p.per_min;
+}
+int plan_gemm(int n_cu, int M, int N, int K, int64_t ws_floats, const cc_launch_override* ovr) {
+    const cc_gemm_plan p = cc_plan_gemm(n_cu, M, N, K, K, K, ws_floats > 0, ws_floats, *ovr);
+    return p.tile + 256 * p.shares;
 }
 int plan_attn_workgroups(int n_cu, int64_t tiles, int64_t t_max) { return cc_plan_attn_workgroups(n_cu, tiles, t_max); }
 }
@@ -43,6 +48,35 @@ def attn(plan, H_q, H_kv, d_h, N, M, n_cu=256, ovr=0, slots=None, wide=0):
     out = (C.c_int * 4)()
     plan.plan_attention(n_cu, n_row_tiles, H_kv, d_h, t_max, slots, wide, ovr, out)
     return tuple(out) + (slots,)
+
+
+def gemm(plan, M, N, K, n_cu=256, ws_floats=32 << 20, **ovr):
+    plan.plan_gemm.argtypes = [C.c_int, C.c_int, C.c_int, C.c_int, C.c_int64, C.POINTER(LaunchOverride)]
+    if "gemm_tile" in ovr:
+        ovr["gemm_tile"] = ord(ovr["gemm_tile"])
+    r = plan.plan_gemm(n_cu, M, N, K, ws_floats, C.byref(LaunchOverride(**ovr)))
+    return chr(r % 256), r // 256
+
+
+def test_gemm_plans_fit_their_loops_and_workspace(plan):
+    """Every plan over a wide range of sizes: loops that divide K, shares that divide it further and
+    fit the workspace and one round; a forced shape is taken wherever it has a loop for K."""
+    for M in (1, 16, 64, 65, 200, 257, 883, 1523, 3404, 16576, 66000):
+        for N in (64, 192, 512, 4096, 6144, 28672):
+            for K in (64, 128, 192, 256, 448, 1984, 4096, 14336):
+                for ws in (0, 1 << 16, 32 << 20):
+                    tile, shares = gemm(plan, M, N, K, ws_floats=ws)
+                    assert tile in ("bmhst" if K % 128 == 0 else "bst") and 1 <= shares <= 16 and K % (64 * shares) == 0
+                    bm, bn = {"b": (256, 256), "m": (192, 256), "h": (256, 128), "s": (128, 128), "t": (64, 128)}[tile]
+                    tiles = -(-M // bm) * -(-N // bn)
+                    if shares > 1:
+                        assert tile in "bmt" and ws
+                        last = tiles if tile == "t" else (tiles % 256 or 256)
+                        assert last * shares <= 256 and last * shares * (8192 if tile == "t" else 65536) <= ws
+                        assert tile == "t" or K % (128 * shares) == 0
+                for force in "bmhst":
+                    want = force if K % 128 == 0 or force in "bst" else None
+                    assert gemm(plan, M, N, K, gemm_tile=force)[0] in ((want,) if want else ("b", "s"))
 
 
 @pytest.mark.parametrize("H_q,H_kv,d_h,N,M,kind", [
