@@ -105,8 +105,10 @@ inline cc_gemm_plan cc_plan_gemm(int n_cu, int M, int N, int K, int64_t lda, int
     };
     // ring loop: whole groups of slices, 32-bit lane offsets within a tile's rows
     const bool ring = K % CC_GEMM_GROUP == 0 && lda * 256 * 2 < (1ll << 31) && ldb * 256 * 2 < (1ll << 31) && !ovr.gemm_staged;
+    // without the ring loops the 256x256 tile is no faster than it was: 128x128 at 0.67 of its rate, 0.75 us
+    // a slice (M = 3000, N = 10880, K = 1984: three rounds of 256x256 tiles 179 us, four of 128x128 147)
     const double cb = cost(256, 256, 1, 1.00), cm = cost(192, 256, 1, 0.70), ch = cost(256, 128, 1, 0.61),
-                 cs = cost(128, 128, 2, 0.58);
+                 cs = cost(128, 128, 2, ring ? 0.58 : 0.67);
     char pick = cb <= cs ? 'b' : 's';
     double best = cb <= cs ? cb : cs;
     if (ring && ch < best) pick = 'h', best = ch;               // these two have no staged variant
@@ -121,7 +123,7 @@ inline cc_gemm_plan cc_plan_gemm(int n_cu, int M, int N, int K, int64_t lda, int
     // 384 tiles, takes 208 split against 199 with the 192-row tile, so the estimate has to be
     // 10 % below the unsplit one to be taken).
     int S = 1;
-    const double slice_us = 0.65 * K / CC_GEMM_SLICE / 65536.0;  // per unit of tile area
+    const double slice_us = (ring ? 0.65 : 0.75) * K / CC_GEMM_SLICE / 65536.0;  // per unit of tile area
     double t_best = best * slice_us + 6.0 * rounds_of(pick == 's' ? 128 : pick == 'm' ? 192 : 256,
                                                       (pick == 'b' || pick == 'm') ? 256 : 128, pick == 's' ? 2 : 1);
     if (ring && ws) {

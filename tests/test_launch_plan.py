@@ -79,6 +79,14 @@ def test_gemm_plans_fit_their_loops_and_workspace(plan):
                     assert gemm(plan, M, N, K, gemm_tile=force)[0] in ((want,) if want else ("b", "s"))
 
 
+@pytest.mark.parametrize("M,N,K,tile", [
+    (3000, 10880, 1984, "s"),           # three rounds of 256x256 tiles 179 us, four of 128x128 147
+    (8320, 10880, 1984, "b"),           # 375, 394
+])
+def test_the_staged_loop_is_priced_by_its_own_rates(plan, M, N, K, tile):
+    assert gemm(plan, M, N, K) == (tile, 1)
+
+
 @pytest.mark.parametrize("H_q,H_kv,d_h,N,M,kind", [
     (64, 8, 128, 330, 256, WHOLE),      # 20.5 us against 21.1 cut and 26.8 in even ranges
     (64, 8, 128, 592, 512, WHOLE),      # 26.4, 29.1, 33.6
