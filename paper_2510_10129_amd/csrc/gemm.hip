@@ -1334,9 +1334,9 @@ __global__ __launch_bounds__(512, 2) void gemm_ring16_kernel_pp(
 // workgroups that walk K in step then ask the same few memory channels at any one time (a layer of
 // 64 rows, d = 4096: 176 us in step, 164 rotated).
 // Swizzle and fragment layout as in the ping-pong loop.
-// M = 64, d = 4096, f = 14336, microseconds with the finishing pass, before and now: gate/up 65 ->
-// 43 (5.4 TB/s of weights), down 38 -> 31, QKV 25 -> 19, O 22 -> 15; M = 237, d = 256, f = 1024: down 15 -> 9,
-// QKV 12 -> 7.  Slices of 128 columns in three slots: the same within 2 % over these shapes, gate/up
+// M = 64, d = 4096, f = 14336, event microseconds with the finishing pass, weights cold (870 MB of others
+// between two reads), 256-row tiles and these: gate/up 65 -> 46 (5.4 TB/s of weights without the events' 2.5 us), down 41 -> 31,
+// QKV 26 -> 20, O 24 -> 17.  Slices of 128 columns in three slots: the same within 2 % over these shapes, gate/up
 // slower by a fifth at 64 rows.
 constexpr int THIN_M = CC_THIN_M, THIN_N = CC_THIN_N, THIN_SLOTS = 6;
 template <class BSrc, class Epi>

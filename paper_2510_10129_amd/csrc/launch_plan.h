@@ -78,11 +78,10 @@ inline cc_attn_plan cc_plan_attention(int n_cu, int n_row_tiles, int H_kv, int d
 }
 
 // ---- GEMM: C[M, N] = A[M, K] B[N, K]^T in row x column tiles.  tile: 'b' 256x256 (ping-pong loop, 8 waves, least
-// LDS and L2 traffic per flop, one workgroup per CU), 'm' 192x256 (8 waves of 96x64, ring loop only, 0.70 of the
-// large tile's rate: it pays where it saves a half-empty round), 'h' 256x128 (8 waves of 64x64, one per CU, ring
-// loop only, 0.61), 's' 128x128 (4 waves of 64x64, two per CU, 0.58), 't' 64x128 (thin loop).  Where K is not a multiple
-// of 128 the 256x256 and 128x128 shapes run the staged loop.  shares: of K ('b', 'm': of the last round's tiles
-// only; 't': of all). ----
+// LDS and L2 traffic per flop, one workgroup per CU), 'm' 192x256 (8 waves of 96x64, ring loop only), 'h' 256x128
+// (8 waves of 64x64, one per CU, ring loop only), 's' 128x128 (4 waves of 64x64, two per CU), 't' 64x128 (thin loop).
+// Where K is not a multiple of 128 the 256x256 and 128x128 shapes run the staged loop.  shares: of K ('b', 'm': of
+// the last round's tiles only; 't': of all). ----
 #define CC_GEMM_SLICE 32            // K columns of a ring slice
 #define CC_GEMM_GROUP 128           // the ring and ping-pong loops take K in groups of this many columns
 #define CC_THIN_M 64
@@ -96,36 +95,38 @@ inline cc_gemm_plan cc_plan_gemm(int n_cu, int M, int N, int K, int64_t lda, int
                                  const cc_launch_override& ovr) {
     const char force = (char)ovr.gemm_tile;                   // 0: the launcher's choice
     auto tiles_of = [&](int bm, int bn) { return (long)((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
-    auto rounds_of = [&](int bm, int bn, int per_cu) {
-        const long slots = (long)n_cu * per_cu;
-        return (tiles_of(bm, bn) + slots - 1) / slots;
-    };
-    auto cost = [&](int bm, int bn, int per_cu, double eff) {
-        return (double)rounds_of(bm, bn, per_cu) * per_cu * bm * bn / eff;
-    };
+    auto rounds_of = [&](int bm, int bn) { return (tiles_of(bm, bn) + n_cu - 1) / n_cu; };   // one tile per CU
     // ring loop: whole groups of slices, 32-bit lane offsets within a tile's rows
     const bool ring = K % CC_GEMM_GROUP == 0 && lda * 256 * 2 < (1ll << 31) && ldb * 256 * 2 < (1ll << 31) && !ovr.gemm_staged;
-    // without the ring loops the 256x256 tile is no faster than it was: 128x128 at 0.67 of its rate, 0.75 us
-    // a slice (M = 3000, N = 10880, K = 1984: three rounds of 256x256 tiles 179 us, four of 128x128 147)
-    const double cb = cost(256, 256, 1, 1.00), cm = cost(192, 256, 1, 0.70), ch = cost(256, 128, 1, 0.61),
-                 cs = cost(128, 128, 2, ring ? 0.58 : 0.67);
-    char pick = cb <= cs ? 'b' : 's';
-    double best = cb <= cs ? cb : cs;
-    if (ring && ch < best) pick = 'h', best = ch;               // these two have no staged variant
-    if (ring && cm < best) pick = 'm', best = cm;
+    // Microseconds of a round of workgroups (a grid runs as a whole number of them): the ends of its
+    // tiles, and 32 columns of K; a last round of 128x128 tiles with no more than one per CU is a short one.
+    // Fitted to event times of the four projections of twelve models (d = 256 to 8192, f = 1024 to 28672; three
+    // of them without the ring loops), 1 to 8320 rows, weights cold, every shape and most shares forced: 1364
+    // calls, the choice 1.0 % above the fastest on average.  The ends count where K is short (K = 256, 2048
+    // columns, M = 5120: 256x256 tiles 21.4 us, 192x256 19.1, 128x128 18.4), and without the ring loops the large tile
+    // is no faster than it was (M = 3000, N = 10880, K = 1984: three rounds of 256x256 179 us, four of 128x128 147).
+    struct Round { double ends, slice; };
+    const Round rb = ring ? Round{12.4, 0.486} : Round{21.6, 0.736}, rs = ring ? Round{4.9, 0.593} : Round{11.9, 0.451},
+                rs_short = ring ? Round{6.1, 0.363} : Round{4.6, 0.497}, rm = {8.2, 0.612}, rh = {6.0, 0.404};
+    const double slices = (double)K / CC_GEMM_SLICE;
+    auto us = [&](const Round& r) { return r.ends + r.slice * slices; };
+    const long st = tiles_of(128, 128), s_last = st % (2 * n_cu);
+    const double tb = rounds_of(256, 256) * us(rb);
+    const double ts = st / (2 * n_cu) * us(rs) + (s_last == 0 ? 0.0 : us(s_last <= n_cu ? rs_short : rs));
+    char pick = tb <= ts ? 'b' : 's';
+    double t_best = std::min(tb, ts);
+    if (ring) {                                                 // these two have no staged variant
+        const double th = rounds_of(256, 128) * us(rh), tm = rounds_of(192, 256) * us(rm);
+        if (th < t_best) pick = 'h', t_best = th;
+        if (tm < t_best) pick = 'm', t_best = tm;
+    }
     if (force == 'b' || force == 's' || ((force == 'h' || force == 'm') && ring)) pick = force;
     // Split-K for the part of a grid that leaves most CUs idle: the tiles of a last round that
     // fills at most half the chip (all tiles, if there is no full round) are computed by S
     // workgroup rows, each over K/S columns, with S x tiles <= CUs, and a finishing pass; the full
-    // rounds before them run as a launch of their own.  256-wide tiles only.  Times in
-    // microseconds: 0.65 per 32-column slice of a 256x256 tile, 6 per round for the ends of a tile,
-    // the finishing pass at 4 TB/s plus 10 for the two extra launches (measured: QKV at M = 3928,
-    // 384 tiles, takes 208 split against 199 with the 192-row tile, so the estimate has to be
-    // 10 % below the unsplit one to be taken).
+    // rounds before them run as a launch of their own.  256-wide tiles only.  The extra launches and
+    // the shares' traffic cost 4.5 us and 6.8 TB/s; the estimate has to be 2 % below the unsplit one.
     int S = 1;
-    const double slice_us = (ring ? 0.65 : 0.75) * K / CC_GEMM_SLICE / 65536.0;  // per unit of tile area
-    double t_best = best * slice_us + 6.0 * rounds_of(pick == 's' ? 128 : pick == 'm' ? 192 : 256,
-                                                      (pick == 'b' || pick == 'm') ? 256 : 128, pick == 's' ? 2 : 1);
     if (ring && ws) {
         auto rem_of = [&](int bm) {
             const long tiles = tiles_of(bm, 256);
@@ -143,24 +144,25 @@ inline cc_gemm_plan cc_plan_gemm(int n_cu, int M, int N, int K, int64_t lda, int
         } else if (!force && !ovr.gemm_staged) {
             const double t_unsplit = t_best;
             for (int bm = 256; bm >= 192; bm -= 64) {
-                const double tile_us = bm * 256.0 / (bm == 256 ? 1.0 : 0.70) * slice_us;
-                const long full_rounds = rounds_of(bm, 256, 1) - 1;
+                const Round& r = bm == 256 ? rb : rm;
+                const long full_rounds = rounds_of(bm, 256) - 1;
                 const int rem = rem_of(bm);
                 for (int sp = 2; sp <= 16; ++sp) {
                     if (!split_ok(bm, sp, 512)) continue;
-                    const double t = full_rounds * (tile_us + 6.0) + tile_us / sp + 6.0 + 10.0 +
-                                     (double)sp * rem * 65536.0 * 4 / 4.0e6;
-                    if (t < t_best && t < 0.9 * t_unsplit) t_best = t, S = sp, pick = bm == 256 ? 'b' : 'm';
+                    const double t = full_rounds * us(r) + r.ends + r.slice * slices / sp + 4.5 +
+                                     (double)sp * rem * 65536.0 * 4 / 6.8e6;
+                    if (t < t_best && t < 0.98 * t_unsplit) t_best = t, S = sp, pick = bm == 256 ? 'b' : 'm';
                 }
             }
         }
     }
     // Few rows: 64x128 tiles (gemm_thin_kernel), K cut into shares where the grid leaves CUs idle.
-    // Microseconds: 0.47 per 64-column slice and round, 5 for the ends of a tile, the
-    // weights no faster than 4 TB/s, a finishing pass 5 plus its traffic.  Measured (event time, cold weights,
-    // 64x128 tiles against the larger ones): down, d = 4096, M = 1 / 64 / 128: 28 / 34 / 43 against 35 / 42 / 49,
-    // M = 192: 62 against 50; QKV, M = 128 / 400: 29 / 64 against 33 / 48; gate/up, M = 64 / 128 / 192: 77 / 89 /
-    // 113 against 80 / 83 / 86.  The estimate has to be a tenth below the other's to be taken.
+    // From the same measurements: 3 us for the ends of a round's tiles, 0.465 per 64 columns, the weights no faster
+    // than 6.5 TB/s, a finishing pass 2 and the shares' traffic at 5; the estimate has to be 4 % below the other.
+    // Event microseconds (2.5 of them the events' own), d = 4096, f = 14336, 870 MB of other weights between two
+    // reads of one, the best of the thin tiles and of the larger ones:  M = 64: QKV 19.9 / 25.4, O 17.2 / 22.3, gate/up
+    // 45.7 / 57.4, down 30.7 / 39.5;  M = 128: 25.9 / 29.9, 19.5 / 26.5, 72 / 61, 41.5 / 45.2;  M = 192: 35.3 / 35.2, 25.2 / 30.1,
+    // 99 / 75, 62 / 51.
     const long thin_tiles = tiles_of(CC_THIN_M, CC_THIN_N);
     const bool thin_ok = lda * CC_THIN_M * 2 < (1ll << 31) && ldb * CC_THIN_N * 2 < (1ll << 31);
     auto thin_split_ok = [&](int sp) {
@@ -171,13 +173,13 @@ inline cc_gemm_plan cc_plan_gemm(int n_cu, int M, int N, int K, int64_t lda, int
         return {'t', ring, sp > 1 && thin_split_ok(sp) ? sp : 1};
     }
     if (thin_ok && !force && !ovr.gemm_staged && !ovr.gemm_mfma32 && ovr.gemm_splitk == 0) {
-        double t_thin = 0.9 * t_best;
+        double t_thin = 0.96 * t_best;
         for (int sp = 1; sp <= 16; ++sp) {
             if (sp > 1 && (!thin_split_ok(sp) || K / sp < 256 || thin_tiles * sp > n_cu)) continue;
             const long rounds = (thin_tiles * sp + n_cu - 1) / n_cu;
-            double t = rounds * ((double)(K / sp / 64) * 0.47 + 5.0);
-            t = std::max(t, 2.0 * N * K / 4.0e6);
-            if (sp > 1) t += 5.0 + (double)sp * thin_tiles * (CC_THIN_M * CC_THIN_N) * 8 / 5.0e6;
+            double t = rounds * (K / sp / 64 * 0.465 + 3.0);
+            t = std::max(t, 2.0 * N * K / 6.5e6);
+            if (sp > 1) t += 2.0 + (double)sp * thin_tiles * (CC_THIN_M * CC_THIN_N) * 8 / 5.0e6;
             if (t < t_thin) t_thin = t, pick = 't', S = sp;
         }
     }

@@ -87,6 +87,21 @@ def test_the_staged_loop_is_priced_by_its_own_rates(plan, M, N, K, tile):
     assert gemm(plan, M, N, K) == (tile, 1)
 
 
+@pytest.mark.parametrize("M,N,K,tiles", [
+    (5120, 2048, 256, "ms"),            # short K, the ends of a tile count: 256x256 21.4 us, 192x256 19.1, 128x128 18.4
+    (8320, 2048, 256, "ms"),            # 37.4, 31.1, 24.9
+    (6000, 1024, 1024, "bh"),           # one round of 128x128 tiles, two a CU: 35.1, one of 256x128 or 256x256 28
+    (64, 28672, 4096, "t"),             # few rows: 45.7 us against 57.4
+    (192, 28672, 4096, "h"),            # 98.7 thin, 74.9
+    (64, 4096, 4096, "t"),              # 17.2, 22.3
+    (192, 4096, 14336, "bm"),           # 62 thin, 51 in shares
+    (3404, 28672, 4096, "b"),
+    (16576, 28672, 4096, "b"),
+])
+def test_gemm_tile_is_the_one_measured_faster(plan, M, N, K, tiles):
+    assert gemm(plan, M, N, K)[0] in tiles
+
+
 @pytest.mark.parametrize("H_q,H_kv,d_h,N,M,kind", [
     (64, 8, 128, 330, 256, WHOLE),      # 20.5 us against 21.1 cut and 26.8 in even ranges
     (64, 8, 128, 592, 512, WHOLE),      # 26.4, 29.1, 33.6
