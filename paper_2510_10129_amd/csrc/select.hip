@@ -206,9 +206,13 @@ void cc_launch_block_scores(const cc_blk_args& a, int H, int Q_a, float* score, 
 // 16-token quarter of a word from its set bits; longer windows are tested per
 // token with popcounts over the words they span.
 // ----------------------------------------------------------------------------
+// One workgroup up to SEL_ONE_MAX tokens: it takes 11 us and 0.75 us more per 1024 tokens, the four
+// launches of the other path 22 us and next to nothing more (8192: 15.3 against 21.6, 16384: 21.8 against 22.3,
+// 32768: 33.4 against 22.8).
+#define SEL_ONE_MAX 16384
 #define SEL_THREADS 1024
 #define SEL_WAVES 16
-#define SEL_TCAP 131072
+#define SEL_TCAP SEL_ONE_MAX
 #define SEL_WORDS (SEL_TCAP / 64 + 20)   // bitmap words incl. zero padding past T + window
 #define SEL_BINS 2048
 #define SEL_BATCH 8                      // keys a thread loads together
@@ -364,9 +368,10 @@ struct SelLds {
     uint32_t sh_list_n;
 };
 
-__device__ __forceinline__ void select_one_workgroup(
-    SelLds& L, const float* __restrict__ score, int T, int k, int window, int tau, int grouping,
+__global__ __launch_bounds__(SEL_THREADS) void select_kernel(
+    const float* __restrict__ score, int T, int k, int window, int tau, int grouping,
     int idx_offset, int n_tail, int32_t* __restrict__ idx_out, int32_t* __restrict__ n_out) {
+    __shared__ SelLds L;
     uint64_t* const cand = L.cand;
     uint64_t* const pass = L.pass;
     uint64_t* const marked = cand;      // the chosen-token bitmap takes the candidates' place once the windows are judged
@@ -617,13 +622,6 @@ __device__ __forceinline__ void select_one_workgroup(
     if (tid == 0) *n_out = (int32_t)n_sel + n_tail;
 }
 
-__global__ __launch_bounds__(SEL_THREADS) void select_kernel(
-    const float* __restrict__ score, int T, int k, int window, int tau, int grouping,
-    int idx_offset, int n_tail, int32_t* __restrict__ idx_out, int32_t* __restrict__ n_out) {
-    __shared__ SelLds L;
-    select_one_workgroup(L, score, T, k, window, tau, grouping, idx_offset, n_tail, idx_out, n_out);
-}
-
 // ----------------------------------------------------------------------------
 // The same selection by several workgroups, SEL_TILE tokens each, in four short launches (long
 // requests: one compute unit then is what the selection waits for, and the leading digits of a
@@ -637,11 +635,15 @@ __global__ __launch_bounds__(SEL_THREADS) void select_kernel(
 //           keys the lowest tokens, by their place in the list), sets the candidates of its tile and of
 //           1024 tokens around it, judges the windows and writes its chosen words and their count.
 //   write   every workgroup adds up the counts before it and writes its indices.
-// A list of more than SELM_LIST keys (scores that mostly agree) goes to the one-workgroup
-// selection, inside the mark launch.
-// Against one workgroup (sum of the launches, k = T / 5, window 16): T = 65536: 58 -> 23.5 us,
-// 131072: 108 -> 25; what is left are four launches' latencies and, per launch, three or four loads
-// that wait for one another.
+// The list is short where the scores spread over the range: softmax sums of a request put a few dozen of
+// 65536 keys in a bin.  One score far below the others (a masked column's zero) stretches the range to 2^30
+// keys, a bin to a sixteenth of an octave; scores within an octave then crowd into it, and scores that
+// mostly agree always do.  With more than SELM_LIST keys every mark workgroup takes the digits below the bin, and
+// the equal keys before its tile, from all scores instead of the list.
+// Against one workgroup (sum of the launches, k = T / 5, window 16): T = 65536: 51 -> 23 us, 131072: 94 -> 24;
+// what is left are four launches' latencies and, per launch, three or four loads that wait for one another.
+// Crowded, one workgroup / that in the mark launch / now: T = 65536, a zero beside scores within an octave
+// 82 / 96 / 48, all equal 88 / 103 / 32, five values 90 / 104 / 50;  T = 131072: 122 / 136 / 61, 167 / 183 / 39, 171 / 185 / 71.
 // ----------------------------------------------------------------------------
 #define SELM_TILE CC_SEL_TILE
 #define SELM_LIST 8192
@@ -776,16 +778,99 @@ struct SelMarkLds {
     uint64_t cand[SELM_LOC + 20], pass[SELM_LOC + 20];
 };
 
-__global__ __launch_bounds__(SEL_THREADS) void select_mark_kernel(
-    const float* __restrict__ score, int T, int k, int window, int tau, int grouping, int idx_offset, int n_tail,
-    int32_t* __restrict__ idx_out, int32_t* __restrict__ n_out, cc_sel_ws ws) {
-    __shared__ union { SelLds one; SelMarkLds m; } lds;
-    if (ws->bin_count > SELM_LIST) {         // the same for every workgroup
-        if (blockIdx.x == 0)
-            select_one_workgroup(lds.one, score, T, k, window, tau, grouping, idx_offset, n_tail, idx_out, n_out);
-        return;
+// f(token, key) for every score, thread tid taking tokens 4 tid .., 4 (tid + 1024) .. (score 16-byte aligned): eight
+// 16-byte loads a thread are out together.
+template <class F>
+__device__ __forceinline__ void for_all_scores(const float* __restrict__ score, int T, F&& f) {
+    const int n4 = T >> 2;
+    for (int base = 0; base < n4; base += SEL_THREADS * SEL_BATCH) {
+        f32x4 v[SEL_BATCH];
+#pragma unroll
+        for (int j = 0; j < SEL_BATCH; ++j) {
+            const int i = base + j * SEL_THREADS + (int)threadIdx.x;
+            if (i < n4) v[j] = reinterpret_cast<const f32x4*>(score)[i];
+        }
+#pragma unroll
+        for (int j = 0; j < SEL_BATCH; ++j) {
+            const int i = base + j * SEL_THREADS + (int)threadIdx.x;
+            if (i < n4) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) f(4 * i + e, score_key(v[j][e]));
+            }
+        }
     }
-    SelMarkLds& L = lds.m;
+    if ((int)threadIdx.x < (T & 3)) f(4 * n4 + (int)threadIdx.x, score_key(score[4 * n4 + threadIdx.x]));
+}
+
+// Candidates of the local words among the keys of a threshold bin [base, base + 2^shift) that holds
+// `in_bin` keys of which the krem largest are taken, from all scores: radix passes over the bits below
+// the bin, then of equal keys the lowest tokens, ranked by a count of those before the local words.
+// Ends with a barrier.
+__device__ __forceinline__ void mark_crowded(SelMarkLds& L, const float* __restrict__ score, int T, int wb,
+                                             uint32_t base, int shift, uint32_t krem, uint32_t in_bin) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const uint32_t width = 1u << shift;                          // shift <= 21
+    uint32_t ties = in_bin, kth = 0, mask = 0;
+    for (int hi = shift; hi > 0;) {
+        const int lo = hi > 11 ? hi - 11 : 0;
+        const uint32_t dmask = (1u << (hi - lo)) - 1u;
+        for (int i = tid; i < SEL_BINS; i += SEL_THREADS) L.hist[i] = 0;
+        __syncthreads();
+        uint32_t run_d = 0, run_n = 0;
+        for_all_scores(score, T, [&](int, uint32_t key) __attribute__((always_inline)) {
+            const uint32_t low = key - base;                     // a key below the bin wraps round past its width
+            if (low < width && (low & mask) == kth) run_add(L.hist, (low >> lo) & dmask, run_d, run_n);
+        });
+        if (run_n) atomicAdd(&L.hist[run_d], run_n);
+        __syncthreads();
+        pick_bin(L.hist, SEL_BINS, krem, L.wave_tot, L.sh);
+        kth |= L.sh[0] << lo;
+        mask |= dmask << lo;
+        krem = L.sh[1];
+        ties = L.sh[2];
+        hi = lo;
+    }
+    const uint32_t thr = base + kth;                             // the threshold key: krem of its `ties` tokens are taken
+    const bool rank = krem < ties;
+    uint32_t before = 0;                                         // its tokens before the local words
+    if (rank && wb > 0) {
+        uint32_t n = 0;
+        for_all_scores(score, 64 * wb, [&](int, uint32_t key) __attribute__((always_inline)) { n += key == thr; });
+        for (int off = 32; off > 0; off >>= 1) n += (uint32_t)__shfl_xor((int)n, off);
+        if (lane == 0) L.wave_tot[wave] = n;
+        __syncthreads();
+        for (int w = 0; w < SEL_WAVES; ++w) before += L.wave_tot[w];
+        __syncthreads();
+    }
+    constexpr int WPW = SELM_LOC / SEL_WAVES;                    // local words of a wave
+    static_assert(SELM_LOC % SEL_WAVES == 0, "whole waves of local words");
+    uint64_t gt[WPW], eq[WPW];
+#pragma unroll
+    for (int j = 0; j < WPW; ++j) {
+        const int i = j * SEL_WAVES + wave, t = 64 * (wb + i) + lane;
+        const bool ok = t >= 0 && t < T;
+        const uint32_t key = ok ? score_key(score[t]) : 0u;
+        gt[j] = __ballot(ok && key - base < width && key > thr);
+        eq[j] = __ballot(ok && key == thr);
+        if (lane == 0) L.eq[i] = (uint32_t)__popcll(eq[j]);
+    }
+    __syncthreads();
+    if (rank) (void)block_exclusive_scan(L.eq, SELM_LOC, L.wave_tot);
+#pragma unroll
+    for (int j = 0; j < WPW; ++j) {
+        const int i = j * SEL_WAVES + wave;
+        const uint32_t at = before + L.eq[i] + (uint32_t)__popcll(eq[j] & ((1ULL << lane) - 1ULL));
+        const uint64_t take = __ballot((eq[j] >> lane & 1ULL) && (!rank || at < krem));
+        if (lane == 0) L.cand[i] |= gt[j] | take;
+    }
+    __syncthreads();
+}
+
+__global__ __launch_bounds__(SEL_THREADS) void select_mark_kernel(
+    const float* __restrict__ score, int T, int window, int tau, int grouping, cc_sel_ws ws) {
+    __shared__ SelMarkLds L;
+    const uint32_t in_bin = ws->bin_count;
+    const bool crowded = in_bin > SELM_LIST;                     // the same for every workgroup
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, G = gridDim.x;
     const int n_words = (T + 63) >> 6;
     const int wb = (int)blockIdx.x * SELM_WORDS - SELM_PAD;      // word of the bitmaps' first local word
@@ -794,58 +879,62 @@ __global__ __launch_bounds__(SEL_THREADS) void select_mark_kernel(
         L.cand[i] = i < SELM_LOC && wi >= 0 && wi < n_words ? ws->cand[wi] : 0ULL;
         L.pass[i] = 0ULL;
     }
-    // ---- the list: place of every tile's first key, then the keys ----
-    if (wave == 0) {
-        const uint32_t c = lane < G ? ws->list_n[lane] : 0u;
-        uint32_t inc = c;
-        for (int off = 1; off < 64; off <<= 1) {
-            const uint32_t o = __shfl_up(inc, off);
-            if (lane >= off) inc += o;
-        }
-        if (lane <= CC_SEL_TILES) L.pre[lane] = inc - c;
-    }
-    __syncthreads();
-    const int n_list = min((int)L.pre[G], SELM_LIST);            // G <= CC_SEL_TILES: lane G holds the total
-    const uint32_t base = ws->base;
-    for (int i = tid; i < n_list; i += SEL_THREADS) {
-        int g = 0;
-        for (int step = CC_SEL_TILES / 2; step > 0; step >>= 1)
-            if (g + step < G && (int)L.pre[g + step] <= i) g += step;
-        const uint32_t t = (uint32_t)g * SELM_TILE + ws->list[g][i - (int)L.pre[g]];
-        L.t[i] = t;
-        L.low[i] = score_key(score[t]) - base;
-    }
-    __syncthreads();
-    if (n_list > 0) {
-        // the bits below the bin, at most 21: 11 (or all of them), then the rest
-        uint32_t krem = ws->krem, ties = ws->bin_count, kth = 0, mask = 0;
-        for (int hi = ws->shift; hi > 0;) {
-            const int lo = hi > 11 ? hi - 11 : 0;
-            const uint32_t dmask = (1u << (hi - lo)) - 1u;
-            for (int i = tid; i < SEL_BINS; i += SEL_THREADS) L.hist[i] = 0;
-            __syncthreads();
-            for (int i = tid; i < n_list; i += SEL_THREADS)
-                if ((L.low[i] & mask) == kth) atomicAdd(&L.hist[(L.low[i] >> lo) & dmask], 1u);
-            __syncthreads();
-            pick_bin(L.hist, SEL_BINS, krem, L.wave_tot, L.sh);
-            kth |= L.sh[0] << lo;
-            mask |= dmask << lo;
-            krem = L.sh[1];
-            ties = L.sh[2];
-            hi = lo;
-        }
-        const bool rank = krem < ties;       // of `ties` equal keys the first krem of the list
-        if (rank) {
-            for (int i = tid; i < n_list; i += SEL_THREADS) L.eq[i] = L.low[i] == kth;
-            __syncthreads();
-            (void)block_exclusive_scan(L.eq, n_list, L.wave_tot);
-        }
-        for (int i = tid; i < n_list; i += SEL_THREADS) {
-            const int wi = (int)(L.t[i] >> 6) - wb;
-            if (wi >= 0 && wi < SELM_LOC && (L.low[i] > kth || (L.low[i] == kth && (!rank || L.eq[i] < krem))))
-                atomicOr(reinterpret_cast<unsigned long long*>(&L.cand[wi]), 1ULL << (L.t[i] & 63));
+    if (!crowded) {
+        // ---- the list: place of every tile's first key, then the keys ----
+        if (wave == 0) {
+            const uint32_t c = lane < G ? ws->list_n[lane] : 0u;
+            uint32_t inc = c;
+            for (int off = 1; off < 64; off <<= 1) {
+                const uint32_t o = __shfl_up(inc, off);
+                if (lane >= off) inc += o;
+            }
+            if (lane <= CC_SEL_TILES) L.pre[lane] = inc - c;
         }
         __syncthreads();
+        const int n_list = min((int)L.pre[G], SELM_LIST);            // G <= CC_SEL_TILES: lane G holds the total
+        const uint32_t base = ws->base;
+        for (int i = tid; i < n_list; i += SEL_THREADS) {
+            int g = 0;
+            for (int step = CC_SEL_TILES / 2; step > 0; step >>= 1)
+                if (g + step < G && (int)L.pre[g + step] <= i) g += step;
+            const uint32_t t = (uint32_t)g * SELM_TILE + ws->list[g][i - (int)L.pre[g]];
+            L.t[i] = t;
+            L.low[i] = score_key(score[t]) - base;
+        }
+        __syncthreads();
+        if (n_list > 0) {
+            // the bits below the bin, at most 21: 11 (or all of them), then the rest
+            uint32_t krem = ws->krem, ties = in_bin, kth = 0, mask = 0;
+            for (int hi = ws->shift; hi > 0;) {
+                const int lo = hi > 11 ? hi - 11 : 0;
+                const uint32_t dmask = (1u << (hi - lo)) - 1u;
+                for (int i = tid; i < SEL_BINS; i += SEL_THREADS) L.hist[i] = 0;
+                __syncthreads();
+                for (int i = tid; i < n_list; i += SEL_THREADS)
+                    if ((L.low[i] & mask) == kth) atomicAdd(&L.hist[(L.low[i] >> lo) & dmask], 1u);
+                __syncthreads();
+                pick_bin(L.hist, SEL_BINS, krem, L.wave_tot, L.sh);
+                kth |= L.sh[0] << lo;
+                mask |= dmask << lo;
+                krem = L.sh[1];
+                ties = L.sh[2];
+                hi = lo;
+            }
+            const bool rank = krem < ties;       // of `ties` equal keys the first krem of the list
+            if (rank) {
+                for (int i = tid; i < n_list; i += SEL_THREADS) L.eq[i] = L.low[i] == kth;
+                __syncthreads();
+                (void)block_exclusive_scan(L.eq, n_list, L.wave_tot);
+            }
+            for (int i = tid; i < n_list; i += SEL_THREADS) {
+                const int wi = (int)(L.t[i] >> 6) - wb;
+                if (wi >= 0 && wi < SELM_LOC && (L.low[i] > kth || (L.low[i] == kth && (!rank || L.eq[i] < krem))))
+                    atomicOr(reinterpret_cast<unsigned long long*>(&L.cand[wi]), 1ULL << (L.t[i] & 63));
+            }
+            __syncthreads();
+        }
+    } else {
+        mark_crowded(L, score, T, wb, ws->base, ws->shift, ws->krem, in_bin);
     }
     // ---- windows, as in the one-workgroup selection, on local words ----
     uint64_t* const marked = L.cand;
@@ -901,7 +990,6 @@ __global__ __launch_bounds__(SEL_THREADS) void select_mark_kernel(
 
 __global__ __launch_bounds__(256) void select_write_kernel(int T, int idx_offset, int n_tail, int32_t* __restrict__ idx_out,
                                                            int32_t* __restrict__ n_out, cc_sel_ws ws) {
-    if (ws->bin_count > SELM_LIST) return;                       // written by the mark launch
     __shared__ uint64_t words[SELM_WORDS];
     __shared__ uint32_t first[SELM_WORDS];
     const int tid = threadIdx.x, lane = tid & 63, G = gridDim.x;
@@ -941,10 +1029,6 @@ __global__ __launch_bounds__(256) void select_write_kernel(int T, int idx_offset
     if (blockIdx.x == 0 && tid == 0) *n_out = (int32_t)n_sel + n_tail;
 }
 
-// One workgroup up to SEL_ONE_MAX tokens: it takes 11 us and 0.75 us more per 1024 tokens, the four
-// launches of the other path 22 us and next to nothing more (8192: 15.3 against 21.6, 16384: 21.8 against 22.3,
-// 32768: 33.4 against 22.8).
-#define SEL_ONE_MAX 16384
 bool cc_select_uses_ranges(int T) { return T > SEL_ONE_MAX; }
 
 void cc_launch_select(const float* score, int T, int k, int window, int tau, int grouping,
@@ -958,8 +1042,7 @@ void cc_launch_select(const float* score, int T, int k, int window, int tau, int
     const dim3 grid((T + SELM_TILE - 1) / SELM_TILE), block(SEL_THREADS);
     hipLaunchKernelGGL(select_hist_kernel, grid, block, 0, s, score, T, key_range, n_range, ws);
     hipLaunchKernelGGL(select_cand_kernel, grid, block, 0, s, score, T, k, key_range, n_range, ws);
-    hipLaunchKernelGGL(select_mark_kernel, grid, block, 0, s, score, T, k, window, tau, grouping, idx_offset, n_tail,
-                       idx_out, n_out, ws);
+    hipLaunchKernelGGL(select_mark_kernel, grid, block, 0, s, score, T, window, tau, grouping, ws);
     hipLaunchKernelGGL(select_write_kernel, grid, dim3(256), 0, s, T, idx_offset, n_tail, idx_out, n_out, ws);
 }
 

@@ -264,3 +264,87 @@ def test_block_scores_leave_ranges_for_the_selection(ctx):
         ref = osel.select_from_scores(osel.block_scores(blocks), 3000, 8, 0, True, 2, 3)
         idx, n = ctx.select_blocks(_dev_blocks(blocks), 3000, 8, 0, 0, 2, 3)
         assert n == len(ref) and np.array_equal(idx[:n].cpu().numpy(), ref), len(lens)
+
+
+def _order_by_key(score):
+    """Candidates' order by the key of the score's bits (larger first, then the lower token): the order of
+    the numbers where they are numbers, infinities and NaN (above them, by its bits) included."""
+    u = (score + np.float32(0.0)).view(np.uint32)
+    key = np.where(u >> 31, ~u, u | np.uint32(0x80000000)).astype(np.int64)
+    return np.lexsort((np.arange(len(key)), -key))
+
+
+def _check_by_key(ctx, A, bp, w, off=0, tail=0):
+    s = osel.column_scores(A)
+    T = len(s)
+    cand = np.zeros(T, bool)
+    cand[_order_by_key(s)[:osel.candidate_count(T, bp)]] = True
+    ref = np.r_[off + np.nonzero(osel.group_windows(cand, w, osel.default_tau(w)))[0], off + T + np.arange(tail)]
+    got, n = _run(ctx, A, bp, w, 0, 0, off, tail)
+    assert n == len(ref) and np.array_equal(got, ref), (T, bp, w)
+
+
+def _crowded(kind, T, rng):
+    if kind == "zero":                  # scores within an octave and one that stretches the range of the keys
+        s = (1.0 + 0.9 * rng.random((1, T))).astype(np.float32)
+        s[0, T // 3] = 0.0
+    elif kind == "equal":
+        s = np.full((1, T), 0.125, np.float32)
+    elif kind == "steps":               # a handful of values: the threshold's ties run over many tiles
+        s = rng.integers(1, 6, size=(1, T)).astype(np.float32) * 0.25
+    elif kind == "low bits":            # two values that differ in the last bit, and a zero far below
+        s = np.where(rng.random((1, T)) < 0.5, np.float32(0.7), np.nextafter(np.float32(0.7), np.float32(1))).astype(np.float32)
+        s[0, 5] = 0.0
+    else:                               # "few below": nearly all keys above the threshold's bin, most of it tied
+        s = np.full((1, T), 3.0, np.float32)
+        s[0, rng.choice(T, T // 2, replace=False)] = 1.0
+        s[0, rng.choice(T, 9, replace=False)] = 1e-30
+    return s
+
+
+@pytest.mark.parametrize("kind", ["zero", "equal", "steps", "low bits", "few below"])
+@pytest.mark.parametrize("T", [20545, 24576, 65539, 131072])
+def test_threshold_bin_with_more_keys_than_the_list(ctx, T, kind):
+    """Several workgroups with most of the scores in the threshold's bin: digits and ties from all
+    scores, at sizes that end a tile, a 16-byte load and a word, at ratios whose threshold lies in different tiles."""
+    rng = np.random.default_rng(T)
+    s = _crowded(kind, T, rng)
+    for bp, w in ((1, 1), (2000, 16), (5000, 32), (7777, 8), (9999, 64), (3000, 1000)):
+        _check_by_key(ctx, s, bp, w, 3, 5)
+
+
+@pytest.mark.parametrize("T", [16384, 24576, 40001])
+def test_infinite_and_nan_scores(ctx, T):
+    """Sums that overflow to infinity, and NaN, take part by the order of their bits in every path."""
+    rng = np.random.default_rng(T)
+    s = rng.random((2, T)).astype(np.float32)
+    s[:, rng.choice(T, 300, replace=False)] = 3e38                   # their sum is infinite
+    for bp in (50, 1000, 6000):
+        _check_by_key(ctx, s, bp, 16)
+    s[0, rng.choice(T, 200, replace=False)] = np.nan
+    for bp in (50, 1000, 6000):
+        _check_by_key(ctx, s, bp, 16, 1, 2)
+    _check_by_key(ctx, np.full((2, T), 3e38, np.float32), 3000, 8)   # nothing but infinities
+
+
+def test_crowded_selection_is_shared_by_the_workgroups(ctx):
+    """A crowded threshold bin costs a few passes over the scores (measured: see select.hip), not a selection by
+    one workgroup after the others, which took four times the ordinary call."""
+    T, idx = 65536, torch.empty(65536 + 8, dtype=torch.int32, device=DEV)
+    n = torch.empty(1, dtype=torch.int32, device=DEV)
+    rng = np.random.default_rng(0)
+    us = {}
+    for kind in ("ordinary", "zero", "equal", "steps"):
+        s = np.exp(rng.standard_normal((1, T))).astype(np.float32) if kind == "ordinary" else _crowded(kind, T, rng)
+        At, best = torch.from_numpy(s).to(DEV), 1e9
+        for _ in range(5):
+            ctx.profile_enable(True)
+            ctx.profile_read()
+            for _ in range(10):
+                ctx.select(At, 2000, 16, 0, 0, 0, 8, idx, n, sync=False)
+            ms, count = ctx.profile_read()["select"]
+            ctx.profile_enable(False)
+            best = min(best, ms * 1e3 / count)
+        us[kind] = best
+    print({k: round(v, 1) for k, v in us.items()})
+    assert max(us.values()) < 3 * us["ordinary"], us
