@@ -6,6 +6,7 @@
 #include <string.h>
 
 #include "cc_internal.h"
+#include "launch_plan.h"
 
 // Scratch of cc_select_noalloc: the importance scores between its two kernels live here
 // instead of in a context's workspace.  One copy per GPU, held until the process ends.  In host

@@ -118,8 +118,7 @@ struct cc_sel_buf {
     int32_t shift;                               // its width: 2^shift keys
 };
 typedef cc_sel_buf* cc_sel_ws;
-// Whether a selection over T tokens takes key_range (n_range entries) and ws; otherwise they may be NULL.
-bool cc_select_uses_ranges(int T);
+// key_range (n_range entries) and ws may be NULL where cc_select_uses_ranges(T) says no.
 void cc_launch_select(const float* score, int T, int k, int window, int tau, int grouping,
                       int idx_offset, int n_tail, int32_t* idx_out, int32_t* n_out, const uint2* key_range,
                       int n_range, cc_sel_ws ws, hipStream_t s);

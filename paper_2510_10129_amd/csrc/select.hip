@@ -2,6 +2,7 @@
 // lowest-index tie-break, sliding-window grouping and compaction
 // (Sections 4.2 and 4.3 of the paper).
 #include "cc_internal.h"
+#include "launch_plan.h"
 
 // Order-preserving 32-bit key of a score: a larger score has a larger key.
 __device__ __forceinline__ uint32_t score_key(float s) {
@@ -206,13 +207,9 @@ void cc_launch_block_scores(const cc_blk_args& a, int H, int Q_a, float* score, 
 // 16-token quarter of a word from its set bits; longer windows are tested per
 // token with popcounts over the words they span.
 // ----------------------------------------------------------------------------
-// One workgroup up to SEL_ONE_MAX tokens: it takes 11 us and 0.75 us more per 1024 tokens, the four
-// launches of the other path 22 us and next to nothing more (8192: 15.3 against 21.6, 16384: 21.8 against 22.3,
-// 32768: 33.4 against 22.8).
-#define SEL_ONE_MAX 16384
 #define SEL_THREADS 1024
 #define SEL_WAVES 16
-#define SEL_TCAP SEL_ONE_MAX
+#define SEL_TCAP CC_SEL_ONE_MAX
 #define SEL_WORDS (SEL_TCAP / 64 + 20)   // bitmap words incl. zero padding past T + window
 #define SEL_BINS 2048
 #define SEL_BATCH 8                      // keys a thread loads together
@@ -1028,8 +1025,6 @@ __global__ __launch_bounds__(256) void select_write_kernel(int T, int idx_offset
     for (int j = blockIdx.x * 256 + tid; j < n_tail; j += G * 256) idx_out[n_sel + j] = idx_offset + T + j;
     if (blockIdx.x == 0 && tid == 0) *n_out = (int32_t)n_sel + n_tail;
 }
-
-bool cc_select_uses_ranges(int T) { return T > SEL_ONE_MAX; }
 
 void cc_launch_select(const float* score, int T, int k, int window, int tau, int grouping,
                       int idx_offset, int n_tail, int32_t* idx_out, int32_t* n_out, const uint2* key_range,

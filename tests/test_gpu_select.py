@@ -225,7 +225,7 @@ def test_blocks_window_sweep_and_no_prefix(ctx, name, prefix):
         print(f"{name} prefix={P} w={w}: M_sel/T = {(len(osel.select_from_scores(s, 2000, w, 0, True, P, wl.Q)) - wl.Q) / wl.T:.3f}")
 
 
-@pytest.mark.parametrize("T", [16384, 16385, 20479, 20480, 20545, 45001, 131072])
+@pytest.mark.parametrize("T", [16384, 16385, 20479, 20480, 20481, 20545, 24575, 24576, 45001, 131072])
 def test_selection_by_several_workgroups_edges(ctx, T):
     """Both sides of the size where several workgroups share a selection and of its 4096-token
     tiles: windows that reach over tile edges (up to 1024 tokens), equal scores at the threshold in
@@ -313,6 +313,7 @@ def test_threshold_bin_with_more_keys_than_the_list(ctx, T, kind):
         _check_by_key(ctx, s, bp, w, 3, 5)
 
 
+@pytest.mark.filterwarnings("ignore:overflow encountered")
 @pytest.mark.parametrize("T", [16384, 24576, 40001])
 def test_infinite_and_nan_scores(ctx, T):
     """Sums that overflow to infinity, and NaN, take part by the order of their bits in every path."""

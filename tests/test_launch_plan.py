@@ -24,6 +24,7 @@ int plan_gemm(int n_cu, int M, int N, int K, int64_t ws_floats, const cc_launch_
     const cc_gemm_plan p = cc_plan_gemm(n_cu, M, N, K, K, K, ws_floats > 0, ws_floats, *ovr);
     return p.tile + 256 * p.shares;
 }
+int select_uses_ranges(int T) { return cc_select_uses_ranges(T); }
 int plan_attn_workgroups(int n_cu, int64_t tiles, int64_t t_max) { return cc_plan_attn_workgroups(n_cu, tiles, t_max); }
 }
 """
@@ -161,3 +162,8 @@ def test_attention_plans_fit_their_workspace(plan):
                                 assert ovr or ranges <= n_cu
                             assert kind == WHOLE or ovr != 1
                             assert not (wide and kind == EVEN)
+
+
+@pytest.mark.parametrize("T,tiled", [(1, False), (16385, False), (20000, False), (24000, True), (131072, True)])
+def test_selection_is_tiled_where_that_was_measured_faster(plan, T, tiled):
+    assert bool(plan.select_uses_ranges(T)) == tiled
