@@ -192,3 +192,18 @@ inline cc_gemm_plan cc_plan_gemm(int n_cu, int M, int N, int K, int64_t lda, int
 // 22.5 / 22.8, 24000: 24.2 / 22.7, 32768: 30.4 / 22.3;  crowded by a zero 18000: 27.1 / 30.9, 28000: 34.7 / 34.7, 32768: 37.6 / 35.2. ----
 #define CC_SEL_ONE_MAX 20480
 inline bool cc_select_uses_ranges(int T) { return T > CC_SEL_ONE_MAX; }
+
+// ---- row norms: waves that share a row of d elements of elem_bytes (2: bf16 hidden rows, 4: the fp32 residual; a
+// workgroup is four waves, 8 of them are resident on a CU).  Event microseconds with one, two and four waves:
+//   short rows leave waves without a chunk:  d = 576 fp32, M = 16384 13.2 / 12.6 / 15.5;  d = 1024 bf16 16.1 / 16.3 / 20.2;
+//   few rows want every wave:  d = 4096 bf16, M = 64 6.7 / 6.1 / 6.2, 884 9.8 / 8.0 / 7.3;  d = 8192 fp32, 64 11.2 / 6.9 / 6.4,
+//   2047 24.0 / 18.7 / 18.4, 16384 180 / 168 / 160;
+//   bf16 rows a little past one round of workgroups pay for the second:  d = 4096, M = 4096 15.3 / 14.7 / 17.1, 8192
+//   24.7 / 27.6 / 27.5, 12000 39.0 / 37.3 / 36.9;  d = 8192, M = 3000 20.8 / 19.3 / 22.0, 6000 42.8 / 39.5 / 38.9;  d = 1088, M = 16384
+//   18.7 / 19.0 / 21.1. ----
+inline int cc_norm_waves(int n_cu, int M, int d, int elem_bytes) {
+    if (d <= 1024) return 1;
+    if (elem_bytes == 4 || M <= 8 * n_cu) return 4;
+    if (d <= 1536 || (d <= 4096 && M <= 40 * n_cu)) return 1;
+    return d <= 8192 && M <= 16 * n_cu ? 2 : 4;
+}

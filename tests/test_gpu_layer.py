@@ -532,6 +532,37 @@ def test_stage_attention_never_reads_past_the_valid_slots():
     ctx.close()
 
 
+@pytest.mark.parametrize("d,M", [(576, 5), (1024, 5), (1088, 7), (1088, 2050), (1600, 2049), (3648, 2049), (4096, 2051),
+                                 (5120, 2049), (8192, 3), (8256, 3), (8256, 2049), (16384, 5), (16384, 2049)])
+def test_stage_norms_widths_and_waves(d, M):
+    """Both norms where some of a row's waves own no chunk, where the last chunk is cut or whole, at the
+    widest rows, and on both sides of the row counts that change the waves a row has (the fp32 norm through
+    an MLP of 64 columns)."""
+    rng = np.random.default_rng(d + M)
+    model = ModelShape(d, 1, 1, 64, 64, 1e4, 1e-5, False, 1)
+    ctx = _ctx(model, 64, M)
+    xb, wb = _x_bits(M, d, d), _x_bits(1, d, 7)[0]
+    xn = torch.full((M, d), float("nan"), dtype=torch.bfloat16, device=DEV)
+    gather = rng.permutation(M)
+    ctx.step_gather_rmsnorm(dev_bf16(xb), dev_i32(gather), M, dev_bf16(wb), xn)
+    ref = layer.rmsnorm(obf.bits_to_f64(xb[gather]), obf.bits_to_f64(wb), model.rms_eps)
+    assert np.all(np.abs(bits_f64(host_bits(xn)) - ref) <= 2.0 ** -8 * np.abs(ref) + 1e-30)     # one rounding to bf16
+    y = rng.standard_normal((M, d)).astype(np.float32)
+    y[:, d // 2:] *= 3.0                            # a chunk left out or counted twice moves the whole row
+    wg, wu, wd = (_x_bits(n, k, s, k ** -0.5) for n, k, s in ((64, d, 1), (64, d, 2), (d, 64, 3)))
+    out = torch.full((M, d), float("nan"), dtype=torch.bfloat16, device=DEV)
+    ctx.step_mlp(torch.from_numpy(y).to(DEV), M, dev_bf16(wb), dev_bf16(wg), dev_bf16(wu), dev_bf16(wd), out)
+    rows = np.unique(np.r_[0, M - 1, rng.integers(0, M, size=40)])
+    m = layer.rmsnorm(y[rows].astype(np.float64), obf.bits_to_f64(wb), model.rms_eps)
+    g, u = m @ obf.bits_to_f64(wg).T, m @ obf.bits_to_f64(wu).T
+    ref = y[rows] + (g / (1.0 + np.exp(-g)) * u) @ obf.bits_to_f64(wd).T
+    got = bits_f64(host_bits(out))
+    assert np.isfinite(got).all()
+    mx, mn = err_stats(got[rows], ref)
+    assert mx <= 2.0 ** -8 * np.abs(ref).max() + MAX_ABS and mn <= 4 * MEAN_ABS, (mx, mn)   # rows of rms 2.2: spacing of the values
+    ctx.close()
+
+
 @pytest.mark.parametrize("tile,splitk,mfma", [("", "", ""), ("b", "", ""), ("b", "", "32"), ("m", "", ""), ("h", "", ""),
                                               ("s", "", ""), ("bt", "", ""), ("st", "", ""), ("", "2", ""), ("", "3", ""),
                                               ("", "4", ""), ("m", "2", ""), ("b", "2", "32"), ("m", "", "32"), ("m", "2", "32"), ("h", "", "32"), ("s", "", "32")])

@@ -24,6 +24,7 @@ int plan_gemm(int n_cu, int M, int N, int K, int64_t ws_floats, const cc_launch_
     const cc_gemm_plan p = cc_plan_gemm(n_cu, M, N, K, K, K, ws_floats > 0, ws_floats, *ovr);
     return p.tile + 256 * p.shares;
 }
+int norm_waves(int n_cu, int M, int d, int elem_bytes) { return cc_norm_waves(n_cu, M, d, elem_bytes); }
 int select_uses_ranges(int T) { return cc_select_uses_ranges(T); }
 int plan_attn_workgroups(int n_cu, int64_t tiles, int64_t t_max) { return cc_plan_attn_workgroups(n_cu, tiles, t_max); }
 }
@@ -167,3 +168,22 @@ def test_attention_plans_fit_their_workspace(plan):
 @pytest.mark.parametrize("T,tiled", [(1, False), (16385, False), (20000, False), (24000, True), (131072, True)])
 def test_selection_is_tiled_where_that_was_measured_faster(plan, T, tiled):
     assert bool(plan.select_uses_ranges(T)) == tiled
+
+
+@pytest.mark.parametrize("M,d,elem_bytes,waves", [
+    (16384, 576, 4, 1), (4096, 1024, 4, 1), (64, 1024, 2, 1),      # 13.2 us against 15.5; 7.9, 8.3
+    (884, 4096, 2, 4), (64, 8192, 4, 4), (16384, 4096, 4, 4),      # 7.3, 9.8; 6.4, 11.2; 76, 84
+    (4096, 4096, 2, 1), (8192, 2048, 2, 1), (16384, 1088, 2, 1),   # 15.3, 17.1; 15.0, 16.3; 18.7, 21.1
+    (12000, 4096, 2, 4), (3000, 8192, 2, 2), (6000, 8192, 2, 4),   # 36.9, 39.0; 19.3, 22.0; 38.9, 39.5
+    (16384, 16384, 2, 4),
+])
+def test_waves_of_a_row_norm(plan, M, d, elem_bytes, waves):
+    assert plan.norm_waves(256, M, d, elem_bytes) == waves
+
+
+def test_norm_plans_have_a_kernel(plan):
+    """One wave holds rows of up to 4096 bf16 or 1024 fp32 elements, two up to 8192."""
+    for d in range(64, 16385, 64):
+        for M in (1, 64, 2048, 2049, 4096, 4097, 10240, 10241, 70000):
+            assert plan.norm_waves(256, M, d, 2) in ((1, 2, 4) if d <= 4096 else (2, 4) if d <= 8192 else (4,))
+            assert plan.norm_waves(256, M, d, 4) in ((1, 4) if d <= 1024 else (4,))
