@@ -540,9 +540,7 @@ cc_status cc_assemble_cache(cc_ctx* c, const cc_chunk_kv* chunks, int32_t n_chun
     if ((int64_t)P + T + n_tail > dst->N) return fail(c, CC_ERR_SHAPE, "P + T + n_tail exceeds dst->N");
     // segments: the prefix (from chunk 0), every chunk's own rows, the zeroed tail
     std::vector<cc_asm_seg> segs;
-    // rows per wave: 16, fewer where that leaves CUs without a workgroup of four waves
-    const int64_t n_rows = (int64_t)P + T + n_tail;
-    const int rows = n_rows >= 16 * 1024 ? 16 : n_rows >= 8 * 1024 ? 8 : 4;
+    const int rows = cc_asm_rows((int64_t)P + T + n_tail, c->m.H_kv * c->m.d_h);
     auto blocks_of = [rows](int len) { return (len + rows - 1) / rows; };
     if (P > 0) segs.push_back({(const bf16_t*)chunks[0].K, (const bf16_t*)chunks[0].V, 0, P, 0, 0});
     int32_t start = 0;

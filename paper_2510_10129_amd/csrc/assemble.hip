@@ -12,8 +12,8 @@
 // rows a lane are issued before their stores.
 // Bytes in flight bound it; with keys and values of 16 rows in one wave and a row's units alone across
 // its lanes a small model's request was a few waves deep in latency: H_kv = 2, d_h = 64, 1072 rows
-// 14 -> 4.2 us; H_kv = 8, d_h = 128, 66k rows 108 -> 93 us (5.8 TB/s), 10 us of it the second launch that
-// 66 segments took.
+// 14.5 -> 6.2 us by events (2.5 of it theirs); H_kv = 8, d_h = 128, 66k rows 111 -> 94 (5.9 TB/s), 10 us of it the second
+// launch that 66 segments took, 5 the rows of a wave (cc_asm_rows).
 #include "cc_internal.h"
 
 namespace {

@@ -207,3 +207,12 @@ inline int cc_norm_waves(int n_cu, int M, int d, int elem_bytes) {
     if (d <= 1536 || (d <= 4096 && M <= 40 * n_cu)) return 1;
     return d <= 8192 && M <= 16 * n_cu ? 2 : 4;
 }
+
+// ---- cache assembly: destination rows of `width` elements (all heads) that a wave moves, of n_rows.  Event
+// microseconds with 4, 8 and 16:  width 1024 (8 heads of 128): 1072 rows 7.2 / 7.7 / 9.7, 4144: 11.6 / 10.6 / 12.7, 65584: 98 /
+// 94 / 99;  width 4096: 1072: 15.6 / 18.4 / 26.3, 28720: 183 / 186 / 200, 65584: 402 / 420 / 459;  width 512 (8 of 64): 4144: 9.4 /
+// 9.1 / 9.8, 16432: 20.5 / 18.6 / 16.9, 65584: 64 / 56 / 53;  width 64: 4144: 6.4 / 6.5 / 6.3, 65584: 28.6 / 19.0 / 13.8. ----
+inline int cc_asm_rows(int64_t n_rows, int width) {
+    if (n_rows < 2048) return 4;
+    return width >= 1024 || n_rows < 6000 ? 8 : 16;
+}

@@ -77,9 +77,11 @@ def test_real_chunk_caches_against_concat_caches():
     assert (Kg[:n] == Kref[0]).mean() > 0.995
 
 
-@pytest.mark.parametrize("H_kv,d_h,P,Q,n_chunks", [(8, 128, 64, 128, 16), (1, 64, 0, 0, 3), (4, 128, 16, 5, 70)])
+@pytest.mark.parametrize("H_kv,d_h,P,Q,n_chunks", [(8, 128, 64, 128, 16), (1, 64, 0, 0, 3), (4, 128, 16, 5, 70),
+                                                   (32, 128, 7, 9, 50)])
 def test_random_store_shapes(H_kv, d_h, P, Q, n_chunks):
-    """Llama-3-8B cache rows at the 16k layout; no prefix and no tail; more chunks than one launch takes."""
+    """Llama-3-8B cache rows at the 16k layout; no prefix and no tail; more chunks than one launch takes;
+    rows of several units a lane."""
     rng = np.random.default_rng(n_chunks)
     model = ModelShape(H_kv * d_h, H_kv, H_kv, d_h, 64, 5e5, 1e-5, False, 1)
     lens = [1024] * n_chunks if n_chunks == 16 else [int(v) for v in rng.integers(1, 90, size=n_chunks)]

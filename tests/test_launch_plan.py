@@ -25,6 +25,7 @@ int plan_gemm(int n_cu, int M, int N, int K, int64_t ws_floats, const cc_launch_
     return p.tile + 256 * p.shares;
 }
 int norm_waves(int n_cu, int M, int d, int elem_bytes) { return cc_norm_waves(n_cu, M, d, elem_bytes); }
+int asm_rows(int64_t n_rows, int width) { return cc_asm_rows(n_rows, width); }
 int select_uses_ranges(int T) { return cc_select_uses_ranges(T); }
 int plan_attn_workgroups(int n_cu, int64_t tiles, int64_t t_max) { return cc_plan_attn_workgroups(n_cu, tiles, t_max); }
 }
@@ -187,3 +188,12 @@ def test_norm_plans_have_a_kernel(plan):
         for M in (1, 64, 2048, 2049, 4096, 4097, 10240, 10241, 70000):
             assert plan.norm_waves(256, M, d, 2) in ((1, 2, 4) if d <= 4096 else (2, 4) if d <= 8192 else (4,))
             assert plan.norm_waves(256, M, d, 4) in ((1, 4) if d <= 1024 else (4,))
+
+
+@pytest.mark.parametrize("n_rows,width,rows", [
+    (1072, 1024, 4), (1072, 4096, 4), (4144, 1024, 8), (65584, 1024, 8),        # 7.2 us against 7.7 and 9.7; 94 against 99
+    (28720, 4096, 8), (65584, 4096, 8), (16432, 512, 16), (65584, 64, 16),      # 186 and 420 against 200 and 459
+])
+def test_rows_of_an_assembly_wave(plan, n_rows, width, rows):
+    plan.asm_rows.argtypes = [C.c_int64, C.c_int]
+    assert plan.asm_rows(n_rows, width) == rows
