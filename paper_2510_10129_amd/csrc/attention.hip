@@ -70,6 +70,8 @@ __device__ __forceinline__ void dma16(const bf16_t* gsrc_minus_off, bf16_t* lds_
 // compiler's scheduler, short of registers, would issue every read right before its use).
 // The waits for them are written by hand: LDS operations of a wave return in order, so
 // "at most N outstanding" after N younger reads means this one has arrived.
+// Transposing LDS read: within each group of 16 lanes, lane i receives, as element e, element (i % 4) of
+// the 8-byte row addressed by lane (i / 4 + 4 e).
 template <int IMM>
 __device__ __forceinline__ bf16x4 lds_read_tr_at(uint32_t addr) {
     bf16x4 v;
@@ -93,12 +95,6 @@ __device__ __forceinline__ void static_for(F&& f) {
         f(std::integral_constant<int, I>{});
         static_for<NI, I + 1>(f);
     }
-}
-
-// Transposing LDS read.  Within each group of 16 lanes, lane i receives, as
-// element e, element (i % 4) of the 8-byte row addressed by lane (i / 4 + 4 e).
-__device__ __forceinline__ bf16x4 lds_read_tr(const bf16_t* p) {
-    return __builtin_amdgcn_ds_read_tr16_b64_v4bf16((bf16x4 __attribute__((address_space(3)))*)p);
 }
 
 constexpr int LDS_TILES = 7;              // K tile t lives in stage t % 3, V tile t in stage 3 + t % 4

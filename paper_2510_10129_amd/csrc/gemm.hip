@@ -11,7 +11,7 @@
 // go from global memory straight into LDS (16-byte global->LDS loads, no register
 // staging), XOR-swizzled so that the 16-byte fragment reads are conflict-free on the
 // 64-bank LDS.  Five K loops:
-//   ping-pong (K % 128 == 0; gemm_ring16_kernel_pp, the 256x256 tile) two LDS buffers of
+//   ping-pong (K % 128 == 0; gemm_pingpong_kernel, the 256x256 tile) two LDS buffers of
 //          64 columns filled half tile by half tile, four phases per 64 columns, the two
 //          waves of a SIMD alternating between fragment reads and MFMAs.
 //   ring16 (K % 128 == 0; gemm_ring16_kernel, the smaller tiles) slices of 32 columns
@@ -1123,7 +1123,7 @@ __device__ __forceinline__ bf16x8 lds_read16(uint32_t addr) {
 // wave's priority around the MFMAs, waiting for the reads after the barrier instead of before it,
 // and issuing the loads before the reads: each within 1 %.
 template <class BSrc, class Epi>
-__global__ __launch_bounds__(512, 2) void gemm_ring16_kernel_pp(
+__global__ __launch_bounds__(512, 2) void gemm_pingpong_kernel(
     const bf16_t* __restrict__ A, int lda, int M, int K, int tiles_m, int tiles_n, int GM, int nb, int vb0,
     BSrc bsrc, Epi epi) {
     constexpr int H = 128, BM = 2 * H, BN = 2 * H;
@@ -1514,7 +1514,7 @@ void launch_gemm(const bf16_t* A, int lda, int M, int N_tiles_cols, int K, int l
     hipLaunchKernelGGL((KERN<BM_, BN_, WM_, WN_, BSrc, EPI_T>), dim3(NB_, GY_), dim3(WM_ * WN_ * 64), 0, s, A, \
                        lda, M, K_, tiles_m, tiles_n, GM, NB_, VB0_, bsrc, EPI_V)
 #define CC_LAUNCH_PP(EPI_T, EPI_V, K_, NB_, VB0_, GY_)                                                      \
-    hipLaunchKernelGGL((gemm_ring16_kernel_pp<BSrc, EPI_T>), dim3(NB_, GY_), dim3(512), 0, s, A, lda, M, K_,    \
+    hipLaunchKernelGGL((gemm_pingpong_kernel<BSrc, EPI_T>), dim3(NB_, GY_), dim3(512), 0, s, A, lda, M, K_,    \
                        tiles_m, tiles_n, GM, NB_, VB0_, bsrc, EPI_V)
 #define CC_LAUNCH_NT(BM_, BN_, WM_, WN_)                                                                    \
     hipLaunchKernelGGL((gemm_nt_kernel<BM_, BN_, WM_, WN_, BSrc, Epi>), dim3(n_tiles), dim3(WM_ * WN_ * 64), 0, \

@@ -1,5 +1,5 @@
-"""Static check of the machine code of the kernels with hand-written LDS reads (attention and
-the 16x16x32 GEMM ring loop).
+"""Static check of the machine code of the kernels with hand-written LDS reads (attention, the
+16x16x32 GEMM ring loop, the ping-pong loop and the thin loop).
 
 Their LDS fragment reads are inline assembly with hand-written `s_waitcnt lgkmcnt(n)`: the
 compiler does not know that the destination registers of such a read are filled later, so
@@ -145,10 +145,25 @@ def test_gemm_ring16_kernel_reads_are_waited_for(tmp_path):
     assert r.returncode == 0, r.stdout
     text = out.read_text()
     kernels = re.findall(r"^(_ZN\S*gemm_ring16_kernel\S*):[^\n]*\n(.*?)s_endpgm", text, flags=re.S | re.M)
-    assert len(kernels) >= 20, [k[0] for k in kernels]    # four tile shapes x four epilogues + 2 x two split-K instances
+    assert len(kernels) == 14, [k[0] for k in kernels]    # three tile shapes x four epilogues + two split-K instances
     for name, body in kernels:
         seen, bad = audit(body)
-        assert seen >= 8 * 8, (name, seen)                # 8, 10 or 12 fragment reads per slice, 8 slice blocks
+        assert seen >= 8 * 8, (name, seen)                # 8 or 10 fragment reads per slice, 8 slice blocks
+        assert not bad, (name, bad[:5])
+
+
+@pytest.mark.skipif(shutil.which(HIPCC) is None, reason="hipcc not found")
+def test_gemm_pingpong_kernel_reads_are_waited_for(tmp_path):
+    out = tmp_path / "gemm.s"
+    cmd = [HIPCC, *build.FLAGS, "-S", "--cuda-device-only", "-o", str(out), os.path.join(build.CSRC, "gemm.hip")]
+    r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    assert r.returncode == 0, r.stdout
+    kernels = re.findall(r"^(_ZN\S*gemm_pingpong_kernel\S*):[^\n]*\n(.*?)\.end_amdhsa_kernel", out.read_text(), flags=re.S | re.M)
+    assert len(kernels) == 6, [k[0] for k in kernels]     # four epilogues + two split-K instances
+    for name, body in kernels:
+        seen, bad = audit(body)
+        # B0 of the first K tile, two K tiles of the loop and the last but one (8 + 4 + 8 + 4 reads), the last one
+        assert seen == 4 + 3 * 24 + 20, (name, seen)
         assert not bad, (name, bad[:5])
 
 
