@@ -239,7 +239,7 @@ def test_selection_by_several_workgroups_edges(ctx, T):
     for w, tau in ((1, 0), (7, 0), (64, 20), (65, 0), (1000, 400), (1024, 1)):
         _check(ctx, runs, 2000, w, tau, True, 5, 3)
     _check(ctx, smooth, 2000, 16, 0, False, 0, 0)
-    tied = rng.integers(1, 6, size=(1, T)).astype(np.float32) * 0.25        # crowded: the one-workgroup selection
+    tied = rng.integers(1, 6, size=(1, T)).astype(np.float32) * 0.25        # crowded: five values, one bin each
     _check(ctx, tied, 3000, 16, 0, True, 1, 2)
     some = smooth.copy()
     some[:, rng.choice(T, size=min(T // 2, 7000), replace=False)] = 0.5    # equal sums at the median, within the list
