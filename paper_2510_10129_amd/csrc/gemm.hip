@@ -329,6 +329,14 @@ __device__ __forceinline__ void dma16_at(const char* gsrc_minus_off, bf16_t* lds
         (const void __attribute__((address_space(1)))*)gsrc_minus_off,
         (void __attribute__((address_space(3)))*)lds_wave_base, 16, OFF, 0);
 }
+// The same for lines that no other workgroup reads: kept out of the caches behind it.
+template <int OFF>
+__device__ __forceinline__ void dma16_stream_at(const char* gsrc_minus_off, bf16_t* lds_wave_base) {
+    static_assert(OFF >= 0 && OFF < 4096, "the instruction offset is 13 bits signed; a larger value wraps silently");
+    __builtin_amdgcn_global_load_lds(
+        (const void __attribute__((address_space(1)))*)gsrc_minus_off,
+        (void __attribute__((address_space(3)))*)lds_wave_base, 16, OFF, 2 /* nt */);
+}
 template <int N, int I = 0, class F>
 __device__ __forceinline__ void unrolled(F&& f) {
     if constexpr (I < N) {
@@ -1332,11 +1340,15 @@ __global__ __launch_bounds__(512, 2) void gemm_pingpong_kernel(
 // of 64x32; one barrier per slice; any K % 64 == 0.  Column tile bn starts bn slices into K and
 // wraps round: rows of a weight matrix are a power of two bytes apart as often as not, and
 // workgroups that walk K in step then ask the same few memory channels at any one time (a layer of
-// 64 rows, d = 4096: 176 us in step, 164 rotated).
+// 64 rows, d = 4096: 176 us in step, 164 rotated).  With one row tile every line of B is read once and
+// is not kept in the caches (nt): 7.1 TB/s instead of 6.0 in a kernel of nothing but loads, gate/up below 48.7 -> 41.9;
+// with more row tiles the others find it there (M = 128, O 19.3 us, 21.1 with nt).  The loads of a slice lie
+// between its fragment reads and MFMAs, in a loop without conditions (the last five slices are a loop of
+// their own): O and QKV at 16 rows 16.6 -> 16.2 and 17.7 -> 17.1.
 // Swizzle and fragment layout as in the ping-pong loop.
 // M = 64, d = 4096, f = 14336, event microseconds with the finishing pass, weights cold (870 MB of others
-// between two reads), 256-row tiles and these: gate/up 65 -> 46 (5.4 TB/s of weights without the events' 2.5 us), down 41 -> 31,
-// QKV 26 -> 20, O 24 -> 17.  Slices of 128 columns in three slots: the same within 2 % over these shapes, gate/up
+// between two reads), 256-row tiles and these: gate/up 65 -> 42 (6.0 TB/s of weights without the events' 2.5 us), down 41 -> 28,
+// QKV 26 -> 19, O 24 -> 18.  Slices of 128 columns in three slots: the same within 2 % over these shapes, gate/up
 // slower by a fifth at 64 rows.
 constexpr int THIN_M = CC_THIN_M, THIN_N = CC_THIN_N, THIN_SLOTS = 6;
 template <class BSrc, class Epi>
@@ -1379,20 +1391,22 @@ __global__ __launch_bounds__(256, 1) void gemm_thin_kernel(const bf16_t* __restr
         return reinterpret_cast<const char*>((hi << 32) | lo);
     };
     const int KT = K / 64, rot = bn % KT;
-    auto load_slice = [&](int n, int slot) __attribute__((always_inline)) {
+    // load i of slice n: B's first
+    auto load_one = [&](auto xc, auto streamc, int n, int slot) __attribute__((always_inline)) {
+        constexpr int x = decltype(xc)::value;
         const int t = n + rot < KT ? n + rot : n + rot - KT;
-        unrolled<B_L>([&](auto ic) __attribute__((always_inline)) {
-            constexpr int i = decltype(ic)::value;
-            const char* g = scalar_ptr(bbase + (int64_t)t * ROWB - i * 1024);   // the immediate adds it back
-            asm volatile("" : "+v"(bo[i]));
-            dma16_at<i * 1024>(g + bo[i], reinterpret_cast<bf16_t*>(smem + slot * SLOT + BM * ROWB + wave * B_L * 1024));
-        });
-        unrolled<A_L>([&](auto ic) __attribute__((always_inline)) {
-            constexpr int i = decltype(ic)::value;
+        if constexpr (x < B_L) {
+            const char* g = scalar_ptr(bbase + (int64_t)t * ROWB - x * 1024);   // the immediate adds it back
+            bf16_t* at = reinterpret_cast<bf16_t*>(smem + slot * SLOT + BM * ROWB + wave * B_L * 1024);
+            asm volatile("" : "+v"(bo[x]));
+            if constexpr (decltype(streamc)::value) dma16_stream_at<x * 1024>(g + bo[x], at);
+            else dma16_at<x * 1024>(g + bo[x], at);
+        } else {
+            constexpr int i = x - B_L;
             const char* g = scalar_ptr(abase + (int64_t)t * ROWB - i * 1024);
             asm volatile("" : "+v"(ao[i]));
             dma16_at<i * 1024>(g + ao[i], reinterpret_cast<bf16_t*>(smem + slot * SLOT + wave * A_L * 1024));
-        });
+        }
     };
 
     f32x4 acc[4][2];
@@ -1409,48 +1423,66 @@ __global__ __launch_bounds__(256, 1) void gemm_thin_kernel(const bf16_t* __restr
         a_addr[ks] = smem_base + frow * ROWB + ((fk + 4 * ks) ^ fsw) * 16;
         b_addr[ks] = a_addr[ks] + (BM + wave * 32) * ROWB;
     }
+    auto k_loop = [&](auto streamc) __attribute__((always_inline)) {
+        int rd = 0, wrs = D - 1;                       // slots of slice t and of slice t + D - 1
+        // One slice, with at most `younger` slices' loads out when it is read.  The loads of slice t + D - 1 go
+        // between the fragment reads and between the MFMAs: a wave's loads in a row wait for one another
+        // (64 clocks each with four waves at it), and nothing behind them starts meanwhile.
+        auto slice = [&](auto loadc, auto youngerc, int t) __attribute__((always_inline)) {
+            constexpr bool LOAD = decltype(loadc)::value;
+            asm volatile("s_waitcnt vmcnt(%0)" : : "n"(decltype(youngerc)::value * LPS));
+            wg_barrier();                              // for every wave; and slot wrs (slice t - 1) has been read
+            auto load = [&](auto xc) __attribute__((always_inline)) {
+                if constexpr (LOAD) {
+                    __builtin_amdgcn_sched_barrier(0);
+                    load_one(xc, streamc, t + D - 1, wrs);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            };
+            bf16x8 af[2][4], bf[2][2];
+            const uint32_t at = rd * SLOT;
+            unrolled<2>([&](auto kc) __attribute__((always_inline)) {
+                constexpr int ks = decltype(kc)::value;
+                const uint32_t a = a_addr[ks] + at, b = b_addr[ks] + at;
+                unrolled<2>([&](auto ic) __attribute__((always_inline)) { bf[ks][ic.value] = lds_read16<ic.value * 16 * ROWB>(b); });
+                unrolled<4>([&](auto ic) __attribute__((always_inline)) { af[ks][ic.value] = lds_read16<ic.value * 16 * ROWB>(a); });
+                load(std::integral_constant<int, ks>{});
+            });
+            unrolled<2>([&](auto kc) __attribute__((always_inline)) {
+                constexpr int ks = decltype(kc)::value;
+                if constexpr (ks == 0) asm volatile("s_waitcnt lgkmcnt(6)");
+                else asm volatile("s_waitcnt lgkmcnt(0)");
 #pragma unroll
-    for (int t = 0; t < D - 1; ++t)
-        if (t < KT) load_slice(t, t);
-    int rd = 0, wrs = D - 1;                           // slot of slice t, slot of slice t + D - 1
-    for (int t = 0; t < KT; ++t) {
-        // slice t has landed when at most the loads of the younger ones are out
-        switch (min(KT - 1 - t, D - 2)) {
-            case 4: asm volatile("s_waitcnt vmcnt(%0)" : : "n"(4 * LPS)); break;
-            case 3: asm volatile("s_waitcnt vmcnt(%0)" : : "n"(3 * LPS)); break;
-            case 2: asm volatile("s_waitcnt vmcnt(%0)" : : "n"(2 * LPS)); break;
-            case 1: asm volatile("s_waitcnt vmcnt(%0)" : : "n"(1 * LPS)); break;
-            default: asm volatile("s_waitcnt vmcnt(0)"); break;
-        }
-        static_assert(D - 2 == 4, "cases of the wait");
-        wg_barrier();                                  // for every wave; and slot wrs (slice t - 1) has been read
-        if (t + D - 1 < KT) load_slice(t + D - 1, wrs);
-        __builtin_amdgcn_sched_barrier(0);
-        bf16x8 af[2][4], bf[2][2];
-        const uint32_t at = rd * SLOT;
-        const uint32_t a0 = a_addr[0] + at, a1 = a_addr[1] + at, b0 = b_addr[0] + at, b1 = b_addr[1] + at;
-        unrolled<2>([&](auto ic) __attribute__((always_inline)) { bf[0][ic.value] = lds_read16<ic.value * 16 * ROWB>(b0); });
-        unrolled<4>([&](auto ic) __attribute__((always_inline)) { af[0][ic.value] = lds_read16<ic.value * 16 * ROWB>(a0); });
-        unrolled<2>([&](auto ic) __attribute__((always_inline)) { bf[1][ic.value] = lds_read16<ic.value * 16 * ROWB>(b1); });
-        unrolled<4>([&](auto ic) __attribute__((always_inline)) { af[1][ic.value] = lds_read16<ic.value * 16 * ROWB>(a1); });
-        unrolled<2>([&](auto kc) __attribute__((always_inline)) {
-            constexpr int ks = decltype(kc)::value;
-            if constexpr (ks == 0) asm volatile("s_waitcnt lgkmcnt(6)");
-            else asm volatile("s_waitcnt lgkmcnt(0)");
+                for (int i = 0; i < 4; ++i) asm volatile("" : "+v"(af[ks][i]));
 #pragma unroll
-            for (int i = 0; i < 4; ++i) asm volatile("" : "+v"(af[ks][i]));
+                for (int j = 0; j < 2; ++j) asm volatile("" : "+v"(bf[ks][j]));
+                unrolled<2>([&](auto hc) __attribute__((always_inline)) {
+                    constexpr int hh = decltype(hc)::value;
 #pragma unroll
-            for (int j = 0; j < 2; ++j) asm volatile("" : "+v"(bf[ks][j]));
+                    for (int i = 2 * hh; i < 2 * hh + 2; ++i)
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int j = 0; j < 2; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[ks][i], bf[ks][j], acc[i][j], 0, 0, 0);
-            __builtin_amdgcn_sched_barrier(0);
+                        for (int j = 0; j < 2; ++j)
+                            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[ks][i], bf[ks][j], acc[i][j], 0, 0, 0);
+                    load(std::integral_constant<int, 2 + 2 * ks + hh>{});
+                });
+            });
+            wrs = rd;
+            rd = rd + 1 == D ? 0 : rd + 1;
+        };
+        static_assert(LPS == 6, "places of the loads");
+        unrolled<D - 1>([&](auto tc) __attribute__((always_inline)) {
+            if (tc.value < KT) unrolled<LPS>([&](auto xc) __attribute__((always_inline)) { load_one(xc, streamc, tc.value, tc.value); });
         });
-        wrs = rd;
-        rd = rd + 1 == D ? 0 : rd + 1;
-    }
+        int t = 0;
+        for (; t + D - 1 < KT; ++t) slice(std::true_type{}, std::integral_constant<int, D - 2>{}, t);
+        // the last D - 1 slices (or all of a shorter K): nothing left to load
+        unrolled<D - 1>([&](auto jc) __attribute__((always_inline)) {
+            constexpr int after = D - 2 - decltype(jc)::value;
+            if (KT > after) slice(std::false_type{}, std::integral_constant<int, after>{}, t);
+        });
+    };
+    if (tiles_m == 1) k_loop(std::true_type{});        // every line of B is read once
+    else k_loop(std::false_type{});
 
     // ---- epilogue through LDS as fp32 [BM][BN], column c of row r at c ^ 16*((r>>2)&3) ----
     __syncthreads();
