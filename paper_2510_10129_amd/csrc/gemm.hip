@@ -10,11 +10,14 @@
 // Tiling: one workgroup of WAVES_M x WAVES_N waves computes a BM x BN tile.  Operands
 // go from global memory straight into LDS (16-byte global->LDS loads, no register
 // staging), XOR-swizzled so that the 16-byte fragment reads are conflict-free on the
-// 64-bank LDS.  Five K loops:
+// 64-bank LDS.  Six K loops:
 //   ping-pong (K % 128 == 0; gemm_pingpong_kernel, the 256x256 tile) two LDS buffers of
 //          64 columns filled half tile by half tile, four phases per 64 columns, the two
 //          waves of a SIMD alternating between fragment reads and MFMAs.
-//   ring16 (K % 128 == 0; gemm_ring16_kernel, the smaller tiles) slices of 32 columns
+//   duo    (K % 128 == 0; gemm_duo_kernel, 256x128 and 128x128 where K is not short) K tiles of
+//          64 columns, 64x64 waves in two groups, a whole K tile per turn.
+//   ring16 (K % 128 == 0; gemm_ring16_kernel, 192x256 and, where K is short, 128x128; 256x128 as a
+//          cross-check behind cc_debug_set_launch) slices of 32 columns
 //          in a ring of four LDS slots; a slice is requested three slices (96 columns of
 //          MFMA work) before it is read, which hides the L2/fabric latency that a
 //          two-stage pipeline exposes; one barrier per slice, waits by explicit vmcnt;
@@ -1329,6 +1332,197 @@ __global__ __launch_bounds__(512, 2) void gemm_pingpong_kernel(
     }
 }
 
+// ------------------------------------------------------------------ duo loop
+// 256x128 and 128x128 tiles, whole K tiles of 64 columns, eight waves of 64x64 in two groups half a step
+// apart as in the ping-pong loop: one group multiplies a K tile (32 MFMAs, 512 clocks of the pipe) while the
+// other reads the fragments of its next one and asks for the one after.  A wave of 64x64 reads 16 fragments for
+// 32 MFMAs.  256x128: the groups are the upper and the lower 128 rows and share B.  128x128: the groups
+// take the even and the odd K tiles (each holds sums of the whole tile, added at the end), for a 64x32
+// wave would read half as much again per MFMA.
+//
+// What bounds it: a CU takes in 150 KB/us that the L2 holds but only 55 to 60 of lines that it does not
+// (a kernel of nothing but loads, any number in flight), and a tile of these shapes asks for 48 or 32 KB
+// per 64 columns.  With every load in the same column 128x128 takes 0.27 us per K tile, with real addresses
+// 0.56; the L2 asked ahead by a ninth wave changed nothing.  A wave's loads go between its fragment
+// reads: eight in a row wait for one another (16 clocks each for every wave that issues them), which the reads
+// behind them then wait for too (128x128 0.36 us per K tile instead of 0.27, all in the same column).
+// LDS: 256x128 three slots of A0 | A1 | B (48 KB), 128x128 five of A | B (32 KB); a K tile is asked for
+// four half steps before it is read (the second group's half of a shared B three).
+// Against the ring loop with the same tile, event us of 2.5 more than the kernel's: M = 883, d = 4096: O (128x128)
+// 59.8 -> 44.0, QKV (256x128) 79.9 -> 63;  M = 1523, d = 3584: QKV 80.8 -> 61, O 79 -> 62 (256x128);  M = 3404, N = 2048,
+// K = 256 (432 tiles of 128x128, two on a CU in the ring loop) 14.5 -> 19, where the ring loop stays.
+template <int BM, class BSrc, class Epi>
+__global__ __launch_bounds__(512, 2) void gemm_duo_kernel(
+    const bf16_t* __restrict__ A, int lda, int M, int K, int tiles_m, int tiles_n, int GM, int nb,
+    BSrc bsrc, Epi epi) {
+    constexpr int BN = 128, KG = 256 / BM;             // waves of 64x64; groups along K
+    static_assert(BM == 128 || BM == 256, "eight waves");
+    constexpr int AR = BM / 128;                       // 128-row regions of A in a K tile
+    constexpr int ROWB = 128, REG = 128 * ROWB;        // bytes of a K tile's row and of a region
+    constexpr int SLOT = (AR + 1) * REG, NSLOT = KG == 2 ? 5 : 3;
+    constexpr int LA = 4, LB = KG == 2 ? 4 : 2, L = LA + LB;        // loads of a wave and K tile, 8 rows each
+    static_assert(BM * BN * 4 <= NSLOT * SLOT, "the fp32 tile fits for the epilogue");
+    __shared__ __align__(16) char smem[NSLOT * SLOT];
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int grp = wave >> 2, w = wave & 3;
+    int bm, bn;
+    (void)tile_of_block(blockIdx.x, nb, 0, tiles_m, tiles_n, GM, &bm, &bn);
+    const int m0 = bm * BM;
+    const int ar = AR == 2 ? grp : 0;                  // this group's region of A
+
+    // ---- global -> LDS: wave w of a group moves rows 32 w .. of the group's A region and rows 32 w .. of B (of a
+    //      K tile that both groups read, the eight waves 16 rows each); lane L fills slot L%8 of row L/8.
+    //      Wave-uniform bases advance along K in scalar registers. ----
+    uint32_t ao[LA], bo[LB];
+    const int ra0 = w * 32, rb0 = (KG == 2 ? w : wave) * 8 * LB;
+    const int bh = rb0 / (BN / 2);                     // half of the tile that the wave's B rows lie in
+    const int a_rows = M - m0, left = bsrc.template rows_left<BN>(bn, bh);
+#pragma unroll
+    for (int i = 0; i < LA; ++i) {
+        const int r = ra0 + i * 8 + (lane >> 3);
+        ao[i] = (uint32_t)((min(ar * 128 + r, a_rows - 1) * lda + ((lane & 7) ^ ((r >> 1) & 7)) * 8) * 2);   // rows past the end repeat the last
+    }
+#pragma unroll
+    for (int i = 0; i < LB; ++i) {
+        const int r = rb0 + i * 8 + (lane >> 3);
+        bo[i] = (uint32_t)((min(r - bh * (BN / 2), left - 1) * bsrc.ldb + ((lane & 7) ^ ((r >> 1) & 7)) * 8) * 2);
+    }
+    const char* const abase = reinterpret_cast<const char*>(A + (int64_t)m0 * lda);
+    const char* const bbase = reinterpret_cast<const char*>(bsrc.template base<BN>(bn, bh));
+    auto scalar_ptr = [](const char* p) -> const char* {   // keeps the base in scalar registers
+        const uint64_t u = reinterpret_cast<uint64_t>(p);
+        const uint64_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)u);
+        const uint64_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(u >> 32));
+        return reinterpret_cast<const char*>((hi << 32) | lo);
+    };
+    // load i of K tile kt into a slot: B's first
+    auto load_one = [&](auto ic, int kt, int slot) __attribute__((always_inline)) {
+        constexpr int x = decltype(ic)::value;
+        if constexpr (x < LB) {
+            const char* g = scalar_ptr(bbase + (int64_t)kt * ROWB - x * 1024);   // the immediate adds it back
+            asm volatile("" : "+v"(bo[x]));   // keeps the offset a 32-bit register operand of the load
+            dma16_at<x * 1024>(g + bo[x], reinterpret_cast<bf16_t*>(smem + slot * SLOT + AR * REG + rb0 * ROWB));
+        } else {
+            constexpr int i = x - LB;
+            const char* g = scalar_ptr(abase + (int64_t)kt * ROWB - i * 1024);
+            asm volatile("" : "+v"(ao[i]));
+            dma16_at<i * 1024>(g + ao[i], reinterpret_cast<bf16_t*>(smem + slot * SLOT + ar * REG + ra0 * ROWB));
+        }
+    };
+
+    f32x4 acc[4][4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const int frow = lane & 15, fk = lane >> 4;
+    const int fsw = (frow >> 1) & 7;
+    const uint32_t smem_base = (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void*)smem;
+    uint32_t a_addr[2], b_addr[2];                     // [k-step of 32 columns], in slot 0
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) {
+        const uint32_t at = smem_base + frow * ROWB + ((fk + 4 * ks) ^ fsw) * 16;
+        a_addr[ks] = at + ar * REG + (w & 1) * 64 * ROWB;
+        b_addr[ks] = at + AR * REG + (w >> 1) * 64 * ROWB;
+    }
+    bf16x8 af[2][4], bf[2][4];
+
+    // The K tiles of this group are KG n + (KG == 2 ? grp : 0), n < NT, in slots by their index modulo NSLOT.
+    const int k0 = KG == 2 ? grp : 0, NT = K / 64 / KG;             // K % 128 == 0
+    int rd = k0, wrs = KG == 2 ? (grp ? 0 : 4) : 2;                 // slots of tiles n and n + 2
+    using yes = std::integral_constant<int, 1>;
+    using no = std::integral_constant<int, 0>;
+    // One K tile: 16 fragment reads with the loads of tile n + 2 between them, barrier, 32 MFMAs, barrier.
+    auto k_tile = [&](auto loadc, int n) __attribute__((always_inline)) {
+        constexpr bool LOAD = decltype(loadc)::value;
+        const uint32_t at = rd * SLOT;
+        const uint32_t a0 = a_addr[0] + at, a1 = a_addr[1] + at, b0 = b_addr[0] + at, b1 = b_addr[1] + at;
+        unrolled<8>([&](auto xc) __attribute__((always_inline)) {
+            constexpr int x = decltype(xc)::value, ks = x >> 2, y = (x & 1) * 2;
+            if constexpr ((x & 2) == 0) {
+                bf[ks][y] = lds_read16<y * 16 * ROWB>(ks ? b1 : b0);
+                bf[ks][y + 1] = lds_read16<(y + 1) * 16 * ROWB>(ks ? b1 : b0);
+            } else {
+                af[ks][y] = lds_read16<y * 16 * ROWB>(ks ? a1 : a0);
+                af[ks][y + 1] = lds_read16<(y + 1) * 16 * ROWB>(ks ? a1 : a0);
+            }
+            if constexpr (LOAD && x < L) {
+                __builtin_amdgcn_sched_barrier(0);
+                load_one(xc, KG * (n + 2) + k0, wrs);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        });
+        // where the groups share B: this wave's part of tile n + 1 has landed (the other group reads it next)
+        if constexpr (KG == 1 && LOAD) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" : : "n"(L + LA));
+        else if constexpr (KG == 1) asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)");
+        else asm volatile("s_waitcnt lgkmcnt(0)");
+#pragma unroll
+        for (int x = 0; x < 8; ++x) asm volatile("" : "+v"(af[x >> 2][x & 3]), "+v"(bf[x >> 2][x & 3]));
+        wg_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[ks][i], bf[ks][j], acc[i][j], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (LOAD) asm volatile("s_waitcnt vmcnt(%0)" : : "n"(L));      // tile n + 1 has landed
+        else asm volatile("s_waitcnt vmcnt(0)");
+        wg_barrier();
+        rd = rd + KG >= NSLOT ? rd + KG - NSLOT : rd + KG;
+        wrs = wrs + KG >= NSLOT ? wrs + KG - NSLOT : wrs + KG;
+    };
+    unrolled<L>([&](auto x) __attribute__((always_inline)) { load_one(x, k0, rd); });
+    if (NT > 1) {
+        unrolled<L>([&](auto x) __attribute__((always_inline)) { load_one(x, KG + k0, rd + KG); });
+        asm volatile("s_waitcnt vmcnt(%0)" : : "n"(L));
+    } else {
+        asm volatile("s_waitcnt vmcnt(0)");
+    }
+    wg_barrier();                                      // the first K tile of either group is in place
+    if (grp) wg_barrier();                             // the second group runs one barrier behind
+    int n = 0;
+    for (; n + 2 < NT; ++n) k_tile(yes{}, n);
+    for (; n < NT; ++n) k_tile(no{}, n);
+    if (!grp) wg_barrier();
+
+    // ---- epilogue through LDS as fp32 [BM][BN], column c of row r at c ^ 16*((r>>2)&3) (the four 16-lane
+    //      groups of an accumulator store hit disjoint banks); with two groups along K the second
+    //      leaves its sums there and the first adds them to its own ----
+    __syncthreads();
+    float* stage = reinterpret_cast<float*>(smem);
+    auto each = [&](auto f) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const int r = ar * 128 + (w & 1) * 64 + i * 16 + 4 * fk + v;
+                    const int c = (w >> 1) * 64 + j * 16 + frow;
+                    f(stage[r * BN + (c ^ (fk << 4))], acc[i][j][v]);
+                }
+    };
+    if (KG == 1 || grp == 1) each([](float& at, float v) __attribute__((always_inline)) { at = v; });
+    __syncthreads();
+    if constexpr (KG == 2) {
+        if (grp == 0) each([](float& at, float v) __attribute__((always_inline)) { at = v + at; });
+        __syncthreads();
+    }
+    constexpr int TPR = BN / 8, RPP = 512 / TPR;       // threads per row, rows per pass
+    const int cc = (tid % TPR) * 8;
+#pragma unroll
+    for (int k = 0; k < BM / RPP; ++k) {
+        const int r = tid / TPR + k * RPP;
+        const int m = m0 + r;
+        if (m < M) epi.template operator()<BN>(m, bn, cc, stage + r * BN, ((r >> 2) & 3) << 4);
+    }
+}
+
 // ------------------------------------------------------------------ thin tiles
 // 64x128 tiles for few rows, where a call reads a whole weight matrix for one or two row tiles.
 //
@@ -1548,6 +1742,9 @@ void launch_gemm(const bf16_t* A, int lda, int M, int N_tiles_cols, int K, int l
 #define CC_LAUNCH_PP(EPI_T, EPI_V, K_, NB_, VB0_, GY_)                                                      \
     hipLaunchKernelGGL((gemm_pingpong_kernel<BSrc, EPI_T>), dim3(NB_, GY_), dim3(512), 0, s, A, lda, M, K_,    \
                        tiles_m, tiles_n, GM, NB_, VB0_, bsrc, EPI_V)
+#define CC_LAUNCH_DUO(BM_)                                                                                  \
+    hipLaunchKernelGGL((gemm_duo_kernel<BM_, BSrc, Epi>), dim3(n_tiles), dim3(512), 0, s, A, lda, M, K,   \
+                       tiles_m, tiles_n, GM, n_tiles, bsrc, epi)
 #define CC_LAUNCH_NT(BM_, BN_, WM_, WN_)                                                                    \
     hipLaunchKernelGGL((gemm_nt_kernel<BM_, BN_, WM_, WN_, BSrc, Epi>), dim3(n_tiles), dim3(WM_ * WN_ * 64), 0, \
                        s, A, lda, M, K, tiles_m, tiles_n, GM, bsrc, epi)
@@ -1577,15 +1774,18 @@ void launch_gemm(const bf16_t* A, int lda, int M, int N_tiles_cols, int K, int l
         if (mfma16) CC_LAUNCH(gemm_ring16_kernel, 192, 256, 2, 4, Epi, epi, K, n_tiles, 0, 1);
         else CC_LAUNCH(gemm_ring_kernel, 192, 256, 2, 4, Epi, epi, K, n_tiles, 0, 1);
     } else if (pick == 'h') {
-        if (mfma16) CC_LAUNCH(gemm_ring16_kernel, 256, 128, 4, 2, Epi, epi, K, n_tiles, 0, 1);
+        if (mfma16 && plan.duo) CC_LAUNCH_DUO(256);
+        else if (mfma16) CC_LAUNCH(gemm_ring16_kernel, 256, 128, 4, 2, Epi, epi, K, n_tiles, 0, 1);
         else CC_LAUNCH(gemm_ring_kernel, 256, 128, 4, 2, Epi, epi, K, n_tiles, 0, 1);
     } else {
-        if (ring && mfma16) CC_LAUNCH(gemm_ring16_kernel, 128, 128, 2, 2, Epi, epi, K, n_tiles, 0, 1);
+        if (mfma16 && plan.duo) CC_LAUNCH_DUO(128);
+        else if (ring && mfma16) CC_LAUNCH(gemm_ring16_kernel, 128, 128, 2, 2, Epi, epi, K, n_tiles, 0, 1);
         else if (ring) CC_LAUNCH(gemm_ring_kernel, 128, 128, 2, 2, Epi, epi, K, n_tiles, 0, 1);
         else CC_LAUNCH_NT(128, 128, 2, 2);
     }
 #undef CC_LAUNCH
 #undef CC_LAUNCH_NT
+#undef CC_LAUNCH_DUO
 #undef CC_LAUNCH_PP
 }
 

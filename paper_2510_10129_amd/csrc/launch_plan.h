@@ -79,7 +79,8 @@ inline cc_attn_plan cc_plan_attention(int n_cu, int n_row_tiles, int H_kv, int d
 
 // ---- GEMM: C[M, N] = A[M, K] B[N, K]^T in row x column tiles.  tile: 'b' 256x256 (ping-pong loop, 8 waves, least
 // LDS and L2 traffic per flop, one workgroup per CU), 'm' 192x256 (8 waves of 96x64, ring loop only), 'h' 256x128
-// (8 waves of 64x64, one per CU, ring loop only), 's' 128x128 (4 waves of 64x64, two per CU), 't' 64x128 (thin loop).
+// (duo or ring loop, 8 waves of 64x64, one per CU), 's' 128x128 (duo loop, 8 waves of 64x64 in two groups along K, one per
+// CU; ring loop, 4 waves of 64x64, two per CU), 't' 64x128 (thin loop).
 // Where K is not a multiple of 128 the 256x256 and 128x128 shapes run the staged loop.  shares: of K ('b', 'm': of
 // the last round's tiles only; 't': of all). ----
 #define CC_GEMM_SLICE 32            // K columns of a ring slice
@@ -90,6 +91,7 @@ struct cc_gemm_plan {
     char tile;
     bool ring;
     int shares;
+    bool duo;       // 'h', 's': the duo loop (else the ring loop)
 };
 inline cc_gemm_plan cc_plan_gemm(int n_cu, int M, int N, int K, int64_t lda, int64_t ldb, bool ws, int64_t ws_floats,
                                  const cc_launch_override& ovr) {
@@ -97,26 +99,43 @@ inline cc_gemm_plan cc_plan_gemm(int n_cu, int M, int N, int K, int64_t lda, int
     auto tiles_of = [&](int bm, int bn) { return (long)((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
     auto rounds_of = [&](int bm, int bn) { return (tiles_of(bm, bn) + n_cu - 1) / n_cu; };   // one tile per CU
     // ring loop: whole groups of slices, 32-bit lane offsets within a tile's rows
-    const bool ring = K % CC_GEMM_GROUP == 0 && lda * 256 * 2 < (1ll << 31) && ldb * 256 * 2 < (1ll << 31) && !ovr.gemm_staged;
+    const bool ring = K % CC_GEMM_GROUP == 0 && lda * 256 * 2 < (1ll << 31) && ldb * 256 * 2 < (1ll << 31) && ovr.gemm_staged != 1;
     // Microseconds of a round of workgroups (a grid runs as a whole number of them): the ends of its
-    // tiles, and 32 columns of K; a last round of 128x128 tiles with no more than one per CU is a short one.
-    // Fitted to event times of the four projections of twelve models (d = 256 to 8192, f = 1024 to 28672; three
-    // of them without the ring loops), 1 to 8320 rows, weights cold, every shape and most shares forced: 1364
-    // calls, the choice 1.0 % above the fastest on average.  The ends count where K is short (K = 256, 2048
-    // columns, M = 5120: 256x256 tiles 21.4 us, 192x256 19.1, 128x128 18.4), and without the ring loops the large tile
-    // is no faster than it was (M = 3000, N = 10880, K = 1984: three rounds of 256x256 179 us, four of 128x128 147).
-    struct Round { double ends, slice; };
-    const Round rb = ring ? Round{12.4, 0.486} : Round{21.6, 0.736}, rs = ring ? Round{4.9, 0.593} : Round{11.9, 0.451},
-                rs_short = ring ? Round{6.1, 0.363} : Round{4.6, 0.497}, rm = {8.2, 0.612}, rh = {6.0, 0.404};
+    // tiles, and 32 columns of K; and what both cost more where every CU has a tile (power, and the
+    // traffic behind the caches) in proportion to the CUs that have one.
+    // Fitted to event times of the four projections of nine models (d = 256 to 8192, f = 1024 to 28672), 1 to
+    // 8320 rows, weights cold, every shape and most shares forced: 1032 calls, the choice 0.7 % above the fastest
+    // on average.  The rates without the ring loops are of three more models (364 calls): there the large tile is no
+    // faster than it was (M = 3000, N = 10880, K = 1984: three rounds of 256x256 179 us, four of 128x128 147).
+    // The ends count where K is short (K = 256, 2048 columns, M = 5120: 256x256 tiles 21.4 us, 192x256 19.1,
+    // 128x128 in the ring 18.4, with two of its tiles on a CU).
+    struct Round { double ends, slice, more_ends, more_slice; };
+    const Round rb = ring ? Round{7.1, 0.41, 7.3, 0.151} : Round{21.6, 0.736, 0, 0}, rm = {9.2, 0.542, 5.65, 0.124},
+                rh = {7.8, 0.357, 2.3, 0.175}, rhd = {6.5, 0.298, 2.1, 0.104}, rsd = {7.6, 0.21, 0, 0.047};
+    // 128x128 tiles in the ring or staged loop: two on a CU, or one where there are no more
+    const Round rs = ring ? Round{2.3, 0.6, 0, 0} : Round{11.9, 0.451, 0, 0},
+                rs_short = ring ? Round{3.9, 0.34, 2.1, 0.104} : Round{4.6, 0.497, 0, 0};
     const double slices = (double)K / CC_GEMM_SLICE;
-    auto us = [&](const Round& r) { return r.ends + r.slice * slices; };
+    auto us = [&](const Round& r, double fill, int share) {   // a round with tiles on `fill` of the CUs, 1 / share of K
+        return r.ends + r.more_ends * fill + (r.slice + r.more_slice * fill) * slices / share;
+    };
+    auto grid_us = [&](const Round& r, int bm, int bn) {
+        const double fill = (double)tiles_of(bm, bn) / n_cu;  // of all its rounds
+        return rounds_of(bm, bn) * us(r, 0, 1) + fill * (us(r, 1, 1) - us(r, 0, 1));
+    };
     const long st = tiles_of(128, 128), s_last = st % (2 * n_cu);
-    const double tb = rounds_of(256, 256) * us(rb);
-    const double ts = st / (2 * n_cu) * us(rs) + (s_last == 0 ? 0.0 : us(s_last <= n_cu ? rs_short : rs));
+    const double tb = grid_us(rb, 256, 256);
+    const double ts = st / (2 * n_cu) * us(rs, 1, 1) +
+                      (s_last == 0 ? 0.0 : s_last <= n_cu ? us(rs_short, (double)s_last / n_cu, 1) : us(rs, 1, 1));
     char pick = tb <= ts ? 'b' : 's';
     double t_best = std::min(tb, ts);
-    if (ring) {                                                 // these two have no staged variant
-        const double th = rounds_of(256, 128) * us(rh), tm = rounds_of(192, 256) * us(rm);
+    bool duo_h = false, duo_s = false;
+    if (ring) {                                                 // these have no staged variant
+        const double thr = grid_us(rh, 256, 128), thd = grid_us(rhd, 256, 128), tsd = grid_us(rsd, 128, 128);
+        const double tm = grid_us(rm, 192, 256), th = std::min(thr, thd);
+        duo_h = ovr.gemm_staged ? ovr.gemm_staged == 2 : thd < thr;
+        duo_s = ovr.gemm_staged ? ovr.gemm_staged == 2 : tsd < ts;
+        if (tsd < t_best) pick = 's', t_best = tsd;
         if (th < t_best) pick = 'h', t_best = th;
         if (tm < t_best) pick = 'm', t_best = tm;
     }
@@ -125,7 +144,7 @@ inline cc_gemm_plan cc_plan_gemm(int n_cu, int M, int N, int K, int64_t lda, int
     // fills at most half the chip (all tiles, if there is no full round) are computed by S
     // workgroup rows, each over K/S columns, with S x tiles <= CUs, and a finishing pass; the full
     // rounds before them run as a launch of their own.  256-wide tiles only.  The extra launches and
-    // the shares' traffic cost 4.5 us and 6.8 TB/s; the estimate has to be 2 % below the unsplit one.
+    // the shares' traffic cost 4.3 us and 6.8 TB/s; the estimate has to be 2 % below the unsplit one.
     int S = 1;
     if (ring && ws) {
         auto rem_of = [&](int bm) {
@@ -149,7 +168,7 @@ inline cc_gemm_plan cc_plan_gemm(int n_cu, int M, int N, int K, int64_t lda, int
                 const int rem = rem_of(bm);
                 for (int sp = 2; sp <= 16; ++sp) {
                     if (!split_ok(bm, sp, 512)) continue;
-                    const double t = full_rounds * us(r) + r.ends + r.slice * slices / sp + 4.5 +
+                    const double t = full_rounds * us(r, 1, 1) + us(r, (double)rem * sp / n_cu, sp) + 4.3 +
                                      (double)sp * rem * 65536.0 * 4 / 6.8e6;
                     if (t < t_best && t < 0.98 * t_unsplit) t_best = t, S = sp, pick = bm == 256 ? 'b' : 'm';
                 }
@@ -158,11 +177,11 @@ inline cc_gemm_plan cc_plan_gemm(int n_cu, int M, int N, int K, int64_t lda, int
     }
     // Few rows: 64x128 tiles (gemm_thin_kernel), K cut into shares where the grid leaves CUs idle.
     // From the same measurements: 3 us for the ends of a round's tiles, 0.465 per 64 columns, the weights no faster
-    // than 6.5 TB/s, a finishing pass 2 and the shares' traffic at 5; the estimate has to be 4 % below the other.
+    // than 7 TB/s, a finishing pass 2 and the shares' traffic at 4.2; the estimate has to be 4 % below the other.
     // Event microseconds (2.5 of them the events' own), d = 4096, f = 14336, 870 MB of other weights between two
-    // reads of one, the best of the thin tiles and of the larger ones:  M = 64: QKV 19.9 / 25.4, O 17.2 / 22.3, gate/up
-    // 45.7 / 57.4, down 30.7 / 39.5;  M = 128: 25.9 / 29.9, 19.5 / 26.5, 72 / 61, 41.5 / 45.2;  M = 192: 35.3 / 35.2, 25.2 / 30.1,
-    // 99 / 75, 62 / 51.
+    // reads of one, the best of the thin tiles and of the larger ones:  M = 64: QKV 19.2 / 25.5, O 18.0 / 22.6, gate/up
+    // 41.9 / 52.9, down 28.2 / 38.1;  M = 128: 26.2 / 30.0, 19.2 / 26.5, 71.6 / 58.0, 40.8 / 44.5;  M = 192: 35.7 / 35.0, 25.5 /
+    // 30.0, 99.7 / 70.1, 61.1 / 50.1.
     const long thin_tiles = tiles_of(CC_THIN_M, CC_THIN_N);
     const bool thin_ok = lda * CC_THIN_M * 2 < (1ll << 31) && ldb * CC_THIN_N * 2 < (1ll << 31);
     auto thin_split_ok = [&](int sp) {
@@ -170,7 +189,7 @@ inline cc_gemm_plan cc_plan_gemm(int n_cu, int M, int N, int K, int64_t lda, int
     };
     if (thin_ok && force == 't') {
         const int sp = ovr.gemm_splitk;
-        return {'t', ring, sp > 1 && thin_split_ok(sp) ? sp : 1};
+        return {'t', ring, sp > 1 && thin_split_ok(sp) ? sp : 1, false};
     }
     if (thin_ok && !force && !ovr.gemm_staged && !ovr.gemm_mfma32 && ovr.gemm_splitk == 0) {
         double t_thin = 0.96 * t_best;
@@ -178,12 +197,12 @@ inline cc_gemm_plan cc_plan_gemm(int n_cu, int M, int N, int K, int64_t lda, int
             if (sp > 1 && (!thin_split_ok(sp) || K / sp < 256 || thin_tiles * sp > n_cu)) continue;
             const long rounds = (thin_tiles * sp + n_cu - 1) / n_cu;
             double t = rounds * (K / sp / 64 * 0.465 + 3.0);
-            t = std::max(t, 2.0 * N * K / 6.5e6);
-            if (sp > 1) t += 2.0 + (double)sp * thin_tiles * (CC_THIN_M * CC_THIN_N) * 8 / 5.0e6;
+            t = std::max(t, 2.0 * N * K / 7.0e6);
+            if (sp > 1) t += 2.0 + (double)sp * thin_tiles * (CC_THIN_M * CC_THIN_N) * 8 / 4.2e6;
             if (t < t_thin) t_thin = t, pick = 't', S = sp;
         }
     }
-    return {pick, ring, S};
+    return {pick, ring, S, pick == 'h' ? duo_h : pick == 's' && duo_s};
 }
 
 // ---- selection: one workgroup up to CC_SEL_ONE_MAX tokens (it takes 11 us and 0.6 us more per 1024 tokens), beyond

@@ -921,3 +921,44 @@ def test_stage_projections_on_thin_tiles(M, splitk):
     mx, mn = err_stats(bits_f64(host_bits(out))[:M], z)
     assert mx <= MAX_ABS and mn <= MEAN_ABS and bool((out[M] == 7.0).all()), (mx, mn)
     ctx.close()
+
+
+@pytest.mark.parametrize("tile,d,f,M", [("s", 128, 384, 1), ("s", 128, 384, 129), ("s", 640, 256, 255), ("h", 128, 384, 127),
+                                        ("h", 128, 384, 257), ("h", 640, 256, 513)])
+def test_stage_projections_in_the_duo_loop(tile, d, f, M):
+    """256x128 and 128x128 tiles with the duo loop forced: K of one, two, three and five K tiles a group (128, 256,
+    384, 640 columns), partial row and column tiles, rows past the last of a tile.  Same bounds as above."""
+    model = ModelShape(d, d // 64, d // 128, 64, f, 1e4, 1e-5, True, 1)
+    N = 600
+    rng = np.random.default_rng(M)
+    w = gen.layer_weights(model, 0, seed=23)
+    xb = _x_bits(N, d, 8)
+    idx = np.sort(rng.choice(N, size=M, replace=False))
+    ctx = _ctx(model, N, M)
+    ctx.debug_set_launch(gemm_tile=tile, gemm_staged=2, gemm_splitk=1)
+    dw, hid, xf = dev_weights(w), dev_bf16(xb), obf.bits_to_f64(xb[idx])
+    xn = torch.empty((M, d), dtype=torch.bfloat16, device=DEV)
+    ctx.step_gather_rmsnorm(hid, dev_i32(idx), M, dw.w_in_norm, xn)
+    Kd, Vd = (torch.zeros((N, model.H_kv, 64), dtype=torch.bfloat16, device=DEV) for _ in range(2))
+    q = torch.empty((M, d), dtype=torch.bfloat16, device=DEV)
+    ctx.step_qkv_rope_scatter(xn, M, dev_i32(idx), dw.w_qkv, dw.b_qkv, cc.KVLayer(Kd, Vd), q, _lib.FLAG_CHECK_IDX)
+    q_ref, k_ref, v_ref = layer.qkv_rows(xf, w, model, idx)
+    for got, ref in ((host_bits(q).reshape(M, model.H_q, -1), q_ref), (host_bits(Kd)[idx], k_ref), (host_bits(Vd)[idx], v_ref)):
+        mx, mn = err_stats(bits_f64(got), ref)
+        assert mx <= MAX_ABS and mn <= MEAN_ABS, (mx, mn)
+    rest = np.setdiff1d(np.arange(N), idx)
+    assert not host_bits(Kd)[rest].any() and not host_bits(Vd)[rest].any()
+    ob = _x_bits(M, d, 9, 0.5)
+    y = torch.full((M + 1, d), 7.0, dtype=torch.float32, device=DEV)
+    ctx.step_oproj_residual(dev_bf16(ob), M, dw.w_o, hid, dev_i32(idx), y)
+    yf = y[:M].cpu().numpy().astype(np.float64)
+    y_ref = xf + obf.bits_to_f64(ob) @ obf.bits_to_f64(w["w_o"]).T
+    assert err_stats(yf, y_ref)[0] <= 1e-4 and bool((y[M] == 7.0).all())      # fp32 sums of exact bf16 products
+    out = torch.full((M + 1, d), 7.0, dtype=torch.bfloat16, device=DEV)
+    ctx.step_mlp(y, M, dw.w_post_norm, dw.w_gate, dw.w_up, dw.w_down, out)
+    torch.cuda.synchronize()
+    m = layer.rmsnorm(yf, obf.bits_to_f64(w["w_post_norm"]), model.rms_eps)
+    z = yf + (layer.silu(m @ obf.bits_to_f64(w["w_gate"]).T) * (m @ obf.bits_to_f64(w["w_up"]).T)) @ obf.bits_to_f64(w["w_down"]).T
+    mx, mn = err_stats(bits_f64(host_bits(out))[:M], z)
+    assert mx <= MAX_ABS and mn <= MEAN_ABS and bool((out[M] == 7.0).all()), (mx, mn)
+    ctx.close()

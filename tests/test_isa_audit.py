@@ -179,3 +179,17 @@ def test_gemm_thin_kernel_reads_are_waited_for(tmp_path):
         seen, bad = audit(body)
         assert seen >= 12, (name, seen)                   # twelve fragment reads per slice
         assert not bad, (name, bad[:5])
+
+
+@pytest.mark.skipif(shutil.which(HIPCC) is None, reason="hipcc not found")
+def test_gemm_duo_kernel_reads_are_waited_for(tmp_path):
+    out = tmp_path / "gemm.s"
+    cmd = [HIPCC, *build.FLAGS, "-S", "--cuda-device-only", "-o", str(out), os.path.join(build.CSRC, "gemm.hip")]
+    r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    assert r.returncode == 0, r.stdout
+    kernels = re.findall(r"^(_ZN\S*gemm_duo_kernel\S*):[^\n]*\n(.*?)\.end_amdhsa_kernel", out.read_text(), flags=re.S | re.M)
+    assert len(kernels) == 8, [k[0] for k in kernels]     # two tile shapes x four epilogues
+    for name, body in kernels:
+        seen, bad = audit(body)
+        assert seen >= 2 * 16, (name, seen)               # sixteen fragment reads in the loop and in its end
+        assert not bad, (name, bad[:5])

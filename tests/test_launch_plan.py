@@ -24,6 +24,12 @@ int plan_gemm(int n_cu, int M, int N, int K, int64_t ws_floats, const cc_launch_
     const cc_gemm_plan p = cc_plan_gemm(n_cu, M, N, K, K, K, ws_floats > 0, ws_floats, *ovr);
     return p.tile + 256 * p.shares;
 }
+int plan_gemm_duo(int n_cu, int M, int N, int K, int tile) {
+    cc_launch_override o{};
+    o.gemm_tile = tile;
+    const cc_gemm_plan p = cc_plan_gemm(n_cu, M, N, K, K, K, false, 0, o);
+    return p.duo ? p.tile : 0;
+}
 int norm_waves(int n_cu, int M, int d, int elem_bytes) { return cc_norm_waves(n_cu, M, d, elem_bytes); }
 int asm_rows(int64_t n_rows, int width) { return cc_asm_rows(n_rows, width); }
 int select_uses_ranges(int T) { return cc_select_uses_ranges(T); }
@@ -197,3 +203,13 @@ def test_norm_plans_have_a_kernel(plan):
 def test_rows_of_an_assembly_wave(plan, n_rows, width, rows):
     plan.asm_rows.argtypes = [C.c_int64, C.c_int]
     assert plan.asm_rows(n_rows, width) == rows
+
+
+@pytest.mark.parametrize("M,N,K,tile,duo", [
+    (883, 4096, 4096, "s", True), (883, 6144, 4096, "h", True),        # 44.0 us against 59.8 in the ring loop, 63 against 79.9
+    (1523, 4608, 3584, "h", True), (128, 4096, 14336, "s", True),      # 61, 80.8; 141, 168
+    (3404, 2048, 256, "s", False),                                     # 19, 14.5 (two tiles a CU)
+    (300, 512, 1984, "s", False),                                      # K % 128: the staged loop
+])
+def test_loop_of_the_smaller_tiles(plan, M, N, K, tile, duo):
+    assert bool(plan.plan_gemm_duo(256, M, N, K, ord(tile))) == duo
