@@ -159,7 +159,7 @@ cc_status cc_create(cc_ctx** out, const cc_model_desc* desc, void* hip_stream) {
     memset(c->prof_n, 0, sizeof(c->prof_n));
     c->rope = nullptr; c->xn = nullptr; c->q = nullptr; c->o = nullptr; c->y = nullptr;
     c->mn = nullptr; c->act = nullptr; c->attn_part = nullptr; c->attn_table = nullptr; c->gemm_part = nullptr; c->score = nullptr; c->key_range = nullptr; c->sel = nullptr; c->n_sel = nullptr; c->flag = nullptr;
-    c->pinned = nullptr;
+    c->pinned = c->pinned_dev = nullptr;
     const cc_model_desc& m = c->m;
     const size_t Mc = (size_t)m.M_cap, nq = (size_t)m.H_q * m.d_h;
     hipError_t e = hipGetDevice(&c->device);
@@ -197,6 +197,7 @@ cc_status cc_create(cc_ctx** out, const cc_model_desc* desc, void* hip_stream) {
     alloc((void**)&c->n_sel, 4);
     alloc((void**)&c->flag, 4);
     if (e == hipSuccess) e = hipHostMalloc((void**)&c->pinned, 2 * sizeof(int32_t), hipHostMallocDefault);
+    if (e == hipSuccess) e = hipHostGetDevicePointer((void**)&c->pinned_dev, c->pinned, 0);
     if (e != hipSuccess) {
         std::string msg = std::string("workspace allocation: ") + hipGetErrorString(e);
         cc_destroy(c);
@@ -309,11 +310,11 @@ cc_status cc_select_blocks(cc_ctx* c, const cc_aux_block* blocks, int32_t n_bloc
     {
         cc_prof_scope ps(c, CC_K_SELECT);
         cc_launch_select(c->score, T, k, window, tau_eff, (flags & CC_FLAG_NO_GROUPING) ? 0 : 1,
-                         idx_offset, n_tail, idx_out, n_out, c->key_range, n_range, c->sel, c->stream);
+                         idx_offset, n_tail, idx_out, n_out, n_out_host ? c->pinned_dev + 1 : nullptr, c->key_range, n_range,
+                         c->sel, c->stream);
     }
     CC_HIP(c, hipGetLastError());
     if (n_out_host) {
-        CC_HIP(c, hipMemcpyAsync(c->pinned + 1, n_out, sizeof(int32_t), hipMemcpyDeviceToHost, c->stream));
         CC_HIP(c, hipStreamSynchronize(c->stream));
         *n_out_host = c->pinned[1];
     }
@@ -341,11 +342,11 @@ cc_status cc_select(cc_ctx* c, const float* attn, int32_t Q_a, int32_t T, int64_
     {
         cc_prof_scope ps(c, CC_K_SELECT);
         cc_launch_select(c->score, T, k, window, tau_eff, (flags & CC_FLAG_NO_GROUPING) ? 0 : 1,
-                         idx_offset, n_tail, idx_out, n_out, c->key_range, (T + 63) / 64, c->sel, c->stream);
+                         idx_offset, n_tail, idx_out, n_out, n_out_host ? c->pinned_dev + 1 : nullptr, c->key_range, (T + 63) / 64,
+                         c->sel, c->stream);
     }
     CC_HIP(c, hipGetLastError());
     if (n_out_host) {
-        CC_HIP(c, hipMemcpyAsync(c->pinned + 1, n_out, sizeof(int32_t), hipMemcpyDeviceToHost, c->stream));
         CC_HIP(c, hipStreamSynchronize(c->stream));
         *n_out_host = c->pinned[1];
     }
@@ -375,7 +376,7 @@ cc_status cc_select_noalloc(void* hip_stream, const float* attn, int32_t Q_a, in
     cc_sel_buf* sel = reinterpret_cast<cc_sel_buf*>(static_cast<char*>(sp) + CC_NOALLOC_SEL_AT);
     cc_launch_colsum(attn, Q_a, T, ld, score, cc_select_uses_ranges(T) ? key_range : nullptr, stream);
     cc_launch_select(score, T, k, window, tau_eff, (flags & CC_FLAG_NO_GROUPING) ? 0 : 1, idx_offset, n_tail,
-                     idx_out, n_out, key_range, (T + 63) / 64, sel, stream);
+                     idx_out, n_out, nullptr, key_range, (T + 63) / 64, sel, stream);
     e = hipGetLastError();
     if (e != hipSuccess) return fail(nullptr, CC_ERR_HIP, std::string("launch: ") + hipGetErrorString(e));
     return CC_OK;

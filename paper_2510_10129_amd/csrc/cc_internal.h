@@ -46,6 +46,7 @@ struct cc_ctx {
     int32_t* n_sel;    // [1]
     int32_t* flag;     // [1] idx check result
     int32_t* pinned;   // host pinned [2]
+    int32_t* pinned_dev;   // the device's address of it
     cc_launch_override ovr;   // test overrides of the launch shapes (all zero: none)
 
     // profiling
@@ -118,9 +119,10 @@ struct cc_sel_buf {
     int32_t shift;                               // its width: 2^shift keys
 };
 typedef cc_sel_buf* cc_sel_ws;
+// n_host (may be NULL): host memory that the device can write, for the count as well.
 // key_range (n_range entries) and ws may be NULL where cc_select_uses_ranges(T) says no.
 void cc_launch_select(const float* score, int T, int k, int window, int tau, int grouping,
-                      int idx_offset, int n_tail, int32_t* idx_out, int32_t* n_out, const uint2* key_range,
+                      int idx_offset, int n_tail, int32_t* idx_out, int32_t* n_out, int32_t* n_host, const uint2* key_range,
                       int n_range, cc_sel_ws ws, hipStream_t s);
 void cc_launch_check_idx(const int32_t* idx, int M, int lo, int hi, int strict, int32_t* flag,
                          hipStream_t s);

@@ -205,10 +205,10 @@ inline cc_gemm_plan cc_plan_gemm(int n_cu, int M, int N, int K, int64_t lda, int
     return {pick, ring, S, pick == 'h' ? duo_h : pick == 's' && duo_s};
 }
 
-// ---- selection: one workgroup up to CC_SEL_ONE_MAX tokens (it takes 11 us and 0.6 us more per 1024 tokens), beyond
-// that four launches over tiles (22 us and next to nothing more), which take the ranges of the keys and
-// their workspace.  One workgroup / four launches, microseconds: scores of a softmax 16385: 21.1 / 22.2, 20000:
-// 22.5 / 22.8, 24000: 24.2 / 22.7, 32768: 30.4 / 22.3;  crowded by a zero 18000: 27.1 / 30.9, 28000: 34.7 / 34.7, 32768: 37.6 / 35.2. ----
+// ---- selection: one workgroup up to CC_SEL_ONE_MAX tokens (five rows of 4096 keys in LDS; 6.5 us and 0.36 us more per
+// 1024 tokens), beyond that four launches over tiles (21 us and next to nothing more), which take the ranges of
+// the keys and their workspace.  One workgroup / four launches, microseconds: scores of a softmax 16384: 12.1 / 21.0,
+// 20480: 13.8 / 21.2; crowded by a zero 20480: 23.9 / 30. ----
 #define CC_SEL_ONE_MAX 20480
 inline bool cc_select_uses_ranges(int T) { return T > CC_SEL_ONE_MAX; }
 

@@ -10,14 +10,39 @@ __device__ __forceinline__ uint32_t score_key(float s) {
     return u ^ ((uint32_t)((int32_t)u >> 31) | 0x80000000u);   // negative: all bits flipped; else the sign bit set
 }
 
+// Wave-wide steps in the vector ALU (data-parallel primitives: a row shift moves a value N lanes up within 16 lanes,
+// the two row broadcasts hand lane 15 of a row to the next row, lane 31 to the upper half), a few clocks each
+// where a lane exchange through LDS takes over a hundred.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint32_t dpp(uint32_t old, uint32_t x) {       // lanes without a source get `old`
+    return (uint32_t)__builtin_amdgcn_update_dpp((int)old, (int)x, CTRL, ROWS, 0xF, false);
+}
+// inclusive scan over the wave; F(old, x): the identity of the operation is passed
+template <class F>
+__device__ __forceinline__ uint32_t wave_scan(uint32_t x, uint32_t identity, F&& f) {
+    x = f(x, dpp<0x111, 0xF>(identity, x));
+    x = f(x, dpp<0x112, 0xF>(identity, x));
+    x = f(x, dpp<0x114, 0xF>(identity, x));
+    x = f(x, dpp<0x118, 0xF>(identity, x));
+    x = f(x, dpp<0x142, 0xA>(identity, x));
+    x = f(x, dpp<0x143, 0xC>(identity, x));
+    return x;
+}
+__device__ __forceinline__ uint32_t wave_scan_add(uint32_t x) {
+    return wave_scan(x, 0u, [](uint32_t a, uint32_t b) __attribute__((always_inline)) { return a + b; });
+}
+__device__ __forceinline__ uint32_t lane_value(uint32_t x, int lane) { return (uint32_t)__builtin_amdgcn_readlane((int)x, lane); }
+__device__ __forceinline__ uint32_t wave_min(uint32_t x) {
+    return lane_value(wave_scan(x, 0xFFFFFFFFu, [](uint32_t a, uint32_t b) __attribute__((always_inline)) { return min(a, b); }), 63);
+}
+__device__ __forceinline__ uint32_t wave_max(uint32_t x) {
+    return lane_value(wave_scan(x, 0u, [](uint32_t a, uint32_t b) __attribute__((always_inline)) { return max(a, b); }), 63);
+}
+
 // Smallest and largest key of a score kernel's 64 columns (lanes whose column does not exist pass
 // ok = false), for the digits of the selection.
 __device__ __forceinline__ void write_key_range(float acc, bool ok, uint2* dst) {
-    uint32_t mn = ok ? score_key(acc) : 0xFFFFFFFFu, mx = ok ? score_key(acc) : 0u;
-    for (int off = 32; off > 0; off >>= 1) {
-        mn = min(mn, (uint32_t)__shfl_xor((int)mn, off));
-        mx = max(mx, (uint32_t)__shfl_xor((int)mx, off));
-    }
+    const uint32_t mn = wave_min(ok ? score_key(acc) : 0xFFFFFFFFu), mx = wave_max(ok ? score_key(acc) : 0u);
     if ((threadIdx.x & 63) == 0) *dst = make_uint2(mn, mx);
 }
 
@@ -180,40 +205,38 @@ void cc_launch_block_scores(const cc_blk_args& a, int H, int Q_a, float* score, 
 }
 
 // ----------------------------------------------------------------------------
-// Top-k + grouping + compaction in one workgroup of 16 waves.  One compute unit
-// executes all of it, so the work per token is kept to two passes over the
-// scores and everything after them runs per 64-token bitmap word.
+// Top-k + grouping + compaction in one workgroup of 16 waves.
 //
-// Scores become order-preserving 32-bit keys; the k-th largest key is found by a
-// most-significant-digit-first radix search over 11 + 11 + 10 bits (LDS
-// histogram, then the bin of the k-th key by a suffix sum over the bins).
-//   scan 1  histogram of the first digit of every key.  The scores of a request
-//           sit in a few binades, so neighbouring keys mostly share the digit: a
-//           thread merges runs of equal digits among its own keys and adds a run
-//           with one LDS atomic (same-address atomics serialise).
-//   scan 2  keys above the threshold digit are candidates (one ballot per word);
-//           keys of the threshold digit go, with their token index, into a list in
-//           LDS.  The two remaining digits are resolved on that list, and the
-//           list entries at or above the threshold set their candidate bits.
-// A list that would not fit (more than SEL_LIST keys share the threshold digit)
-// or a threshold value of which only some keys are taken (equal scores: the lowest
-// indices win, ranked with wave ballots and a scan over per-word counts) takes the
-// general path: the remaining digits and the candidates from further passes over
-// the scores.
-// Candidates, passing window starts and chosen tokens are bitmaps in LDS.  For
-// windows up to 64 tokens a thread owns a bitmap word: it tests the windows that
-// start at the word's candidates with shifts and popcounts, spreads passing
-// starts over their windows by doubling shifts, and writes the indices of a
-// 16-token quarter of a word from its set bits; longer windows are tested per
-// token with popcounts over the words they span.
+// What bounds it: one compute unit, for its latencies (a barrier, a load, a chain of lane exchanges), a dozen of
+// them in a row, its vector instructions (16 waves of which four share a SIMD) and the fetch of its
+// instructions, which it runs once: unrolled over a thread's keys the same steps took twice as long.  So
+// every score is loaded once, 16 bytes a lane and all of a thread's loads together, its order-preserving 32-bit key
+// (a larger score has a larger key) stays in LDS where only its thread reads it, loops are rolled, scans and
+// reductions run in the vector ALU, and a bitmap is written and judged by threads that own some bits of it.
+// The k-th largest key is found by histograms of 2048 equal bins: the first over the range of the keys, so that
+// the bin of the k-th key holds a few dozen of them, then over that bin, until it holds at most SEL_LIST keys,
+// all of them are taken, or it is one key wide.  The keys of a bin of which some are taken are ranked against
+// each other (equal keys by token, the lowest first); more than SEL_LIST equal keys by ballots and a scan
+// over per-word counts.
+// Candidates, passing window starts and chosen tokens are bitmaps in LDS.  For windows up to 64 tokens a thread
+// judges the 16 starts of a quarter word (the first window's count, then a token in and a token out), then
+// spreads a word's passing starts over their windows by doubling shifts; longer windows are tested per token with
+// popcounts over the words they span.
+// Against a radix search over the keys' digits with the scores read twice (event us, k = T / 5, window 16): T = 1024
+// 11.0 -> 6.9, 4096 12.4 -> 7.5, 16384 19.7 -> 12.1, 20480 22.4 -> 13.8; 16384 equal scores 30 -> 20, a zero beside scores within
+// an octave 27 -> 20.5.  Clocks at 16384: load 2700, key range 1500, histogram and bin 5500, candidates 4100, list 500,
+// windows 2700, scan 600, indices 4500.
 // ----------------------------------------------------------------------------
 #define SEL_THREADS 1024
 #define SEL_WAVES 16
 #define SEL_TCAP CC_SEL_ONE_MAX
+#define SEL_ROWS (SEL_TCAP / (4 * SEL_THREADS))   // rows of 4096 tokens, four consecutive ones a thread
 #define SEL_WORDS (SEL_TCAP / 64 + 20)   // bitmap words incl. zero padding past T + window
 #define SEL_BINS 2048
-#define SEL_BATCH 8                      // keys a thread loads together
-#define SEL_LIST 12288                   // keys of the threshold digit that the LDS list holds
+#define SEL_BATCH 8                      // loads of a thread that are out together, in passes over more than SEL_TCAP scores
+#define SEL_LIST 64                      // keys of the threshold bin that are ranked against each other
+static_assert(SEL_TCAP % (4 * SEL_THREADS) == 0 && SEL_TCAP / 64 <= SEL_THREADS && SEL_LIST <= 64,
+              "whole rows of keys; a word a thread; a listed key a lane");
 
 // popcount of bits [b0, b1) of a zero-padded bitmap
 __device__ __forceinline__ int window_popc(const uint64_t* bm, int b0, int b1) {
@@ -234,28 +257,19 @@ __device__ __forceinline__ int window_popc(const uint64_t* bm, int b0, int b1) {
 // In-place exclusive prefix sum of v[0 .. n) by the whole workgroup; returns the total.
 // wave_tot: SEL_WAVES words of LDS.  Ends with a barrier.
 __device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t* v, int n, uint32_t* wave_tot) {
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     uint32_t run = 0;
     for (int base = 0; base < n; base += SEL_THREADS) {
         const int i = base + tid;
         const uint32_t c = i < n ? v[i] : 0u;
-        uint32_t inc = c;
-        for (int off = 1; off < 64; off <<= 1) {
-            const uint32_t o = __shfl_up(inc, off);
-            if (lane >= off) inc += o;
-        }
+        const uint32_t inc = wave_scan_add(c);
         if (lane == 63) wave_tot[wave] = inc;
         __syncthreads();
-        // lanes 0..15 of every wave hold the sixteen totals; inclusive prefix over them by shuffles
-        uint32_t wt = lane < SEL_WAVES ? wave_tot[lane] : 0u;
-        for (int off = 1; off < SEL_WAVES; off <<= 1) {
-            const uint32_t o = __shfl_up(wt, off);
-            if (lane >= off) wt += o;
-        }
-        const uint32_t before = run + (wave ? __shfl(wt, wave - 1) : 0u);
-        const uint32_t total = __shfl(wt, SEL_WAVES - 1);
+        const uint32_t wt = wave_scan_add(lane < SEL_WAVES ? wave_tot[lane] : 0u);     // in every wave
+        const uint32_t before = run + (wave ? lane_value(wt, wave - 1) : 0u);
         if (i < n) v[i] = before + inc - c;
-        run += total;
+        run += lane_value(wt, SEL_WAVES - 1);
         __syncthreads();
     }
     return run;
@@ -274,349 +288,270 @@ __device__ __forceinline__ void run_add(uint32_t* hist, uint32_t dgt, uint32_t& 
     }
 }
 
-// Histogram (nb = dmask + 1 bins, zeroed here) of digit (key >> shift) & dmask over the keys
-// with (key & mask) == prefix.  Thread tid takes tokens tid, tid + 1024, ...; the loads of the
-// next batch are issued before the current one is processed.  Ends with a barrier.
-__device__ __forceinline__ void hist_of_scores(const float* __restrict__ score, int T, uint32_t prefix,
-                                               uint32_t mask, int shift, uint32_t dmask, uint32_t* hist) {
-    const int tid = threadIdx.x;
-    for (int i = tid; i <= (int)dmask; i += SEL_THREADS) hist[i] = 0;
+// The bin b of the krem-th largest of `total` entries of a histogram of SEL_BINS bins: the entries in bins above b are
+// fewer than krem, those and bin b's are not.  Returns b, krem minus the entries above b, and the bin's
+// count through sh[0..2].  Thread t holds bins 2t, 2t+1; prefix sums, entry total - krem from below.  Ends with a barrier.
+__device__ __forceinline__ void pick_bin(const uint32_t* hist, uint32_t total, uint32_t krem, uint32_t* wave_tot, uint32_t* sh) {
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const uint2 h = reinterpret_cast<const uint2*>(hist)[tid];
+    const uint32_t inc = wave_scan_add(h.x + h.y);
+    if (lane == 63) wave_tot[wave] = inc;
     __syncthreads();
-    constexpr int STEP = SEL_THREADS * SEL_BATCH;
-    float cur[SEL_BATCH], nxt[SEL_BATCH];
-#pragma unroll
-    for (int j = 0; j < SEL_BATCH; ++j) {
-        const int t = j * SEL_THREADS + tid;
-        cur[j] = t < T ? score[t] : 0.0f;
-        nxt[j] = 0.0f;
-    }
-    uint32_t run_d = 0, run_n = 0;
-    for (int base = 0; base < T; base += STEP) {
-        if (base + STEP < T) {
-#pragma unroll
-            for (int j = 0; j < SEL_BATCH; ++j) {
-                const int t = base + STEP + j * SEL_THREADS + tid;
-                nxt[j] = t < T ? score[t] : 0.0f;
-            }
-        }
-#pragma unroll
-        for (int j = 0; j < SEL_BATCH; ++j) {
-            const int t = base + j * SEL_THREADS + tid;
-            const uint32_t key = score_key(cur[j]);
-            if (t < T && (key & mask) == prefix) run_add(hist, (key >> shift) & dmask, run_d, run_n);
-        }
-#pragma unroll
-        for (int j = 0; j < SEL_BATCH; ++j) cur[j] = nxt[j];
-    }
-    if (run_n) atomicAdd(&hist[run_d], run_n);
-    __syncthreads();
-}
-
-// The bin b of the krem-th largest entry of a histogram of nb (1024 or 2048) bins: the largest b
-// with (entries in bins above b) < krem <= (those + bin b).  Returns b, krem minus the entries
-// above b, and the bin's count through sh[0..2].  Thread t holds bins 2t, 2t+1 (nb = 2048) or
-// bin t; suffix sums by wave shuffles, then over the waves' totals.  Ends with a barrier.
-__device__ __forceinline__ void pick_bin(const uint32_t* hist, int nb, uint32_t krem, uint32_t* wave_tot,
-                                         uint32_t* sh) {
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int per = nb / SEL_THREADS;
-    const uint32_t h0 = hist[tid * per], h1 = per == 2 ? hist[tid * per + 1] : 0u;
-    const uint32_t mine = h0 + h1;
-    uint32_t inc = mine;                              // this thread's bins .. end of the wave
-    for (int off = 1; off < 64; off <<= 1) {
-        const uint32_t o = __shfl_down(inc, off);
-        if (lane + off < 64) inc += o;
-    }
-    if (lane == 0) wave_tot[wave] = inc;
-    __syncthreads();
-    // lanes 0..15 of every wave hold the sixteen totals; suffix sums over them by shuffles
-    uint32_t wt = lane < SEL_WAVES ? wave_tot[lane] : 0u;
-    for (int off = 1; off < SEL_WAVES; off <<= 1) {
-        const uint32_t o = __shfl_down(wt, off);
-        if (lane + off < SEL_WAVES) wt += o;
-    }
-    // entries in bins above this thread's: the rest of its wave, then the waves above
-    uint32_t above = inc - mine + (wave + 1 < SEL_WAVES ? __shfl(wt, wave + 1) : 0u);
-    if (per == 2) {                                   // the upper of the two bins first
-        if (above < krem && krem <= above + h1) {
-            sh[0] = (uint32_t)(tid * 2 + 1);
-            sh[1] = krem - above;
-            sh[2] = h1;
-        }
-        above += h1;
-    }
-    if (above < krem && krem <= above + h0) {
-        sh[0] = (uint32_t)(tid * per);
-        sh[1] = krem - above;
-        sh[2] = h0;
+    const uint32_t wt = wave_scan_add(lane < SEL_WAVES ? wave_tot[lane] : 0u);         // in every wave
+    const uint32_t end = inc + (wave ? lane_value(wt, wave - 1) : 0u), mid = end - h.y, begin = mid - h.x;
+    const uint32_t r = total - krem;                  // 0 <= r < total
+    if (begin <= r && r < end) {
+        const bool hi = r >= mid;
+        sh[0] = (uint32_t)(2 * tid + (hi ? 1 : 0));
+        sh[1] = (hi ? end : mid) - r;                 // krem - (total - the entries up to this bin)
+        sh[2] = hi ? h.y : h.x;
     }
     __syncthreads();
 }
 
 struct SelLds {
+    u32x4 key[SEL_ROWS][SEL_THREADS];
     uint64_t cand[SEL_WORDS];
     uint64_t pass[SEL_WORDS];
-    uint32_t word_prefix[SEL_TCAP / 64 + 1];
+    uint32_t word_n[SEL_TCAP / 64];
     uint32_t hist[SEL_BINS];
-    uint32_t list_t[SEL_LIST];       // token index and low 21 key bits of the keys of the threshold digit
-    uint32_t list_low[SEL_LIST];
-    uint32_t wave_tot[SEL_WAVES];
-    uint32_t sh[3];
-    uint32_t sh_list_n;
+    uint32_t list_t[SEL_LIST], list_key[SEL_LIST];
+    uint32_t wave_tot[SEL_WAVES], mn[SEL_WAVES], mx[SEL_WAVES];
+    uint32_t sh[3], list_n;
 };
 
+// n_host (may be NULL): a second place for the count, in host memory.
 __global__ __launch_bounds__(SEL_THREADS) void select_kernel(
     const float* __restrict__ score, int T, int k, int window, int tau, int grouping,
-    int idx_offset, int n_tail, int32_t* __restrict__ idx_out, int32_t* __restrict__ n_out) {
+    int idx_offset, int n_tail, int32_t* __restrict__ idx_out, int32_t* __restrict__ n_out, int32_t* __restrict__ n_host) {
     __shared__ SelLds L;
     uint64_t* const cand = L.cand;
     uint64_t* const pass = L.pass;
     uint64_t* const marked = cand;      // the chosen-token bitmap takes the candidates' place once the windows are judged
-    uint32_t* const word_prefix = L.word_prefix;
-    uint32_t* const hist = L.hist;
-    uint32_t* const list_t = L.list_t;
-    uint32_t* const list_low = L.list_low;
-    uint32_t* const wave_tot = L.wave_tot;
-    uint32_t* const sh = L.sh;
-    uint32_t& sh_list_n = L.sh_list_n;
-
-    const int tid = threadIdx.x;
-    const int lane = tid & 63;
-    const int wave = tid >> 6;
-    const uint64_t lane_lt = (1ULL << lane) - 1ULL;
-    const int n_words = (T + 63) >> 6;
-
-    // the bitmaps are read up to `window` bits past T: clear the words that the phases below
-    // do not write
-    for (int i = n_words + tid; i < n_words + 20 && i < SEL_WORDS; i += SEL_THREADS) {
-        cand[i] = 0;
-        pass[i] = 0;
-    }
-    if (tid == 0) sh_list_n = 0;
-
-    // ---- threshold key: the k-th largest (0 < k < T) ----
-    uint32_t kth = 0, krem = 0;
-    bool rank_ties = false, have_cand = false;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int n_words = (T + 63) >> 6, n_rows = (T + 4 * SEL_THREADS - 1) / (4 * SEL_THREADS);
     const bool all = k >= T, none = k <= 0;
-    if (!all && !none) {
-        // scan 1: first digit (bits 31..21)
-        hist_of_scores(score, T, 0u, 0u, 21, 2047u, hist);
-        pick_bin(hist, 2048, (uint32_t)k, wave_tot, sh);
-        const uint32_t b0 = sh[0];
-        krem = sh[1];
-        uint32_t bin_count = sh[2];
-        uint32_t prefix = b0 << 21, mask = 2047u << 21;
-        if (bin_count <= SEL_LIST) {
-            // scan 2: candidates above the threshold digit; the keys of that digit into the list
-            constexpr int STEP = SEL_THREADS * SEL_BATCH;
-            float cur[SEL_BATCH], nxt[SEL_BATCH];
+
+    // ---- keys: row j, thread tid: tokens 4096 j + 4 tid .. + 3 (past the end: the last token's key) ----
+    uint32_t mn = 0xFFFFFFFFu, mx = 0;
+    {
+        f32x4 v[SEL_ROWS];
 #pragma unroll
-            for (int j = 0; j < SEL_BATCH; ++j) {
-                const int t = j * SEL_THREADS + tid;
-                cur[j] = t < T ? score[t] : 0.0f;
-                nxt[j] = 0.0f;
+        for (int j = 0; j < SEL_ROWS; ++j) {
+            const int t = 4 * (j * SEL_THREADS + tid);
+            if (t + 3 < T) {
+                v[j] = *reinterpret_cast<const f32x4*>(score + t);
+            } else if (j < n_rows) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[j][e] = score[min(t + e, T - 1)];
             }
-            for (int base = 0; base < T; base += STEP) {
-                if (base + STEP < T) {
+        }
+        L.hist[tid] = 0;
+        L.hist[tid + SEL_THREADS] = 0;
+        // the bitmaps are read up to `window` bits past T: clear the words behind the rows
+        if (tid < 20) cand[64 * n_rows + tid] = pass[64 * n_rows + tid] = 0;
+        if (tid == 0) L.list_n = 0;
 #pragma unroll
-                    for (int j = 0; j < SEL_BATCH; ++j) {
-                        const int t = base + STEP + j * SEL_THREADS + tid;
-                        nxt[j] = t < T ? score[t] : 0.0f;
-                    }
+        for (int j = 0; j < SEL_ROWS; ++j)
+            if (j < n_rows) {
+                u32x4 q;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    q[e] = score_key(v[j][e]);
+                    mn = min(mn, q[e]);
+                    mx = max(mx, q[e]);
                 }
+                L.key[j][tid] = q;                  // read by this thread alone
+            }
+    }
+
+    uint32_t base = 0, krem = 0, in_bin = 0;        // threshold bin: first key, keys taken of it, keys in it
+    int shift = 0;                                  // its width: 2^shift keys
+    if (!all && !none) {
+        mn = wave_min(mn);
+        mx = wave_max(mx);
+        if (lane == 0) {
+            L.mn[wave] = mn;
+            L.mx[wave] = mx;
+        }
+        __syncthreads();
+        mn = wave_min(L.mn[lane & (SEL_WAVES - 1)]);
+        mx = wave_max(L.mx[lane & (SEL_WAVES - 1)]);
+        base = mn;
+        krem = (uint32_t)k;
+        in_bin = (uint32_t)T;
+        const int bits = mx == mn ? 0 : 32 - __clz((int)(mx - mn));
+        shift = bits > 11 ? bits - 11 : 0;
+        uint32_t last = mx - mn;                    // the bin's last key, from its base
+#pragma unroll 1
+        for (;;) {
+#pragma unroll 1
+            for (int j = 0; j < n_rows; ++j) {
+                const u32x4 q = L.key[j][tid];
+                const int n_ok = T - 4 * (j * SEL_THREADS + tid);
+                uint32_t bin[4];
 #pragma unroll
-                for (int j = 0; j < SEL_BATCH; ++j) {
-                    const int r0 = base + j * SEL_THREADS;       // first token of this row of the batch
-                    if (r0 < T) {                                // workgroup-uniform
-                        const int t = r0 + tid;
-                        const uint32_t key = score_key(cur[j]);
-                        const uint32_t dgt = key >> 21;
-                        const bool gt = t < T && dgt > b0, eq = t < T && dgt == b0;
-                        const uint64_t bg = __ballot(gt), be = __ballot(eq);
-                        if (lane == 0 && (r0 >> 6) + wave < n_words) cand[(r0 >> 6) + wave] = bg;
-                        if (be) {
-                            uint32_t at = 0;
-                            if (lane == 0) at = atomicAdd(&sh_list_n, (uint32_t)__popcll(be));
-                            at = __shfl(at, 0) + (uint32_t)__popcll(be & lane_lt);
-                            if (eq) {
-                                list_t[at] = (uint32_t)t;
-                                list_low[at] = key & 0x1FFFFFu;
-                            }
-                        }
-                    }
+                for (int e = 0; e < 4; ++e) {       // a key below the bin wraps round past its width
+                    const uint32_t low = q[e] - base;
+                    bin[e] = e < n_ok && low <= last ? low >> shift : SEL_BINS;
                 }
+                // equal scores share a bin, and adds to one address go one after the other
+                if (bin[0] == bin[1] && bin[0] == bin[2] && bin[0] == bin[3]) {
+                    if (bin[0] < SEL_BINS) atomicAdd(&L.hist[bin[0]], 4u);
+                } else {
 #pragma unroll
-                for (int j = 0; j < SEL_BATCH; ++j) cur[j] = nxt[j];
+                    for (int e = 0; e < 4; ++e)
+                        if (bin[e] < SEL_BINS) atomicAdd(&L.hist[bin[e]], 1u);
+                }
             }
             __syncthreads();
-            const int n_list = (int)sh_list_n;                   // == bin_count
-            // second and third digit (bits 20..10, 9..0) on the list
-            uint32_t lprefix = 0, lmask = 0;
-#pragma unroll 1
-            for (int p = 1; p < 3; ++p) {
-                const int shift = p == 1 ? 10 : 0;
-                const uint32_t dmask = p == 1 ? 2047u : 1023u;
-                for (int i = tid; i <= (int)dmask; i += SEL_THREADS) hist[i] = 0;
-                __syncthreads();
-                uint32_t run_d = 0, run_n = 0;
-                for (int i = tid; i < n_list; i += SEL_THREADS) {
-                    const uint32_t low = list_low[i];
-                    if ((low & lmask) == lprefix) run_add(hist, (low >> shift) & dmask, run_d, run_n);
-                }
-                if (run_n) atomicAdd(&hist[run_d], run_n);
-                __syncthreads();
-                pick_bin(hist, (int)dmask + 1, krem, wave_tot, sh);
-                lprefix |= sh[0] << shift;
-                lmask |= dmask << shift;
-                krem = sh[1];
-                bin_count = sh[2];
-            }
-            kth = prefix | lprefix;
-            // bin_count keys equal the threshold and krem of them are candidates
-            rank_ties = krem < bin_count;
-            if (!rank_ties) {
-                for (int i = tid; i < n_list; i += SEL_THREADS)
-                    if (list_low[i] >= lprefix) {
-                        const uint32_t t = list_t[i];
-                        atomicOr(reinterpret_cast<unsigned long long*>(&cand[t >> 6]), 1ULL << (t & 63));
-                    }
-                have_cand = true;
-            }
-        } else {
-            // general path: the other two digits from passes over all scores
-#pragma unroll 1
-            for (int p = 1; p < 3; ++p) {
-                const int shift = p == 1 ? 10 : 0;
-                const uint32_t dmask = p == 1 ? 2047u : 1023u;
-                hist_of_scores(score, T, prefix, mask, shift, dmask, hist);
-                pick_bin(hist, (int)dmask + 1, krem, wave_tot, sh);
-                prefix |= sh[0] << shift;
-                mask |= dmask << shift;
-                krem = sh[1];
-                bin_count = sh[2];
-            }
-            kth = prefix;
-            rank_ties = krem < bin_count;
+            pick_bin(L.hist, in_bin, krem, L.wave_tot, L.sh);
+            base += L.sh[0] << shift;
+            krem = L.sh[1];
+            in_bin = L.sh[2];
+            if (in_bin <= SEL_LIST || shift == 0 || krem == in_bin) break;
+            last = (1u << shift) - 1u;
+            shift = shift > 11 ? shift - 11 : 0;
+            L.hist[tid] = 0;
+            L.hist[tid + SEL_THREADS] = 0;
+            __syncthreads();
         }
     }
 
-    // ---- candidate bitmap, general path: word (r0 >> 6) + wave is written by wave `wave` ----
-    if (!have_cand) {
-        if (rank_ties) {
-            // threshold keys per word, exclusive scan over the words = rank of a word's first one
-            for (int base = 0; base < T; base += SEL_THREADS) {
-                const int t = base + tid;
-                const bool eq = t < T && score_key(score[t]) == kth;
-                const uint64_t be = __ballot(eq);
-                if (lane == 0 && (base >> 6) + wave < n_words) word_prefix[(base >> 6) + wave] = (uint32_t)__popcll(be);
-            }
-            __syncthreads();
-            (void)block_exclusive_scan(word_prefix, n_words, wave_tot);
+    // ---- candidates: the keys above the bin, those in it that are taken.  A thread has four bits of the bitmap,
+    //      two threads write a byte ----
+    const bool whole = krem == in_bin;              // all of the bin
+    const bool listed = !whole && in_bin <= SEL_LIST;
+#pragma unroll 1
+    for (int j = 0; j < n_rows; ++j) {
+        const u32x4 q = L.key[j][tid];
+        const int t = 4 * (j * SEL_THREADS + tid);
+        uint32_t gt = 0, eq = 0;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const uint32_t above = q[e] < base ? 0u : (q[e] - base) >> shift;
+            gt |= (uint32_t)(above > 0) << e;
+            eq |= (uint32_t)(q[e] >= base && above == 0) << e;
         }
-        for (int base = 0; base < T; base += SEL_THREADS * SEL_BATCH) {
-            float sv[SEL_BATCH];
-#pragma unroll
-            for (int j = 0; j < SEL_BATCH; ++j) {
-                const int t = base + j * SEL_THREADS + tid;
-                sv[j] = t < T ? score[t] : 0.0f;
-            }
-#pragma unroll
-            for (int j = 0; j < SEL_BATCH; ++j) {
-                const int r0 = base + j * SEL_THREADS;
-                if (r0 < T) {                                // workgroup-uniform
-                    const int t = r0 + tid;
-                    const int wi = (r0 >> 6) + wave;
-                    const uint32_t key = score_key(sv[j]);
-                    const bool eq = t < T && !all && !none && key == kth;
-                    bool take = t < T && (all || (!none && key > kth));
-                    if (rank_ties) {
-                        const uint64_t be = __ballot(eq);
-                        const uint32_t before = wi < n_words ? word_prefix[wi] : 0u;
-                        if (eq && before + (uint32_t)__popcll(be & lane_lt) < krem) take = true;
-                    } else if (eq) {
-                        take = true;
-                    }
-                    const uint64_t bc = __ballot(take);
-                    if (lane == 0 && wi < n_words) cand[wi] = bc;
-                }
+        const uint32_t ok = T - t >= 4 ? 15u : T - t <= 0 ? 0u : (1u << (T - t)) - 1u;
+        eq &= ok;
+        uint32_t bits = none ? 0u : all ? ok : (gt & ok) | (whole ? eq : 0u);
+        const uint32_t other = dpp<0xB1, 0xF>(0u, bits);         // quad permutation 1 0 3 2: the neighbour's
+        if (!(lane & 1)) reinterpret_cast<uint8_t*>(cand)[(j * SEL_THREADS + tid) >> 1] = (uint8_t)(bits | other << 4);
+        if (listed) {
+            for (; eq; eq &= eq - 1) {
+                const int e = __ffs((int)eq) - 1;
+                const uint32_t at = atomicAdd(&L.list_n, 1u);
+                L.list_t[at] = (uint32_t)(t + e);
+                L.list_key[at] = e == 0 ? q[0] : e == 1 ? q[1] : e == 2 ? q[2] : q[3];
             }
         }
     }
     __syncthreads();
+    if (listed) {
+        if (wave == 0) {                            // the list holds in_bin keys, one a lane
+            const uint32_t my_key = L.list_key[lane], my_t = L.list_t[lane];
+            uint32_t rank = 0;
+            for (int i = 0; i < (int)in_bin; ++i) {
+                const uint32_t key = lane_value(my_key, i), t = lane_value(my_t, i);
+                rank += key > my_key || (key == my_key && t < my_t);
+            }
+            if (lane < (int)in_bin && rank < krem)
+                atomicOr(reinterpret_cast<unsigned long long*>(&cand[my_t >> 6]), 1ULL << (my_t & 63));
+        }
+        __syncthreads();
+    } else if (!whole) {                            // equal keys: the first krem tokens
+        const uint32_t* keys = reinterpret_cast<const uint32_t*>(L.key);      // in token order
+        for (int i = wave; i < n_words; i += SEL_WAVES) {
+            const uint64_t be = __ballot(64 * i + lane < T && keys[64 * i + lane] == base);
+            if (lane == 0) L.word_n[i] = (uint32_t)__popcll(be);
+        }
+        __syncthreads();
+        (void)block_exclusive_scan(L.word_n, n_words, L.wave_tot);
+        for (int i = wave; i < n_words; i += SEL_WAVES) {
+            const uint64_t be = __ballot(64 * i + lane < T && keys[64 * i + lane] == base);
+            const uint32_t before = L.word_n[i] + (uint32_t)__popcll(be & ((1ULL << lane) - 1ULL));
+            const uint64_t take = __ballot((be >> lane & 1ULL) && before < krem);
+            if (lane == 0) cand[i] |= take;
+        }
+        __syncthreads();
+    }
 
     // ---- windows that start at a candidate and hold >= tau candidates; a token is chosen when
     //      some passing window covers it ----
     if (grouping && window <= 64) {
-        const uint64_t wmask = window == 64 ? ~0ULL : (1ULL << window) - 1ULL;
-        // a wave takes a word, lane = token: the window's tokens are bits lane .. lane + window - 1
-        // of the 128 bits (word i, word i + 1), fetched as two 32-bit funnel shifts
-        const uint32_t m0 = (uint32_t)wmask, m1 = (uint32_t)(wmask >> 32);
+        // a thread judges 16 starts: the count of the first one's window, then one token in and one out
         const uint32_t* c32 = reinterpret_cast<const uint32_t*>(cand);
-        for (int i = wave; i < n_words; i += SEL_WAVES) {
-            const uint32_t* wp = c32 + 2 * i + (lane >> 5);      // word n_words is zero padding
-            const uint32_t w0 = wp[0], w1 = wp[1], w2 = wp[2];
-            const uint32_t sh5 = lane & 31;
-            const uint32_t v0 = __builtin_amdgcn_alignbit(w1, w0, sh5), v1 = __builtin_amdgcn_alignbit(w2, w1, sh5);
-            const int cnt = __popc(v0 & m0) + __popc(v1 & m1);
-            const uint64_t b = __ballot((v0 & 1u) && cnt >= tau);
-            if (lane == 0) pass[i] = b;
+#pragma unroll 1
+        for (int g = tid; g < 4 * n_words; g += SEL_THREADS) {
+            const uint32_t a0 = c32[g >> 1], a1 = c32[(g >> 1) + 1], a2 = c32[(g >> 1) + 2];   // past the last word: zeros
+            const int off = 16 * (g & 1);
+            const uint64_t w = __builtin_amdgcn_alignbit(a1, a0, off) | (uint64_t)__builtin_amdgcn_alignbit(a2, a1, off) << 32;
+            const uint64_t next = a2 >> off;                                                   // tokens 64 .. of w
+            const uint32_t in = (uint32_t)(window == 64 ? next : w >> window | next << 1 << (63 - window));
+            int cnt = __popcll(window == 64 ? w : w & ((1ULL << window) - 1ULL));
+            uint32_t ok = 0;
+#pragma unroll
+            for (int s = 0; s < 16; ++s) {
+                ok |= (uint32_t)(cnt >= tau) << s;
+                cnt += (int)(in >> s & 1u) - (int)((uint32_t)w >> s & 1u);
+            }
+            reinterpret_cast<uint16_t*>(pass)[g] = (uint16_t)(ok & (uint32_t)w);
         }
         __syncthreads();
-        for (int i = tid; i < n_words; i += SEL_THREADS) {
+        if (tid < n_words) {
             // bits (lo, hi) = tokens 64(i-1) .. 64i+63; OR of the shifts by 0 .. window-1, by doubling
-            uint64_t lo = i ? pass[i - 1] : 0ULL, hi = pass[i];
+            uint64_t lo = tid ? pass[tid - 1] : 0ULL, hi = pass[tid];
             for (int covered = 1; covered < window;) {
                 const int st = min(covered, window - covered);  // 1 <= st <= 32
                 hi |= (hi << st) | (lo >> (64 - st));
                 lo |= lo << st;
                 covered += st;
             }
-            if (i == n_words - 1 && (T & 63)) hi &= (1ULL << (T & 63)) - 1ULL;   // windows are cut at T
-            marked[i] = hi;
+            if (tid == n_words - 1 && (T & 63)) hi &= (1ULL << (T & 63)) - 1ULL;   // windows are cut at T
+            marked[tid] = hi;
         }
     } else if (grouping) {
-        for (int base = 0; base < T; base += SEL_THREADS) {
-            int t = base + tid;
-            bool ok = false;
-            if (t < T && ((cand[t >> 6] >> (t & 63)) & 1ULL))
-                ok = window_popc(cand, t, t + window) >= tau;   // bits past T are zero
-            uint64_t b = __ballot(ok);
-            if (lane == 0 && (base >> 6) + wave < n_words) pass[(base >> 6) + wave] = b;
+        for (int i = wave; i < n_words; i += SEL_WAVES) {
+            const int t = 64 * i + lane;                        // bits past T are zero
+            const uint64_t b = __ballot((cand[i] >> lane & 1ULL) && window_popc(cand, t, t + window) >= tau);
+            if (lane == 0) pass[i] = b;
         }
         __syncthreads();
-        for (int base = 0; base < T; base += SEL_THREADS) {
-            int t = base + tid;
-            bool ok = false;
-            if (t < T) {
-                int b0 = t - window + 1;
-                ok = window_popc(pass, b0 < 0 ? 0 : b0, t + 1) > 0;
-            }
-            uint64_t b = __ballot(ok);
-            if (lane == 0 && (base >> 6) + wave < n_words) marked[(base >> 6) + wave] = b;
+        for (int i = wave; i < n_words; i += SEL_WAVES) {
+            const int t = 64 * i + lane;
+            const uint64_t b = __ballot(t < T && window_popc(pass, max(t - window + 1, 0), t + 1) > 0);
+            if (lane == 0) marked[i] = b;
         }
+        __syncthreads();
     }                                   // without grouping the candidates are the chosen tokens
-    __syncthreads();
 
-    // ---- exclusive scan of per-word popcounts ----
-    for (int i = tid; i < n_words; i += SEL_THREADS) word_prefix[i] = (uint32_t)__popcll(marked[i]);
+    // ---- place of every word's first token: scan of the popcounts of a wave's 64 words (a thread has the word that it
+    //      has just written), and the waves' totals ----
+    const uint32_t c = tid < n_words ? (uint32_t)__popcll(marked[tid]) : 0u;
+    const uint32_t inc = wave_scan_add(c);
+    if (tid < n_words) L.word_n[tid] = inc - c;
+    if (lane == 63) L.wave_tot[wave] = inc;
     __syncthreads();
-    const uint32_t n_sel = block_exclusive_scan(word_prefix, n_words, wave_tot);
+    const uint32_t wt = wave_scan_add(lane < SEL_WAVES ? L.wave_tot[lane] : 0u);
+    const uint32_t n_sel = lane_value(wt, SEL_WAVES - 1);
 
-    // ---- compaction: a thread writes the indices of a 16-token quarter of a word ----
-    for (int q = tid; q < 4 * n_words; q += SEL_THREADS) {
-        const uint64_t word = marked[q >> 2];
-        const int sb = 16 * (q & 3);
-        uint32_t sub = (uint32_t)(word >> sb) & 0xFFFFu;
-        uint32_t pos = word_prefix[q >> 2] + (uint32_t)__popcll(word & ((1ULL << sb) - 1ULL));
-        const int t0 = idx_offset + 64 * (q >> 2) + sb;
-        while (sub) {
-            const int b = __ffs((int)sub) - 1;
-            sub &= sub - 1;
-            idx_out[pos++] = t0 + b;
-        }
+    // ---- compaction: a wave writes the indices of its words ----
+#pragma unroll 1
+    for (int i = wave; i < n_words; i += SEL_WAVES) {
+        const uint64_t word = marked[i];
+        const uint32_t at = L.word_n[i] + (i >= 64 ? lane_value(wt, (i >> 6) - 1) : 0u);
+        if (word >> lane & 1ULL)
+            idx_out[at + __builtin_amdgcn_mbcnt_hi((uint32_t)(word >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)word, 0u))] =
+                idx_offset + 64 * i + lane;
     }
     for (int j = tid; j < n_tail; j += SEL_THREADS) idx_out[n_sel + j] = idx_offset + T + j;
-    if (tid == 0) *n_out = (int32_t)n_sel + n_tail;
+    if (tid == 0) {
+        *n_out = (int32_t)n_sel + n_tail;
+        if (n_host) *n_host = (int32_t)n_sel + n_tail;
+    }
 }
 
 // ----------------------------------------------------------------------------
@@ -637,8 +572,8 @@ __global__ __launch_bounds__(SEL_THREADS) void select_kernel(
 // keys, a bin to a sixteenth of an octave; scores within an octave then crowd into it, and scores that
 // mostly agree always do.  With more than SELM_LIST keys every mark workgroup takes the digits below the bin, and
 // the equal keys before its tile, from all scores instead of the list.
-// Against one workgroup (sum of the launches, k = T / 5, window 16): T = 65536: 51 -> 23 us, 131072: 94 -> 24;
-// what is left are four launches' latencies and, per launch, three or four loads that wait for one another.
+// Against one workgroup of the radix search (sum of the launches, k = T / 5, window 16): T = 65536: 51 -> 23 us, 131072:
+// 94 -> 24, and 21.8 at 65536 with scans in the vector ALU; what is left are four launches' latencies and, per launch, three or four loads that wait for one another.
 // Crowded, one workgroup / that in the mark launch / now: T = 65536, a zero beside scores within an octave
 // 82 / 96 / 48, all equal 88 / 103 / 32, five values 90 / 104 / 50;  T = 131072: 122 / 136 / 61, 167 / 183 / 39, 171 / 185 / 71.
 // ----------------------------------------------------------------------------
@@ -708,7 +643,8 @@ __global__ __launch_bounds__(SEL_THREADS) void select_cand_kernel(const float* _
                                                                   const uint2* __restrict__ range, int n_range,
                                                                   cc_sel_ws ws) {
     constexpr int KPT = SELM_TILE / SEL_THREADS;
-    __shared__ uint32_t hist[SEL_BINS], mn[SEL_WAVES], mx[SEL_WAVES], wave_tot[SEL_WAVES], sh[3], eq_n[SELM_WORDS];
+    __shared__ __align__(16) uint32_t hist[SEL_BINS];
+    __shared__ uint32_t mn[SEL_WAVES], mx[SEL_WAVES], wave_tot[SEL_WAVES], sh[3], eq_n[SELM_WORDS];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, G = gridDim.x;
     const uint64_t lane_lt = (1ULL << lane) - 1ULL;
     const int n_words = (T + 63) >> 6;
@@ -730,7 +666,7 @@ __global__ __launch_bounds__(SEL_THREADS) void select_cand_kernel(const float* _
     hist[2 * tid + 1] = h1;
     if (tid < 3) sh[tid] = 0;
     const SelRange r = key_range_of(range, n_range, mn, mx);
-    if (!all && !none) pick_bin(hist, SEL_BINS, (uint32_t)k, wave_tot, sh);
+    if (!all && !none) pick_bin(hist, (uint32_t)T, (uint32_t)k, wave_tot, sh);
     const uint32_t b0 = sh[0];
     uint64_t be[KPT];
 #pragma unroll
@@ -820,7 +756,7 @@ __device__ __forceinline__ void mark_crowded(SelMarkLds& L, const float* __restr
         });
         if (run_n) atomicAdd(&L.hist[run_d], run_n);
         __syncthreads();
-        pick_bin(L.hist, SEL_BINS, krem, L.wave_tot, L.sh);
+        pick_bin(L.hist, ties, krem, L.wave_tot, L.sh);
         kth |= L.sh[0] << lo;
         mask |= dmask << lo;
         krem = L.sh[1];
@@ -910,7 +846,7 @@ __global__ __launch_bounds__(SEL_THREADS) void select_mark_kernel(
                 for (int i = tid; i < n_list; i += SEL_THREADS)
                     if ((L.low[i] & mask) == kth) atomicAdd(&L.hist[(L.low[i] >> lo) & dmask], 1u);
                 __syncthreads();
-                pick_bin(L.hist, SEL_BINS, krem, L.wave_tot, L.sh);
+                pick_bin(L.hist, ties, krem, L.wave_tot, L.sh);
                 kth |= L.sh[0] << lo;
                 mask |= dmask << lo;
                 krem = L.sh[1];
@@ -986,7 +922,8 @@ __global__ __launch_bounds__(SEL_THREADS) void select_mark_kernel(
 }
 
 __global__ __launch_bounds__(256) void select_write_kernel(int T, int idx_offset, int n_tail, int32_t* __restrict__ idx_out,
-                                                           int32_t* __restrict__ n_out, cc_sel_ws ws) {
+                                                           int32_t* __restrict__ n_out, int32_t* __restrict__ n_host,
+                                                           cc_sel_ws ws) {
     __shared__ uint64_t words[SELM_WORDS];
     __shared__ uint32_t first[SELM_WORDS];
     const int tid = threadIdx.x, lane = tid & 63, G = gridDim.x;
@@ -1023,22 +960,25 @@ __global__ __launch_bounds__(256) void select_write_kernel(int T, int idx_offset
         idx_out[pos++] = t0 + b;
     }
     for (int j = blockIdx.x * 256 + tid; j < n_tail; j += G * 256) idx_out[n_sel + j] = idx_offset + T + j;
-    if (blockIdx.x == 0 && tid == 0) *n_out = (int32_t)n_sel + n_tail;
+    if (blockIdx.x == 0 && tid == 0) {
+        *n_out = (int32_t)n_sel + n_tail;
+        if (n_host) *n_host = (int32_t)n_sel + n_tail;
+    }
 }
 
 void cc_launch_select(const float* score, int T, int k, int window, int tau, int grouping,
-                      int idx_offset, int n_tail, int32_t* idx_out, int32_t* n_out, const uint2* key_range,
+                      int idx_offset, int n_tail, int32_t* idx_out, int32_t* n_out, int32_t* n_host, const uint2* key_range,
                       int n_range, cc_sel_ws ws, hipStream_t s) {
     if (!cc_select_uses_ranges(T)) {
         hipLaunchKernelGGL(select_kernel, dim3(1), dim3(SEL_THREADS), 0, s, score, T, k, window, tau,
-                           grouping, idx_offset, n_tail, idx_out, n_out);
+                           grouping, idx_offset, n_tail, idx_out, n_out, n_host);
         return;
     }
     const dim3 grid((T + SELM_TILE - 1) / SELM_TILE), block(SEL_THREADS);
     hipLaunchKernelGGL(select_hist_kernel, grid, block, 0, s, score, T, key_range, n_range, ws);
     hipLaunchKernelGGL(select_cand_kernel, grid, block, 0, s, score, T, k, key_range, n_range, ws);
     hipLaunchKernelGGL(select_mark_kernel, grid, block, 0, s, score, T, window, tau, grouping, ws);
-    hipLaunchKernelGGL(select_write_kernel, grid, dim3(256), 0, s, T, idx_offset, n_tail, idx_out, n_out, ws);
+    hipLaunchKernelGGL(select_write_kernel, grid, dim3(256), 0, s, T, idx_offset, n_tail, idx_out, n_out, n_host, ws);
 }
 
 // ----------------------------------------------------------------------------

@@ -349,3 +349,30 @@ def test_crowded_selection_is_shared_by_the_workgroups(ctx):
         us[kind] = best
     print({k: round(v, 1) for k, v in us.items()})
     assert max(us.values()) < 3 * us["ordinary"], us
+
+
+@pytest.mark.parametrize("window", [1, 16, 64, 65])
+@pytest.mark.parametrize("T", [1, 17, 64, 4095, 4097, 8192, 20480])
+def test_one_workgroup_selection_edges(ctx, T, window):
+    """Rows of 4096 keys that end anywhere, thresholds inside 64 and 65 equal scores (the most that are ranked in a
+    list, and one more) and inside all of them, scores whose range makes the first bins one key wide or crowds them, no
+    and all tokens; the count on the device is the one handed back."""
+    rng = np.random.default_rng(T + window)
+    spread = rng.random((1, T), dtype=np.float32)
+    cases = [spread, np.full((1, T), 0.25, np.float32), (1.0 + spread * 2.0 ** -13).astype(np.float32)]
+    for n in (64, 65):
+        a = spread.copy()
+        at = rng.permutation(T)[:n]
+        a[0, at] = np.float32(0.75)
+        cases.append(a)
+    far = 1.0 + spread
+    far[0, T // 2] = 0.0
+    cases.append(far)
+    for a in cases:
+        for bp in (0, 700, 2500, 10000):
+            At = torch.from_numpy(a).to(DEV)
+            n_dev = torch.full((1,), -1, dtype=torch.int32, device=DEV)
+            idx, n = ctx.select(At, bp, window, 0, 0, 5, 3, n_out=n_dev)
+            ref = osel.select(a, bp, window, 0, True, 5, 3)
+            assert n == len(ref) == int(n_dev.item())
+            assert np.array_equal(idx[:n].cpu().numpy(), ref)
