@@ -6,6 +6,7 @@ from __future__ import annotations
 
 import ctypes as C
 import os
+from array import array
 from dataclasses import dataclass
 from typing import Optional, Sequence, Tuple
 
@@ -224,19 +225,22 @@ class Context:
     @staticmethod
     def _aux_blocks(blocks):
         """blocks: sequence of (attn cuda fp32 [H, Q_a, W], col0, len)."""
-        arr = (_AuxBlock * len(blocks))()
-        H = Q_a = None
-        for i, (a, col0, ln) in enumerate(blocks):
-            if a.dim() != 3 or a.stride(2) != 1:
+        first = None
+        flat = []                               # an _AuxBlock is an address, two strides and two 32-bit halves
+        for a, col0, ln in blocks:
+            shape, st = a.shape, a.stride()
+            if len(shape) != 3 or st[2] != 1:
                 raise ValueError("a block must be [H, Q_a, W] with unit column stride")
-            if H is None:
-                H, Q_a = a.shape[0], a.shape[1]
-            elif (a.shape[0], a.shape[1]) != (H, Q_a):
+            if first is None:
+                first = shape
+            elif shape[0] != first[0] or shape[1] != first[1]:
                 raise ValueError("all blocks must have the same H and Q_a")
-            if col0 + ln > a.shape[2]:
+            if col0 + ln > shape[2]:
                 raise ValueError("col0 + len exceeds the block's width")
-            arr[i] = _AuxBlock(a.data_ptr(), a.stride(0), a.stride(1), col0, ln)
-        return arr, H, Q_a
+            flat += (a.data_ptr(), st[0], st[1], col0 & 0xFFFFFFFF | (ln & 0xFFFFFFFF) << 32)
+        if first is None:
+            return (_AuxBlock * 0)(), None, None
+        return (_AuxBlock * (len(flat) // 4)).from_buffer(array("Q", flat)), first[0], first[1]
 
     def step_block_scores(self, blocks, score):
         arr, H, Q_a = self._aux_blocks(blocks)
@@ -248,12 +252,10 @@ class Context:
         """blocks: sequence of (attn cuda fp32 [H, Q_a, W], col0, len).  Returns (idx_out, count or None)."""
         import torch
         arr, H, Q_a = self._aux_blocks(blocks)
-        T = sum(b[2] for b in blocks)
-        dev = blocks[0][0].device
         if idx_out is None:
-            idx_out = torch.empty(T + n_tail, dtype=torch.int32, device=dev)
+            idx_out = torch.empty(sum(b[2] for b in blocks) + n_tail, dtype=torch.int32, device=blocks[0][0].device)
         if n_out is None:
-            n_out = torch.empty(1, dtype=torch.int32, device=dev)
+            n_out = torch.empty(1, dtype=torch.int32, device=blocks[0][0].device)
         host = C.c_int32(-1)
         self._check(self._lib.cc_select_blocks(self._h, arr, len(blocks), H, Q_a, recomp_bp, window, tau,
                                                flags, idx_offset, n_tail, idx_out.data_ptr(),
@@ -305,7 +307,7 @@ class Context:
             shape = K.shape
             assert shape == V.shape and K.stride() == st and V.stride() == st
             flat += (K.data_ptr(), V.data_ptr(), (shape[0] - P) & 0xFFFFFFFF)
-        arr = (_Chunk * n).from_buffer((C.c_uint64 * (3 * n))(*flat))
+        arr = (_Chunk * n).from_buffer(array("Q", flat))
         kvs = dst.c_struct()
         self._check(self._lib.cc_assemble_cache(self._h, arr, n, P, st[0], st[1], n_tail, C.byref(kvs)))
 
