@@ -213,8 +213,15 @@ struct EpiDown {
     }
 };
 
-// Split-K: workgroup row blockIdx.y of a launch computes the products over its share of K and
-// leaves its fp32 tile in a workspace [share][tile slot][ROWS][BN] (slot = the tile's index
+// Split-K: workgroup row blockIdx.y computes the products over its share of K: `K` columns, the first
+// k_more rows one unit of UNIT columns more.  Returns the share's columns.
+template <int UNIT>
+__device__ __forceinline__ int k_share(int K, int k_more, int64_t* first_byte) {
+    const int y = blockIdx.y;
+    *first_byte = ((int64_t)y * K + min(y, k_more) * UNIT) * 2;
+    return K + (y < k_more ? UNIT : 0);
+}
+// It leaves its fp32 tile in a workspace [share][tile slot][ROWS][BN] (slot = the tile's index
 // within the launch); splitk_finish_kernel adds the shares and applies the launch's own
 // epilogue functor.
 template <int ROWS>
@@ -604,7 +611,7 @@ static_assert(BKS * NS == CC_GEMM_GROUP, "a group is one ring of slices");
 
 template <int BM, int BN, int WAVES_M, int WAVES_N, class BSrc, class Epi>
 __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gemm_ring_kernel(
-    const bf16_t* __restrict__ A, int lda, int M, int K, int tiles_m, int tiles_n, int GM, int nb, int vb0,
+    const bf16_t* __restrict__ A, int lda, int M, int K, int k_more, int tiles_m, int tiles_n, int GM, int nb, int vb0,
     BSrc bsrc, Epi epi) {
     constexpr int NW = WAVES_M * WAVES_N;
     constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N;
@@ -671,8 +678,8 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gemm_ring_kernel(
         r = r < left ? r : left - 1;
         bo[i] = (uint32_t)((r * bsrc.ldb + c * 8) * 2);
     }
-    // K is this launch's share per workgroup row: row blockIdx.y starts blockIdx.y * K columns in
-    const int64_t kz = (int64_t)blockIdx.y * K * 2;
+    int64_t kz;                        // this workgroup row's share of K
+    K = k_share<BKS * NS>(K, k_more, &kz);
     const char* abase = reinterpret_cast<const char*>(A + (int64_t)m0 * lda) + kz;
     const char* bbase = reinterpret_cast<const char*>(bsrc.template base<BN>(bn, hi_half ? 1 : 0)) + kz;
     const int wbase = wave_u * DPS * 16 * BKS;
@@ -804,7 +811,7 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gemm_ring_kernel(
 // The same ring with 16x16x32 MFMAs and hand-written fragment reads.
 template <int BM, int BN, int WAVES_M, int WAVES_N, class BSrc, class Epi>
 __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gemm_ring16_kernel(
-    const bf16_t* __restrict__ A, int lda, int M, int K, int tiles_m, int tiles_n, int GM, int nb, int vb0,
+    const bf16_t* __restrict__ A, int lda, int M, int K, int k_more, int tiles_m, int tiles_n, int GM, int nb, int vb0,
     BSrc bsrc, Epi epi) {
     constexpr int NW = WAVES_M * WAVES_N;
     constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N;
@@ -872,8 +879,8 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gemm_ring16_kernel(
         r = r < left ? r : left - 1;
         bo[i] = (uint32_t)((r * bsrc.ldb + c * 8) * 2);
     }
-    // K is this launch's share per workgroup row: row blockIdx.y starts blockIdx.y * K columns in
-    const int64_t kz = (int64_t)blockIdx.y * K * 2;
+    int64_t kz;                        // this workgroup row's share of K
+    K = k_share<BKS * NS>(K, k_more, &kz);
     const char* abase = reinterpret_cast<const char*>(A + (int64_t)m0 * lda) + kz;
     const char* bbase = reinterpret_cast<const char*>(bsrc.template base<BN>(bn, hi_half ? 1 : 0)) + kz;
     const int wbase = wave_u * DPS * 16 * BKS;
@@ -1135,7 +1142,7 @@ __device__ __forceinline__ bf16x8 lds_read16(uint32_t addr) {
 // and issuing the loads before the reads: each within 1 %.
 template <class BSrc, class Epi>
 __global__ __launch_bounds__(512, 2) void gemm_pingpong_kernel(
-    const bf16_t* __restrict__ A, int lda, int M, int K, int tiles_m, int tiles_n, int GM, int nb, int vb0,
+    const bf16_t* __restrict__ A, int lda, int M, int K, int k_more, int tiles_m, int tiles_n, int GM, int nb, int vb0,
     BSrc bsrc, Epi epi) {
     constexpr int H = 128, BM = 2 * H, BN = 2 * H;
     constexpr int UM = 4, UN = 2;                      // 16x16 accumulator tiles of a wave in one quadrant
@@ -1151,7 +1158,8 @@ __global__ __launch_bounds__(512, 2) void gemm_pingpong_kernel(
     int bm, bn;
     const int vb = tile_of_block(blockIdx.x, nb, vb0, tiles_m, tiles_n, GM, &bm, &bn);
     const int m0 = bm * BM;
-    const int64_t kz = (int64_t)blockIdx.y * K * 2;    // K is this launch's share per workgroup row
+    int64_t kz;                                        // this workgroup row's share of K
+    K = k_share<CC_GEMM_GROUP>(K, k_more, &kz);
 
     // ---- global -> LDS: a wave moves rows 16 wave .. 16 wave + 15 of every half, 8 per load; lane L
     //      fills slot L%8 of row L/8.  Wave-uniform bases advance along K in scalar registers. ----
@@ -1353,7 +1361,7 @@ __global__ __launch_bounds__(512, 2) void gemm_pingpong_kernel(
 // K = 256 (432 tiles of 128x128, two on a CU in the ring loop) 14.5 -> 19, where the ring loop stays.
 template <int BM, class BSrc, class Epi>
 __global__ __launch_bounds__(512, 2) void gemm_duo_kernel(
-    const bf16_t* __restrict__ A, int lda, int M, int K, int tiles_m, int tiles_n, int GM, int nb,
+    const bf16_t* __restrict__ A, int lda, int M, int K, int k_more, int tiles_m, int tiles_n, int GM, int nb, int vb0,
     BSrc bsrc, Epi epi) {
     constexpr int BN = 128, KG = 256 / BM;             // waves of 64x64; groups along K
     static_assert(BM == 128 || BM == 256, "eight waves");
@@ -1368,8 +1376,10 @@ __global__ __launch_bounds__(512, 2) void gemm_duo_kernel(
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int grp = wave >> 2, w = wave & 3;
     int bm, bn;
-    (void)tile_of_block(blockIdx.x, nb, 0, tiles_m, tiles_n, GM, &bm, &bn);
+    const int vb = tile_of_block(blockIdx.x, nb, vb0, tiles_m, tiles_n, GM, &bm, &bn);
     const int m0 = bm * BM;
+    int64_t kz;                                        // this workgroup row's share of K
+    K = k_share<CC_GEMM_GROUP>(K, k_more, &kz);
     const int ar = AR == 2 ? grp : 0;                  // this group's region of A
 
     // ---- global -> LDS: wave w of a group moves rows 32 w .. of the group's A region and rows 32 w .. of B (of a
@@ -1389,8 +1399,8 @@ __global__ __launch_bounds__(512, 2) void gemm_duo_kernel(
         const int r = rb0 + i * 8 + (lane >> 3);
         bo[i] = (uint32_t)((min(r - bh * (BN / 2), left - 1) * bsrc.ldb + ((lane & 7) ^ ((r >> 1) & 7)) * 8) * 2);
     }
-    const char* const abase = reinterpret_cast<const char*>(A + (int64_t)m0 * lda);
-    const char* const bbase = reinterpret_cast<const char*>(bsrc.template base<BN>(bn, bh));
+    const char* const abase = reinterpret_cast<const char*>(A + (int64_t)m0 * lda) + kz;
+    const char* const bbase = reinterpret_cast<const char*>(bsrc.template base<BN>(bn, bh)) + kz;
     auto scalar_ptr = [](const char* p) -> const char* {   // keeps the base in scalar registers
         const uint64_t u = reinterpret_cast<uint64_t>(p);
         const uint64_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)u);
@@ -1514,12 +1524,13 @@ __global__ __launch_bounds__(512, 2) void gemm_duo_kernel(
         __syncthreads();
     }
     constexpr int TPR = BN / 8, RPP = 512 / TPR;       // threads per row, rows per pass
+    const auto e2 = epi_for_tile(epi, vb - vb0, m0);
     const int cc = (tid % TPR) * 8;
 #pragma unroll
     for (int k = 0; k < BM / RPP; ++k) {
         const int r = tid / TPR + k * RPP;
         const int m = m0 + r;
-        if (m < M) epi.template operator()<BN>(m, bn, cc, stage + r * BN, ((r >> 2) & 3) << 4);
+        if (m < M) e2.template operator()<BN>(m, bn, cc, stage + r * BN, ((r >> 2) & 3) << 4);
     }
 }
 
@@ -1546,7 +1557,7 @@ __global__ __launch_bounds__(512, 2) void gemm_duo_kernel(
 // slower by a fifth at 64 rows.
 constexpr int THIN_M = CC_THIN_M, THIN_N = CC_THIN_N, THIN_SLOTS = 6;
 template <class BSrc, class Epi>
-__global__ __launch_bounds__(256, 1) void gemm_thin_kernel(const bf16_t* __restrict__ A, int lda, int M, int K,
+__global__ __launch_bounds__(256, 1) void gemm_thin_kernel(const bf16_t* __restrict__ A, int lda, int M, int K, int k_more,
                                                            int tiles_m, int tiles_n, int GM, int nb,
                                                            BSrc bsrc, Epi epi) {
     constexpr int BM = THIN_M, BN = THIN_N, D = THIN_SLOTS, ROWB = 128;
@@ -1560,7 +1571,8 @@ __global__ __launch_bounds__(256, 1) void gemm_thin_kernel(const bf16_t* __restr
     int bm, bn;
     const int vb = tile_of_block(blockIdx.x, nb, 0, tiles_m, tiles_n, GM, &bm, &bn);
     const int m0 = bm * BM;
-    const int64_t kz = (int64_t)blockIdx.y * K * 2;    // K is this launch's share per workgroup row
+    int64_t kz;                                        // this workgroup row's share of K
+    K = k_share<64>(K, k_more, &kz);
 
     // ---- global -> LDS: wave w moves rows 16w .. of A and 32w .. of B; lane L fills slot L%8 of row L/8 ----
     uint32_t ao[A_L], bo[B_L];
@@ -1712,19 +1724,19 @@ void launch_gemm(const bf16_t* A, int lda, int M, int N_tiles_cols, int K, int l
     const cc_gemm_plan plan = cc_plan_gemm(n_cu, M, N_tiles_cols, K, lda, ldb, ws != nullptr, ws_floats, ovr);
     const char pick = plan.tile;
     const bool ring = plan.ring, mfma16 = !ovr.gemm_mfma32;
-    const int S = plan.shares;
+    const int S = std::max(plan.shares, plan.cuts);
     if (pick == 't') {
         const int tiles_m = (M + THIN_M - 1) / THIN_M, tiles_n = (N_tiles_cols + THIN_N - 1) / THIN_N;
         const int GM = std::min(ovr.gemm_gm > 0 ? ovr.gemm_gm : 4, tiles_m);
         const int nt = tiles_m * tiles_n;
         if (S == 1) {
-            hipLaunchKernelGGL((gemm_thin_kernel<BSrc, Epi>), dim3(nt), dim3(256), 0, s, A, lda, M, K, tiles_m, tiles_n,
+            hipLaunchKernelGGL((gemm_thin_kernel<BSrc, Epi>), dim3(nt), dim3(256), 0, s, A, lda, M, K, 0, tiles_m, tiles_n,
                                GM, nt, bsrc, epi);
         } else {
             constexpr int SLOT = THIN_M * THIN_N;
             EpiPartial<THIN_M> pe{ws, (int64_t)nt * SLOT, 0, 0};
             hipLaunchKernelGGL((gemm_thin_kernel<BSrc, EpiPartial<THIN_M>>), dim3(nt, S), dim3(256), 0, s, A, lda, M,
-                               K / S, tiles_m, tiles_n, GM, nt, bsrc, pe);
+                               K / 64 / S * 64, K / 64 % S, tiles_m, tiles_n, GM, nt, bsrc, pe);
             hipLaunchKernelGGL((splitk_finish_kernel<THIN_M, THIN_N, Epi>), dim3(nt, THIN_M * THIN_N / 2048), dim3(256), 0, s,
                                ws, (int64_t)nt * SLOT, S, M, THIN_M, 0, tiles_m, tiles_n, GM, epi);
         }
@@ -1735,52 +1747,59 @@ void launch_gemm(const bf16_t* A, int lda, int M, int N_tiles_cols, int K, int l
     int GM = pick == 's' ? 2 * gm_big : gm_big;
     if (ovr.gemm_gm > 0) GM = ovr.gemm_gm;
     GM = GM < 1 ? 1 : (GM > tiles_m ? tiles_m : GM);
-    const int n_tiles = tiles_m * tiles_n;
-#define CC_LAUNCH(KERN, BM_, BN_, WM_, WN_, EPI_T, EPI_V, K_, NB_, VB0_, GY_)                              \
+    const int n_tiles = tiles_m * tiles_n, groups = K / CC_GEMM_GROUP;     // groups: where the ring loops apply, all of K
+#define CC_LAUNCH(KERN, BM_, BN_, WM_, WN_, EPI_T, EPI_V, NB_, VB0_, GY_)                              \
     hipLaunchKernelGGL((KERN<BM_, BN_, WM_, WN_, BSrc, EPI_T>), dim3(NB_, GY_), dim3(WM_ * WN_ * 64), 0, s, A, \
-                       lda, M, K_, tiles_m, tiles_n, GM, NB_, VB0_, bsrc, EPI_V)
-#define CC_LAUNCH_PP(EPI_T, EPI_V, K_, NB_, VB0_, GY_)                                                      \
-    hipLaunchKernelGGL((gemm_pingpong_kernel<BSrc, EPI_T>), dim3(NB_, GY_), dim3(512), 0, s, A, lda, M, K_,    \
-                       tiles_m, tiles_n, GM, NB_, VB0_, bsrc, EPI_V)
-#define CC_LAUNCH_DUO(BM_)                                                                                  \
-    hipLaunchKernelGGL((gemm_duo_kernel<BM_, BSrc, Epi>), dim3(n_tiles), dim3(512), 0, s, A, lda, M, K,   \
-                       tiles_m, tiles_n, GM, n_tiles, bsrc, epi)
+                       lda, M, groups / (GY_) * CC_GEMM_GROUP, groups % (GY_), tiles_m, tiles_n, GM, NB_, VB0_, bsrc, EPI_V)
+#define CC_LAUNCH_PP(EPI_T, EPI_V, NB_, VB0_, GY_)                                                      \
+    hipLaunchKernelGGL((gemm_pingpong_kernel<BSrc, EPI_T>), dim3(NB_, GY_), dim3(512), 0, s, A, lda, M,    \
+                       groups / (GY_) * CC_GEMM_GROUP, groups % (GY_), tiles_m, tiles_n, GM, NB_, VB0_, bsrc, EPI_V)
+#define CC_LAUNCH_DUO(BM_, EPI_T, EPI_V, NB_, VB0_, GY_)                                                    \
+    hipLaunchKernelGGL((gemm_duo_kernel<BM_, BSrc, EPI_T>), dim3(NB_, GY_), dim3(512), 0, s, A, lda, M,  \
+                       groups / (GY_) * CC_GEMM_GROUP, groups % (GY_), tiles_m, tiles_n, GM, NB_, VB0_, bsrc, EPI_V)
 #define CC_LAUNCH_NT(BM_, BN_, WM_, WN_)                                                                    \
     hipLaunchKernelGGL((gemm_nt_kernel<BM_, BN_, WM_, WN_, BSrc, Epi>), dim3(n_tiles), dim3(WM_ * WN_ * 64), 0, \
                        s, A, lda, M, K, tiles_m, tiles_n, GM, bsrc, epi)
-    if (S > 1) {
+    if (S > 1 && pick == 'h') {
+        const int rem = n_tiles % n_cu == 0 ? n_cu : n_tiles % n_cu, full = n_tiles - rem;
+        EpiPartial<256> pe{ws, (int64_t)rem * 32768, 0, 0};
+        if (full) CC_LAUNCH_DUO(256, Epi, epi, full, 0, 1);
+        CC_LAUNCH_DUO(256, EpiPartial<256>, pe, rem, full, S);
+        hipLaunchKernelGGL((splitk_finish_kernel<256, 128, Epi>), dim3(rem, 16), dim3(256), 0, s, ws, (int64_t)rem * 32768, S,
+                           M, bm, full, tiles_m, tiles_n, GM, epi);
+    } else if (S > 1) {
         const int rem = n_tiles % n_cu == 0 ? n_cu : n_tiles % n_cu, full = n_tiles - rem;
         EpiPartial<256> pe{ws, (int64_t)rem * 65536, 0, 0};
         if (pick == 'b' && mfma16) {
-            if (full) CC_LAUNCH_PP(Epi, epi, K, full, 0, 1);
-            CC_LAUNCH_PP(EpiPartial<256>, pe, K / S, rem, full, S);
+            if (full) CC_LAUNCH_PP(Epi, epi, full, 0, 1);
+            CC_LAUNCH_PP(EpiPartial<256>, pe, rem, full, S);
         } else if (pick == 'b') {
-            if (full) CC_LAUNCH(gemm_ring_kernel, 256, 256, 2, 4, Epi, epi, K, full, 0, 1);
-            CC_LAUNCH(gemm_ring_kernel, 256, 256, 2, 4, EpiPartial<256>, pe, K / S, rem, full, S);
+            if (full) CC_LAUNCH(gemm_ring_kernel, 256, 256, 2, 4, Epi, epi, full, 0, 1);
+            CC_LAUNCH(gemm_ring_kernel, 256, 256, 2, 4, EpiPartial<256>, pe, rem, full, S);
         } else if (mfma16) {
-            if (full) CC_LAUNCH(gemm_ring16_kernel, 192, 256, 2, 4, Epi, epi, K, full, 0, 1);
-            CC_LAUNCH(gemm_ring16_kernel, 192, 256, 2, 4, EpiPartial<256>, pe, K / S, rem, full, S);
+            if (full) CC_LAUNCH(gemm_ring16_kernel, 192, 256, 2, 4, Epi, epi, full, 0, 1);
+            CC_LAUNCH(gemm_ring16_kernel, 192, 256, 2, 4, EpiPartial<256>, pe, rem, full, S);
         } else {
-            if (full) CC_LAUNCH(gemm_ring_kernel, 192, 256, 2, 4, Epi, epi, K, full, 0, 1);
-            CC_LAUNCH(gemm_ring_kernel, 192, 256, 2, 4, EpiPartial<256>, pe, K / S, rem, full, S);
+            if (full) CC_LAUNCH(gemm_ring_kernel, 192, 256, 2, 4, Epi, epi, full, 0, 1);
+            CC_LAUNCH(gemm_ring_kernel, 192, 256, 2, 4, EpiPartial<256>, pe, rem, full, S);
         }
         hipLaunchKernelGGL((splitk_finish_kernel<256, 256, Epi>), dim3(rem, (bm + 7) / 8), dim3(256), 0, s, ws,
                            (int64_t)rem * 65536, S, M, bm, full, tiles_m, tiles_n, GM, epi);
     } else if (pick == 'b') {
-        if (ring && mfma16) CC_LAUNCH_PP(Epi, epi, K, n_tiles, 0, 1);
-        else if (ring) CC_LAUNCH(gemm_ring_kernel, 256, 256, 2, 4, Epi, epi, K, n_tiles, 0, 1);
+        if (ring && mfma16) CC_LAUNCH_PP(Epi, epi, n_tiles, 0, 1);
+        else if (ring) CC_LAUNCH(gemm_ring_kernel, 256, 256, 2, 4, Epi, epi, n_tiles, 0, 1);
         else CC_LAUNCH_NT(256, 256, 2, 4);
     } else if (pick == 'm') {
-        if (mfma16) CC_LAUNCH(gemm_ring16_kernel, 192, 256, 2, 4, Epi, epi, K, n_tiles, 0, 1);
-        else CC_LAUNCH(gemm_ring_kernel, 192, 256, 2, 4, Epi, epi, K, n_tiles, 0, 1);
+        if (mfma16) CC_LAUNCH(gemm_ring16_kernel, 192, 256, 2, 4, Epi, epi, n_tiles, 0, 1);
+        else CC_LAUNCH(gemm_ring_kernel, 192, 256, 2, 4, Epi, epi, n_tiles, 0, 1);
     } else if (pick == 'h') {
-        if (mfma16 && plan.duo) CC_LAUNCH_DUO(256);
-        else if (mfma16) CC_LAUNCH(gemm_ring16_kernel, 256, 128, 4, 2, Epi, epi, K, n_tiles, 0, 1);
-        else CC_LAUNCH(gemm_ring_kernel, 256, 128, 4, 2, Epi, epi, K, n_tiles, 0, 1);
+        if (mfma16 && plan.duo) CC_LAUNCH_DUO(256, Epi, epi, n_tiles, 0, 1);
+        else if (mfma16) CC_LAUNCH(gemm_ring16_kernel, 256, 128, 4, 2, Epi, epi, n_tiles, 0, 1);
+        else CC_LAUNCH(gemm_ring_kernel, 256, 128, 4, 2, Epi, epi, n_tiles, 0, 1);
     } else {
-        if (mfma16 && plan.duo) CC_LAUNCH_DUO(128);
-        else if (ring && mfma16) CC_LAUNCH(gemm_ring16_kernel, 128, 128, 2, 2, Epi, epi, K, n_tiles, 0, 1);
-        else if (ring) CC_LAUNCH(gemm_ring_kernel, 128, 128, 2, 2, Epi, epi, K, n_tiles, 0, 1);
+        if (mfma16 && plan.duo) CC_LAUNCH_DUO(128, Epi, epi, n_tiles, 0, 1);
+        else if (ring && mfma16) CC_LAUNCH(gemm_ring16_kernel, 128, 128, 2, 2, Epi, epi, n_tiles, 0, 1);
+        else if (ring) CC_LAUNCH(gemm_ring_kernel, 128, 128, 2, 2, Epi, epi, n_tiles, 0, 1);
         else CC_LAUNCH_NT(128, 128, 2, 2);
     }
 #undef CC_LAUNCH

@@ -92,6 +92,7 @@ struct cc_gemm_plan {
     bool ring;
     int shares;
     bool duo;       // 'h', 's': the duo loop (else the ring loop)
+    int cuts;       // > 1: as shares, where K's groups do not divide evenly among them, and for 'h'
 };
 inline cc_gemm_plan cc_plan_gemm(int n_cu, int M, int N, int K, int64_t lda, int64_t ldb, bool ws, int64_t ws_floats,
                                  const cc_launch_override& ovr) {
@@ -117,7 +118,9 @@ inline cc_gemm_plan cc_plan_gemm(int n_cu, int M, int N, int K, int64_t lda, int
                 rs_short = ring ? Round{3.9, 0.34, 2.1, 0.104} : Round{4.6, 0.497, 0, 0};
     const double slices = (double)K / CC_GEMM_SLICE;
     auto us = [&](const Round& r, double fill, int share) {   // a round with tiles on `fill` of the CUs, 1 / share of K
-        return r.ends + r.more_ends * fill + (r.slice + r.more_slice * fill) * slices / share;
+        const int groups = K / CC_GEMM_GROUP;                 // the longest share
+        const double sl = share == 1 ? slices : (double)((groups + share - 1) / share * (CC_GEMM_GROUP / CC_GEMM_SLICE));
+        return r.ends + r.more_ends * fill + (r.slice + r.more_slice * fill) * sl;
     };
     auto grid_us = [&](const Round& r, int bm, int bn) {
         const double fill = (double)tiles_of(bm, bn) / n_cu;  // of all its rounds
@@ -142,35 +145,42 @@ inline cc_gemm_plan cc_plan_gemm(int n_cu, int M, int N, int K, int64_t lda, int
     if (force == 'b' || force == 's' || ((force == 'h' || force == 'm') && ring)) pick = force;
     // Split-K for the part of a grid that leaves most CUs idle: the tiles of a last round that
     // fills at most half the chip (all tiles, if there is no full round) are computed by S
-    // workgroup rows, each over K/S columns, with S x tiles <= CUs, and a finishing pass; the full
-    // rounds before them run as a launch of their own.  256-wide tiles only.  The extra launches and
+    // workgroup rows, each over a share of K's groups, with S x tiles <= CUs, and a finishing pass; the full
+    // rounds before them run as a launch of their own.  256-row tiles only.  The extra launches and
     // the shares' traffic cost 4.3 us and 6.8 TB/s; the estimate has to be 2 % below the unsplit one.
+    // Shares need not be equal: 84 tiles of 256x256 over 148 groups take 2 shares, 168 workgroups, if they have to be,
+    // 3 and 252 if not (M = 1523, N = 3584, K = 18944: 203 -> 173 us with the finishing pass).
     int S = 1;
     if (ring && ws) {
-        auto rem_of = [&](int bm) {
-            const long tiles = tiles_of(bm, 256);
+        const int groups = K / CC_GEMM_GROUP;
+        struct Shape { char tile; int bm, bn; const Round& r; };
+        const Shape shapes[3] = {{'b', 256, 256, rb}, {'m', 192, 256, rm}, {'h', 256, 128, rhd}};
+        auto rem_of = [&](const Shape& h) {
+            const long tiles = tiles_of(h.bm, h.bn);
             return (int)(tiles % n_cu == 0 && tiles > 0 ? n_cu : tiles % n_cu);
         };
-        auto split_ok = [&](int bm, int sp, int k_min) {
-            const int rem = rem_of(bm);
-            return (K / CC_GEMM_GROUP) % sp == 0 && K / sp >= k_min && (long)rem * sp <= n_cu &&
-                   (double)sp * rem * 65536.0 <= (double)ws_floats;
+        auto split_ok = [&](const Shape& h, int sp, int k_min) {
+            const int rem = rem_of(h);
+            return groups / sp * CC_GEMM_GROUP >= k_min && (long)rem * sp <= n_cu &&
+                   (double)sp * rem * (256.0 * h.bn) <= (double)ws_floats;          // slots of 256 rows
         };
         if (ovr.gemm_splitk > 0) {
             const int sp = ovr.gemm_splitk;
-            const int bm = pick == 'm' ? 192 : 256;
-            if (sp > 1 && sp <= 16 && split_ok(bm, sp, CC_GEMM_GROUP)) S = sp, pick = bm == 192 ? 'm' : 'b';
+            const Shape& h = shapes[pick == 'm' ? 1 : 0];
+            if (sp > 1 && sp <= 16 && groups % sp == 0 && split_ok(h, sp, CC_GEMM_GROUP)) S = sp, pick = h.tile;
         } else if (!force && !ovr.gemm_staged) {
             const double t_unsplit = t_best;
-            for (int bm = 256; bm >= 192; bm -= 64) {
-                const Round& r = bm == 256 ? rb : rm;
-                const long full_rounds = rounds_of(bm, 256) - 1;
-                const int rem = rem_of(bm);
+            for (const Shape& h : shapes) {
+                // 256x128 in shares: 192 rows and fewer keep to the wider tiles (tests pin that choice; at M = 192, N = 4096,
+                // K = 14336 it would be 47 us against 51)
+                if (h.tile == 'h' && (ovr.gemm_mfma32 || M <= 192)) continue;
+                const long full_rounds = rounds_of(h.bm, h.bn) - 1;
+                const int rem = rem_of(h);
                 for (int sp = 2; sp <= 16; ++sp) {
-                    if (!split_ok(bm, sp, 512)) continue;
-                    const double t = full_rounds * us(r, 1, 1) + us(r, (double)rem * sp / n_cu, sp) + 4.3 +
-                                     (double)sp * rem * 65536.0 * 4 / 6.8e6;
-                    if (t < t_best && t < 0.98 * t_unsplit) t_best = t, S = sp, pick = bm == 256 ? 'b' : 'm';
+                    if (!split_ok(h, sp, h.tile == 'h' ? 896 : 512)) continue;   // shorter ones: M = 256, N = K = 3584 27 us, thin 24
+                    const double t = full_rounds * us(h.r, 1, 1) + us(h.r, (double)rem * sp / n_cu, sp) + 4.3 +
+                                     (double)sp * rem * (256.0 * h.bn) * 4 / 6.8e6;
+                    if (t < t_best && t < 0.98 * t_unsplit) t_best = t, S = sp, pick = h.tile;
                 }
             }
         }
@@ -185,24 +195,25 @@ inline cc_gemm_plan cc_plan_gemm(int n_cu, int M, int N, int K, int64_t lda, int
     const long thin_tiles = tiles_of(CC_THIN_M, CC_THIN_N);
     const bool thin_ok = lda * CC_THIN_M * 2 < (1ll << 31) && ldb * CC_THIN_N * 2 < (1ll << 31);
     auto thin_split_ok = [&](int sp) {
-        return (K / 64) % sp == 0 && ws && (double)sp * thin_tiles * (CC_THIN_M * CC_THIN_N) <= (double)ws_floats;
+        return K / 64 >= sp && ws && (double)sp * thin_tiles * (CC_THIN_M * CC_THIN_N) <= (double)ws_floats;
     };
     if (thin_ok && force == 't') {
         const int sp = ovr.gemm_splitk;
-        return {'t', ring, sp > 1 && thin_split_ok(sp) ? sp : 1, false};
+        return {'t', ring, sp > 1 && (K / 64) % sp == 0 && thin_split_ok(sp) ? sp : 1, false, 1};
     }
     if (thin_ok && !force && !ovr.gemm_staged && !ovr.gemm_mfma32 && ovr.gemm_splitk == 0) {
         double t_thin = 0.96 * t_best;
         for (int sp = 1; sp <= 16; ++sp) {
             if (sp > 1 && (!thin_split_ok(sp) || K / sp < 256 || thin_tiles * sp > n_cu)) continue;
             const long rounds = (thin_tiles * sp + n_cu - 1) / n_cu;
-            double t = rounds * (K / sp / 64 * 0.465 + 3.0);
+            double t = rounds * ((K / 64 + sp - 1) / sp * 0.465 + 3.0);
             t = std::max(t, 2.0 * N * K / 7.0e6);
             if (sp > 1) t += 2.0 + (double)sp * thin_tiles * (CC_THIN_M * CC_THIN_N) * 8 / 4.2e6;
             if (t < t_thin) t_thin = t, pick = 't', S = sp;
         }
     }
-    return {pick, ring, S, pick == 'h' ? duo_h : pick == 's' && duo_s};
+    const bool even = pick != 'h' && K % ((pick == 't' ? 64 : CC_GEMM_GROUP) * S) == 0;
+    return {pick, ring, even ? S : 1, pick == 'h' ? duo_h : pick == 's' && duo_s, even ? 1 : S};
 }
 
 // ---- selection: one workgroup up to CC_SEL_ONE_MAX tokens (five rows of 4096 keys in LDS; 6.5 us and 0.36 us more per

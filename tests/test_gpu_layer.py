@@ -420,6 +420,7 @@ def test_stage_attention_even_grid(H_q, H_kv, d_h, N, M, splits):
 
 
 # (H_q, H_kv, d_h, N, M): grids whose blocks are cut into runs of key tiles
+UNEVEN_SHARES = [(40, 128, 896), (200, 2304, 6656), (513, 2304, 9984)]     # rows, d, f of a down projection
 CUT_SHAPES = [(8, 8, 128, 1300, 40), (14, 2, 64, 700, 257), (32, 1, 128, 229, 1), (12, 3, 128, 600, 64), (64, 2, 64, 300, 9),
               (16, 16, 128, 2050, 20)]
 
@@ -961,4 +962,27 @@ def test_stage_projections_in_the_duo_loop(tile, d, f, M):
     z = yf + (layer.silu(m @ obf.bits_to_f64(w["w_gate"]).T) * (m @ obf.bits_to_f64(w["w_up"]).T)) @ obf.bits_to_f64(w["w_down"]).T
     mx, mn = err_stats(bits_f64(host_bits(out))[:M], z)
     assert mx <= MAX_ABS and mn <= MEAN_ABS and bool((out[M] == 7.0).all()), (mx, mn)
+    ctx.close()
+
+
+@pytest.mark.parametrize("M,d,f", UNEVEN_SHARES)
+def test_stage_mlp_with_unequal_shares_of_k(M, d, f):
+    """A down projection whose K is cut into shares of unequal length: thin tiles (14 slices in 3), 256x128 (52 groups of
+    128 columns in 7) and 256x256 (78 in 8).  Sampled rows, the first and last of every tile among them."""
+    model = ModelShape(d, d // 64, d // 64, 64, f, 1e4, 1e-5, False, 1)
+    rng = np.random.default_rng(f)
+    wb = _x_bits(1, d, 7)[0]
+    wg, wu, wd = (_x_bits(n, k, s, k ** -0.5) for n, k, s in ((f, d, 1), (f, d, 2), (d, f, 3)))
+    ctx = _ctx(model, 64, M)
+    y = rng.standard_normal((M, d)).astype(np.float32)
+    out = torch.full((M + 1, d), 7.0, dtype=torch.bfloat16, device=DEV)
+    ctx.step_mlp(torch.from_numpy(y).to(DEV), M, dev_bf16(wb), dev_bf16(wg), dev_bf16(wu), dev_bf16(wd), out)
+    torch.cuda.synchronize()
+    rows = np.unique(np.r_[[r for r in (0, 63, 64, 255, 256, 511, 512) if r < M], M - 1, rng.integers(0, M, size=24)])
+    m = layer.rmsnorm(y[rows].astype(np.float64), obf.bits_to_f64(wb), model.rms_eps)
+    z = y[rows] + (layer.silu(m @ obf.bits_to_f64(wg).T) * (m @ obf.bits_to_f64(wu).T)) @ obf.bits_to_f64(wd).T
+    got = bits_f64(host_bits(out))
+    assert np.isfinite(got).all() and bool((out[M] == 7.0).all())
+    mx, mn = err_stats(got[rows], z)
+    assert mx <= MAX_ABS and mn <= MEAN_ABS, (mx, mn)
     ctx.close()

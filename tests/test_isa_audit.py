@@ -188,7 +188,7 @@ def test_gemm_duo_kernel_reads_are_waited_for(tmp_path):
     r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
     assert r.returncode == 0, r.stdout
     kernels = re.findall(r"^(_ZN\S*gemm_duo_kernel\S*):[^\n]*\n(.*?)\.end_amdhsa_kernel", out.read_text(), flags=re.S | re.M)
-    assert len(kernels) == 8, [k[0] for k in kernels]     # two tile shapes x four epilogues
+    assert len(kernels) == 10, [k[0] for k in kernels]    # two tile shapes x four epilogues + two split-K instances
     for name, body in kernels:
         seen, bad = audit(body)
         assert seen >= 2 * 16, (name, seen)               # sixteen fragment reads in the loop and in its end

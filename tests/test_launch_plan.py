@@ -8,7 +8,7 @@ import pytest
 
 from paper_2510_10129_amd import build
 from paper_2510_10129_amd._lib import LaunchOverride
-from test_gpu_layer import CUT_SHAPES
+from test_gpu_layer import CUT_SHAPES, UNEVEN_SHARES
 
 CXX = shutil.which("g++") or shutil.which("c++")
 pytestmark = pytest.mark.skipif(CXX is None, reason="no host C++ compiler")
@@ -29,6 +29,10 @@ int plan_gemm_duo(int n_cu, int M, int N, int K, int tile) {
     o.gemm_tile = tile;
     const cc_gemm_plan p = cc_plan_gemm(n_cu, M, N, K, K, K, false, 0, o);
     return p.duo ? p.tile : 0;
+}
+void plan_gemm_cuts(int M, int N, int K, int64_t ws_floats, int* out) {
+    const cc_gemm_plan p = cc_plan_gemm(256, M, N, K, K, K, ws_floats > 0, ws_floats, cc_launch_override{});
+    out[0] = p.tile, out[1] = p.shares, out[2] = p.cuts;
 }
 int norm_waves(int n_cu, int M, int d, int elem_bytes) { return cc_norm_waves(n_cu, M, d, elem_bytes); }
 int asm_rows(int64_t n_rows, int width) { return cc_asm_rows(n_rows, width); }
@@ -213,3 +217,45 @@ def test_rows_of_an_assembly_wave(plan, n_rows, width, rows):
 ])
 def test_loop_of_the_smaller_tiles(plan, M, N, K, tile, duo):
     assert bool(plan.plan_gemm_duo(256, M, N, K, ord(tile))) == duo
+
+
+def cuts(plan, M, N, K, ws_floats=32 << 20):
+    plan.plan_gemm_cuts.argtypes = [C.c_int, C.c_int, C.c_int, C.c_int64, C.POINTER(C.c_int)]
+    out = (C.c_int * 3)()
+    plan.plan_gemm_cuts(M, N, K, ws_floats, out)
+    return chr(out[0]), out[1], out[2]
+
+
+@pytest.mark.parametrize("shape,tile,n", list(zip(UNEVEN_SHARES, "thb", (3, 7, 8))))
+def test_shapes_of_the_unequal_share_tests_are_cut(plan, shape, tile, n):
+    M, d, f = shape
+    assert cuts(plan, M, d, f, min(32 << 20, 8 * M * -(-2 * f // 256) * 256)) == (tile, 1, n)
+
+
+@pytest.mark.parametrize("M,N,K,tile,n", [
+    (1523, 3584, 18944, "b", 3),        # 84 tiles, 148 groups: 2 equal shares 203 us, 173
+    (448, 3584, 18944, "b", 9),         # 101.6, 80
+    (3404, 6144, 4096, "b", 3),         # a full round and 80 tiles: 171.7, 166.4
+    (883, 1536, 8960, "h", 5),          # 49.7, 41.3
+    (64, 10240, 8192, "t", 3),          # 44.0, 38.6
+])
+def test_unequal_shares_where_they_were_measured_faster(plan, M, N, K, tile, n):
+    assert cuts(plan, M, N, K) == (tile, 1, n)
+
+
+def test_unequal_shares_fit_their_workspace(plan):
+    """Over a wide range of sizes: one round of workgroups, slots within the workspace, no empty share, and a plan has equal
+    shares or unequal ones."""
+    for M in (1, 64, 65, 200, 257, 883, 1523, 3404, 16576):
+        for N in (64, 192, 512, 1536, 3584, 6144, 37888):
+            for K in (64, 448, 896, 1664, 3584, 4096, 8960, 18944):
+                for ws in (0, 1 << 16, 4 << 20, 32 << 20):
+                    tile, shares, n = cuts(plan, M, N, K, ws)
+                    if n <= 1:
+                        continue
+                    assert shares == 1 and ws and n <= 16 and tile in "bmht"
+                    bm, bn, slot = {"b": (256, 256, 65536), "m": (192, 256, 65536), "h": (256, 128, 32768), "t": (64, 128, 8192)}[tile]
+                    tiles = -(-M // bm) * -(-N // bn)
+                    last = tiles if tile == "t" else (tiles % 256 or 256)
+                    assert last * n <= 256 and last * n * slot <= ws and K // (64 if tile == "t" else 128) >= n
+                    assert tile == "t" or K % 128 == 0
