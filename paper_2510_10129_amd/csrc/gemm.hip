@@ -95,6 +95,8 @@ __device__ __forceinline__ void store_bf16x8(bf16_t* dst, const float* v) {
     *reinterpret_cast<bf16x8*>(dst) = o;
 }
 
+// What an epilogue does with 8 columns of a staged fp32 row (column c of it at c ^ swz).  `pre` loads what it needs from
+// memory besides, by the row's key (a load of its own), so that a kernel can ask for both early.
 struct EpiQKV {
     const int32_t* idx;
     const bf16_t* bias;
@@ -104,17 +106,23 @@ struct EpiQKV {
     bf16_t* K;
     bf16_t* V;
     int64_t st, sh;
+    // the rotary pairs are not asked for early: 64 bytes a lane from rows far apart, 1 us more for thin tiles of a short K
+    struct Pre {
+        int pos;
+    };
+    __device__ __forceinline__ int key(int m) const { return idx[m]; }
     template <int BN>
-    __device__ __forceinline__ void operator()(int m, int bn, int cc, const float* crow, int swz) const {
+    __device__ __forceinline__ Pre pre(int, int, int, int pos) const { return {pos}; }
+    template <int BN>
+    __device__ __forceinline__ void operator()(int m, int bn, int cc, const float* crow, int swz, const Pre& pr) const {
         const int n = bn * BN + cc;
         if (n >= N) return;
         const int head = n / d_h, c = n - head * d_h, half = d_h >> 1;
-        const int pos = idx[m];
         float v[8];
 #pragma unroll
         for (int u = 0; u < 8; ++u) v[u] = crow[(cc ^ swz) + u];
         if (bias) {
-            bf16x8 b = *reinterpret_cast<const bf16x8*>(bias + n);
+            const bf16x8 b = *reinterpret_cast<const bf16x8*>(bias + n);
 #pragma unroll
             for (int u = 0; u < 8; ++u) v[u] += (float)b[u];
         }
@@ -131,7 +139,7 @@ struct EpiQKV {
 #pragma unroll
                 for (int u = 0; u < 8; ++u) p[u] += (float)b[u];
             }
-            const float2* cs = rope + (int64_t)pos * half + j;
+            const float2* cs = rope + (int64_t)pr.pos * half + j;
 #pragma unroll
             for (int u = 0; u < 8; ++u) {
                 float2 t = cs[u];
@@ -142,10 +150,14 @@ struct EpiQKV {
         if (head < H_q)
             dst = q_out + (int64_t)m * H_q * d_h + n;
         else if (head < H_q + H_kv)
-            dst = K + (int64_t)pos * st + (int64_t)(head - H_q) * sh + c;
+            dst = K + (int64_t)pr.pos * st + (int64_t)(head - H_q) * sh + c;
         else
-            dst = V + (int64_t)pos * st + (int64_t)(head - H_q - H_kv) * sh + c;
+            dst = V + (int64_t)pr.pos * st + (int64_t)(head - H_q - H_kv) * sh + c;
         store_bf16x8(dst, v);
+    }
+    template <int BN>
+    __device__ __forceinline__ void operator()(int m, int bn, int cc, const float* crow, int swz) const {
+        operator()<BN>(m, bn, cc, crow, swz, pre<BN>(m, bn, cc, key(m)));
     }
 };
 
@@ -154,12 +166,27 @@ struct EpiOProj {
     const int32_t* gather_idx;
     int d;
     float* y;
+    struct Pre {
+        bf16x8 x;
+    };
+    __device__ __forceinline__ int key(int m) const { return gather_idx ? gather_idx[m] : m; }
+    template <int BN>
+    __device__ __forceinline__ Pre pre(int, int bn, int cc, int src) const {
+        Pre p;
+        const int n = bn * BN + cc;
+        if (n >= d) return p;
+        p.x = *reinterpret_cast<const bf16x8*>(hidden + (int64_t)src * d + n);
+        return p;
+    }
     template <int BN>
     __device__ __forceinline__ void operator()(int m, int bn, int cc, const float* crow, int swz) const {
+        operator()<BN>(m, bn, cc, crow, swz, pre<BN>(m, bn, cc, key(m)));
+    }
+    template <int BN>
+    __device__ __forceinline__ void operator()(int m, int bn, int cc, const float* crow, int swz, const Pre& p) const {
         const int n = bn * BN + cc;
         if (n >= d) return;
-        const int64_t src = gather_idx ? (int64_t)gather_idx[m] : (int64_t)m;
-        bf16x8 x = *reinterpret_cast<const bf16x8*>(hidden + src * d + n);
+        const bf16x8 x = p.x;
         const float* cr = crow + (cc ^ swz);
         f32x4 a, b;
 #pragma unroll
@@ -176,8 +203,12 @@ struct EpiOProj {
 struct EpiGateUp {
     int f;
     bf16_t* act;
+    struct Pre {};
+    __device__ __forceinline__ int key(int) const { return 0; }
     template <int BN>
-    __device__ __forceinline__ void operator()(int m, int bn, int cc, const float* crow, int swz) const {
+    __device__ __forceinline__ Pre pre(int, int, int, int) const { return {}; }
+    template <int BN>
+    __device__ __forceinline__ void operator()(int m, int bn, int cc, const float* crow, int swz, const Pre& = {}) const {
         constexpr int H = BN / 2;
         if (cc >= H) return;
         const int n = bn * H + cc;
@@ -196,12 +227,29 @@ struct EpiDown {
     const float* y;
     int d;
     bf16_t* out;
+    struct Pre {
+        f32x4 a, b;
+    };
+    __device__ __forceinline__ int key(int) const { return 0; }
+    template <int BN>
+    __device__ __forceinline__ Pre pre(int m, int bn, int cc, int) const {
+        Pre p;
+        const int n = bn * BN + cc;
+        if (n >= d) return p;
+        const f32x4* r = reinterpret_cast<const f32x4*>(y + (int64_t)m * d + n);
+        p.a = r[0];
+        p.b = r[1];
+        return p;
+    }
     template <int BN>
     __device__ __forceinline__ void operator()(int m, int bn, int cc, const float* crow, int swz) const {
+        operator()<BN>(m, bn, cc, crow, swz, pre<BN>(m, bn, cc, key(m)));
+    }
+    template <int BN>
+    __device__ __forceinline__ void operator()(int m, int bn, int cc, const float* crow, int swz, const Pre& p) const {
         const int n = bn * BN + cc;
         if (n >= d) return;
-        const f32x4* r = reinterpret_cast<const f32x4*>(y + (int64_t)m * d + n);
-        f32x4 a = r[0], b = r[1];
+        const f32x4 a = p.a, b = p.b;
         const float* cr = crow + (cc ^ swz);
         float v[8];
 #pragma unroll
@@ -229,8 +277,12 @@ struct EpiPartial {
     float* ws;
     int64_t share_stride;     // floats per share: slots * ROWS * BN
     int slot, m0;             // set by the kernel: this workgroup's slot and first row
+    struct Pre {};
+    __device__ __forceinline__ int key(int) const { return 0; }
     template <int BN>
-    __device__ __forceinline__ void operator()(int m, int bn, int cc, const float* crow, int swz) const {
+    __device__ __forceinline__ Pre pre(int, int, int, int) const { return {}; }
+    template <int BN>
+    __device__ __forceinline__ void operator()(int m, int bn, int cc, const float* crow, int swz, const Pre& = {}) const {
         float* dst = ws + blockIdx.y * share_stride + (int64_t)slot * (ROWS * BN) + (m - m0) * BN + cc;
         const f32x4* cr = reinterpret_cast<const f32x4*>(crow + (cc ^ swz));
         reinterpret_cast<f32x4*>(dst)[0] = cr[0];
@@ -264,7 +316,9 @@ __global__ __launch_bounds__(256) void splitk_finish_kernel(const float* __restr
     tile_of_seq(vb0 + blockIdx.x, tiles_m, tiles_n, GM, &bm, &bn);
     const int row = blockIdx.y * ROWS + r, m = bm * BM + row;
     const bool on = row < BM && m < M;
+    typename Epi::Pre pre;
     if (on) {
+        pre = epi.template pre<BN>(m, bn, cc, epi.key(m));
         const float* src = ws + (int64_t)blockIdx.x * (SLOT_ROWS * BN) + row * BN + cc;
         f32x4 a = {0.f, 0.f, 0.f, 0.f}, b = {0.f, 0.f, 0.f, 0.f};
         int sp = 0;
@@ -291,7 +345,7 @@ __global__ __launch_bounds__(256) void splitk_finish_kernel(const float* __restr
         *reinterpret_cast<f32x4*>(&stage[r][cc + 4]) = b;
     }
     __syncthreads();
-    if (on) epi.template operator()<BN>(m, bn, cc, stage[r], 0);
+    if (on) epi.template operator()<BN>(m, bn, cc, stage[r], 0, pre);
 }
 
 // Consecutive workgroup ids go round-robin to the 8 XCDs (each with its own
@@ -301,11 +355,16 @@ __global__ __launch_bounds__(256) void splitk_finish_kernel(const float* __restr
 // tiles of A and 32/GM tiles of B through that L2.
 // tile `vb` of the sequence (bands of GM row-tiles, column by column)
 __device__ __forceinline__ void tile_of_seq(int vb, int tiles_m, int tiles_n, int GM, int* bm, int* bn) {
+    if (tiles_m == 1) {                       // the divisions take 0.1 us each
+        *bm = 0;
+        *bn = vb;
+        return;
+    }
     const int band = GM * tiles_n;
-    const int b = vb / band, rb = vb - b * band;
+    const int b = GM >= tiles_m ? 0 : vb / band, rb = vb - b * band;
     const int gm = min(GM, tiles_m - b * GM);
-    *bm = b * GM + rb % gm;
     *bn = rb / gm;
+    *bm = b * GM + rb - *bn * gm;
 }
 // workgroup `bid` of a launch over tiles vb0 .. vb0 + nb - 1 of the sequence; returns its tile's index
 __device__ __forceinline__ int tile_of_block(int bid, int nb, int vb0, int tiles_m, int tiles_n, int GM,
@@ -1596,7 +1655,7 @@ __global__ __launch_bounds__(256, 1) void gemm_thin_kernel(const bf16_t* __restr
         const uint64_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(u >> 32));
         return reinterpret_cast<const char*>((hi << 32) | lo);
     };
-    const int KT = K / 64, rot = bn % KT;
+    const int KT = K / 64, rot = bn < KT ? bn : bn % KT;
     // load i of slice n: B's first
     auto load_one = [&](auto xc, auto streamc, int n, int slot) __attribute__((always_inline)) {
         constexpr int x = decltype(xc)::value;
@@ -1629,6 +1688,13 @@ __global__ __launch_bounds__(256, 1) void gemm_thin_kernel(const bf16_t* __restr
         a_addr[ks] = smem_base + frow * ROWB + ((fk + 4 * ks) ^ fsw) * 16;
         b_addr[ks] = a_addr[ks] + (BM + wave * 32) * ROWB;
     }
+    const auto e2 = epi_for_tile(epi, vb, m0);
+    constexpr int TPR = BN / 8, RPP = 256 / TPR;       // threads per row, rows per pass
+    const int cc = (tid % TPR) * 8;
+    typename std::remove_const_t<decltype(e2)>::Pre pre[BM / RPP];
+    int key[BM / RPP];                                 // ahead of the first slices: loads return in order
+#pragma unroll
+    for (int k = 0; k < BM / RPP; ++k) key[k] = e2.key(min(m0 + tid / TPR + k * RPP, M - 1));
     auto k_loop = [&](auto streamc) __attribute__((always_inline)) {
         int rd = 0, wrs = D - 1;                       // slots of slice t and of slice t + D - 1
         // One slice, with at most `younger` slices' loads out when it is read.  The loads of slice t + D - 1 go
@@ -1679,6 +1745,9 @@ __global__ __launch_bounds__(256, 1) void gemm_thin_kernel(const bf16_t* __restr
         unrolled<D - 1>([&](auto tc) __attribute__((always_inline)) {
             if (tc.value < KT) unrolled<LPS>([&](auto xc) __attribute__((always_inline)) { load_one(xc, streamc, tc.value, tc.value); });
         });
+        // what the epilogue needs from memory, behind the first slices (a wait for one of them may wait for this too)
+#pragma unroll
+        for (int k = 0; k < BM / RPP; ++k) pre[k] = e2.template pre<BN>(min(m0 + tid / TPR + k * RPP, M - 1), bn, cc, key[k]);
         int t = 0;
         for (; t + D - 1 < KT; ++t) slice(std::true_type{}, std::integral_constant<int, D - 2>{}, t);
         // the last D - 1 slices (or all of a shorter K): nothing left to load
@@ -1703,14 +1772,11 @@ __global__ __launch_bounds__(256, 1) void gemm_thin_kernel(const bf16_t* __restr
                 stage[r * BN + (c ^ (fk << 4))] = acc[i][j][v];
             }
     __syncthreads();
-    const auto e2 = epi_for_tile(epi, vb, m0);
-    constexpr int TPR = BN / 8, RPP = 256 / TPR;
-    const int cc = (tid % TPR) * 8;
 #pragma unroll
     for (int k = 0; k < BM / RPP; ++k) {
         const int r = tid / TPR + k * RPP;
         const int m = m0 + r;
-        if (m < M) e2.template operator()<BN>(m, bn, cc, stage + r * BN, ((r >> 2) & 3) << 4);
+        if (m < M) e2.template operator()<BN>(m, bn, cc, stage + r * BN, ((r >> 2) & 3) << 4, pre[k]);
     }
 }
 
