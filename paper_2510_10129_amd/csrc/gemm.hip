@@ -100,8 +100,11 @@ __device__ __forceinline__ void store_bf16x8(bf16_t* dst, const float* v) {
 // make one output column.  A tile's threads are dealt over BN / COLS columns: with gate and up dealt over all BN, the
 // half at the up columns had nothing to do and each row cost twice its passes (gate/up of 3404 rows and d = 2048
 // 199.0 -> 182.9 us, d = 4096 593.4 -> 571.6; 883 rows 175.9 -> 167.3; 8192 rows 1332.7 -> 1282.2).
+// A lane turns both columns of its rotary pairs: with a lane per 8 columns either side read the other's sums and the same 64
+// bytes of rotary pairs again (us, before -> after: 8192 rows, d = 4096 323.3 -> 308.2, d = 2048 118.0 -> 108.2; 3404 rows
+// 162.7 -> 156.7 and 59.5 -> 52.9; 883 rows, d = 4096 63.1 -> 60.6; 237 rows, d = 256 8.2 -> 7.4).
 struct EpiQKV {
-    static constexpr int COLS = 1;
+    static constexpr int COLS = 2;                         // the two columns of a rotary pair (of a head of V: c and c + d_h/2)
     const int32_t* idx;
     const bf16_t* bias;
     const float2* rope;
@@ -117,47 +120,46 @@ struct EpiQKV {
     __device__ __forceinline__ int key(int m) const { return idx[m]; }
     template <int BN>
     __device__ __forceinline__ Pre pre(int, int, int, int pos) const { return {pos}; }
+    // cc counts pairs: 8 columns of a head's first half and the 8 they are rotated with
     template <int BN>
     __device__ __forceinline__ void operator()(int m, int bn, int cc, const float* crow, int swz, const Pre& pr) const {
-        const int n = bn * BN + cc;
+        const int half = d_h >> 1, hd = cc / half, j = cc - hd * half;
+        const int lo = hd * d_h + j, n = bn * BN + lo;     // a tile holds whole heads
         if (n >= N) return;
-        const int head = n / d_h, c = n - head * d_h, half = d_h >> 1;
-        float v[8];
+        const int head = n / d_h;
+        float v[8], p[8];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) v[u] = crow[(cc ^ swz) + u];
+        for (int u = 0; u < 8; ++u) {
+            v[u] = crow[(lo ^ swz) + u];
+            p[u] = crow[((lo + half) ^ swz) + u];
+        }
         if (bias) {
-            const bf16x8 b = *reinterpret_cast<const bf16x8*>(bias + n);
+            const bf16x8 b = *reinterpret_cast<const bf16x8*>(bias + n), b2 = *reinterpret_cast<const bf16x8*>(bias + n + half);
 #pragma unroll
-            for (int u = 0; u < 8; ++u) v[u] += (float)b[u];
+            for (int u = 0; u < 8; ++u) {
+                v[u] += (float)b[u];
+                p[u] += (float)b2[u];
+            }
         }
         if (head < H_q + H_kv) {
-            const bool lo = c < half;
-            const int pcc = lo ? cc + half : cc - half;
-            const int pn = lo ? n + half : n - half;
-            const int j = lo ? c : c - half;
-            float p[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) p[u] = crow[(pcc ^ swz) + u];
-            if (bias) {
-                bf16x8 b = *reinterpret_cast<const bf16x8*>(bias + pn);
-#pragma unroll
-                for (int u = 0; u < 8; ++u) p[u] += (float)b[u];
-            }
             const float2* cs = rope + (int64_t)pr.pos * half + j;
 #pragma unroll
             for (int u = 0; u < 8; ++u) {
-                float2 t = cs[u];
-                v[u] = lo ? v[u] * t.x - p[u] * t.y : v[u] * t.x + p[u] * t.y;
+                const float2 t = cs[u];
+                const float x = v[u];
+                v[u] = x * t.x - p[u] * t.y;
+                p[u] = p[u] * t.x + x * t.y;
             }
         }
         bf16_t* dst;
         if (head < H_q)
             dst = q_out + (int64_t)m * H_q * d_h + n;
         else if (head < H_q + H_kv)
-            dst = K + (int64_t)pr.pos * st + (int64_t)(head - H_q) * sh + c;
+            dst = K + (int64_t)pr.pos * st + (int64_t)(head - H_q) * sh + j;
         else
-            dst = V + (int64_t)pr.pos * st + (int64_t)(head - H_q - H_kv) * sh + c;
+            dst = V + (int64_t)pr.pos * st + (int64_t)(head - H_q - H_kv) * sh + j;
         store_bf16x8(dst, v);
+        store_bf16x8(dst + half, p);
     }
     template <int BN>
     __device__ __forceinline__ void operator()(int m, int bn, int cc, const float* crow, int swz) const {
@@ -504,10 +506,10 @@ __device__ __forceinline__ void store_tile_ring(f32x16 (&acc)[BM / WAVES_M / 32]
     constexpr int VPG = RG / 2;           // accumulator registers per group and tile
     constexpr int BPP = GPW * RG / 32;    // accumulator row blocks per wave and phase
     constexpr int PHASES = TM / BPP;
-    constexpr int TPR = BN / 8;           // threads per staged row
+    constexpr int TPR = BN / Epi::COLS / 8;   // threads per staged row
     constexpr int RPP = NT / TPR;         // rows per pass
     static_assert(RG == 32 || RG == 16, "row group");
-    static_assert(4 % WAVES_M == 0 && GPW * RG % 32 == 0 && TM % BPP == 0 && RG % RPP == 0, "epilogue shape");
+    static_assert(4 % WAVES_M == 0 && GPW * RG % 32 == 0 && TM % BPP == 0 && 4 * RG % RPP == 0, "epilogue shape");
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave % WAVES_M, wn0 = (wave / WAVES_M) * WN;
     const int frow = lane & 31, fk = lane >> 5;
@@ -534,14 +536,10 @@ __device__ __forceinline__ void store_tile_ring(f32x16 (&acc)[BM / WAVES_M / 32]
         __syncthreads();
         const int cc = (tid % TPR) * 8;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int row0 = (q / GPW) * WM + p * BPP * 32 + (q % GPW) * RG;   // tile row of the slot's first row
-#pragma unroll
-            for (int k = 0; k < RG / RPP; ++k) {
-                const int r = tid / TPR + k * RPP;
-                const int m = m0 + row0 + r;
-                if (m < M && cc < BN / Epi::COLS) epi.template operator()<BN>(m, bn, cc, stage(q) + r * BN, ((r >> 2) & 1) << 5);
-            }
+        for (int k = 0; k < 4 * RG / RPP; ++k) {
+            const int rr = tid / TPR + k * RPP, q = rr / RG, r = rr % RG;
+            const int m = m0 + (q / GPW) * WM + p * BPP * 32 + (q % GPW) * RG + r;   // slot q's first tile row, and r
+            if (m < M) epi.template operator()<BN>(m, bn, cc, stage(q) + r * BN, ((r >> 2) & 1) << 5);
         }
     }
 }
