@@ -95,16 +95,39 @@ __device__ __forceinline__ void store_bf16x8(bf16_t* dst, const float* v) {
     *reinterpret_cast<bf16x8*>(dst) = o;
 }
 
+// Two quads of bf16 columns per lane, as the matrix instruction with its operands exchanged leaves them (lane L
+// has columns 4 (L/16) .. + 3 of two 16-column tiles j): lanes of odd 16-lane rows trade tile 0 for tile 1 with the row
+// below, after which each has 8 columns in a row, from column 16 (L/16 % 2) + 8 (L/32) on.
+__device__ __forceinline__ bf16x8 eight_columns(const f32x4& t0, const f32x4& t1) {
+    union { bf16_t h[4]; uint32_t u[2]; } a, b;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        a.h[v] = (bf16_t)t0[v];
+        b.h[v] = (bf16_t)t1[v];
+    }
+    union { bf16x8 v; uint32_t u[4]; } o;
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        const auto sw = __builtin_amdgcn_permlane16_swap(a.u[k], b.u[k], false, false);
+        o.u[k] = sw[0];
+        o.u[2 + k] = sw[1];
+    }
+    return o.v;
+}
+
 // What an epilogue does with 8 columns of a staged fp32 row (column c of it at c ^ swz).  `pre` loads what it needs from
 // memory besides, by the row's key (a load of its own), so that a kernel can ask for both early.  COLS: tile columns that
 // make one output column.  A tile's threads are dealt over BN / COLS columns: with gate and up dealt over all BN, the
 // half at the up columns had nothing to do and each row cost twice its passes (gate/up of 3404 rows and d = 2048
 // 199.0 -> 182.9 us, d = 4096 593.4 -> 571.6; 883 rows 175.9 -> 167.3; 8192 rows 1332.7 -> 1282.2).
+// DIRECT: the ping-pong loop stores from its accumulators.  `two` takes a lane's quads of columns c and c + 16 of a row (c with
+// the lane's own 4 (L/16)), for which `ask` has loaded what it needs, every lane of the wave with it (`on`: the row exists).
 // A lane turns both columns of its rotary pairs: with a lane per 8 columns either side read the other's sums and the same 64
 // bytes of rotary pairs again (us, before -> after: 8192 rows, d = 4096 323.3 -> 308.2, d = 2048 118.0 -> 108.2; 3404 rows
 // 162.7 -> 156.7 and 59.5 -> 52.9; 883 rows, d = 4096 63.1 -> 60.6; 237 rows, d = 256 8.2 -> 7.4).
 struct EpiQKV {
     static constexpr int COLS = 2;                         // the two columns of a rotary pair (of a head of V: c and c + d_h/2)
+    static constexpr bool DIRECT = false;                  // a column's rotary partner is in another wave
     const int32_t* idx;
     const bf16_t* bias;
     const float2* rope;
@@ -169,6 +192,7 @@ struct EpiQKV {
 
 struct EpiOProj {
     static constexpr int COLS = 1;
+    static constexpr bool DIRECT = true;
     const bf16_t* hidden;
     const int32_t* gather_idx;
     int d;
@@ -205,12 +229,35 @@ struct EpiOProj {
         dst[0] = a;
         dst[1] = b;
     }
+    struct Two {
+        bf16x4 x[2];
+    };
+    template <int BN>
+    __device__ __forceinline__ Two ask(int, int bn, int c, int src) const {
+        Two t;
+        const int n = bn * BN + c;
+#pragma unroll
+        for (int j = 0; j < 2; ++j) t.x[j] = *reinterpret_cast<const bf16x4*>(hidden + (int64_t)src * d + min(n + 16 * j, d - 4));
+        return t;
+    }
+    template <int BN>
+    __device__ __forceinline__ void two(int m, int bn, int c, int, const f32x4 (&t)[2], const Two& p, bool on) const {
+        const int n = bn * BN + c;
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            f32x4 a;
+#pragma unroll
+            for (int u = 0; u < 4; ++u) a[u] = t[j][u] + (float)p.x[j][u];
+            if (on && n + 16 * j < d) *reinterpret_cast<f32x4*>(y + (int64_t)m * d + n + 16 * j) = a;
+        }
+    }
 };
 
 struct EpiGateUp {
     int f;
     bf16_t* act;
     static constexpr int COLS = 2;                         // a gate and an up column
+    static constexpr bool DIRECT = true;
     struct Pre {};
     __device__ __forceinline__ int key(int) const { return 0; }
     template <int BN>
@@ -228,10 +275,22 @@ struct EpiGateUp {
         }
         store_bf16x8(act + (int64_t)m * f + n, v);
     }
+    template <int BN>
+    __device__ __forceinline__ void two(int m, int bn, int c, int fk, const f32x4 (&g)[2], const f32x4 (&up)[2], bool on) const {
+        f32x4 t[2];
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int u = 0; u < 4; ++u) t[j][u] = g[j][u] / (1.0f + __expf(-g[j][u])) * up[j][u];
+        const bf16x8 o = eight_columns(t[0], t[1]);
+        const int n = bn * (BN / 2) + c - 4 * fk + (fk & 1) * 16 + (fk >> 1) * 8;
+        if (on && n < f) *reinterpret_cast<bf16x8*>(act + (int64_t)m * f + n) = o;
+    }
 };
 
 struct EpiDown {
     static constexpr int COLS = 1;
+    static constexpr bool DIRECT = true;
     const float* y;
     int d;
     bf16_t* out;
@@ -267,6 +326,23 @@ struct EpiDown {
         }
         store_bf16x8(out + (int64_t)m * d + n, v);
     }
+    struct Two {
+        f32x4 x[2];
+    };
+    template <int BN>
+    __device__ __forceinline__ Two ask(int m, int bn, int c, int) const {
+        Two t;
+        const int n = bn * BN + c;
+#pragma unroll
+        for (int j = 0; j < 2; ++j) t.x[j] = *reinterpret_cast<const f32x4*>(y + (int64_t)m * d + min(n + 16 * j, d - 4));
+        return t;
+    }
+    template <int BN>
+    __device__ __forceinline__ void two(int m, int bn, int c, int fk, const f32x4 (&t)[2], const Two& p, bool on) const {
+        const bf16x8 o = eight_columns(t[0] + p.x[0], t[1] + p.x[1]);
+        const int n = bn * BN + c - 4 * fk + (fk & 1) * 16 + (fk >> 1) * 8;
+        if (on && n < d) *reinterpret_cast<bf16x8*>(out + (int64_t)m * d + n) = o;
+    }
 };
 
 // Split-K: workgroup row blockIdx.y computes the products over its share of K: `K` columns, the first
@@ -283,6 +359,7 @@ __device__ __forceinline__ int k_share(int K, int k_more, int64_t* first_byte) {
 template <int ROWS>
 struct EpiPartial {
     static constexpr int COLS = 1;
+    static constexpr bool DIRECT = true;
     float* ws;
     int64_t share_stride;     // floats per share: slots * ROWS * BN
     int slot, m0;             // set by the kernel: this workgroup's slot and first row
@@ -296,6 +373,16 @@ struct EpiPartial {
         const f32x4* cr = reinterpret_cast<const f32x4*>(crow + (cc ^ swz));
         reinterpret_cast<f32x4*>(dst)[0] = cr[0];
         reinterpret_cast<f32x4*>(dst)[1] = cr[1];
+    }
+    struct Two {};
+    template <int BN>
+    __device__ __forceinline__ Two ask(int, int, int, int) const { return {}; }
+    template <int BN>
+    __device__ __forceinline__ void two(int m, int, int c, int, const f32x4 (&t)[2], const Two&, bool on) const {
+        float* dst = ws + blockIdx.y * share_stride + (int64_t)slot * (ROWS * BN) + (m - m0) * BN + c;
+        if (!on) return;
+        reinterpret_cast<f32x4*>(dst)[0] = t[0];
+        reinterpret_cast<f32x4*>(dst)[4] = t[1];
     }
 };
 template <class Epi>
@@ -1204,6 +1291,10 @@ __device__ __forceinline__ bf16x8 lds_read16(uint32_t addr) {
 // gate/up 10370 -> 9050, down 5480 -> 4450, QKV 1990 -> 1720, O 1520 -> 1260.  Raising the
 // wave's priority around the MFMAs, waiting for the reads after the barrier instead of before it,
 // and issuing the loads before the reads: each within 1 %.
+// Epilogue: with the operands of the MFMAs exchanged a lane holds four columns of one row and stores them from its registers;
+// through LDS the tile was written a word at a time behind two barriers a half (M = 8192, before -> after: O 239.6 -> 229.9
+// us for d = 4096, 210.7 -> 200.7 for 3584, 77.5 -> 72.4 for 2048, gate/up 1352.7 -> 1339.1, 1604.7 -> 1591.1, 421.8 -> 417.0;
+// down the same, and 5 % more with 8-byte stores, which is why lanes trade columns first).
 template <class BSrc, class Epi>
 __global__ __launch_bounds__(512, 2) void gemm_pingpong_kernel(
     const bf16_t* __restrict__ A, int lda, int M, int K, int k_more, int tiles_m, int tiles_n, int GM, int nb, int vb0,
@@ -1316,7 +1407,9 @@ __global__ __launch_bounds__(512, 2) void gemm_pingpong_kernel(
 #pragma unroll
             for (int i = 0; i < UM; ++i)
 #pragma unroll
-                for (int j = 0; j < UN; ++j) c[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[ks][i], b[ks][j], c[i][j], 0, 0, 0);
+                for (int j = 0; j < UN; ++j)
+                    c[i][j] = Epi::DIRECT ? __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[ks][j], af[ks][i], c[i][j], 0, 0, 0)
+                                          : __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[ks][i], b[ks][j], c[i][j], 0, 0, 0);
         __builtin_amdgcn_sched_barrier(0);
         wg_barrier();
     };
@@ -1373,11 +1466,41 @@ __global__ __launch_bounds__(512, 2) void gemm_pingpong_kernel(
     if (!wr) wg_barrier();
 #undef CC_IC
 
+    const auto e2 = epi_for_tile(epi, vb - vb0, m0);
+    if constexpr (Epi::DIRECT) {
+        // ---- epilogue from the registers (lane L has columns 4 (L/16) .. + 3 of row L%16 of a 16x16 tile): no pass through
+        //      LDS and no barrier, so the waves that are done store while the others still multiply ----
+        const int cl = wc * (H / 4) + 4 * fk;
+        auto row = [&](int ha, int i) __attribute__((always_inline)) { return m0 + ha * H + wr * (H / 2) + i * 16 + frow; };
+        if constexpr (Epi::COLS == 2) {                // B0 and B1 hold the two columns of an output column
+#pragma unroll
+            for (int x = 0; x < 2 * UM; ++x) {
+                const int ha = x / UM, i = x % UM, m = row(ha, i);
+                e2.template two<BN>(m, bn, cl, fk, acc[ha][0][i], acc[ha][1][i], m < M);
+            }
+        } else {
+            int key[2][UM];
+#pragma unroll
+            for (int x = 0; x < 2 * UM; ++x) key[x / UM][x % UM] = e2.key(min(row(x / UM, x % UM), M - 1));
+#pragma unroll
+            for (int ha = 0; ha < 2; ++ha) {
+                typename Epi::Two p[UM][2];
+#pragma unroll
+                for (int x = 0; x < 2 * UM; ++x)
+                    p[x >> 1][x & 1] = e2.template ask<BN>(min(row(ha, x >> 1), M - 1), bn, (x & 1) * H + cl, key[ha][x >> 1]);
+#pragma unroll
+                for (int x = 0; x < 2 * UM; ++x) {
+                    const int i = x >> 1, hb = x & 1, m = row(ha, i);
+                    e2.template two<BN>(m, bn, hb * H + cl, fk, acc[ha][hb][i], p[i][hb], m < M);
+                }
+            }
+        }
+        return;
+    }
     // ---- epilogue: one row half at a time through LDS as fp32 [H][BN], column c of row r at
     //      c ^ 16*((r>>2)&3) (the four 16-lane groups of an accumulator store hit disjoint banks) ----
     constexpr int TPR = BN / Epi::COLS / 8, RPP = 512 / TPR;       // threads per row, rows per pass
     float* stage = reinterpret_cast<float*>(smem);
-    const auto e2 = epi_for_tile(epi, vb - vb0, m0);
     const int cc = (tid % TPR) * 8;
 #pragma unroll
     for (int ha = 0; ha < 2; ++ha) {

@@ -925,10 +925,12 @@ def test_stage_projections_on_thin_tiles(M, splitk):
 
 
 @pytest.mark.parametrize("tile,d,f,M", [("s", 128, 384, 1), ("s", 128, 384, 129), ("s", 640, 256, 255), ("h", 128, 384, 127),
-                                        ("h", 128, 384, 257), ("h", 640, 256, 513)])
+                                        ("h", 128, 384, 257), ("h", 640, 256, 513),
+                                        ("b", 128, 384, 1), ("b", 640, 448, 255), ("b", 640, 384, 513)])
 def test_stage_projections_in_the_duo_loop(tile, d, f, M):
     """256x128 and 128x128 tiles with the duo loop forced: K of one, two, three and five K tiles a group (128, 256,
-    384, 640 columns), partial row and column tiles, rows past the last of a tile.  Same bounds as above."""
+    384, 640 columns), partial row and column tiles, rows past the last of a tile; and 256x256 tiles (ping-pong loop), which
+    store from their accumulators, with the same remainders.  Same bounds as above."""
     model = ModelShape(d, d // 64, d // 128, 64, f, 1e4, 1e-5, True, 1)
     N = 600
     rng = np.random.default_rng(M)
