@@ -31,7 +31,8 @@
 //   staged (any K % 64 == 0; gemm_nt_kernel) two stages of 64 columns, one barrier
 //          per stage, 32x32x16 MFMAs.
 // The accumulators are written back through LDS so that every global store is
-// 16 or 32 contiguous bytes per lane along the row.
+// 16 or 32 contiguous bytes per lane along the row; those of the ping-pong loop, but for QKV, from the registers,
+// 16 bytes a lane.
 #include "cc_internal.h"
 #include "launch_plan.h"
 #include <algorithm>

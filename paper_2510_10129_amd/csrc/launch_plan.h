@@ -106,7 +106,7 @@ inline cc_gemm_plan cc_plan_gemm(int n_cu, int M, int N, int K, int64_t lda, int
     // traffic behind the caches) in proportion to the CUs that have one.
     // Fitted to event times of the four projections of nine models (d = 256 to 8192, f = 1024 to 28672), 1 to
     // 8320 rows, weights cold, every shape and most shares forced: 1032 calls, the choice 0.7 % above the fastest
-    // on average.  The rates without the ring loops are of three more models (364 calls): there the large tile is no
+    // on average (0.8 % since the epilogues are shorter; fitted anew 0.7 %).  The rates without the ring loops are of three more models (364 calls): there the large tile is no
     // faster than it was (M = 3000, N = 10880, K = 1984: three rounds of 256x256 179 us, four of 128x128 147).
     // The ends count where K is short (K = 256, 2048 columns, M = 5120: 256x256 tiles 21.4 us, 192x256 19.1,
     // 128x128 in the ring 18.4, with two of its tiles on a CU).
