@@ -1743,9 +1743,13 @@ __global__ __launch_bounds__(512, 2) void gemm_duo_kernel(
 // between two reads), 256-row tiles and these: gate/up 65 -> 42 (6.0 TB/s of weights without the events' 2.5 us), down 41 -> 28,
 // QKV 26 -> 19, O 24 -> 18.  Slices of 128 columns in three slots: the same within 2 % over these shapes, gate/up
 // slower by a fifth at 64 rows.
+// Launch bounds: 512 threads where 256 are launched, so that a wave has 256 registers.  With 512 of them the compiler kept the
+// sums in accumulation registers and, in a loop without conditions, moved 20 of them to vector registers and back in every
+// slice, between the MFMAs (140 instructions a slice, now 81).  M = 1 without shares, d = 4096: QKV 31.2 us in the loop
+// with conditions, 33.3 so, 26.3 now; 768 rows, N = 2880, K = 7744: 104.7, 110.0, 83.7; d = 576, 512 rows, gate/up 11.1, 10.0, 9.1.
 constexpr int THIN_M = CC_THIN_M, THIN_N = CC_THIN_N, THIN_SLOTS = 6;
 template <class BSrc, class Epi>
-__global__ __launch_bounds__(256, 1) void gemm_thin_kernel(const bf16_t* __restrict__ A, int lda, int M, int K, int k_more,
+__global__ __launch_bounds__(512, 2) void gemm_thin_kernel(const bf16_t* __restrict__ A, int lda, int M, int K, int k_more,
                                                            int tiles_m, int tiles_n, int GM, int nb,
                                                            BSrc bsrc, Epi epi) {
     constexpr int BM = THIN_M, BN = THIN_N, D = THIN_SLOTS, ROWB = 128;

@@ -193,3 +193,23 @@ def test_gemm_duo_kernel_reads_are_waited_for(tmp_path):
         seen, bad = audit(body)
         assert seen >= 2 * 16, (name, seen)               # sixteen fragment reads in the loop and in its end
         assert not bad, (name, bad[:5])
+
+
+@pytest.fixture(scope="module")
+def thin_kernels(tmp_path_factory):
+    """Name and assembly of every instance of the thin GEMM loop."""
+    if shutil.which(HIPCC) is None:
+        pytest.skip("hipcc not found")
+    out = tmp_path_factory.mktemp("isa") / "gemm.s"
+    cmd = [HIPCC, *build.FLAGS, "-S", "--cuda-device-only", "-o", str(out), os.path.join(build.CSRC, "gemm.hip")]
+    r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    assert r.returncode == 0, r.stdout
+    kernels = re.findall(r"^(_ZN\S*gemm_thin_kernel\S*):[^\n]*\n(.*?)\.end_amdhsa_kernel", out.read_text(), flags=re.S | re.M)
+    assert len(kernels) == 6, [k[0] for k in kernels]
+    return kernels
+
+
+def test_gemm_thin_kernel_keeps_its_sums_in_one_register_file(thin_kernels):
+    """No sum of the thin loop is moved between vector and accumulation registers."""
+    for name, body in thin_kernels:
+        assert body.count("v_mfma_f32_16x16x32_bf16") >= 32 and "v_accvgpr" not in body, name
