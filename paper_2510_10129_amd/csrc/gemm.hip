@@ -117,7 +117,8 @@ __device__ __forceinline__ bf16x8 eight_columns(const f32x4& t0, const f32x4& t1
 }
 
 // What an epilogue does with 8 columns of a staged fp32 row (column c of it at c ^ swz).  `pre` loads what it needs from
-// memory besides, by the row's key (a load of its own), so that a kernel can ask for both early.  COLS: tile columns that
+// memory besides, by the row's key (a load of its own), so that a kernel can ask for both early; ASKS_BY_KEY: `pre` loads at an
+// address that the key gives.  COLS: tile columns that
 // make one output column.  A tile's threads are dealt over BN / COLS columns: with gate and up dealt over all BN, the
 // half at the up columns had nothing to do and each row cost twice its passes (gate/up of 3404 rows and d = 2048
 // 199.0 -> 182.9 us, d = 4096 593.4 -> 571.6; 883 rows 175.9 -> 167.3; 8192 rows 1332.7 -> 1282.2).
@@ -128,6 +129,7 @@ __device__ __forceinline__ bf16x8 eight_columns(const f32x4& t0, const f32x4& t1
 // 162.7 -> 156.7 and 59.5 -> 52.9; 883 rows, d = 4096 63.1 -> 60.6; 237 rows, d = 256 8.2 -> 7.4).
 struct EpiQKV {
     static constexpr int COLS = 2;                         // the two columns of a rotary pair (of a head of V: c and c + d_h/2)
+    static constexpr bool ASKS_BY_KEY = false;
     static constexpr bool DIRECT = false;                  // a column's rotary partner is in another wave
     const int32_t* idx;
     const bf16_t* bias;
@@ -193,6 +195,7 @@ struct EpiQKV {
 
 struct EpiOProj {
     static constexpr int COLS = 1;
+    static constexpr bool ASKS_BY_KEY = true;
     static constexpr bool DIRECT = true;
     const bf16_t* hidden;
     const int32_t* gather_idx;
@@ -258,6 +261,7 @@ struct EpiGateUp {
     int f;
     bf16_t* act;
     static constexpr int COLS = 2;                         // a gate and an up column
+    static constexpr bool ASKS_BY_KEY = false;
     static constexpr bool DIRECT = true;
     struct Pre {};
     __device__ __forceinline__ int key(int) const { return 0; }
@@ -291,6 +295,7 @@ struct EpiGateUp {
 
 struct EpiDown {
     static constexpr int COLS = 1;
+    static constexpr bool ASKS_BY_KEY = false;
     static constexpr bool DIRECT = true;
     const float* y;
     int d;
@@ -360,6 +365,7 @@ __device__ __forceinline__ int k_share(int K, int k_more, int64_t* first_byte) {
 template <int ROWS>
 struct EpiPartial {
     static constexpr int COLS = 1;
+    static constexpr bool ASKS_BY_KEY = false;
     static constexpr bool DIRECT = true;
     float* ws;
     int64_t share_stride;     // floats per share: slots * ROWS * BN
@@ -1825,9 +1831,18 @@ __global__ __launch_bounds__(512, 2) void gemm_thin_kernel(const bf16_t* __restr
     constexpr int TPR = BN / Epi::COLS / 8, RPP = 256 / TPR;       // threads per row, rows per pass
     const int cc = (tid % TPR) * 8;
     typename std::remove_const_t<decltype(e2)>::Pre pre[BM / RPP];
-    int key[BM / RPP];                                 // ahead of the first slices: loads return in order
+    // What the epilogue needs from memory is asked for ahead of the first slices (loads return in order).  Behind them the compiler,
+    // which cannot count the loads that a short K leaves out, waited for every slice before it asked and, with one row
+    // tile, again before the first and in the last ones (O by gathered rows, cold: 64 rows, d = 512 10.0 -> 8.8 us, 512 rows,
+    // d = 1024 12.3 -> 12.0; one row, d = 4096 26.7 -> 25.4; all of it behind the K loop 9.3, 13.1, 25.7).
+    int key[BM / RPP];
 #pragma unroll
     for (int k = 0; k < BM / RPP; ++k) key[k] = e2.key(min(m0 + tid / TPR + k * RPP, M - 1));
+    if constexpr (Epi::ASKS_BY_KEY)                    // one wait for all keys, then all loads by them
+#pragma unroll
+        for (int k = 0; k < BM / RPP; ++k) asm volatile("" : "+v"(key[k]));
+#pragma unroll
+    for (int k = 0; k < BM / RPP; ++k) pre[k] = e2.template pre<BN>(min(m0 + tid / TPR + k * RPP, M - 1), bn, cc, key[k]);
     auto k_loop = [&](auto streamc) __attribute__((always_inline)) {
         int rd = 0, wrs = D - 1;                       // slots of slice t and of slice t + D - 1
         // One slice, with at most `younger` slices' loads out when it is read.  The loads of slice t + D - 1 go
@@ -1878,9 +1893,6 @@ __global__ __launch_bounds__(512, 2) void gemm_thin_kernel(const bf16_t* __restr
         unrolled<D - 1>([&](auto tc) __attribute__((always_inline)) {
             if (tc.value < KT) unrolled<LPS>([&](auto xc) __attribute__((always_inline)) { load_one(xc, streamc, tc.value, tc.value); });
         });
-        // what the epilogue needs from memory, behind the first slices (a wait for one of them may wait for this too)
-#pragma unroll
-        for (int k = 0; k < BM / RPP; ++k) pre[k] = e2.template pre<BN>(min(m0 + tid / TPR + k * RPP, M - 1), bn, cc, key[k]);
         int t = 0;
         for (; t + D - 1 < KT; ++t) slice(std::true_type{}, std::integral_constant<int, D - 2>{}, t);
         // the last D - 1 slices (or all of a shorter K): nothing left to load

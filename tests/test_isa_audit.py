@@ -213,3 +213,18 @@ def test_gemm_thin_kernel_keeps_its_sums_in_one_register_file(thin_kernels):
     """No sum of the thin loop is moved between vector and accumulation registers."""
     for name, body in thin_kernels:
         assert body.count("v_mfma_f32_16x16x32_bf16") >= 32 and "v_accvgpr" not in body, name
+
+
+def test_gemm_thin_kernel_waits_for_slices_by_hand_alone(thin_kernels):
+    """From the first load of a slice to the epilogue, and in the blocks of the last slices behind it, every wait for loads is one
+    of the loop's own: a wait that the compiler adds for another load would be for all slices on their way."""
+    for name, body in thin_kernels:
+        lines, in_asm, made = body.split("\n"), False, []
+        at = [n for n, l in enumerate(lines) if l.strip().startswith("global_load_lds")][0]
+        out = [n for n, l in enumerate(lines) if l.strip().startswith(("ds_write", "global_store"))]
+        end = [n for n, l in enumerate(lines) if "v_mfma" in l and n < out[0]][-1]
+        for n, line in enumerate(lines):
+            in_asm = "#ASMSTART" in line or (in_asm and "#ASMEND" not in line)
+            if not in_asm and "vmcnt" in line and "s_waitcnt" in line and (at < n < end or n > out[-1]):
+                made.append((n, line.strip()))
+        assert at < end and not made, (name, made)
