@@ -1739,8 +1739,8 @@ __global__ __launch_bounds__(512, 2) void gemm_duo_kernel(
 // of 64x32; one barrier per slice; any K % 64 == 0.  Column tile bn starts bn slices into K and
 // wraps round: rows of a weight matrix are a power of two bytes apart as often as not, and
 // workgroups that walk K in step then ask the same few memory channels at any one time (a layer of
-// 64 rows, d = 4096: 176 us in step, 164 rotated).  With one row tile every line of B is read once and
-// is not kept in the caches (nt): 7.1 TB/s instead of 6.0 in a kernel of nothing but loads, gate/up below 48.7 -> 41.9;
+// 64 rows, d = 4096: 176 us in step, 164 rotated).  With one row tile every line of B is read once and,
+// where the plan says so, is not kept in the caches (nt): 7.1 TB/s instead of 6.0 in a kernel of nothing but loads, gate/up below 46 -> 41.4;
 // with more row tiles the others find it there (M = 128, O 19.3 us, 21.1 with nt).  The loads of a slice lie
 // between its fragment reads and MFMAs, in a loop without conditions (the last five slices are a loop of
 // their own): O and QKV at 16 rows 16.6 -> 16.2 and 17.7 -> 17.1.
@@ -1756,7 +1756,7 @@ __global__ __launch_bounds__(512, 2) void gemm_duo_kernel(
 constexpr int THIN_M = CC_THIN_M, THIN_N = CC_THIN_N, THIN_SLOTS = 6;
 template <class BSrc, class Epi>
 __global__ __launch_bounds__(512, 2) void gemm_thin_kernel(const bf16_t* __restrict__ A, int lda, int M, int K, int k_more,
-                                                           int tiles_m, int tiles_n, int GM, int nb,
+                                                           int tiles_m, int tiles_n, int GM, int nb, int stream,
                                                            BSrc bsrc, Epi epi) {
     constexpr int BM = THIN_M, BN = THIN_N, D = THIN_SLOTS, ROWB = 128;
     constexpr int A_L = 2, B_L = 4, LPS = A_L + B_L;   // loads of a wave and slice (8 rows each)
@@ -1901,7 +1901,7 @@ __global__ __launch_bounds__(512, 2) void gemm_thin_kernel(const bf16_t* __restr
             if (KT > after) slice(std::false_type{}, std::integral_constant<int, after>{}, t);
         });
     };
-    if (tiles_m == 1) k_loop(std::true_type{});        // every line of B is read once
+    if (stream) k_loop(std::true_type{});
     else k_loop(std::false_type{});
 
     // ---- epilogue through LDS as fp32 [BM][BN], column c of row r at c ^ 16*((r>>2)&3) ----
@@ -1942,12 +1942,12 @@ void launch_gemm(const bf16_t* A, int lda, int M, int N_tiles_cols, int K, int l
         const int nt = tiles_m * tiles_n;
         if (S == 1) {
             hipLaunchKernelGGL((gemm_thin_kernel<BSrc, Epi>), dim3(nt), dim3(256), 0, s, A, lda, M, K, 0, tiles_m, tiles_n,
-                               GM, nt, bsrc, epi);
+                               GM, nt, plan.stream, bsrc, epi);
         } else {
             constexpr int SLOT = THIN_M * THIN_N;
             EpiPartial<THIN_M> pe{ws, (int64_t)nt * SLOT, 0, 0};
             hipLaunchKernelGGL((gemm_thin_kernel<BSrc, EpiPartial<THIN_M>>), dim3(nt, S), dim3(256), 0, s, A, lda, M,
-                               K / 64 / S * 64, K / 64 % S, tiles_m, tiles_n, GM, nt, bsrc, pe);
+                               K / 64 / S * 64, K / 64 % S, tiles_m, tiles_n, GM, nt, plan.stream, bsrc, pe);
             hipLaunchKernelGGL((splitk_finish_kernel<THIN_M, THIN_N, Epi>), dim3(nt, THIN_M * THIN_N / 2048), dim3(256), 0, s,
                                ws, (int64_t)nt * SLOT, S, M, THIN_M, 0, tiles_m, tiles_n, GM, epi);
         }

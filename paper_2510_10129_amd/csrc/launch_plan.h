@@ -93,7 +93,15 @@ struct cc_gemm_plan {
     int shares;
     bool duo;       // 'h', 's': the duo loop (else the ring loop)
     int cuts;       // > 1: as shares, where K's groups do not divide evenly among them, and for 'h'
+    bool stream;    // 't': the weights go past the caches
 };
+// Weights that one row tile reads, each line once, go past the caches from 96 MB on, or for up to 16 rows.  Event us with nt
+// loads / without, weights cold: 117 MB 24.8 / 26.5 (8 rows), 28.3 / 31.2 (64); 101 MB 22.2 / 23.7, 26.4 / 28.6; 50 MB (QKV, d = 4096)
+// 15.6 / 16.4, 16.3 / 16.9 (16), 17.9 / 17.7 (40), 19.7 / 18.8 (64); 34 MB (O) 13.4 / 13.7, 13.5 / 13.9, 15.6 / 15.0, 17.8 / 16.3.  Weights that the
+// 256 MB cache holds from the call before, 67 MB: 17.5 / 16.9 (16), 21.4 / 19.5 (64); 55 MB 15.5 / 13.5, 19.2 / 14.8.
+inline bool cc_gemm_streams(int M, int N, int K) {
+    return M <= CC_THIN_M && (M <= 16 || 2.0 * N * K >= 96e6);
+}
 inline cc_gemm_plan cc_plan_gemm(int n_cu, int M, int N, int K, int64_t lda, int64_t ldb, bool ws, int64_t ws_floats,
                                  const cc_launch_override& ovr) {
     const char force = (char)ovr.gemm_tile;                   // 0: the launcher's choice
@@ -199,7 +207,7 @@ inline cc_gemm_plan cc_plan_gemm(int n_cu, int M, int N, int K, int64_t lda, int
     };
     if (thin_ok && force == 't') {
         const int sp = ovr.gemm_splitk;
-        return {'t', ring, sp > 1 && (K / 64) % sp == 0 && thin_split_ok(sp) ? sp : 1, false, 1};
+        return {'t', ring, sp > 1 && (K / 64) % sp == 0 && thin_split_ok(sp) ? sp : 1, false, 1, cc_gemm_streams(M, N, K)};
     }
     if (thin_ok && !force && !ovr.gemm_staged && !ovr.gemm_mfma32 && ovr.gemm_splitk == 0) {
         double t_thin = 0.96 * t_best;
@@ -213,7 +221,7 @@ inline cc_gemm_plan cc_plan_gemm(int n_cu, int M, int N, int K, int64_t lda, int
         }
     }
     const bool even = pick != 'h' && K % ((pick == 't' ? 64 : CC_GEMM_GROUP) * S) == 0;
-    return {pick, ring, even ? S : 1, pick == 'h' ? duo_h : pick == 's' && duo_s, even ? 1 : S};
+    return {pick, ring, even ? S : 1, pick == 'h' ? duo_h : pick == 's' && duo_s, even ? 1 : S, pick == 't' && cc_gemm_streams(M, N, K)};
 }
 
 // ---- selection: one workgroup up to CC_SEL_ONE_MAX tokens (five rows of 4096 keys in LDS; 6.5 us and 0.36 us more per

@@ -34,6 +34,10 @@ void plan_gemm_cuts(int M, int N, int K, int64_t ws_floats, int* out) {
     const cc_gemm_plan p = cc_plan_gemm(256, M, N, K, K, K, ws_floats > 0, ws_floats, cc_launch_override{});
     out[0] = p.tile, out[1] = p.shares, out[2] = p.cuts;
 }
+int plan_gemm_stream(int M, int N, int K, int64_t ws_floats) {
+    const cc_gemm_plan p = cc_plan_gemm(256, M, N, K, K, K, ws_floats > 0, ws_floats, cc_launch_override{});
+    return p.stream ? p.tile : 0;
+}
 int norm_waves(int n_cu, int M, int d, int elem_bytes) { return cc_norm_waves(n_cu, M, d, elem_bytes); }
 int asm_rows(int64_t n_rows, int width) { return cc_asm_rows(n_rows, width); }
 int select_uses_ranges(int T) { return cc_select_uses_ranges(T); }
@@ -217,6 +221,18 @@ def test_rows_of_an_assembly_wave(plan, n_rows, width, rows):
 ])
 def test_loop_of_the_smaller_tiles(plan, M, N, K, tile, duo):
     assert bool(plan.plan_gemm_duo(256, M, N, K, ord(tile))) == duo
+
+
+@pytest.mark.parametrize("M,N,K,stream", [
+    (64, 4096, 14336, True), (64, 4096, 12288, True), (64, 28672, 4096, True),     # cold 28.3 us against 31.2; 26.4, 28.6; 41.4, 46
+    (64, 4096, 4096, False), (64, 6144, 4096, False), (40, 4096, 4096, False),     # 17.8, 16.3; 19.7, 18.8; 15.6, 15.0
+    (64, 17920, 1536, False), (64, 16384, 2048, False),                            # warm 19.2, 14.8; 21.4, 19.5
+    (16, 6144, 4096, True), (8, 4096, 4096, True),                                 # 16.3, 16.9; 13.4, 13.7
+    (65, 28672, 4096, False),                                                      # two row tiles
+])
+def test_weights_go_past_the_caches_where_that_was_measured_faster(plan, M, N, K, stream):
+    plan.plan_gemm_stream.argtypes = [C.c_int, C.c_int, C.c_int, C.c_int64]
+    assert bool(plan.plan_gemm_stream(M, N, K, 32 << 20)) == stream
 
 
 def cuts(plan, M, N, K, ws_floats=32 << 20):
