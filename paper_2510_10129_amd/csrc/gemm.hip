@@ -1302,10 +1302,10 @@ __device__ __forceinline__ bf16x8 lds_read16(uint32_t addr) {
 // through LDS the tile was written a word at a time behind two barriers a half (M = 8192, before -> after: O 239.6 -> 229.9
 // us for d = 4096, 210.7 -> 200.7 for 3584, 77.5 -> 72.4 for 2048, gate/up 1352.7 -> 1339.1, 1604.7 -> 1591.1, 421.8 -> 417.0;
 // down the same, and 5 % more with 8-byte stores, which is why lanes trade columns first).
-template <class BSrc, class Epi>
-__global__ __launch_bounds__(512, 2) void gemm_pingpong_kernel(
+template <bool DIRECT, class BSrc, class Epi>
+__device__ __forceinline__ void pingpong(
     const bf16_t* __restrict__ A, int lda, int M, int K, int k_more, int tiles_m, int tiles_n, int GM, int nb, int vb0,
-    BSrc bsrc, Epi epi) {
+    const BSrc& bsrc, const Epi& epi) {
     constexpr int H = 128, BM = 2 * H, BN = 2 * H;
     constexpr int UM = 4, UN = 2;                      // 16x16 accumulator tiles of a wave in one quadrant
     constexpr int LPH = 2;                             // loads of a wave per half tile
@@ -1415,8 +1415,8 @@ __global__ __launch_bounds__(512, 2) void gemm_pingpong_kernel(
             for (int i = 0; i < UM; ++i)
 #pragma unroll
                 for (int j = 0; j < UN; ++j)
-                    c[i][j] = Epi::DIRECT ? __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[ks][j], af[ks][i], c[i][j], 0, 0, 0)
-                                          : __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[ks][i], b[ks][j], c[i][j], 0, 0, 0);
+                    c[i][j] = DIRECT ? __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[ks][j], af[ks][i], c[i][j], 0, 0, 0)
+                                     : __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[ks][i], b[ks][j], c[i][j], 0, 0, 0);
         __builtin_amdgcn_sched_barrier(0);
         wg_barrier();
     };
@@ -1474,7 +1474,7 @@ __global__ __launch_bounds__(512, 2) void gemm_pingpong_kernel(
 #undef CC_IC
 
     const auto e2 = epi_for_tile(epi, vb - vb0, m0);
-    if constexpr (Epi::DIRECT) {
+    if constexpr (DIRECT) {
         // ---- epilogue from the registers (lane L has columns 4 (L/16) .. + 3 of row L%16 of a 16x16 tile): no pass through
         //      LDS and no barrier, so the waves that are done store while the others still multiply ----
         const int cl = wc * (H / 4) + 4 * fk;
@@ -1532,6 +1532,22 @@ __global__ __launch_bounds__(512, 2) void gemm_pingpong_kernel(
             if (m < M) e2.template operator()<BN>(m, bn, cc, stage + r * BN, ((r >> 2) & 3) << 4);
         }
     }
+}
+
+template <class BSrc, class Epi>
+__global__ __launch_bounds__(512, 2) void gemm_pingpong_kernel(
+    const bf16_t* __restrict__ A, int lda, int M, int K, int k_more, int tiles_m, int tiles_n, int GM, int nb, int vb0,
+    BSrc bsrc, Epi epi) {
+    pingpong<Epi::DIRECT>(A, lda, M, K, k_more, tiles_m, tiles_n, GM, nb, vb0, bsrc, epi);
+}
+// Shares of K with the operands as QKV has them and the sums through LDS.  Row tiles that end past M read their last row again
+// and again; as the second operand of the MFMAs such rows cost power, and with it clocks, even where nothing is stored
+// (65 rows, d = 8192, down in 8 shares: 93.5 us this way, 123 from the accumulators, 120.6 with the stores left out).
+template <class BSrc, class Epi>
+__global__ __launch_bounds__(512, 2) void gemm_pingpong_parts_kernel(
+    const bf16_t* __restrict__ A, int lda, int M, int K, int k_more, int tiles_m, int tiles_n, int GM, int nb, int vb0,
+    BSrc bsrc, Epi epi) {
+    pingpong<false>(A, lda, M, K, k_more, tiles_m, tiles_n, GM, nb, vb0, bsrc, epi);
 }
 
 // ------------------------------------------------------------------ duo loop
@@ -1962,8 +1978,8 @@ void launch_gemm(const bf16_t* A, int lda, int M, int N_tiles_cols, int K, int l
 #define CC_LAUNCH(KERN, BM_, BN_, WM_, WN_, EPI_T, EPI_V, NB_, VB0_, GY_)                              \
     hipLaunchKernelGGL((KERN<BM_, BN_, WM_, WN_, BSrc, EPI_T>), dim3(NB_, GY_), dim3(WM_ * WN_ * 64), 0, s, A, \
                        lda, M, groups / (GY_) * CC_GEMM_GROUP, groups % (GY_), tiles_m, tiles_n, GM, NB_, VB0_, bsrc, EPI_V)
-#define CC_LAUNCH_PP(EPI_T, EPI_V, NB_, VB0_, GY_)                                                      \
-    hipLaunchKernelGGL((gemm_pingpong_kernel<BSrc, EPI_T>), dim3(NB_, GY_), dim3(512), 0, s, A, lda, M,    \
+#define CC_LAUNCH_PP(KERN, EPI_T, EPI_V, NB_, VB0_, GY_)                                                \
+    hipLaunchKernelGGL((KERN<BSrc, EPI_T>), dim3(NB_, GY_), dim3(512), 0, s, A, lda, M,    \
                        groups / (GY_) * CC_GEMM_GROUP, groups % (GY_), tiles_m, tiles_n, GM, NB_, VB0_, bsrc, EPI_V)
 #define CC_LAUNCH_DUO(BM_, EPI_T, EPI_V, NB_, VB0_, GY_)                                                    \
     hipLaunchKernelGGL((gemm_duo_kernel<BM_, BSrc, EPI_T>), dim3(NB_, GY_), dim3(512), 0, s, A, lda, M,  \
@@ -1982,8 +1998,9 @@ void launch_gemm(const bf16_t* A, int lda, int M, int N_tiles_cols, int K, int l
         const int rem = n_tiles % n_cu == 0 ? n_cu : n_tiles % n_cu, full = n_tiles - rem;
         EpiPartial<256> pe{ws, (int64_t)rem * 65536, 0, 0};
         if (pick == 'b' && mfma16) {
-            if (full) CC_LAUNCH_PP(Epi, epi, full, 0, 1);
-            CC_LAUNCH_PP(EpiPartial<256>, pe, rem, full, S);
+            if (full) CC_LAUNCH_PP(gemm_pingpong_kernel, Epi, epi, full, 0, 1);
+            if (plan.staged_parts) CC_LAUNCH_PP(gemm_pingpong_parts_kernel, EpiPartial<256>, pe, rem, full, S);
+            else CC_LAUNCH_PP(gemm_pingpong_kernel, EpiPartial<256>, pe, rem, full, S);
         } else if (pick == 'b') {
             if (full) CC_LAUNCH(gemm_ring_kernel, 256, 256, 2, 4, Epi, epi, full, 0, 1);
             CC_LAUNCH(gemm_ring_kernel, 256, 256, 2, 4, EpiPartial<256>, pe, rem, full, S);
@@ -1997,7 +2014,7 @@ void launch_gemm(const bf16_t* A, int lda, int M, int N_tiles_cols, int K, int l
         hipLaunchKernelGGL((splitk_finish_kernel<256, 256, Epi>), dim3(rem, (bm + 7) / 8), dim3(256), 0, s, ws,
                            (int64_t)rem * 65536, S, M, bm, full, tiles_m, tiles_n, GM, epi);
     } else if (pick == 'b') {
-        if (ring && mfma16) CC_LAUNCH_PP(Epi, epi, n_tiles, 0, 1);
+        if (ring && mfma16) CC_LAUNCH_PP(gemm_pingpong_kernel, Epi, epi, n_tiles, 0, 1);
         else if (ring) CC_LAUNCH(gemm_ring_kernel, 256, 256, 2, 4, Epi, epi, n_tiles, 0, 1);
         else CC_LAUNCH_NT(256, 256, 2, 4);
     } else if (pick == 'm') {

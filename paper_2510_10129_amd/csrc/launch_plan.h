@@ -94,7 +94,15 @@ struct cc_gemm_plan {
     bool duo;       // 'h', 's': the duo loop (else the ring loop)
     int cuts;       // > 1: as shares, where K's groups do not divide evenly among them, and for 'h'
     bool stream;    // 't': the weights go past the caches
+    bool staged_parts;   // 'b' in shares: the sums leave through LDS instead of from the accumulators
 };
+// Sums of shares go through LDS where an eighth or more of the row tiles' rows lie past M (see gemm_pingpong_parts_kernel).
+// From the accumulators / through LDS: d = 8192, down, 65 rows 123 / 93.2, 128 125 / 104; d = 3584, down, 300 rows 79.0 / 68.3, 384 86.6 / 71.6,
+// 448 81.7 / 76.2, 560 95.0 / 90.6; 640 and 850 rows within 1 %;  d = 4096, down, 480 rows 67.6 / 71.2, 512 70.5 / 73.4; QKV 768 56.2 / 58.7.
+inline bool cc_gemm_stages_parts(int M) {
+    const int rows = (M + 255) / 256 * 256;
+    return 8 * (int64_t)(rows - M) >= rows;
+}
 // Weights that one row tile reads, each line once, go past the caches from 96 MB on, or for up to 16 rows.  Event us with nt
 // loads / without, weights cold: 117 MB 24.8 / 26.5 (8 rows), 28.3 / 31.2 (64); 101 MB 22.2 / 23.7, 26.4 / 28.6; 50 MB (QKV, d = 4096)
 // 15.6 / 16.4, 16.3 / 16.9 (16), 17.9 / 17.7 (40), 19.7 / 18.8 (64); 34 MB (O) 13.4 / 13.7, 13.5 / 13.9, 15.6 / 15.0, 17.8 / 16.3.  Weights that the
@@ -207,7 +215,7 @@ inline cc_gemm_plan cc_plan_gemm(int n_cu, int M, int N, int K, int64_t lda, int
     };
     if (thin_ok && force == 't') {
         const int sp = ovr.gemm_splitk;
-        return {'t', ring, sp > 1 && (K / 64) % sp == 0 && thin_split_ok(sp) ? sp : 1, false, 1, cc_gemm_streams(M, N, K)};
+        return {'t', ring, sp > 1 && (K / 64) % sp == 0 && thin_split_ok(sp) ? sp : 1, false, 1, cc_gemm_streams(M, N, K), false};
     }
     if (thin_ok && !force && !ovr.gemm_staged && !ovr.gemm_mfma32 && ovr.gemm_splitk == 0) {
         double t_thin = 0.96 * t_best;
@@ -221,7 +229,7 @@ inline cc_gemm_plan cc_plan_gemm(int n_cu, int M, int N, int K, int64_t lda, int
         }
     }
     const bool even = pick != 'h' && K % ((pick == 't' ? 64 : CC_GEMM_GROUP) * S) == 0;
-    return {pick, ring, even ? S : 1, pick == 'h' ? duo_h : pick == 's' && duo_s, even ? 1 : S, pick == 't' && cc_gemm_streams(M, N, K)};
+    return {pick, ring, even ? S : 1, pick == 'h' ? duo_h : pick == 's' && duo_s, even ? 1 : S, pick == 't' && cc_gemm_streams(M, N, K), pick == 'b' && S > 1 && cc_gemm_stages_parts(M)};
 }
 
 // ---- selection: one workgroup up to CC_SEL_ONE_MAX tokens (five rows of 4096 keys in LDS; 6.5 us and 0.36 us more per

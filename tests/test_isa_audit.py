@@ -196,17 +196,32 @@ def test_gemm_duo_kernel_reads_are_waited_for(tmp_path):
 
 
 @pytest.fixture(scope="module")
-def thin_kernels(tmp_path_factory):
-    """Name and assembly of every instance of the thin GEMM loop."""
+def gemm_kernels(tmp_path_factory):
+    """Name and assembly of every instance of a GEMM kernel, by the kernel's name."""
     if shutil.which(HIPCC) is None:
         pytest.skip("hipcc not found")
     out = tmp_path_factory.mktemp("isa") / "gemm.s"
     cmd = [HIPCC, *build.FLAGS, "-S", "--cuda-device-only", "-o", str(out), os.path.join(build.CSRC, "gemm.hip")]
     r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
     assert r.returncode == 0, r.stdout
-    kernels = re.findall(r"^(_ZN\S*gemm_thin_kernel\S*):[^\n]*\n(.*?)\.end_amdhsa_kernel", out.read_text(), flags=re.S | re.M)
+    text = out.read_text()
+    return lambda kernel: re.findall(r"^(_ZN\S*%s\S*):[^\n]*\n(.*?)\.end_amdhsa_kernel" % kernel, text, flags=re.S | re.M)
+
+
+@pytest.fixture(scope="module")
+def thin_kernels(gemm_kernels):
+    kernels = gemm_kernels("gemm_thin_kernel")
     assert len(kernels) == 6, [k[0] for k in kernels]
     return kernels
+
+
+def test_gemm_pingpong_parts_kernel_reads_are_waited_for(gemm_kernels):
+    kernels = gemm_kernels("gemm_pingpong_parts_kernel")
+    assert len(kernels) == 2, [k[0] for k in kernels]
+    for name, body in kernels:
+        seen, bad = audit(body)
+        assert seen == 4 + 3 * 24 + 20, (name, seen)
+        assert not bad, (name, bad[:5])
 
 
 def test_gemm_thin_kernel_keeps_its_sums_in_one_register_file(thin_kernels):

@@ -38,6 +38,10 @@ int plan_gemm_stream(int M, int N, int K, int64_t ws_floats) {
     const cc_gemm_plan p = cc_plan_gemm(256, M, N, K, K, K, ws_floats > 0, ws_floats, cc_launch_override{});
     return p.stream ? p.tile : 0;
 }
+int plan_gemm_staged_parts(int M, int N, int K, int64_t ws_floats) {
+    const cc_gemm_plan p = cc_plan_gemm(256, M, N, K, K, K, ws_floats > 0, ws_floats, cc_launch_override{});
+    return p.staged_parts ? p.tile : 0;
+}
 int norm_waves(int n_cu, int M, int d, int elem_bytes) { return cc_norm_waves(n_cu, M, d, elem_bytes); }
 int asm_rows(int64_t n_rows, int width) { return cc_asm_rows(n_rows, width); }
 int select_uses_ranges(int T) { return cc_select_uses_ranges(T); }
@@ -233,6 +237,18 @@ def test_loop_of_the_smaller_tiles(plan, M, N, K, tile, duo):
 def test_weights_go_past_the_caches_where_that_was_measured_faster(plan, M, N, K, stream):
     plan.plan_gemm_stream.argtypes = [C.c_int, C.c_int, C.c_int, C.c_int64]
     assert bool(plan.plan_gemm_stream(M, N, K, 32 << 20)) == stream
+
+
+@pytest.mark.parametrize("M,N,K,staged", [
+    (65, 8192, 28672, True), (128, 8192, 28672, True),                   # 93.2 us against 123 from the accumulators; 104, 125
+    (300, 3584, 18944, True), (448, 3584, 18944, True),                  # 68.3, 79.0; 76.2, 81.7
+    (480, 4096, 14336, False), (512, 4096, 14336, False),                # 71.2, 67.6; 73.4, 70.5
+    (3404, 28672, 4096, False),                                          # 4 % of the rows past M
+    (64, 4096, 4096, False),                                             # thin tiles
+])
+def test_sums_of_shares_go_through_lds_where_that_was_measured_faster(plan, M, N, K, staged):
+    plan.plan_gemm_staged_parts.argtypes = [C.c_int, C.c_int, C.c_int, C.c_int64]
+    assert plan.plan_gemm_staged_parts(M, N, K, 32 << 20) == (ord("b") if staged else 0)
 
 
 def cuts(plan, M, N, K, ws_floats=32 << 20):
