@@ -317,7 +317,7 @@ class Context:
                                             src.numel() * src.element_size()))
 
     # ---- test support ----
-    def debug_set_launch(self, gemm_tile: str = "", gemm_staged: bool = False, gemm_mfma32: bool = False,
+    def debug_set_launch(self, gemm_tile: str = "", gemm_staged: int = 0, gemm_mfma32: bool = False,
                          gemm_gm: int = 0, gemm_splitk: int = 0, attn_splits: int = 0):
         """Overrides the launch shapes until the next call; no arguments = the library's own choices."""
         o = LaunchOverride(ord(gemm_tile) if gemm_tile else 0, int(gemm_staged), int(gemm_mfma32), gemm_gm,

@@ -598,6 +598,7 @@ cc_status cc_debug_set_launch(cc_ctx* c, const cc_launch_override* o) {
     if (o->gemm_gm < 0 || o->gemm_splitk < 0 || o->gemm_splitk > 16 || o->attn_splits < 0 || o->attn_splits > 64)
         return fail(c, CC_ERR_SHAPE, "override values must be >= 0, gemm_splitk <= 16, attn_splits <= 64");
     c->ovr = *o;
+    if (c->ovr.gemm_staged != 0 && c->ovr.gemm_staged != 2 && c->ovr.gemm_staged != 3) c->ovr.gemm_staged = 1;
     return CC_OK;
 }
 

@@ -1951,7 +1951,7 @@ void launch_gemm(const bf16_t* A, int lda, int M, int N_tiles_cols, int K, int l
     const cc_gemm_plan plan = cc_plan_gemm(n_cu, M, N_tiles_cols, K, lda, ldb, ws != nullptr, ws_floats, ovr);
     const char pick = plan.tile;
     const bool ring = plan.ring, mfma16 = !ovr.gemm_mfma32;
-    const int S = std::max(plan.shares, plan.cuts);
+    const int S = plan.shares;
     if (pick == 't') {
         const int tiles_m = (M + THIN_M - 1) / THIN_M, tiles_n = (N_tiles_cols + THIN_N - 1) / THIN_N;
         const int GM = std::min(ovr.gemm_gm > 0 ? ovr.gemm_gm : 4, tiles_m);

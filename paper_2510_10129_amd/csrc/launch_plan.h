@@ -81,8 +81,9 @@ inline cc_attn_plan cc_plan_attention(int n_cu, int n_row_tiles, int H_kv, int d
 // LDS and L2 traffic per flop, one workgroup per CU), 'm' 192x256 (8 waves of 96x64, ring loop only), 'h' 256x128
 // (duo or ring loop, 8 waves of 64x64, one per CU), 's' 128x128 (duo loop, 8 waves of 64x64 in two groups along K, one per
 // CU; ring loop, 4 waves of 64x64, two per CU), 't' 64x128 (thin loop).
-// Where K is not a multiple of 128 the 256x256 and 128x128 shapes run the staged loop.  shares: of K ('b', 'm': of
-// the last round's tiles only; 't': of all). ----
+// Where K is not a multiple of 128 the 256x256 and 128x128 shapes run the staged loop.  shares: of K ('b', 'm', 'h': of
+// the last round's tiles only; 't': of all), in whole groups ('t': slices of 64 columns), the first ones longer by one where
+// they do not divide. ----
 #define CC_GEMM_SLICE 32            // K columns of a ring slice
 #define CC_GEMM_GROUP 128           // the ring and ping-pong loops take K in groups of this many columns
 #define CC_THIN_M 64
@@ -92,7 +93,6 @@ struct cc_gemm_plan {
     bool ring;
     int shares;
     bool duo;       // 'h', 's': the duo loop (else the ring loop)
-    int cuts;       // > 1: as shares, where K's groups do not divide evenly among them, and for 'h'
     bool stream;    // 't': the weights go past the caches
     bool staged_parts;   // 'b' in shares: the sums leave through LDS instead of from the accumulators
 };
@@ -162,7 +162,7 @@ inline cc_gemm_plan cc_plan_gemm(int n_cu, int M, int N, int K, int64_t lda, int
     // Split-K for the part of a grid that leaves most CUs idle: the tiles of a last round that
     // fills at most half the chip (all tiles, if there is no full round) are computed by S
     // workgroup rows, each over a share of K's groups, with S x tiles <= CUs, and a finishing pass; the full
-    // rounds before them run as a launch of their own.  256-row tiles only.  The extra launches and
+    // rounds before them run as a launch of their own.  256x256, 192x256 and 256x128 tiles, in slots of 256 rows.  The extra launches and
     // the shares' traffic cost 4.3 us and 6.8 TB/s; the estimate has to be 2 % below the unsplit one.
     // Shares need not be equal: 84 tiles of 256x256 over 148 groups take 2 shares, 168 workgroups, if they have to be,
     // 3 and 252 if not (M = 1523, N = 3584, K = 18944: 203 -> 173 us with the finishing pass).
@@ -182,8 +182,8 @@ inline cc_gemm_plan cc_plan_gemm(int n_cu, int M, int N, int K, int64_t lda, int
         };
         if (ovr.gemm_splitk > 0) {
             const int sp = ovr.gemm_splitk;
-            const Shape& h = shapes[pick == 'm' ? 1 : 0];
-            if (sp > 1 && sp <= 16 && groups % sp == 0 && split_ok(h, sp, CC_GEMM_GROUP)) S = sp, pick = h.tile;
+            const Shape& h = shapes[pick == 'm' ? 1 : force == 'h' && !ovr.gemm_mfma32 ? 2 : 0];
+            if (sp > 1 && sp <= 16 && split_ok(h, sp, CC_GEMM_GROUP)) S = sp, pick = h.tile;
         } else if (!force && !ovr.gemm_staged) {
             const double t_unsplit = t_best;
             for (const Shape& h : shapes) {
@@ -215,7 +215,7 @@ inline cc_gemm_plan cc_plan_gemm(int n_cu, int M, int N, int K, int64_t lda, int
     };
     if (thin_ok && force == 't') {
         const int sp = ovr.gemm_splitk;
-        return {'t', ring, sp > 1 && (K / 64) % sp == 0 && thin_split_ok(sp) ? sp : 1, false, 1, cc_gemm_streams(M, N, K), false};
+        return {'t', ring, sp > 1 && thin_split_ok(sp) ? sp : 1, false, cc_gemm_streams(M, N, K), false};
     }
     if (thin_ok && !force && !ovr.gemm_staged && !ovr.gemm_mfma32 && ovr.gemm_splitk == 0) {
         double t_thin = 0.96 * t_best;
@@ -228,8 +228,8 @@ inline cc_gemm_plan cc_plan_gemm(int n_cu, int M, int N, int K, int64_t lda, int
             if (t < t_thin) t_thin = t, pick = 't', S = sp;
         }
     }
-    const bool even = pick != 'h' && K % ((pick == 't' ? 64 : CC_GEMM_GROUP) * S) == 0;
-    return {pick, ring, even ? S : 1, pick == 'h' ? duo_h : pick == 's' && duo_s, even ? 1 : S, pick == 't' && cc_gemm_streams(M, N, K), pick == 'b' && S > 1 && cc_gemm_stages_parts(M)};
+    return {pick, ring, S, pick == 'h' ? duo_h : pick == 's' && duo_s, pick == 't' && cc_gemm_streams(M, N, K),
+            pick == 'b' && S > 1 && cc_gemm_stages_parts(M)};
 }
 
 // ---- selection: one workgroup up to CC_SEL_ONE_MAX tokens (five rows of 4096 keys in LDS; 6.5 us and 0.36 us more per

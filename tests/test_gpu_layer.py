@@ -420,6 +420,9 @@ def test_stage_attention_even_grid(H_q, H_kv, d_h, N, M, splits):
 
 
 # (H_q, H_kv, d_h, N, M): grids whose blocks are cut into runs of key tiles
+SHARES_MODEL = ModelShape(640, 10, 10, 64, 1024, 1e4, 1e-5, True, 1)
+FORCED_SHARES = [(tile, shares, M, 700) for tile in "bht" for shares in (2, 3, 5) for M in (300, 130)] + \
+    [("h", 3, 4400, 4400), ("h", 5, 4400, 4400), ("b", 3, 4400, 4400)]      # tile, shares of K, rows, rows of the context
 UNEVEN_SHARES = [(40, 128, 896), (200, 2304, 6656), (513, 2304, 9984)]     # rows, d, f of a down projection
 CUT_SHAPES = [(8, 8, 128, 1300, 40), (14, 2, 64, 700, 257), (32, 1, 128, 229, 1), (12, 3, 128, 600, 64), (64, 2, 64, 300, 9),
               (16, 16, 128, 2050, 20)]
@@ -570,7 +573,7 @@ def test_stage_norms_widths_and_waves(d, M):
 def test_stage_projections_against_oracle_pieces(tile, splitk, mfma):
     """Every projection against the oracle's pieces, by default, with each GEMM tile shape and K
     loop forced (the 256x256 tile with its 16x16x32 loop and with the 32x32x16 one), and with 2, 3
-    and 4 shares of K (3 divides only the down projection's K here, 4 leaves a share of exactly one
+    and 4 shares of K (3 are unequal but for the down projection's K, 4 leave a share of exactly one
     ring of slices); forced through cc_debug_set_launch."""
     model = ModelShape(512, 8, 2, 64, 768, 1e4, 1e-5, True, 1)
     N, M = 500, 203
@@ -627,7 +630,7 @@ def test_stage_projections_against_oracle_pieces(tile, splitk, mfma):
 def test_stage_mlp_wide_grid_with_split_last_round(splitk, tile):
     """A gate/up grid of 258 tiles (one full round of workgroups and two tiles more): with two K
     shares forced the full round runs as one launch and the two remaining tiles as split-K with
-    the finishing pass; three shares divide only the down projection's K (2 tiles, split whole)."""
+    the finishing pass; of three shares only the down projection's K (2 tiles, split whole) has room."""
     model = ModelShape(256, 4, 2, 64, 16512, 1e4, 1e-5, False, 1)
     M = 300
     rng = np.random.default_rng(11)
@@ -884,8 +887,8 @@ def test_llama8b_layer_16k_every_slot_recomputed():
 @pytest.mark.parametrize("M,splitk", [(1, 0), (64, 0), (65, 3), (203, 0), (203, 5), (130, 7)])
 def test_stage_projections_on_thin_tiles(M, splitk):
     """64x128 tiles forced: partial and whole row tiles, columns past the last tile, K of fewer
-    slices (5) than the kernel has slots and of 7 and 15, shares of K down to one slice; a share
-    count that does not divide a projection's slices is ignored for it.  Same bounds as above."""
+    slices (5) than the kernel has slots and of 7 and 15, shares of K down to one slice and of
+    unequal length.  Same bounds as above."""
     model = ModelShape(320, 15, 5, 64, 448, 1e4, 1e-5, True, 1)
     N = 500
     rng = np.random.default_rng(M + splitk)
@@ -988,3 +991,54 @@ def test_stage_mlp_with_unequal_shares_of_k(M, d, f):
     mx, mn = err_stats(got[rows], z)
     assert mx <= MAX_ABS and mn <= MEAN_ABS, (mx, mn)
     ctx.close()
+
+
+def _check_projections(model, N, M, M_cap, seed, **override):
+    """All four projections of M rows under an override of the launch shapes, against the oracle; same bounds as above."""
+    rng = np.random.default_rng(seed)
+    w = gen.layer_weights(model, 0, seed=24)
+    xb = _x_bits(N, model.d, 8)
+    idx = np.sort(rng.choice(N, size=M, replace=False))
+    ctx = _ctx(model, N, M_cap)
+    ctx.debug_set_launch(**override)
+    dw, hid, xf = dev_weights(w), dev_bf16(xb), obf.bits_to_f64(xb[idx])
+    xn = torch.empty((M, model.d), dtype=torch.bfloat16, device=DEV)
+    ctx.step_gather_rmsnorm(hid, dev_i32(idx), M, dw.w_in_norm, xn)
+    Kd, Vd = (torch.zeros((N, model.H_kv, model.d_h), dtype=torch.bfloat16, device=DEV) for _ in range(2))
+    q = torch.empty((M, model.H_q * model.d_h), dtype=torch.bfloat16, device=DEV)
+    ctx.step_qkv_rope_scatter(xn, M, dev_i32(idx), dw.w_qkv, dw.b_qkv, cc.KVLayer(Kd, Vd), q, _lib.FLAG_CHECK_IDX)
+    q_ref, k_ref, v_ref = layer.qkv_rows(xf, w, model, idx)
+    for got, ref in ((host_bits(q).reshape(M, model.H_q, -1), q_ref), (host_bits(Kd)[idx], k_ref), (host_bits(Vd)[idx], v_ref)):
+        mx, mn = err_stats(bits_f64(got), ref)
+        assert mx <= MAX_ABS and mn <= MEAN_ABS, (mx, mn)
+    rest = np.setdiff1d(np.arange(N), idx)
+    assert not host_bits(Kd)[rest].any() and not host_bits(Vd)[rest].any()
+    ob = _x_bits(M, model.H_q * model.d_h, 9, 0.5)
+    y = torch.full((M + 1, model.d), 7.0, dtype=torch.float32, device=DEV)
+    ctx.step_oproj_residual(dev_bf16(ob), M, dw.w_o, hid, dev_i32(idx), y)
+    yf = y[:M].cpu().numpy().astype(np.float64)
+    y_ref = xf + obf.bits_to_f64(ob) @ obf.bits_to_f64(w["w_o"]).T
+    assert err_stats(yf, y_ref)[0] <= 1e-4 and bool((y[M] == 7.0).all())      # fp32 sums of exact bf16 products
+    out = torch.full((M + 1, model.d), 7.0, dtype=torch.bfloat16, device=DEV)
+    ctx.step_mlp(y, M, dw.w_post_norm, dw.w_gate, dw.w_up, dw.w_down, out)
+    torch.cuda.synchronize()
+    m = layer.rmsnorm(yf, obf.bits_to_f64(w["w_post_norm"]), model.rms_eps)
+    z = yf + (layer.silu(m @ obf.bits_to_f64(w["w_gate"]).T) * (m @ obf.bits_to_f64(w["w_up"]).T)) @ obf.bits_to_f64(w["w_down"]).T
+    mx, mn = err_stats(bits_f64(host_bits(out))[:M], z)
+    assert mx <= MAX_ABS and mn <= MEAN_ABS and bool((out[M] == 7.0).all()), (mx, mn)
+    ctx.close()
+
+
+@pytest.mark.parametrize("tile,shares,M,M_cap", FORCED_SHARES)
+def test_stage_projections_in_forced_shares(tile, shares, M, M_cap):
+    """2, 3 and 5 shares of K, for 5 and 8 groups of it (shares of unequal length), with 256x256, 256x128 and 64x128 tiles:
+    every finishing pass, several row tiles, a partial last row and column tile, and grids with a full round of workgroups
+    ahead of the tiles in shares."""
+    _check_projections(SHARES_MODEL, 4600, M, M_cap, M + shares, gemm_tile=tile, gemm_splitk=shares)
+
+
+@pytest.mark.parametrize("tile,M", [("s", 1), ("s", 129), ("s", 300), ("h", 127), ("h", 257)])
+def test_stage_projections_in_the_ring_loop(tile, M):
+    """128x128 and 256x128 tiles with the ring loop forced: K of one and three groups, partial row and column tiles."""
+    model = ModelShape(128, 2, 1, 64, 384, 1e4, 1e-5, True, 1)
+    _check_projections(model, 600, M, M, M, gemm_tile=tile, gemm_staged=3, gemm_splitk=1)

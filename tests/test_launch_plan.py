@@ -8,7 +8,7 @@ import pytest
 
 from paper_2510_10129_amd import build
 from paper_2510_10129_amd._lib import LaunchOverride
-from test_gpu_layer import CUT_SHAPES, UNEVEN_SHARES
+from test_gpu_layer import CUT_SHAPES, FORCED_SHARES, SHARES_MODEL, UNEVEN_SHARES
 
 CXX = shutil.which("g++") or shutil.which("c++")
 pytestmark = pytest.mark.skipif(CXX is None, reason="no host C++ compiler")
@@ -29,10 +29,6 @@ int plan_gemm_duo(int n_cu, int M, int N, int K, int tile) {
     o.gemm_tile = tile;
     const cc_gemm_plan p = cc_plan_gemm(n_cu, M, N, K, K, K, false, 0, o);
     return p.duo ? p.tile : 0;
-}
-void plan_gemm_cuts(int M, int N, int K, int64_t ws_floats, int* out) {
-    const cc_gemm_plan p = cc_plan_gemm(256, M, N, K, K, K, ws_floats > 0, ws_floats, cc_launch_override{});
-    out[0] = p.tile, out[1] = p.shares, out[2] = p.cuts;
 }
 int plan_gemm_stream(int M, int N, int K, int64_t ws_floats) {
     const cc_gemm_plan p = cc_plan_gemm(256, M, N, K, K, K, ws_floats > 0, ws_floats, cc_launch_override{});
@@ -80,21 +76,22 @@ def gemm(plan, M, N, K, n_cu=256, ws_floats=32 << 20, **ovr):
 
 
 def test_gemm_plans_fit_their_loops_and_workspace(plan):
-    """Every plan over a wide range of sizes: loops that divide K, shares that divide it further and
-    fit the workspace and one round; a forced shape is taken wherever it has a loop for K."""
+    """Every plan over a wide range of sizes: loops that divide K, no share without a group of K ('t': a slice), shares of a
+    round that fit one round and, in slots of their tiles, the workspace; a forced shape is taken wherever it has a loop for K."""
     for M in (1, 16, 64, 65, 200, 257, 883, 1523, 3404, 16576, 66000):
-        for N in (64, 192, 512, 4096, 6144, 28672):
-            for K in (64, 128, 192, 256, 448, 1984, 4096, 14336):
-                for ws in (0, 1 << 16, 32 << 20):
+        for N in (64, 192, 512, 1536, 3584, 4096, 6144, 28672, 37888):
+            for K in (64, 128, 192, 256, 448, 896, 1664, 1984, 3584, 4096, 8960, 14336, 18944):
+                for ws in (0, 1 << 16, 4 << 20, 32 << 20):
                     tile, shares = gemm(plan, M, N, K, ws_floats=ws)
-                    assert tile in ("bmhst" if K % 128 == 0 else "bst") and 1 <= shares <= 16 and K % (64 * shares) == 0
-                    bm, bn = {"b": (256, 256), "m": (192, 256), "h": (256, 128), "s": (128, 128), "t": (64, 128)}[tile]
+                    assert tile in ("bmhst" if K % 128 == 0 else "bst") and 1 <= shares <= 16
+                    bm, bn, slot = {"b": (256, 256, 65536), "m": (192, 256, 65536), "h": (256, 128, 32768), "s": (128, 128, 0),
+                                    "t": (64, 128, 8192)}[tile]
                     tiles = -(-M // bm) * -(-N // bn)
                     if shares > 1:
-                        assert tile in "bmt" and ws
+                        assert tile in "bmht" and ws
                         last = tiles if tile == "t" else (tiles % 256 or 256)
-                        assert last * shares <= 256 and last * shares * (8192 if tile == "t" else 65536) <= ws
-                        assert tile == "t" or K % (128 * shares) == 0
+                        assert last * shares <= 256 and last * shares * slot <= ws
+                        assert K // (64 if tile == "t" else 128) >= shares and (tile == "t" or K % 128 == 0)
                 for force in "bmhst":
                     want = force if K % 128 == 0 or force in "bst" else None
                     assert gemm(plan, M, N, K, gemm_tile=force)[0] in ((want,) if want else ("b", "s"))
@@ -251,17 +248,10 @@ def test_sums_of_shares_go_through_lds_where_that_was_measured_faster(plan, M, N
     assert plan.plan_gemm_staged_parts(M, N, K, 32 << 20) == (ord("b") if staged else 0)
 
 
-def cuts(plan, M, N, K, ws_floats=32 << 20):
-    plan.plan_gemm_cuts.argtypes = [C.c_int, C.c_int, C.c_int, C.c_int64, C.POINTER(C.c_int)]
-    out = (C.c_int * 3)()
-    plan.plan_gemm_cuts(M, N, K, ws_floats, out)
-    return chr(out[0]), out[1], out[2]
-
-
 @pytest.mark.parametrize("shape,tile,n", list(zip(UNEVEN_SHARES, "thb", (3, 7, 8))))
 def test_shapes_of_the_unequal_share_tests_are_cut(plan, shape, tile, n):
     M, d, f = shape
-    assert cuts(plan, M, d, f, min(32 << 20, 8 * M * -(-2 * f // 256) * 256)) == (tile, 1, n)
+    assert gemm(plan, M, d, f, ws_floats=min(32 << 20, 8 * M * -(-2 * f // 256) * 256)) == (tile, n)
 
 
 @pytest.mark.parametrize("M,N,K,tile,n", [
@@ -272,22 +262,18 @@ def test_shapes_of_the_unequal_share_tests_are_cut(plan, shape, tile, n):
     (64, 10240, 8192, "t", 3),          # 44.0, 38.6
 ])
 def test_unequal_shares_where_they_were_measured_faster(plan, M, N, K, tile, n):
-    assert cuts(plan, M, N, K) == (tile, 1, n)
+    assert gemm(plan, M, N, K) == (tile, n)
 
 
-def test_unequal_shares_fit_their_workspace(plan):
-    """Over a wide range of sizes: one round of workgroups, slots within the workspace, no empty share, and a plan has equal
-    shares or unequal ones."""
-    for M in (1, 64, 65, 200, 257, 883, 1523, 3404, 16576):
-        for N in (64, 192, 512, 1536, 3584, 6144, 37888):
-            for K in (64, 448, 896, 1664, 3584, 4096, 8960, 18944):
-                for ws in (0, 1 << 16, 4 << 20, 32 << 20):
-                    tile, shares, n = cuts(plan, M, N, K, ws)
-                    if n <= 1:
-                        continue
-                    assert shares == 1 and ws and n <= 16 and tile in "bmht"
-                    bm, bn, slot = {"b": (256, 256, 65536), "m": (192, 256, 65536), "h": (256, 128, 32768), "t": (64, 128, 8192)}[tile]
-                    tiles = -(-M // bm) * -(-N // bn)
-                    last = tiles if tile == "t" else (tiles % 256 or 256)
-                    assert last * n <= 256 and last * n * slot <= ws and K // (64 if tile == "t" else 128) >= n
-                    assert tile == "t" or K % 128 == 0
+@pytest.mark.parametrize("tile,shares,M,M_cap", FORCED_SHARES)
+def test_shapes_of_the_forced_share_tests_are_cut(plan, tile, shares, M, M_cap):
+    """Every projection of those tests in as many shares as forced, but for grids that leave no room for them."""
+    m, got = SHARES_MODEL, []
+    ws = min(32 << 20, 8 * M_cap * -(-max(2 * m.f, m.n_qkv) // 256) * 256)
+    for N, K in ((m.n_qkv, m.d), (m.d, m.H_q * m.d_h), (2 * m.f, m.d), (m.d, m.f)):
+        assert K % 128 == 0
+        got.append(gemm(plan, M, N, K, ws_floats=ws, gemm_tile=tile, gemm_splitk=shares))
+    fit = M <= 300 or tile == "h"
+    assert got[0] == got[2] == ((tile, shares) if fit else (tile, 1)) and (tile, shares) in got, got
+    if M > 4000:                        # a full round ahead of the tiles in shares
+        assert -(-M // 256) * -(-m.n_qkv // 128) > 256 and -(-M // 256) * -(-2 * m.f // 128) > 256
