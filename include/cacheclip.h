@@ -288,8 +288,8 @@ cc_status cc_calib_copy(cc_ctx* ctx, void* dst, const void* src, int64_t bytes);
  * o == NULL restores the library's own choices.  All-zero fields mean "no override".
  */
 typedef struct cc_launch_override {
-    int32_t gemm_tile;    /* 0, or 'b' 256x256, 'm' 192x256, 'h' 256x128, 's' 128x128, 't' 64x128 */
-    int32_t gemm_staged;  /* 1: the two-stage K loop (64 columns per stage) instead of the ring; 'h', 's': 2 the duo loop, 3 the ring loop */
+    int32_t gemm_tile;    /* 0, or 'b' 256x256, 'h' 256x128, 's' 128x128, 't' 64x128; 'm' is taken as 0 */
+    int32_t gemm_staged;  /* 1: the two-stage K loop (64 columns per stage) instead of the ring; 's': 2 the duo loop, 3 the ring loop */
     int32_t gemm_mfma32;  /* 1: the ring loop with 32x32x16 MFMAs instead of 16x16x32 */
     int32_t gemm_gm;      /* > 0: row tiles per band of the XCD-aware tile order */
     int32_t gemm_splitk;  /* > 0: shares of K (1 = never split) */

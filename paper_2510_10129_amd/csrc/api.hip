@@ -594,7 +594,7 @@ cc_status cc_debug_set_launch(cc_ctx* c, const cc_launch_override* o) {
     }
     const int t = o->gemm_tile;
     if (t != 0 && t != 'b' && t != 'm' && t != 'h' && t != 's' && t != 't')
-        return fail(c, CC_ERR_SHAPE, "gemm_tile must be 0, 'b', 'm', 'h', 's' or 't'");
+        return fail(c, CC_ERR_SHAPE, "gemm_tile must be 0, 'b', 'h', 's' or 't'");
     if (o->gemm_gm < 0 || o->gemm_splitk < 0 || o->gemm_splitk > 16 || o->attn_splits < 0 || o->attn_splits > 64)
         return fail(c, CC_ERR_SHAPE, "override values must be >= 0, gemm_splitk <= 16, attn_splits <= 64");
     c->ovr = *o;

@@ -16,8 +16,7 @@
 //          waves of a SIMD alternating between fragment reads and MFMAs.
 //   duo    (K % 128 == 0; gemm_duo_kernel, 256x128 and 128x128 where K is not short) K tiles of
 //          64 columns, 64x64 waves in two groups, a whole K tile per turn.
-//   ring16 (K % 128 == 0; gemm_ring16_kernel, 192x256 and, where K is short, 128x128; 256x128 as a
-//          cross-check behind cc_debug_set_launch) slices of 32 columns
+//   ring16 (K % 128 == 0; gemm_ring16_kernel, 128x128 where K is short) slices of 32 columns
 //          in a ring of four LDS slots; a slice is requested three slices (96 columns of
 //          MFMA work) before it is read, which hides the L2/fabric latency that a
 //          two-stage pipeline exposes; one barrier per slice, waits by explicit vmcnt;
@@ -778,17 +777,13 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gemm_ring_kernel(
     constexpr int NW = WAVES_M * WAVES_N;
     constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N;
     constexpr int TM = WM / 32, TN = WN / 32;
-    // DMA instructions per wave and slice.  Where the A_P 16-row pieces of A do not divide among
-    // the waves, the first A_FULL waves own A_I pieces and the others A_I - 1; those repeat
-    // their last piece so that every wave issues the same number of loads.
-    constexpr int A_P = BM / 16;
-    constexpr int A_I = (A_P + NW - 1) / NW, B_I = BN / 16 / NW;
-    constexpr int A_FULL = A_P - NW * (A_I - 1);
+    // DMA instructions per wave and slice
+    constexpr int A_I = BM / 16 / NW, B_I = BN / 16 / NW;
     constexpr int DPS = A_I + B_I;
     constexpr int SL = NW * DPS * 16 * BKS;
     // rows of a staged fp32 group: 32 if that fits in one slot and a wave's row blocks pair up, else 16
     constexpr int RG = (32 * BN * 4 <= SL * 2 && TM % (4 / WAVES_M) == 0) ? 32 : 16;
-    static_assert(BM % 16 == 0 && BN % (16 * NW) == 0 && BN % 32 == 0, "tile/waves");
+    static_assert(BM % (16 * NW) == 0 && BN % (16 * NW) == 0 && BN % 32 == 0, "tile/waves");
     static_assert(WM % 32 == 0 && WN % 32 == 0, "wave tile");
     static_assert(RG * BN * 4 <= SL * 2, "an fp32 row group fits in one slot");
     static_assert(DPS * (NS - 1) < 64, "vmcnt range");
@@ -820,9 +815,7 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gemm_ring_kernel(
     const int wave_u = __builtin_amdgcn_readfirstlane(wave);
 #pragma unroll
     for (int i = 0; i < A_I; ++i) {
-        const int piece = wave_u < A_FULL ? wave_u * A_I + i
-                                          : A_FULL * A_I + (wave_u - A_FULL) * (A_I - 1) + (i < A_I - 1 ? i : A_I - 2);
-        int r = piece * 16 + (lane >> 2);
+        int r = (wave_u * A_I + i) * 16 + (lane >> 2);
         const int c = (lane & 3) ^ ((r >> 2) & 3);
         r = r < a_rows ? r : a_rows - 1;
         ao[i] = (uint32_t)((r * lda + c * 8) * 2);
@@ -868,15 +861,8 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gemm_ring_kernel(
     auto row_at = [](int r, int is_b) {
         constexpr int per_b = 16 * B_I;
         if (is_b) return ((r / per_b) * DPS * 16 + A_I * 16 + r % per_b) * BKS;
-        const int piece = r / 16;
-        int w, i;
-        if (A_FULL == NW || piece < A_FULL * A_I) {
-            w = piece / A_I, i = piece % A_I;
-        } else {
-            const int q = piece - A_FULL * A_I;
-            w = A_FULL + q / (A_I > 1 ? A_I - 1 : 1), i = q % (A_I > 1 ? A_I - 1 : 1);
-        }
-        return (w * DPS * 16 + i * 16 + r % 16) * BKS;
+        constexpr int per_a = 16 * A_I;
+        return (r / per_a * DPS * 16 + r % per_a) * BKS;
     };
 
     f32x16 acc[TM][TN];
@@ -979,17 +965,13 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gemm_ring16_kernel(
     constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N;
     constexpr int TM = WM / 32;
     constexpr int UM = WM / 16, UN = WN / 16;       // 16x16 accumulator tiles per wave
-    // DMA instructions per wave and slice.  Where the A_P 16-row pieces of A do not divide among
-    // the waves, the first A_FULL waves own A_I pieces and the others A_I - 1; those repeat
-    // their last piece so that every wave issues the same number of loads.
-    constexpr int A_P = BM / 16;
-    constexpr int A_I = (A_P + NW - 1) / NW, B_I = BN / 16 / NW;
-    constexpr int A_FULL = A_P - NW * (A_I - 1);
+    // DMA instructions per wave and slice
+    constexpr int A_I = BM / 16 / NW, B_I = BN / 16 / NW;
     constexpr int DPS = A_I + B_I;
     constexpr int SL = NW * DPS * 16 * BKS;
     // rows of a staged fp32 group: 32 if that fits in one slot and a wave's row blocks pair up, else 16
     constexpr int RG = (32 * BN * 4 <= SL * 2 && TM % (4 / WAVES_M) == 0) ? 32 : 16;
-    static_assert(BM % 16 == 0 && BN % (16 * NW) == 0 && BN % 32 == 0, "tile/waves");
+    static_assert(BM % (16 * NW) == 0 && BN % (16 * NW) == 0 && BN % 32 == 0, "tile/waves");
     static_assert(WM % 32 == 0 && WN % 32 == 0, "wave tile");
     static_assert(RG * BN * 4 <= SL * 2, "an fp32 row group fits in one slot");
     static_assert(DPS * (NS - 1) < 64, "vmcnt range");
@@ -1021,9 +1003,7 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gemm_ring16_kernel(
     const int wave_u = __builtin_amdgcn_readfirstlane(wave);
 #pragma unroll
     for (int i = 0; i < A_I; ++i) {
-        const int piece = wave_u < A_FULL ? wave_u * A_I + i
-                                          : A_FULL * A_I + (wave_u - A_FULL) * (A_I - 1) + (i < A_I - 1 ? i : A_I - 2);
-        int r = piece * 16 + (lane >> 2);
+        int r = (wave_u * A_I + i) * 16 + (lane >> 2);
         const int c = (lane & 3) ^ ((r >> 1) & 3);
         r = r < a_rows ? r : a_rows - 1;
         ao[i] = (uint32_t)((r * lda + c * 8) * 2);
@@ -1072,22 +1052,15 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gemm_ring16_kernel(
     auto row_at = [](int r, int is_b) {
         constexpr int per_b = 16 * B_I;
         if (is_b) return ((r / per_b) * DPS * 16 + A_I * 16 + r % per_b) * BKS;
-        const int piece = r / 16;
-        int w, i;
-        if (A_FULL == NW || piece < A_FULL * A_I) {
-            w = piece / A_I, i = piece % A_I;
-        } else {
-            const int q = piece - A_FULL * A_I;
-            w = A_FULL + q / (A_I > 1 ? A_I - 1 : 1), i = q % (A_I > 1 ? A_I - 1 : 1);
-        }
-        return (w * DPS * 16 + i * 16 + r % 16) * BKS;
+        constexpr int per_a = 16 * A_I;
+        return (r / per_a * DPS * 16 + r % per_a) * BKS;
     };
 
     // ---- 16x16x32 MFMAs: one k-step per slice.  Lane L holds row (column) L%16 and the eight k
     //      values of 16-byte chunk L/16 of the slice row; an accumulator tile is f32x4 with
     //      row 4*(L/16) + v, column L%16 ----
     static_assert(UM % 2 == 0 && UM >= 4 && UN >= 2, "fragment ring");
-    static_assert((A_FULL != NW || WM % (16 * A_I) == 0) && WN % (16 * B_I) == 0, "fragment offsets are lane-independent");
+    static_assert(WM % (16 * A_I) == 0 && WN % (16 * B_I) == 0, "fragment offsets are lane-independent");
     static_assert(DPS <= 2 * UN, "one load per MFMA of a block's first part at most");
     f32x4 acc[UM][UN];
 #pragma unroll
@@ -1107,28 +1080,12 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gemm_ring16_kernel(
     // slots 0, 1 and 2, 3 share an address register each: the offset field of an LDS read is 16 bits
     static_assert(NS == 4, "slot pairs");
     const uint32_t a_addr[2] = {a_lane, a_lane + 2 * 2 * SL}, b_addr[2] = {b_lane, b_lane + 2 * 2 * SL};
-    // Where the pieces of A are not spread evenly (192-row tile) the fragments of a wave are not
-    // at the same distances for both wave rows: one address register per fragment and slot pair.
-    constexpr bool A_EVEN = A_FULL == NW;
-    uint32_t a_fr[A_EVEN ? 1 : UM][2];
-    if constexpr (!A_EVEN) {
-#pragma unroll
-        for (int i = 0; i < UM; ++i) {
-            a_fr[i][0] = ring_base + 2 * (row_at(wm0 + i * 16 + frow, 0) + sl);
-            a_fr[i][1] = a_fr[i][0] + 2 * 2 * SL;
-        }
-    }
     auto read_a = [&](auto jc, auto ic) __attribute__((always_inline)) -> bf16x8 {
         constexpr int j = decltype(jc)::value, i = decltype(ic)::value;
         bf16x8 v;
-        if constexpr (A_EVEN) {
-            constexpr int off = (j & 1) * 2 * SL + delta(i, 16 * A_I, DPS);
-            static_assert(off < 65536, "ds offset field");
-            asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(v) : "v"(a_addr[j >> 1]), "n"(off));
-        } else {
-            constexpr int off = (j & 1) * 2 * SL;
-            asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(v) : "v"(a_fr[i][j >> 1]), "n"(off));
-        }
+        constexpr int off = (j & 1) * 2 * SL + delta(i, 16 * A_I, DPS);
+        static_assert(off < 65536, "ds offset field");
+        asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(v) : "v"(a_addr[j >> 1]), "n"(off));
         return v;
     };
     auto read_b = [&](auto jc, auto ic) __attribute__((always_inline)) -> bf16x8 {
@@ -1969,7 +1926,7 @@ void launch_gemm(const bf16_t* A, int lda, int M, int N_tiles_cols, int K, int l
         }
         return;
     }
-    const int bm = pick == 's' ? 128 : pick == 'm' ? 192 : 256, bn = (pick == 'b' || pick == 'm') ? 256 : 128;
+    const int bm = pick == 's' ? 128 : 256, bn = pick == 'b' ? 256 : 128;
     const int tiles_m = (M + bm - 1) / bm, tiles_n = (N_tiles_cols + bn - 1) / bn;
     int GM = pick == 's' ? 2 * gm_big : gm_big;
     if (ovr.gemm_gm > 0) GM = ovr.gemm_gm;
@@ -1997,19 +1954,13 @@ void launch_gemm(const bf16_t* A, int lda, int M, int N_tiles_cols, int K, int l
     } else if (S > 1) {
         const int rem = n_tiles % n_cu == 0 ? n_cu : n_tiles % n_cu, full = n_tiles - rem;
         EpiPartial<256> pe{ws, (int64_t)rem * 65536, 0, 0};
-        if (pick == 'b' && mfma16) {
+        if (mfma16) {
             if (full) CC_LAUNCH_PP(gemm_pingpong_kernel, Epi, epi, full, 0, 1);
             if (plan.staged_parts) CC_LAUNCH_PP(gemm_pingpong_parts_kernel, EpiPartial<256>, pe, rem, full, S);
             else CC_LAUNCH_PP(gemm_pingpong_kernel, EpiPartial<256>, pe, rem, full, S);
-        } else if (pick == 'b') {
+        } else {
             if (full) CC_LAUNCH(gemm_ring_kernel, 256, 256, 2, 4, Epi, epi, full, 0, 1);
             CC_LAUNCH(gemm_ring_kernel, 256, 256, 2, 4, EpiPartial<256>, pe, rem, full, S);
-        } else if (mfma16) {
-            if (full) CC_LAUNCH(gemm_ring16_kernel, 192, 256, 2, 4, Epi, epi, full, 0, 1);
-            CC_LAUNCH(gemm_ring16_kernel, 192, 256, 2, 4, EpiPartial<256>, pe, rem, full, S);
-        } else {
-            if (full) CC_LAUNCH(gemm_ring_kernel, 192, 256, 2, 4, Epi, epi, full, 0, 1);
-            CC_LAUNCH(gemm_ring_kernel, 192, 256, 2, 4, EpiPartial<256>, pe, rem, full, S);
         }
         hipLaunchKernelGGL((splitk_finish_kernel<256, 256, Epi>), dim3(rem, (bm + 7) / 8), dim3(256), 0, s, ws,
                            (int64_t)rem * 65536, S, M, bm, full, tiles_m, tiles_n, GM, epi);
@@ -2017,13 +1968,8 @@ void launch_gemm(const bf16_t* A, int lda, int M, int N_tiles_cols, int K, int l
         if (ring && mfma16) CC_LAUNCH_PP(gemm_pingpong_kernel, Epi, epi, n_tiles, 0, 1);
         else if (ring) CC_LAUNCH(gemm_ring_kernel, 256, 256, 2, 4, Epi, epi, n_tiles, 0, 1);
         else CC_LAUNCH_NT(256, 256, 2, 4);
-    } else if (pick == 'm') {
-        if (mfma16) CC_LAUNCH(gemm_ring16_kernel, 192, 256, 2, 4, Epi, epi, n_tiles, 0, 1);
-        else CC_LAUNCH(gemm_ring_kernel, 192, 256, 2, 4, Epi, epi, n_tiles, 0, 1);
     } else if (pick == 'h') {
-        if (mfma16 && plan.duo) CC_LAUNCH_DUO(256, Epi, epi, n_tiles, 0, 1);
-        else if (mfma16) CC_LAUNCH(gemm_ring16_kernel, 256, 128, 4, 2, Epi, epi, n_tiles, 0, 1);
-        else CC_LAUNCH(gemm_ring_kernel, 256, 128, 4, 2, Epi, epi, n_tiles, 0, 1);
+        CC_LAUNCH_DUO(256, Epi, epi, n_tiles, 0, 1);
     } else {
         if (mfma16 && plan.duo) CC_LAUNCH_DUO(128, Epi, epi, n_tiles, 0, 1);
         else if (ring && mfma16) CC_LAUNCH(gemm_ring16_kernel, 128, 128, 2, 2, Epi, epi, n_tiles, 0, 1);

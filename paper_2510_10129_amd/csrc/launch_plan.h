@@ -78,10 +78,9 @@ inline cc_attn_plan cc_plan_attention(int n_cu, int n_row_tiles, int H_kv, int d
 }
 
 // ---- GEMM: C[M, N] = A[M, K] B[N, K]^T in row x column tiles.  tile: 'b' 256x256 (ping-pong loop, 8 waves, least
-// LDS and L2 traffic per flop, one workgroup per CU), 'm' 192x256 (8 waves of 96x64, ring loop only), 'h' 256x128
-// (duo or ring loop, 8 waves of 64x64, one per CU), 's' 128x128 (duo loop, 8 waves of 64x64 in two groups along K, one per
+// LDS and L2 traffic per flop, one workgroup per CU), 'h' 256x128 (duo loop, 8 waves of 64x64, one per CU), 's' 128x128 (duo loop, 8 waves of 64x64 in two groups along K, one per
 // CU; ring loop, 4 waves of 64x64, two per CU), 't' 64x128 (thin loop).
-// Where K is not a multiple of 128 the 256x256 and 128x128 shapes run the staged loop.  shares: of K ('b', 'm', 'h': of
+// Where K is not a multiple of 128 the 256x256 and 128x128 shapes run the staged loop.  shares: of K ('b', 'h': of
 // the last round's tiles only; 't': of all), in whole groups ('t': slices of 64 columns), the first ones longer by one where
 // they do not divide. ----
 #define CC_GEMM_SLICE 32            // K columns of a ring slice
@@ -92,7 +91,7 @@ struct cc_gemm_plan {
     char tile;
     bool ring;
     int shares;
-    bool duo;       // 'h', 's': the duo loop (else the ring loop)
+    bool duo;       // 's': the duo loop (else the ring or staged loop); 'h' always
     bool stream;    // 't': the weights go past the caches
     bool staged_parts;   // 'b' in shares: the sums leave through LDS instead of from the accumulators
 };
@@ -124,11 +123,11 @@ inline cc_gemm_plan cc_plan_gemm(int n_cu, int M, int N, int K, int64_t lda, int
     // 8320 rows, weights cold, every shape and most shares forced: 1032 calls, the choice 0.7 % above the fastest
     // on average (0.8 % since the epilogues are shorter; fitted anew 0.7 %).  The rates without the ring loops are of three more models (364 calls): there the large tile is no
     // faster than it was (M = 3000, N = 10880, K = 1984: three rounds of 256x256 179 us, four of 128x128 147).
-    // The ends count where K is short (K = 256, 2048 columns, M = 5120: 256x256 tiles 21.4 us, 192x256 19.1,
-    // 128x128 in the ring 18.4, with two of its tiles on a CU).
+    // The ends count where K is short (K = 256, 2048 columns, M = 5120: 256x256 tiles 21.4 us, 128x128 in the ring 18.4, with
+    // two of its tiles on a CU).
     struct Round { double ends, slice, more_ends, more_slice; };
-    const Round rb = ring ? Round{7.1, 0.41, 7.3, 0.151} : Round{21.6, 0.736, 0, 0}, rm = {9.2, 0.542, 5.65, 0.124},
-                rh = {7.8, 0.357, 2.3, 0.175}, rhd = {6.5, 0.298, 2.1, 0.104}, rsd = {7.6, 0.21, 0, 0.047};
+    const Round rb = ring ? Round{7.1, 0.41, 7.3, 0.151} : Round{21.6, 0.736, 0, 0},
+                rh = {6.5, 0.298, 2.1, 0.104}, rsd = {7.6, 0.21, 0, 0.047};
     // 128x128 tiles in the ring or staged loop: two on a CU, or one where there are no more
     const Round rs = ring ? Round{2.3, 0.6, 0, 0} : Round{11.9, 0.451, 0, 0},
                 rs_short = ring ? Round{3.9, 0.34, 2.1, 0.104} : Round{4.6, 0.497, 0, 0};
@@ -148,21 +147,19 @@ inline cc_gemm_plan cc_plan_gemm(int n_cu, int M, int N, int K, int64_t lda, int
                       (s_last == 0 ? 0.0 : s_last <= n_cu ? us(rs_short, (double)s_last / n_cu, 1) : us(rs, 1, 1));
     char pick = tb <= ts ? 'b' : 's';
     double t_best = std::min(tb, ts);
-    bool duo_h = false, duo_s = false;
-    if (ring) {                                                 // these have no staged variant
-        const double thr = grid_us(rh, 256, 128), thd = grid_us(rhd, 256, 128), tsd = grid_us(rsd, 128, 128);
-        const double tm = grid_us(rm, 192, 256), th = std::min(thr, thd);
-        duo_h = ovr.gemm_staged ? ovr.gemm_staged == 2 : thd < thr;
+    bool duo_s = false;
+    const bool half_tiles = ring && !ovr.gemm_mfma32;           // 256x128 has no other loop than the duo loop
+    if (ring) {
+        const double tsd = grid_us(rsd, 128, 128), th = grid_us(rh, 256, 128);
         duo_s = ovr.gemm_staged ? ovr.gemm_staged == 2 : tsd < ts;
         if (tsd < t_best) pick = 's', t_best = tsd;
-        if (th < t_best) pick = 'h', t_best = th;
-        if (tm < t_best) pick = 'm', t_best = tm;
+        if (half_tiles && th < t_best) pick = 'h', t_best = th;
     }
-    if (force == 'b' || force == 's' || ((force == 'h' || force == 'm') && ring)) pick = force;
+    if (force == 'b' || force == 's' || (force == 'h' && half_tiles)) pick = force;
     // Split-K for the part of a grid that leaves most CUs idle: the tiles of a last round that
     // fills at most half the chip (all tiles, if there is no full round) are computed by S
     // workgroup rows, each over a share of K's groups, with S x tiles <= CUs, and a finishing pass; the full
-    // rounds before them run as a launch of their own.  256x256, 192x256 and 256x128 tiles, in slots of 256 rows.  The extra launches and
+    // rounds before them run as a launch of their own.  256-row tiles only.  The extra launches and
     // the shares' traffic cost 4.3 us and 6.8 TB/s; the estimate has to be 2 % below the unsplit one.
     // Shares need not be equal: 84 tiles of 256x256 over 148 groups take 2 shares, 168 workgroups, if they have to be,
     // 3 and 252 if not (M = 1523, N = 3584, K = 18944: 203 -> 173 us with the finishing pass).
@@ -170,7 +167,7 @@ inline cc_gemm_plan cc_plan_gemm(int n_cu, int M, int N, int K, int64_t lda, int
     if (ring && ws) {
         const int groups = K / CC_GEMM_GROUP;
         struct Shape { char tile; int bm, bn; const Round& r; };
-        const Shape shapes[3] = {{'b', 256, 256, rb}, {'m', 192, 256, rm}, {'h', 256, 128, rhd}};
+        const Shape shapes[2] = {{'b', 256, 256, rb}, {'h', 256, 128, rh}};
         auto rem_of = [&](const Shape& h) {
             const long tiles = tiles_of(h.bm, h.bn);
             return (int)(tiles % n_cu == 0 && tiles > 0 ? n_cu : tiles % n_cu);
@@ -182,14 +179,14 @@ inline cc_gemm_plan cc_plan_gemm(int n_cu, int M, int N, int K, int64_t lda, int
         };
         if (ovr.gemm_splitk > 0) {
             const int sp = ovr.gemm_splitk;
-            const Shape& h = shapes[pick == 'm' ? 1 : force == 'h' && !ovr.gemm_mfma32 ? 2 : 0];
+            const Shape& h = shapes[force == 'h' && half_tiles];
             if (sp > 1 && sp <= 16 && split_ok(h, sp, CC_GEMM_GROUP)) S = sp, pick = h.tile;
         } else if (!force && !ovr.gemm_staged) {
             const double t_unsplit = t_best;
             for (const Shape& h : shapes) {
                 // 256x128 in shares: 192 rows and fewer keep to the wider tiles (tests pin that choice; at M = 192, N = 4096,
                 // K = 14336 it would be 47 us against 51)
-                if (h.tile == 'h' && (ovr.gemm_mfma32 || M <= 192)) continue;
+                if (h.tile == 'h' && (!half_tiles || M <= 192)) continue;
                 const long full_rounds = rounds_of(h.bm, h.bn) - 1;
                 const int rem = rem_of(h);
                 for (int sp = 2; sp <= 16; ++sp) {
@@ -228,7 +225,7 @@ inline cc_gemm_plan cc_plan_gemm(int n_cu, int M, int N, int K, int64_t lda, int
             if (t < t_thin) t_thin = t, pick = 't', S = sp;
         }
     }
-    return {pick, ring, S, pick == 'h' ? duo_h : pick == 's' && duo_s, pick == 't' && cc_gemm_streams(M, N, K),
+    return {pick, ring, S, pick == 'h' || (pick == 's' && duo_s), pick == 't' && cc_gemm_streams(M, N, K),
             pick == 'b' && S > 1 && cc_gemm_stages_parts(M)};
 }
 
