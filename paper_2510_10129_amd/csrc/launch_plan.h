@@ -102,12 +102,14 @@ inline bool cc_gemm_stages_parts(int M) {
     const int rows = (M + 255) / 256 * 256;
     return 8 * (int64_t)(rows - M) >= rows;
 }
-// Weights that one row tile reads, each line once, go past the caches from 96 MB on, or for up to 16 rows.  Event us with nt
-// loads / without, weights cold: 117 MB 24.8 / 26.5 (8 rows), 28.3 / 31.2 (64); 101 MB 22.2 / 23.7, 26.4 / 28.6; 50 MB (QKV, d = 4096)
-// 15.6 / 16.4, 16.3 / 16.9 (16), 17.9 / 17.7 (40), 19.7 / 18.8 (64); 34 MB (O) 13.4 / 13.7, 13.5 / 13.9, 15.6 / 15.0, 17.8 / 16.3.  Weights that the
-// 256 MB cache holds from the call before, 67 MB: 17.5 / 16.9 (16), 21.4 / 19.5 (64); 55 MB 15.5 / 13.5, 19.2 / 14.8.
+// Weights that one row tile reads, each line once, go past the caches, but for widths up to 640: a layer of those takes 13 MB at
+// most, and the 256 MB cache holds two dozen until their next call.  us of a whole layer, distinct layers in a row, all weights
+// past the caches / none (4224 slots; 64 rows, 8 rows):  6 layers of d = 4096 127.1 / 136.3, 107.6 / 116.9;  16 of 2048 78.7 / 81.0, 62.2 / 65.4;
+// 24 of 1024 61.1 / 62.5, 50.4 / 52.3;  24 of 768 58.9 / 60.7, 48.8 / 50.9;  24 of 576 54.9 / 53.8, 45.4 / 44.2;  24 of 512 50.8 / 48.5, 42.0 / 39.9.
+// QKV and O of d = 4096 by themselves are faster through the caches at 64 rows (18.7 against 19.7 us, 15.7 against 17.8); the layer
+// is not (129.1 against 127.9).
 inline bool cc_gemm_streams(int M, int N, int K) {
-    return M <= CC_THIN_M && (M <= 16 || 2.0 * N * K >= 96e6);
+    return M <= CC_THIN_M && (N < K ? N : K) > 640;
 }
 inline cc_gemm_plan cc_plan_gemm(int n_cu, int M, int N, int K, int64_t lda, int64_t ldb, bool ws, int64_t ws_floats,
                                  const cc_launch_override& ovr) {

@@ -224,10 +224,9 @@ def test_loop_of_the_smaller_tiles(plan, M, N, K, tile, duo):
 
 
 @pytest.mark.parametrize("M,N,K,stream", [
-    (64, 4096, 14336, True), (64, 4096, 12288, True), (64, 28672, 4096, True),     # cold 28.3 us against 31.2; 26.4, 28.6; 41.4, 46
-    (64, 4096, 4096, False), (64, 6144, 4096, False), (40, 4096, 4096, False),     # 17.8, 16.3; 19.7, 18.8; 15.6, 15.0
-    (64, 17920, 1536, False), (64, 16384, 2048, False),                            # warm 19.2, 14.8; 21.4, 19.5
-    (16, 6144, 4096, True), (8, 4096, 4096, True),                                 # 16.3, 16.9; 13.4, 13.7
+    (64, 4096, 14336, True), (64, 28672, 4096, True), (64, 4096, 4096, True),      # six layers in a row 127.1 us each, 136.3 through the caches
+    (8, 6144, 4096, True), (64, 16384, 2048, True), (64, 768, 3072, True),         # 107.6, 116.9; d = 2048 78.7, 81.0; 768 58.9, 60.7
+    (64, 3456, 576, False), (64, 512, 2048, False), (8, 768, 512, False),          # 54.9, 53.8; 50.8, 48.5; 42.0, 39.9
     (65, 28672, 4096, False),                                                      # two row tiles
 ])
 def test_weights_go_past_the_caches_where_that_was_measured_faster(plan, M, N, K, stream):
