@@ -122,14 +122,15 @@ inline cc_gemm_plan cc_plan_gemm(int n_cu, int M, int N, int K, int64_t lda, int
     // tiles, and 32 columns of K; and what both cost more where every CU has a tile (power, and the
     // traffic behind the caches) in proportion to the CUs that have one.
     // Fitted to event times of the four projections of nine models (d = 256 to 8192, f = 1024 to 28672), 1 to
-    // 8320 rows, weights cold, every shape and most shares forced: 1032 calls, the choice 0.7 % above the fastest
-    // on average (0.8 % since the epilogues are shorter; fitted anew 0.7 %).  The rates without the ring loops are of three more models (364 calls): there the large tile is no
+    // 8320 rows, weights cold, every shape and most shares forced; 256x128 and thin tiles fitted again with their present loops, to
+    // 1572 calls of those and two models without the ring loops: the choice 0.6 % above the fastest on average (1.3 % before).
+    // The rates without the ring loops are of 364 calls of such models: there the large tile is no
     // faster than it was (M = 3000, N = 10880, K = 1984: three rounds of 256x256 179 us, four of 128x128 147).
     // The ends count where K is short (K = 256, 2048 columns, M = 5120: 256x256 tiles 21.4 us, 128x128 in the ring 18.4, with
     // two of its tiles on a CU).
     struct Round { double ends, slice, more_ends, more_slice; };
     const Round rb = ring ? Round{7.1, 0.41, 7.3, 0.151} : Round{21.6, 0.736, 0, 0},
-                rh = {6.5, 0.298, 2.1, 0.104}, rsd = {7.6, 0.21, 0, 0.047};
+                rh = {6.1, 0.323, 2.87, 0.063}, rsd = {7.6, 0.21, 0, 0.047};
     // 128x128 tiles in the ring or staged loop: two on a CU, or one where there are no more
     const Round rs = ring ? Round{2.3, 0.6, 0, 0} : Round{11.9, 0.451, 0, 0},
                 rs_short = ring ? Round{3.9, 0.34, 2.1, 0.104} : Round{4.6, 0.497, 0, 0};
@@ -162,7 +163,7 @@ inline cc_gemm_plan cc_plan_gemm(int n_cu, int M, int N, int K, int64_t lda, int
     // fills at most half the chip (all tiles, if there is no full round) are computed by S
     // workgroup rows, each over a share of K's groups, with S x tiles <= CUs, and a finishing pass; the full
     // rounds before them run as a launch of their own.  256-row tiles only.  The extra launches and
-    // the shares' traffic cost 4.3 us and 6.8 TB/s; the estimate has to be 2 % below the unsplit one.
+    // the shares' traffic cost 4.45 us and 6.75 TB/s.
     // Shares need not be equal: 84 tiles of 256x256 over 148 groups take 2 shares, 168 workgroups, if they have to be,
     // 3 and 252 if not (M = 1523, N = 3584, K = 18944: 203 -> 173 us with the finishing pass).
     int S = 1;
@@ -184,29 +185,26 @@ inline cc_gemm_plan cc_plan_gemm(int n_cu, int M, int N, int K, int64_t lda, int
             const Shape& h = shapes[force == 'h' && half_tiles];
             if (sp > 1 && sp <= 16 && split_ok(h, sp, CC_GEMM_GROUP)) S = sp, pick = h.tile;
         } else if (!force && !ovr.gemm_staged) {
-            const double t_unsplit = t_best;
             for (const Shape& h : shapes) {
-                // 256x128 in shares: 192 rows and fewer keep to the wider tiles (tests pin that choice; at M = 192, N = 4096,
-                // K = 14336 it would be 47 us against 51)
-                if (h.tile == 'h' && (!half_tiles || M <= 192)) continue;
+                if (h.tile == 'h' && !half_tiles) continue;
                 const long full_rounds = rounds_of(h.bm, h.bn) - 1;
                 const int rem = rem_of(h);
                 for (int sp = 2; sp <= 16; ++sp) {
-                    if (!split_ok(h, sp, h.tile == 'h' ? 896 : 512)) continue;   // shorter ones: M = 256, N = K = 3584 27 us, thin 24
-                    const double t = full_rounds * us(h.r, 1, 1) + us(h.r, (double)rem * sp / n_cu, sp) + 4.3 +
-                                     (double)sp * rem * (256.0 * h.bn) * 4 / 6.8e6;
-                    if (t < t_best && t < 0.98 * t_unsplit) t_best = t, S = sp, pick = h.tile;
+                    if (!split_ok(h, sp, 512)) continue;
+                    const double t = full_rounds * us(h.r, 1, 1) + us(h.r, (double)rem * sp / n_cu, sp) + 4.45 +
+                                     (double)sp * rem * (256.0 * h.bn) * 4 / 6.75e6;
+                    if (t < t_best) t_best = t, S = sp, pick = h.tile;
                 }
             }
         }
     }
     // Few rows: 64x128 tiles (gemm_thin_kernel), K cut into shares where the grid leaves CUs idle.
-    // From the same measurements: 3 us for the ends of a round's tiles, 0.465 per 64 columns, the weights no faster
-    // than 7 TB/s, a finishing pass 2 and the shares' traffic at 4.2; the estimate has to be 4 % below the other.
+    // From the same measurements: 3.1 us for the ends of a round's tiles, 0.41 per 64 columns, the weights no faster
+    // than 7.7 TB/s, a finishing pass 2.3 and its rows' traffic at 3.4; the estimate has to be 2 % below the other.
     // Event microseconds (2.5 of them the events' own), d = 4096, f = 14336, 870 MB of other weights between two
-    // reads of one, the best of the thin tiles and of the larger ones:  M = 64: QKV 19.2 / 25.5, O 18.0 / 22.6, gate/up
-    // 41.9 / 52.9, down 28.2 / 38.1;  M = 128: 26.2 / 30.0, 19.2 / 26.5, 71.6 / 58.0, 40.8 / 44.5;  M = 192: 35.7 / 35.0, 25.5 /
-    // 30.0, 99.7 / 70.1, 61.1 / 50.1.
+    // reads of one, the best of the thin tiles and of the larger ones:  M = 64: QKV 18.3 / 25.7, O 15.7 / 22.5, gate/up
+    // 40.7 / 46.3, down 28.2 / 39.0;  M = 128: 24.8 / 27.0, 18.6 / 23.1, 67.3 / 52.9, 39.9 / 41.9;  M = 192: 33.0 / 30.4, 24.1 /
+    // 25.5, 92.4 / 65.0, 56.6 / 45.3.
     const long thin_tiles = tiles_of(CC_THIN_M, CC_THIN_N);
     const bool thin_ok = lda * CC_THIN_M * 2 < (1ll << 31) && ldb * CC_THIN_N * 2 < (1ll << 31);
     auto thin_split_ok = [&](int sp) {
@@ -217,14 +215,13 @@ inline cc_gemm_plan cc_plan_gemm(int n_cu, int M, int N, int K, int64_t lda, int
         return {'t', ring, sp > 1 && thin_split_ok(sp) ? sp : 1, false, cc_gemm_streams(M, N, K), false};
     }
     if (thin_ok && !force && !ovr.gemm_staged && !ovr.gemm_mfma32 && ovr.gemm_splitk == 0) {
-        double t_thin = 0.96 * t_best;
         for (int sp = 1; sp <= 16; ++sp) {
             if (sp > 1 && (!thin_split_ok(sp) || K / sp < 256 || thin_tiles * sp > n_cu)) continue;
             const long rounds = (thin_tiles * sp + n_cu - 1) / n_cu;
-            double t = rounds * ((K / 64 + sp - 1) / sp * 0.465 + 3.0);
-            t = std::max(t, 2.0 * N * K / 7.0e6);
-            if (sp > 1) t += 2.0 + (double)sp * thin_tiles * (CC_THIN_M * CC_THIN_N) * 8 / 4.2e6;
-            if (t < t_thin) t_thin = t, pick = 't', S = sp;
+            double t = rounds * ((K / 64 + sp - 1) / sp * 0.41 + 3.1);
+            t = std::max(t, 2.0 * N * K / 7.7e6);
+            if (sp > 1) t += 2.3 + (double)sp * M * N * 8 / 3.4e6;
+            if (t < 0.98 * t_best) t_best = t / 0.98, pick = 't', S = sp;
         }
     }
     return {pick, ring, S, pick == 'h' || (pick == 's' && duo_s), pick == 't' && cc_gemm_streams(M, N, K),

@@ -423,7 +423,7 @@ def test_stage_attention_even_grid(H_q, H_kv, d_h, N, M, splits):
 SHARES_MODEL = ModelShape(640, 10, 10, 64, 1024, 1e4, 1e-5, True, 1)
 FORCED_SHARES = [(tile, shares, M, 700) for tile in "bht" for shares in (2, 3, 5) for M in (300, 130)] + \
     [("h", 3, 4400, 4400), ("h", 5, 4400, 4400), ("b", 3, 4400, 4400)]      # tile, shares of K, rows, rows of the context
-UNEVEN_SHARES = [(40, 128, 896), (200, 2304, 6656), (513, 2304, 9984)]     # rows, d, f of a down projection
+UNEVEN_SHARES = [(40, 128, 896), (300, 2304, 7040), (513, 2304, 12160)]     # rows, d, f of a down projection
 CUT_SHAPES = [(8, 8, 128, 1300, 40), (14, 2, 64, 700, 257), (32, 1, 128, 229, 1), (12, 3, 128, 600, 64), (64, 2, 64, 300, 9),
               (16, 16, 128, 2050, 20)]
 
@@ -972,8 +972,8 @@ def test_stage_projections_in_the_duo_loop(tile, d, f, M):
 
 @pytest.mark.parametrize("M,d,f", UNEVEN_SHARES)
 def test_stage_mlp_with_unequal_shares_of_k(M, d, f):
-    """A down projection whose K is cut into shares of unequal length: thin tiles (14 slices in 3), 256x128 (52 groups of
-    128 columns in 7) and 256x256 (78 in 8).  Sampled rows, the first and last of every tile among them."""
+    """A down projection whose K is cut into shares of unequal length: thin tiles (14 slices in 3), 256x128 (55 groups of
+    128 columns in 7) and 256x256 (95 in 8).  Sampled rows, the first and last of every tile among them."""
     model = ModelShape(d, d // 64, d // 64, 64, f, 1e4, 1e-5, False, 1)
     rng = np.random.default_rng(f)
     wb = _x_bits(1, d, 7)[0]

@@ -111,7 +111,12 @@ def test_the_staged_loop_is_priced_by_its_own_rates(plan, M, N, K, tile):
     (64, 28672, 4096, "t"),             # few rows: 45.7 us against 57.4
     (192, 28672, 4096, "h"),            # 98.7 thin, 74.9
     (64, 4096, 4096, "t"),              # 17.2, 22.3
-    (192, 4096, 14336, "b"),            # 62 thin, 51 in shares
+    (192, 4096, 14336, "h"),            # 62 thin, 50.8 in shares of 256x256, 45.3 of 256x128
+    (192, 6144, 4096, "h"),             # 33.0 thin, 35.2, 30.4
+    (176, 10240, 8192, "h"),            # 59.7 thin, 58.0, 53.8
+    (1280, 3584, 3584, "b"),            # 55.2 in shares of 256x256, 65.5 in 256x128
+    (1152, 2880, 2880, "t"),            # 39.6, 54.5 in 128x128
+    (2048, 1024, 4096, "t"),            # 31.4, 39.0 in shares of 256x128
     (3404, 28672, 4096, "b"),
     (16576, 28672, 4096, "b"),
 ])
