@@ -6,8 +6,10 @@ from __future__ import annotations
 
 import ctypes as C
 import os
+import struct
 from array import array
 from dataclasses import dataclass
+from operator import index
 from typing import Optional, Sequence, Tuple
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
@@ -226,7 +228,7 @@ class Context:
     def _aux_blocks(blocks):
         """blocks: sequence of (attn cuda fp32 [H, Q_a, W], col0, len)."""
         first = None
-        flat = []                               # an _AuxBlock is an address, two strides and two 32-bit halves
+        flat = []
         for a, col0, ln in blocks:
             shape, st = a.shape, a.stride()
             if len(shape) != 3 or st[2] != 1:
@@ -237,10 +239,15 @@ class Context:
                 raise ValueError("all blocks must have the same H and Q_a")
             if col0 + ln > shape[2]:
                 raise ValueError("col0 + len exceeds the block's width")
-            flat += (a.data_ptr(), st[0], st[1], col0 & 0xFFFFFFFF | (ln & 0xFFFFFFFF) << 32)
+            flat += (a.data_ptr(), st[0], st[1], col0, ln)
         if first is None:
             return (_AuxBlock * 0)(), None, None
-        return (_AuxBlock * (len(flat) // 4)).from_buffer(array("Q", flat)), first[0], first[1]
+        n = len(flat) // 5
+        try:                                    # an _AuxBlock is an address, two strides and two 32-bit counts
+            packed = struct.pack("Pqqii" * n, *flat)
+        except struct.error as e:
+            raise TypeError(f"col0 and len must be 32-bit integers: {e}") from None
+        return (_AuxBlock * n).from_buffer_copy(packed), first[0], first[1]
 
     def step_block_scores(self, blocks, score):
         arr, H, Q_a = self._aux_blocks(blocks)
@@ -299,7 +306,7 @@ class Context:
     # ---- cache assembly ----
     def assemble_cache(self, chunk_K: Sequence, chunk_V: Sequence, P: int, n_tail: int, dst: KVLayer):
         """chunk_K[c], chunk_V[c]: cuda bf16 [P + L_c, H_kv, d_h], all with the same strides."""
-        n = len(chunk_K)
+        n, P = len(chunk_K), index(P)
         st = chunk_K[0].stride()
         assert st[2] == 1
         flat = []                               # a _Chunk is two addresses and a length padded to 8 bytes
