@@ -351,6 +351,17 @@ def test_crowded_selection_is_shared_by_the_workgroups(ctx):
     assert max(us.values()) < 3 * us["ordinary"], us
 
 
+def _ties_across_the_cut(T, k, n, rng):
+    """Scores that all differ but for n in a row by rank, of which the first k take about half."""
+    lo = min(max(k - n // 2, 0), max(T - n, 0))
+    by_rank = (1.0 - np.arange(T) / (2.0 * T)).astype(np.float32)
+    by_rank[lo:lo + n] = by_rank[lo]
+    a = np.empty((1, T), np.float32)
+    a[0, rng.permutation(T)] = by_rank
+    assert T <= n or not 0 < k < T or (lo < k < lo + n and (a == by_rank[lo]).sum() == n)
+    return a
+
+
 @pytest.mark.parametrize("window", [1, 16, 64, 65])
 @pytest.mark.parametrize("T", [1, 17, 64, 4095, 4097, 8192, 20480])
 def test_one_workgroup_selection_edges(ctx, T, window):
@@ -359,20 +370,15 @@ def test_one_workgroup_selection_edges(ctx, T, window):
     and all tokens; the count on the device is the one handed back."""
     rng = np.random.default_rng(T + window)
     spread = rng.random((1, T), dtype=np.float32)
-    cases = [spread, np.full((1, T), 0.25, np.float32), (1.0 + spread * 2.0 ** -13).astype(np.float32)]
-    for n in (64, 65):
-        a = spread.copy()
-        at = rng.permutation(T)[:n]
-        a[0, at] = np.float32(0.75)
-        cases.append(a)
     far = 1.0 + spread
     far[0, T // 2] = 0.0
-    cases.append(far)
-    for a in cases:
-        for bp in (0, 700, 2500, 10000):
-            At = torch.from_numpy(a).to(DEV)
-            n_dev = torch.full((1,), -1, dtype=torch.int32, device=DEV)
-            idx, n = ctx.select(At, bp, window, 0, 0, 5, 3, n_out=n_dev)
-            ref = osel.select(a, bp, window, 0, True, 5, 3)
-            assert n == len(ref) == int(n_dev.item())
-            assert np.array_equal(idx[:n].cpu().numpy(), ref)
+    cases = [(a, bp) for a in (spread, np.full((1, T), 0.25, np.float32), (1.0 + spread * 2.0 ** -13).astype(np.float32), far)
+             for bp in (0, 700, 2500, 10000)]
+    cases += [(_ties_across_the_cut(T, T * bp // 10000, n, rng), bp) for n in (64, 65) for bp in (700, 2500)]
+    for a, bp in cases:
+        At = torch.from_numpy(a).to(DEV)
+        n_dev = torch.full((1,), -1, dtype=torch.int32, device=DEV)
+        idx, n = ctx.select(At, bp, window, 0, 0, 5, 3, n_out=n_dev)
+        ref = osel.select(a, bp, window, 0, True, 5, 3)
+        assert n == len(ref) == int(n_dev.item())
+        assert np.array_equal(idx[:n].cpu().numpy(), ref)
