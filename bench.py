@@ -79,7 +79,7 @@ def algorithmic_work(model, idx_host, N, Q_a, T):
     keys = int((idx_host.astype("int64") + 1).sum())
     return {
         "colsum": ("hbm", Q_a * T * 4 + T * 4),
-        "select": ("hbm", T * 4 * 5 + M * 4),
+        "select": ("hbm", T * 4 + M * 4),
         "gather_norm": ("hbm", M * d * 2 * 2),
         "qkv": ("mfma", 2 * M * d * nqkv),
         "attn": ("mfma", 4 * dh * Hq * keys),
