@@ -30,8 +30,8 @@
 //   staged (any K % 64 == 0; gemm_nt_kernel) two stages of 64 columns, one barrier
 //          per stage, 32x32x16 MFMAs.
 // The accumulators are written back through LDS so that every global store is
-// 16 or 32 contiguous bytes per lane along the row; those of the ping-pong loop, but for QKV, from the registers,
-// 16 bytes a lane.
+// 16 or 32 contiguous bytes per lane along the row; those of the ping-pong loop, but for QKV and for
+// shares of a grid with many rows past M, from the registers, 16 bytes a lane.
 #include "cc_internal.h"
 #include "launch_plan.h"
 #include <algorithm>
@@ -1515,16 +1515,18 @@ __global__ __launch_bounds__(512, 2) void gemm_pingpong_parts_kernel(
 // take the even and the odd K tiles (each holds sums of the whole tile, added at the end), for a 64x32
 // wave would read half as much again per MFMA.
 //
-// What bounds it: a CU takes in 150 KB/us that the L2 holds but only 55 to 60 of lines that it does not
-// (a kernel of nothing but loads, any number in flight), and a tile of these shapes asks for 48 or 32 KB
-// per 64 columns.  With every load in the same column 128x128 takes 0.27 us per K tile, with real addresses
-// 0.56; the L2 asked ahead by a ninth wave changed nothing.  A wave's loads go between its fragment
+// What bounds it: the arrival of its K tiles.  With every load in the same column 128x128 takes 0.27 us per K tile, with real
+// addresses 0.56 (57 KB/us a CU).  It is neither the L2's rate (150 KB/us a CU in a kernel of nothing but loads that hit) nor the
+// lines that the L2 does not hold: QKV of 1025 rows, d = 4096 (256x128) finds 75 % of its requests there and takes 12 of its 46 KB/us
+// a CU from behind it, QKV and O of 1787 rows, d = 3584 find 81 and 77 %, with the matrix pipes busy in 0.68, 0.56 and 0.48 of the
+// CUs' busy clocks.  The L2 asked ahead by a ninth wave changed nothing.  A wave's loads go between its fragment
 // reads: eight in a row wait for one another (16 clocks each for every wave that issues them), which the reads
 // behind them then wait for too (128x128 0.36 us per K tile instead of 0.27, all in the same column).
 // LDS: 256x128 three slots of A0 | A1 | B (48 KB), 128x128 five of A | B (32 KB); a K tile is asked for
 // four half steps before it is read (the second group's half of a shared B three).
 // Against the ring loop with the same tile, event us of 2.5 more than the kernel's: M = 883, d = 4096: O (128x128)
-// 59.8 -> 44.0, QKV (256x128) 79.9 -> 63;  M = 1523, d = 3584: QKV 80.8 -> 61, O 79 -> 62 (256x128);  M = 3404, N = 2048,
+// 59.8 -> 44.0, QKV (256x128) 79.9 -> 63 (256x256 tiles in 2 and 4 shares, which such calls took before: 55.9, 69.2);  M = 1523, d = 3584:
+// QKV 80.8 -> 61, O 79 -> 62 (256x128);  M = 3404, N = 2048,
 // K = 256 (432 tiles of 128x128, two on a CU in the ring loop) 14.5 -> 19, where the ring loop stays.
 template <int BM, class BSrc, class Epi>
 __global__ __launch_bounds__(512, 2) void gemm_duo_kernel(
@@ -1719,8 +1721,8 @@ __global__ __launch_bounds__(512, 2) void gemm_duo_kernel(
 // their own): O and QKV at 16 rows 16.6 -> 16.2 and 17.7 -> 17.1.
 // Swizzle and fragment layout as in the ping-pong loop.
 // M = 64, d = 4096, f = 14336, event microseconds with the finishing pass, weights cold (870 MB of others
-// between two reads), 256-row tiles and these: gate/up 65 -> 42 (6.0 TB/s of weights without the events' 2.5 us), down 41 -> 28,
-// QKV 26 -> 19, O 24 -> 18.  Slices of 128 columns in three slots: the same within 2 % over these shapes, gate/up
+// between two reads), 256-row tiles and these: gate/up 65 -> 41 (6.1 TB/s of weights without the events' 2.5 us), down 41 -> 28,
+// QKV 26 -> 20, O 24 -> 18.  Slices of 128 columns in three slots: the same within 2 % over these shapes, gate/up
 // slower by a fifth at 64 rows.
 // Launch bounds: 512 threads where 256 are launched, so that a wave has 256 registers.  With 512 of them the compiler kept the
 // sums in accumulation registers and, in a loop without conditions, moved 20 of them to vector registers and back in every

@@ -202,8 +202,8 @@ inline cc_gemm_plan cc_plan_gemm(int n_cu, int M, int N, int K, int64_t lda, int
     // From the same measurements: 3.1 us for the ends of a round's tiles, 0.41 per 64 columns, the weights no faster
     // than 7.7 TB/s, a finishing pass 2.3 and its rows' traffic at 3.4; the estimate has to be 2 % below the other.
     // Event microseconds (2.5 of them the events' own), d = 4096, f = 14336, 870 MB of other weights between two
-    // reads of one, the best of the thin tiles and of the larger ones:  M = 64: QKV 18.3 / 25.7, O 15.7 / 22.5, gate/up
-    // 40.7 / 46.3, down 28.2 / 39.0;  M = 128: 24.8 / 27.0, 18.6 / 23.1, 67.3 / 52.9, 39.9 / 41.9;  M = 192: 33.0 / 30.4, 24.1 /
+    // reads of one, the best of the thin tiles and of the larger ones:  M = 64: QKV 19.7 / 25.7, O 17.8 / 22.5, gate/up
+    // 41.2 / 46.3, down 28.3 / 39.0;  M = 128: 24.8 / 27.0, 18.6 / 23.1, 67.3 / 52.9, 39.9 / 41.9;  M = 192: 33.0 / 30.4, 24.1 /
     // 25.5, 92.4 / 65.0, 56.6 / 45.3.
     const long thin_tiles = tiles_of(CC_THIN_M, CC_THIN_N);
     const bool thin_ok = lda * CC_THIN_M * 2 < (1ll << 31) && ldb * CC_THIN_N * 2 < (1ll << 31);
@@ -228,10 +228,11 @@ inline cc_gemm_plan cc_plan_gemm(int n_cu, int M, int N, int K, int64_t lda, int
             pick == 'b' && S > 1 && cc_gemm_stages_parts(M)};
 }
 
-// ---- selection: one workgroup up to CC_SEL_ONE_MAX tokens (five rows of 4096 keys in LDS; 6.5 us and 0.36 us more per
-// 1024 tokens), beyond that four launches over tiles (21 us and next to nothing more), which take the ranges of
-// the keys and their workspace.  One workgroup / four launches, microseconds: scores of a softmax 16384: 12.1 / 21.0,
-// 20480: 13.8 / 21.2; crowded by a zero 20480: 23.9 / 30. ----
+// ---- selection: one workgroup up to CC_SEL_ONE_MAX tokens (6.5 us and 0.36 us more per 1024 tokens), beyond that four launches
+// over tiles (21 us and next to nothing more), which take the ranges of the keys and their workspace.  One workgroup / four
+// launches, microseconds: scores of a softmax 16384: 12.1 / 21.0, 20480: 13.8 / 21.2; crowded by a zero 20480: 23.9 / 30.  The line
+// lies where the one workgroup's arrays end (five rows of 4096 keys in LDS, 95 KB with the rest), not where the two meet: by these
+// rates that would be further up, but no larger one is built or measured. ----
 #define CC_SEL_ONE_MAX 20480
 inline bool cc_select_uses_ranges(int T) { return T > CC_SEL_ONE_MAX; }
 
