@@ -794,7 +794,7 @@ def _stratified_rows(M, g, n_extra, seed):
     """The rows whose layer output is compared in a full-size case: the first and the last, one
     (drawn at random) in every block of 256 (token, head) columns that an attention workgroup
     owns, one in every aligned group of 128 rows where those blocks are wider than that (every
-    128-, 192- and 256-row GEMM tile then holds a sampled row), and n_extra more at random."""
+    128- and 256-row GEMM tile then holds a sampled row), and n_extra more at random."""
     rng = np.random.default_rng(seed)
     cols = M * g
     picks = [0, M - 1]

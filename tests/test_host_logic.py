@@ -17,7 +17,7 @@ def test_stratified_rows_cover_every_attention_block_and_gemm_tile(M, g):
     for r in rows:                                   # the 256-column blocks of (token, head) columns a row touches
         cols.update(range((r * g) // 256, (r * g + g - 1) // 256 + 1))
     assert cols >= set(range((M * g + 255) // 256))
-    for tile in (128, 192, 256):                     # every GEMM row tile holds a compared row
+    for tile in (128, 192, 256):                     # every row tile of these heights holds a compared row
         assert set(rows // tile) == set(range((M + tile - 1) // tile)), tile
 
 
